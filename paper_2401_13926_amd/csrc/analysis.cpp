@@ -1144,6 +1144,266 @@ void build_vector_order(Analysis &a) {
     }
 }
 
+// The refactorization's tile schedule (RefTiles).  Leaves a.ref empty when the patterns of L and
+// U differ or a single node does not fit a tile; the hand-out items are used then.
+void build_ref_tiles(const AnalysisOptions &opt, Analysis &a) {
+    const int64_t n = a.n;
+    RefTiles &t = a.ref;
+    t = RefTiles();
+    if (opt.ref_lds <= 0 || n < 1) return;
+    // node m: column m of L (rows srow(m, .), ascending) and row m of U have the same indices
+    auto l0 = [&](int64_t m) { return a.fp[m] + a.fdiag[m] + 1; };
+    auto deg = [&](int64_t m) { return a.fp[m + 1] - l0(m); };
+    if (a.lrp[n] != a.urp[n]) return;
+    for (int64_t m = 0; m < n; ++m) {
+        if (a.urp[m + 1] - a.urp[m] != deg(m)) return;
+        if (!std::equal(a.uci.begin() + a.urp[m], a.uci.begin() + a.urp[m + 1], a.fi.begin() + l0(m))) return;
+    }
+    // F positions of U's entries by rows, and for the entries of L's rows (sources of a node)
+    // their offset within the source's column
+    std::vector<int32_t> upos(a.urp[n]);
+    std::vector<int32_t> loff(a.lrp[n]);
+    {
+        std::vector<int64_t> unext(a.urp.begin(), a.urp.end() - 1), lnext(a.lrp.begin(), a.lrp.end() - 1);
+        for (int64_t j = 0; j < n; ++j) {
+            for (int64_t p = a.fp[j]; p < a.fp[j] + a.fdiag[j]; ++p) upos[unext[a.fi[p]]++] = (int32_t)p;
+            for (int64_t p = l0(j); p < a.fp[j + 1]; ++p) loff[lnext[a.fi[p]]++] = (int32_t)(p - l0(j));
+        }
+    }
+    // layers of tiles
+    std::vector<int32_t> tile_of(n, -1), root(n, -1);
+    std::vector<int64_t> own(n), cost(n);
+    for (int64_t m = 0; m < n; ++m) {
+        int64_t upd = 0;
+        for (int64_t p = a.lrp[m]; p < a.lrp[m + 1]; ++p) upd += 1 + 2 * (deg(a.lci[p]) - loff[p] - 1);
+        // an item has at least one update
+        own[m] = ref_lds_bytes(8, 1 + 2 * deg(m), 0, 1, upd, upd, deg(m)) - 20;
+    }
+    std::vector<uint8_t> fit(n);
+    std::vector<std::vector<int32_t>> members;  // nodes of each tile, ascending
+    int64_t left = n;
+    while (left > 0) {
+        for (int64_t m = 0; m < n; ++m) {
+            cost[m] = tile_of[m] < 0 ? own[m] : 0;
+            fit[m] = 1;
+        }
+        for (int64_t k = 0; k < n; ++k) {
+            if (tile_of[k] < 0) continue;
+            for (int64_t p = l0(k); p < a.fp[k + 1]; ++p)
+                if (tile_of[a.fi[p]] < 0) {
+                    cost[a.fi[p]] += 8 * 2 * (a.fp[k + 1] - p);
+                    break;
+                }
+        }
+        std::vector<int32_t> roots;
+        for (int64_t m = 0; m < n; ++m) {
+            if (tile_of[m] >= 0) continue;
+            fit[m] = fit[m] && cost[m] + 20 <= opt.ref_lds;
+            if (deg(m) == 0) continue;
+            const int32_t up = a.fi[l0(m)];
+            if (fit[m]) cost[up] += cost[m];
+            else fit[up] = 0;
+        }
+        for (int64_t m = n - 1; m >= 0; --m) {
+            if (tile_of[m] >= 0 || !fit[m]) continue;
+            const int64_t up = deg(m) ? a.fi[l0(m)] : -1;
+            if (up >= 0 && fit[up]) {
+                root[m] = root[up];
+            } else {
+                root[m] = (int32_t)m;
+                roots.push_back((int32_t)m);
+            }
+        }
+        if (roots.empty()) {
+            t = RefTiles();
+            return;
+        }
+        // subtrees packed in the order of their roots in the vector order (entries of nearby rows
+        // of K's copy)
+        std::sort(roots.begin(), roots.end(), [&](int32_t x, int32_t y) { return a.q_k[x] < a.q_k[y]; });
+        std::vector<int32_t> tile_of_root(n, -1);
+        int64_t fill = 0;
+        for (int32_t r : roots) {
+            if (members.empty() || fill < 0 || fill + cost[r] + 20 > opt.ref_lds || fill == 0) {
+                members.emplace_back();
+                fill = 0;
+            }
+            fill += cost[r];
+            tile_of_root[r] = (int32_t)members.size() - 1;
+        }
+        for (int64_t m = 0; m < n; ++m) {
+            if (tile_of[m] >= 0 || !fit[m]) continue;
+            tile_of[m] = tile_of_root[root[m]];
+            members[tile_of[m]].push_back((int32_t)m);
+            --left;
+        }
+        ++t.layers;
+    }
+    // exports: entries whose other index is in another (later) tile; the export of each entry
+    std::vector<int32_t> export_of(a.nnz_f(), -1);
+    std::vector<int32_t> slot(a.nnz_f(), -1);      // slot of an entry within its tile
+    std::vector<int32_t> ext_slot(a.nnz_f(), -1);  // slot of an external within the current tile
+    std::vector<int32_t> seg_of(n, 0), node_of(n, -1), where(n, -1);
+    struct Item {
+        int32_t slot, seg, first, count;
+    };
+    for (size_t ti = 0; ti < members.size(); ++ti) {
+        std::vector<int32_t> nodes = members[ti];
+        const int32_t tid = (int32_t)ti;
+        int32_t nseg = 0;
+        for (int32_t m : nodes) {
+            int32_t g = 0;
+            for (int64_t p = a.lrp[m]; p < a.lrp[m + 1]; ++p)
+                if (tile_of[a.lci[p]] == tid) g = std::max(g, seg_of[a.lci[p]] + 1);
+            seg_of[m] = g;
+            nseg = std::max(nseg, g + 1);
+        }
+        std::stable_sort(nodes.begin(), nodes.end(), [&](int32_t x, int32_t y) { return seg_of[x] < seg_of[y]; });
+        std::vector<int32_t> first(nseg + 1, 0);  // first node of each segment
+        for (int32_t m : nodes) ++first[seg_of[m] + 1];
+        for (int32_t g = 0; g < nseg; ++g) first[g + 1] += first[g];
+        for (size_t k = 0; k < nodes.size(); ++k) node_of[nodes[k]] = (int32_t)k;
+        int32_t d[kRefDesc] = {};
+        d[0] = (int32_t)(t.seg.size() / 3);
+        d[1] = nseg;
+        d[2] = (int32_t)t.src.size();
+        d[4] = (int32_t)t.item.size();
+        d[6] = (int32_t)t.upd.size();
+        d[8] = (int32_t)t.lq.size();
+        d[10] = (int32_t)t.exp.size();
+        d[12] = (int32_t)t.ext.size();
+        d[14] = (int32_t)nodes.size();
+        d[15] = (int32_t)t.cmx_src.size();
+        // slots
+        std::vector<int32_t> fpos;  // F position of each slot
+        std::vector<int32_t> seg_slot(nseg + 1, 0), seg_l(nseg + 1, 0), seg_exp(nseg + 1, 0);
+        auto add = [&](int32_t f, int32_t col) {
+            slot[f] = (int32_t)fpos.size();
+            fpos.push_back(f);
+            t.src.push_back((int32_t)a.fsrc_k[f]);
+            t.col.push_back(tile_of[col] == tid ? (uint16_t)node_of[col] : (uint16_t)0xFFFF);
+        };
+        for (int32_t g = 0; g < nseg; ++g) {
+            seg_slot[g] = (int32_t)fpos.size();
+            for (int32_t k = first[g]; k < first[g + 1]; ++k) add((int32_t)(a.fp[nodes[k]] + a.fdiag[nodes[k]]), nodes[k]);
+            for (int32_t k = first[g]; k < first[g + 1]; ++k)
+                for (int64_t p = l0(nodes[k]); p < a.fp[nodes[k] + 1]; ++p) {
+                    add((int32_t)p, nodes[k]);
+                    t.lq.push_back((uint16_t)(k - first[g]));
+                    if (tile_of[a.fi[p]] != tid) {
+                        export_of[p] = (int32_t)t.exp.size();
+                        t.exp.push_back((uint16_t)slot[p]);
+                    }
+                }
+            for (int32_t k = first[g]; k < first[g + 1]; ++k)
+                for (int64_t p = a.urp[nodes[k]]; p < a.urp[nodes[k] + 1]; ++p) {
+                    add(upos[p], a.uci[p]);
+                    if (tile_of[a.uci[p]] != tid) {
+                        export_of[upos[p]] = (int32_t)t.exp.size();
+                        t.exp.push_back((uint16_t)slot[upos[p]]);
+                    }
+                }
+            seg_l[g + 1] = (int32_t)(t.lq.size() - d[8]);
+            seg_exp[g + 1] = (int32_t)(t.exp.size() - d[10]);
+        }
+        const int32_t ne = (int32_t)fpos.size();
+        // updates: for each node, its sources k ascending, each giving one update of the
+        // diagonal and of the L and U entries of the later indices in column k
+        std::vector<std::vector<std::pair<uint32_t, int32_t>>> chain;  // per entry of a node: (factors, segment)
+        std::vector<Item> items;
+        std::vector<uint32_t> upds;  // of `items`, in their order
+        auto slot_of = [&](int64_t f, int32_t k) -> uint32_t {
+            if (tile_of[k] == tid) return (uint32_t)slot[f];
+            if (ext_slot[f] < 0) {
+                ext_slot[f] = ne + (int32_t)(t.ext.size() - d[12]);
+                t.ext.push_back(export_of[f]);
+                fpos.push_back((int32_t)f);  // beyond ne: the externals, to clear ext_slot below
+            }
+            return (uint32_t)ext_slot[f];
+        };
+        for (int32_t m : nodes) {
+            const int64_t s = deg(m), lm = l0(m);
+            chain.assign(1 + 2 * s, {});
+            for (int64_t q = 0; q < s; ++q) where[a.fi[lm + q]] = (int32_t)q;
+            for (int64_t p = a.lrp[m]; p < a.lrp[m + 1]; ++p) {
+                const int32_t k = a.lci[p];
+                const int64_t lk = l0(k), uk = a.urp[k];
+                const int32_t at = tile_of[k] == tid ? seg_of[k] + 1 : 0;
+                const uint32_t lmk = slot_of(lk + loff[p], k), ukm = slot_of(upos[uk + loff[p]], k);
+                chain[0].emplace_back(lmk | (ukm << 16), at);
+                for (int64_t b = loff[p] + 1; b < deg(k); ++b) {
+                    const int32_t q = where[a.fi[lk + b]];
+                    chain[1 + q].emplace_back(slot_of(lk + b, k) | (ukm << 16), at);
+                    chain[1 + s + q].emplace_back(lmk | (slot_of(upos[uk + b], k) << 16), at);
+                }
+            }
+            for (int64_t e = 0; e < 1 + 2 * s; ++e) {
+                const int32_t sl = e == 0 ? slot[lm - 1] : e <= s ? slot[lm + e - 1] : slot[upos[a.urp[m] + e - 1 - s]];
+                int32_t seg = -1;
+                for (const auto &u : chain[e]) {
+                    if (u.second > seg) {
+                        seg = u.second;
+                        items.push_back(Item{sl, seg, (int32_t)upds.size(), 0});
+                    }
+                    ++items.back().count;
+                    upds.push_back(u.first);
+                }
+            }
+        }
+        // items by segment, longer ones first (the lanes of a wavefront then have about the same
+        // number of updates)
+        std::vector<int32_t> order(items.size());
+        for (size_t k = 0; k < order.size(); ++k) order[k] = (int32_t)k;
+        std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) {
+            if (items[x].seg != items[y].seg) return items[x].seg < items[y].seg;
+            return items[x].count > items[y].count;
+        });
+        std::vector<int32_t> seg_item(nseg + 1, 0);
+        for (int32_t k : order) {
+            const Item &it = items[k];
+            ++seg_item[it.seg + 1];
+            t.item.push_back((uint32_t)it.slot | ((uint32_t)(t.upd.size() - d[6]) << 16));
+            t.upd.insert(t.upd.end(), upds.begin() + it.first, upds.begin() + it.first + it.count);
+        }
+        t.item.push_back((uint32_t)(t.upd.size() - d[6]) << 16);
+        for (int32_t g = 0; g < nseg; ++g) {
+            seg_item[g + 1] += seg_item[g];
+            t.seg.push_back((uint32_t)seg_item[g + 1] | ((uint32_t)seg_slot[g] << 16));
+            t.seg.push_back((uint32_t)first[g + 1] | ((uint32_t)seg_l[g + 1] << 16));
+            t.seg.push_back((uint32_t)seg_exp[g + 1]);
+        }
+        // column maxima: a column's entries of K above the diagonal whose U entry is an earlier tile's
+        for (size_t k = 0; k < nodes.size(); ++k)
+            for (int64_t p = a.fp[nodes[k]]; p < a.fp[nodes[k]] + a.fdiag[nodes[k]]; ++p)
+                if (a.fsrc_k[p] >= 0 && tile_of[a.fi[p]] != tid) {
+                    t.cmx_node.push_back((uint32_t)k);
+                    t.cmx_src.push_back((int32_t)a.fsrc_k[p]);
+                }
+        // the way out: entries by their position in the solve layout
+        std::vector<std::pair<int32_t, uint16_t>> out(ne);
+        for (int32_t e = 0; e < ne; ++e) out[e] = {a.f2t[fpos[e]], (uint16_t)e};
+        std::sort(out.begin(), out.end());
+        for (const auto &e : out) {
+            t.out_pos.push_back(e.first);
+            t.out_slot.push_back(e.second);
+        }
+        d[3] = ne;
+        d[5] = (int32_t)items.size();
+        d[7] = (int32_t)(t.upd.size() - d[6]);
+        d[9] = (int32_t)(t.lq.size() - d[8]);
+        d[11] = (int32_t)(t.exp.size() - d[10]);
+        d[13] = (int32_t)(t.ext.size() - d[12]);
+        d[16] = (int32_t)(t.cmx_src.size() - d[15]);
+        t.desc.insert(t.desc.end(), d, d + kRefDesc);
+        t.lds = std::max(t.lds, ref_lds_bytes(8, ne, d[13], d[14], d[7], d[5], d[9]));
+        for (size_t e = ne; e < fpos.size(); ++e) ext_slot[fpos[e]] = -1;
+        if (t.lds > opt.ref_lds || ne + d[13] > 0xFFFF || d[7] > 0xFFFF || d[5] > 0xFFFF) {
+            t = RefTiles();
+            return;
+        }
+    }
+}
+
 // The device layout of the flat refactorization (see Analysis::phys): F positions and update
 // lists renumbered in col_order.
 void build_phys_layout(Analysis &a) {
@@ -1236,6 +1496,7 @@ int analyze(const AnalysisOptions &opt, int64_t n, const int64_t *rowptr, const 
         rc = build_layouts(opt, a, msg);
         if (rc != AN_OK) return rc;
         build_vector_order(a);
+        build_ref_tiles(opt, a);
         if (!a.relsrc.empty()) build_phys_layout(a);
     } catch (const std::bad_alloc &) {
         *msg = "out of host memory";

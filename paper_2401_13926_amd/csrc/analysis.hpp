@@ -31,6 +31,7 @@ struct AnalysisOptions {
     int64_t dense_reserve_u = 0;
     int narrow_columns = 1024;   // refactorization levels with at most this many columns are
                                  // handed out one column at a time
+    int64_t ref_lds = 0;         // LDS bytes of a refactorization tile (0: no tiles)
 };
 
 // Flags in TriSchedule::seg_lg: the segment's rows fit one wavefront; the segment is a
@@ -89,6 +90,50 @@ inline int64_t tile_lds_bytes(int64_t rows, int64_t ext, int64_t ent, int64_t de
 }
 inline int64_t dense_block_values(int64_t m) { return m * (m - 1) / 2; }
 
+// Schedule of the refactorization by tiles, for factors whose L and U patterns are each other's
+// transposes (diagonal pivots on a symmetric pattern).  Node m is pivot step m with the entries
+// it finishes: its diagonal, column m of L and row m of U.  Every update of an entry (i, j)
+// with min(i, j) = m comes from a step k that has both i and j in its column, hence from a
+// descendant of m in the elimination tree.  A tile is a set of whole subtrees of what earlier
+// layers of tiles left over; it keeps all its entries in LDS, so that an update reads its two
+// factors there: own entries, or externals (entries of earlier tiles' nodes, staged with the
+// tile).  Tiles are handed out in layer order, so a tile only waits for earlier ones.
+//
+// Inside a tile, nodes are solved by level (segment) with a barrier in between.  Segment g
+// first runs its items (an item applies consecutive updates of one entry, in ascending k, whose
+// factors are all final by then), then divides the L entries of its nodes.  Entry slots are
+// ordered by segment: the nodes' diagonals, their L entries, their U entries.
+constexpr int kRefDesc = 20;  // int32 per tile descriptor
+struct RefTiles {
+    // per tile: 0 first segment, 1 segments, 2 first entry, 3 entries, 4 first item, 5 items, 6 first
+    // update, 7 updates, 8 first L entry, 9 L entries, 10 first export, 11 exports, 12 first
+    // external, 13 externals, 14 nodes, 15 first column-maximum extra, 16 extras
+    std::vector<int32_t> desc;
+    // per segment, three words of cumulative counts within the tile: items | first slot << 16,
+    // nodes | L entries << 16, exports (each at the segment's end, the slot at its start)
+    std::vector<uint32_t> seg;
+    std::vector<int32_t> src;     // per entry slot: its value's entry in the copy of K, or -1 (fill)
+    std::vector<uint16_t> col;    // per entry slot: tile-local node of its column, 0xFFFF if none
+    std::vector<uint32_t> item;   // per item (and one past a tile's last): slot | first update << 16
+    std::vector<uint32_t> upd;    // per update: slot of its L factor | slot of its U factor << 16
+    std::vector<uint16_t> lq;     // per L entry: its node's index within the segment
+    std::vector<uint16_t> exp;    // per export: slot (entries whose other index is in a later tile)
+    std::vector<int32_t> ext;     // per external: the export it is
+    std::vector<uint32_t> cmx_node;  // column-maximum extras: entries of K in a node's column whose
+    std::vector<int32_t> cmx_src;    // U entry belongs to an earlier tile (node; entry of K's copy)
+    std::vector<int32_t> out_pos;   // per entry, by ascending position in the solve layout: that
+    std::vector<uint16_t> out_slot;  // position and the entry's slot
+    int64_t lds = 0;              // LDS bytes of the largest tile (FP64)
+    int64_t layers = 0;
+    int64_t tiles() const { return (int64_t)desc.size() / kRefDesc; }
+};
+// LDS bytes of a refactorization tile with values of `word` bytes: entry and external slots,
+// column maxima; updates, items; L entries' nodes.
+inline int64_t ref_lds_bytes(int64_t word, int64_t entries, int64_t ext, int64_t nodes, int64_t upd, int64_t items,
+                             int64_t nl) {
+    return word * (entries + ext + nodes) + 4 * (upd + items + 1) + 2 * nl + 16;
+}
+
 // Everything derived from the pattern and the first system's values.
 //
 // Index spaces: "original" rows/columns are those of K; "steps" are pivot steps of the
@@ -139,6 +184,8 @@ struct Analysis {
     // lane-sized columns first.
     std::vector<int32_t> ref_item;
     std::vector<uint8_t> ref_item_lane;
+
+    RefTiles ref;  // empty when the factor does not qualify (the items above are used then)
 
     // Row-wise triangles in step space (strict L, strict U), from which the solve schedules
     // are built.  Solve layout T = [L values | strict U values | U diagonal (n, step order)],

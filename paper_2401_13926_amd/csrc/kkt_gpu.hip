@@ -205,6 +205,25 @@ __global__ void k_prep_refactor(Control *c) {
     c->counter = 0;
 }
 
+// Tiles: everything a refactorization needs zeroed or armed before it, in one launch: the exports'
+// sentinels, the hand-out counter and guard counts and, when new values follow (values), the
+// row-norm maximum and the finiteness flag.
+template <typename T> __global__ void k_prep_tiles(Control *c, int values, int64_t nx, T *X) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        if (values) {
+            c->knorm_bits = 0;
+            c->nonfinite = 0;
+        }
+        c->work_refactor[0] = 0;
+        c->hang = 0;
+        c->guard_fail = 0;
+        c->nguard = 0;
+        c->counter = 0;
+    }
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nx; i += stride) X[i] = sentinel<T>();
+}
+
 // New values: K's values (original CSR order, vals) into the Krylov side's copy in the vector
 // order, one thread per row of the copy (row k is an original row whose entries start at
 // ostart[k] and keep their order); also ||K||_inf (each row's absolute values summed in
@@ -862,6 +881,307 @@ k_refactor(RefactorArgs<T> args, RefactorBatch<T> batch) {
     }
 }
 
+// Read-only schedule data seen through the constant address space: with a uniform index the
+// compiler loads it through the scalar cache, so waiting for it never waits for the
+// kernel's outstanding vector stores.
+template <typename P> __device__ __forceinline__ const __attribute__((address_space(4))) P *uniform_ro(const P *p) {
+    return (const __attribute__((address_space(4))) P *)p;
+}
+
+// ---------------------------------------------------------------------------------------
+// refactorization by tiles (RefTiles): subtrees of the elimination tree kept in LDS
+// ---------------------------------------------------------------------------------------
+
+struct RefTileArgs {
+    int64_t ntiles;
+    const int32_t *desc;
+    const uint32_t *seg;
+    const int32_t *src;
+    const uint16_t *col;
+    const uint32_t *item, *upd;
+    const uint16_t *lq, *exp;
+    const int32_t *ext;
+    const uint32_t *cmx_node;
+    const int32_t *cmx_src;
+    const int32_t *out_pos;
+    const uint16_t *out_slot;
+    int guard_fail_policy;
+};
+
+// Several systems of one pattern refactored by one launch, as in RefactorBatch.
+template <typename T> struct RefTileBatch {
+    int nslots;
+    struct {
+        T *Tv;  // solve layout
+        T *X;   // exports: sentinel until written
+        Control *ctl;
+        const double *kval;
+    } slot[kMaxBatch];
+};
+
+// Staging loads per thread and pass of a refactorization tile.
+constexpr int kRefEnt = 8, kRefUpd = 8, kRefItem = 8, kRefL = 4, kRefExt = 4, kRefCmx = 2;
+
+__device__ __forceinline__ void lds_max(double *p, double v) {
+    atomicMax(reinterpret_cast<unsigned long long *>(p), (unsigned long long)__double_as_longlong(v));
+}
+__device__ __forceinline__ void lds_max(float *p, float v) {
+    atomicMax(reinterpret_cast<unsigned int *>(p), (unsigned int)__float_as_int(v));
+}
+
+// The pivot d of a column whose largest entry of K is cm, under the tiny-pivot guard.  Applied
+// to a guarded pivot it gives the same value again.
+template <typename T> __device__ __forceinline__ T guarded_pivot(T d, T cm, bool &hit) {
+    const T ur = unit_roundoff<T>();
+    const T cmx = cm > T(0) ? cm : T(1);
+    hit = !(fabs(d) > ur * cmx) || !isfinite(d);
+    return hit ? (d < T(0) ? T(-1) : T(1)) * ur * cmx : d;
+}
+
+// kBatch: more than one slot (the slot table's pointers cost the single-system kernel spills).
+template <typename T, bool kBatch>
+__global__ void __launch_bounds__(kCoopBlock) k_refactor_tiles(RefTileArgs a, RefTileBatch<T> batch) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ unsigned int tile_sh;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int nslots = kBatch ? batch.nslots : 1;
+    Control *const ctl0 = batch.slot[0].ctl;
+    for (;;) {
+        if (tid == 0) tile_sh = atomicAdd(&ctl0->work_refactor[0], 1u);
+        __syncthreads();
+        const unsigned int w = (unsigned int)__builtin_amdgcn_readfirstlane((int)tile_sh);
+        __syncthreads();
+        if ((int64_t)w >= a.ntiles * nslots) break;
+        const unsigned int t = kBatch ? w / nslots : w;
+        T *Tv = batch.slot[0].Tv, *X = batch.slot[0].X;
+        Control *ctl = ctl0;
+        const double *kval = batch.slot[0].kval;
+        if (kBatch) {
+            // by uniform compares, not a dynamic index into the argument array
+            const int sb = (int)(w - t * nslots);
+#pragma unroll
+            for (int q = 1; q < kMaxBatch; ++q)
+                if (q == sb) {
+                    Tv = batch.slot[q].Tv;
+                    X = batch.slot[q].X;
+                    ctl = batch.slot[q].ctl;
+                    kval = batch.slot[q].kval;
+                }
+        }
+        const auto td = uniform_ro(a.desc) + (int64_t)kRefDesc * t;
+        const int s0 = td[0], ns = td[1], ne = td[3], ni = td[5], nu = td[7], nl = td[9], nx = td[13], nn = td[14],
+                  nc = td[16];
+        const int64_t eb = td[2], ib = td[4], ub = td[6], lb = td[8], pb = td[10], xb = td[12], cb = td[15];
+        T *cm = reinterpret_cast<T *>(smem);                      // nn column maxima
+        T *xs = cm + nn;                                          // ne entries, nx externals
+        uint32_t *upd = reinterpret_cast<uint32_t *>(xs + ne + nx);  // nu
+        uint32_t *item = upd + nu;                                // ni + 1
+        uint16_t *lq = reinterpret_cast<uint16_t *>(item + ni + 1);  // nl
+        for (int k = tid; k < nn; k += kCoopBlock) cm[k] = T(0);
+        // lane l of every wavefront holds segment l's words
+        uint32_t m0 = 0, m1 = 0, m2 = 0;
+        auto seg_words = [&](int g0) {
+            m0 = m1 = m2 = 0;
+            if (g0 + lane < ns) {
+                const uint32_t *p = a.seg + 3 * (int64_t)(s0 + g0 + lane);
+                m0 = p[0];
+                m1 = p[1];
+                m2 = p[2];
+            }
+        };
+        seg_words(0);
+        __syncthreads();
+        // Staging, in two rounds of loads per pass: the schedule's own data, then the values it
+        // points to (K's entries, the externals), then LDS.
+        for (int pe = 0, pu = 0, pi = 0, pl = 0, px = 0, pc = 0;
+             pe < ne || pu < nu || pi <= ni || pl < nl || px < nx || pc < nc;
+             pe += kRefEnt * kCoopBlock, pu += kRefUpd * kCoopBlock, pi += kRefItem * kCoopBlock,
+             pl += kRefL * kCoopBlock, px += kRefExt * kCoopBlock, pc += kRefCmx * kCoopBlock) {
+            int src[kRefEnt], xsrc[kRefExt], csrc[kRefCmx];
+            uint32_t uv[kRefUpd], iv[kRefItem], cn[kRefCmx];
+            uint16_t col[kRefEnt], lv[kRefL];
+            double v[kRefEnt], cv[kRefCmx];
+            T xv[kRefExt];
+#pragma unroll
+            for (int u = 0; u < kRefEnt; ++u) {
+                const int k = pe + tid + u * kCoopBlock;
+                src[u] = k < ne ? a.src[eb + k] : -1;
+                col[u] = k < ne ? a.col[eb + k] : (uint16_t)0xFFFF;
+            }
+#pragma unroll
+            for (int u = 0; u < kRefExt; ++u) {
+                const int k = px + tid + u * kCoopBlock;
+                xsrc[u] = k < nx ? a.ext[xb + k] : 0;
+            }
+#pragma unroll
+            for (int u = 0; u < kRefCmx; ++u) {
+                const int k = pc + tid + u * kCoopBlock;
+                csrc[u] = k < nc ? a.cmx_src[cb + k] : -1;
+                cn[u] = k < nc ? a.cmx_node[cb + k] : 0u;
+            }
+#pragma unroll
+            for (int u = 0; u < kRefUpd; ++u) {
+                const int k = pu + tid + u * kCoopBlock;
+                uv[u] = k < nu ? a.upd[ub + k] : 0u;
+            }
+#pragma unroll
+            for (int u = 0; u < kRefItem; ++u) {
+                const int k = pi + tid + u * kCoopBlock;
+                iv[u] = k <= ni ? a.item[ib + k] : 0u;
+            }
+#pragma unroll
+            for (int u = 0; u < kRefL; ++u) {
+                const int k = pl + tid + u * kCoopBlock;
+                lv[u] = k < nl ? a.lq[lb + k] : (uint16_t)0;
+            }
+            // dependent loads
+#pragma unroll
+            for (int u = 0; u < kRefEnt; ++u) v[u] = src[u] >= 0 ? kval[src[u]] : 0.0;
+#pragma unroll
+            for (int u = 0; u < kRefCmx; ++u) cv[u] = csrc[u] >= 0 ? kval[csrc[u]] : 0.0;
+#pragma unroll
+            for (int u = 0; u < kRefExt; ++u) xv[u] = px + tid + u * kCoopBlock < nx ? X[xsrc[u]] : T(0);
+            // LDS
+#pragma unroll
+            for (int u = 0; u < kRefUpd; ++u) {
+                const int k = pu + tid + u * kCoopBlock;
+                if (k < nu) upd[k] = uv[u];
+            }
+#pragma unroll
+            for (int u = 0; u < kRefItem; ++u) {
+                const int k = pi + tid + u * kCoopBlock;
+                if (k <= ni) item[k] = iv[u];
+            }
+#pragma unroll
+            for (int u = 0; u < kRefL; ++u) {
+                const int k = pl + tid + u * kCoopBlock;
+                if (k < nl) lq[k] = lv[u];
+            }
+            // (a NaN never raises a column maximum, as with fmax)
+#pragma unroll
+            for (int u = 0; u < kRefEnt; ++u) {
+                const int k = pe + tid + u * kCoopBlock;
+                const T x = (T)v[u];
+                if (k < ne) xs[k] = x;
+                if (col[u] != 0xFFFF && fabs(x) > T(0)) lds_max(cm + col[u], fabs(x));
+            }
+#pragma unroll
+            for (int u = 0; u < kRefCmx; ++u) {
+                const T x = (T)cv[u];
+                if (csrc[u] >= 0 && fabs(x) > T(0)) lds_max(cm + cn[u], fabs(x));
+            }
+#pragma unroll
+            for (int u = 0; u < kRefExt; ++u) {
+                const int k = px + tid + u * kCoopBlock;
+                if (k < nx) {
+                    T x = xv[u];
+                    if (is_sentinel(x)) x = load_ready<T, 1>(X + xsrc[u], &ctl->hang);
+                    xs[ne + k] = x;
+                }
+            }
+        }
+        __syncthreads();
+        // An export that carries the sentinel's bits (only a value of K itself could) becomes
+        // another NaN, so that no wait mistakes it for an unwritten one.
+        auto do_exports = [&](int x0, int x1, int stride) {
+            for (int k = x0 + tid; k < x1; k += stride) {
+                T x = xs[a.exp[pb + k]];
+                if (is_sentinel(x)) x = T(NAN);
+                store_ready(X + pb + k, x);
+            }
+        };
+        // The segments.  One whose items and L entries fit a wavefront is wavefront 0's alone,
+        // without block barriers (a wavefront's LDS accesses complete in order).
+        bool prev_wave = false;
+        int gb = 0, i0 = 0, n0 = 0, q0 = 0, x0 = 0, px0 = 0;
+        for (int g = 0; g < ns; ++g) {
+            if (g >= gb + 64) {
+                gb = g;
+                seg_words(gb);
+            }
+            const uint32_t w0 = (uint32_t)__builtin_amdgcn_readlane((int)m0, g - gb);
+            const uint32_t w1 = (uint32_t)__builtin_amdgcn_readlane((int)m1, g - gb);
+            const int x1 = __builtin_amdgcn_readlane((int)m2, g - gb);
+            const int i1 = (int)(w0 & 0xFFFFu), sl0 = (int)(w0 >> 16);
+            const int n1 = (int)(w1 & 0xFFFFu), q1 = (int)(w1 >> 16);
+            const int nd = n1 - n0;
+            const bool wave = i1 - i0 <= 64 && q1 - q0 <= 64 && nd <= 64;
+            if (g > 0 && !(wave && prev_wave)) __syncthreads();
+            if (px0 < x0) {  // exports of the block segment before
+                do_exports(px0, x0, kCoopBlock);
+                px0 = x0;
+            }
+            prev_wave = wave;
+            if (!wave || tid < 64) {
+                const int stride = wave ? 64 : kCoopBlock;
+                for (int i = i0 + tid; i < i1; i += stride) {
+                    const uint32_t ia = item[i], ie = item[i + 1];
+                    const int u1 = (int)(ie >> 16);
+                    T x = xs[ia & 0xFFFFu];
+                    for (int u = (int)(ia >> 16); u < u1; u += 4) {
+                        T l[4], f[4];
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) {
+                            const uint32_t p = upd[u + k < u1 ? u + k : u];
+                            l[k] = xs[p & 0xFFFFu];
+                            f[k] = xs[p >> 16];
+                        }
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) {
+                            const T prod = l[k] * f[k];
+                            if (u + k < u1) x = x - prod;
+                        }
+                    }
+                    xs[ia & 0xFFFFu] = x;
+                }
+                if (wave) __builtin_amdgcn_wave_barrier();
+                else __syncthreads();
+                // pivots (every lane of a column guards its pivot by itself) and divisions
+                for (int q = q0 + tid; q < q1; q += stride) {
+                    const int node = lq[q], e = sl0 + nd + (q - q0);
+                    bool hit;
+                    const T d = guarded_pivot(xs[sl0 + node], cm[n0 + node], hit);
+                    xs[e] = xs[e] / d;
+                }
+                for (int k = tid; k < nd; k += stride) {
+                    bool hit;
+                    const T d = guarded_pivot(xs[sl0 + k], cm[n0 + k], hit);
+                    if (hit) {
+                        xs[sl0 + k] = d;
+                        atomicAdd(&ctl->nguard, 1ull);
+                        if (a.guard_fail_policy) atomicOr(&ctl->guard_fail, 1u);
+                    }
+                }
+                if (wave) {
+                    __builtin_amdgcn_wave_barrier();
+                    do_exports(x0, x1, 64);
+                }
+            }
+            if (wave) px0 = x1;
+            i0 = i1;
+            n0 = n1;
+            q0 = q1;
+            x0 = x1;
+        }
+        __syncthreads();
+        if (px0 < x0) do_exports(px0, x0, kCoopBlock);
+        // the finished entries into the solve layout, by ascending position
+        for (int e0 = 0; e0 < ne; e0 += 8 * kCoopBlock) {
+            int pos[8], sl[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int e = e0 + tid + u * kCoopBlock;
+                pos[u] = e < ne ? a.out_pos[eb + e] : 0;
+                sl[u] = e < ne ? a.out_slot[eb + e] : 0;
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (e0 + tid + u * kCoopBlock < ne) Tv[pos[u]] = xs[sl[u]];
+        }
+        __syncthreads();
+    }
+}
+
 // ---------------------------------------------------------------------------------------
 // triangular solves in solve layout (step space), by tiles of segments
 // ---------------------------------------------------------------------------------------
@@ -970,13 +1290,6 @@ __device__ __forceinline__ double lane_value(double v, int l) {
 }
 __device__ __forceinline__ float lane_value(float v, int l) {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
-}
-
-// Read-only schedule data seen through the constant address space: with a uniform index the
-// compiler loads it through the scalar cache, so waiting for it never waits for the
-// kernel's outstanding vector stores.
-template <typename P> __device__ __forceinline__ const __attribute__((address_space(4))) P *uniform_ro(const P *p) {
-    return (const __attribute__((address_space(4))) P *)p;
 }
 
 template <typename T, bool kLower, bool kDense>
@@ -1828,6 +2141,12 @@ struct DevLayout {
     int32_t *relpos, *relsrc, *item, *relslot, *pnu;
     int64_t *pc, *pu;
     uint8_t *item_lane;
+    // refactorization tiles
+    int32_t *rt_desc, *rt_src, *rt_ext, *rt_cmxs, *rt_opos;
+    uint32_t *rt_seg, *rt_item, *rt_upd, *rt_cmxn;
+    uint16_t *rt_col, *rt_lq, *rt_exp, *rt_oslot;
+    double *X64;
+    float *X32;
     int64_t *krp;
     int32_t *lci, *uci, *kci;
     int32_t *prow, *q;
@@ -1981,33 +2300,55 @@ struct Offsets {
         l_ref, l_slg, l_esrc, l_rent, l_sdof, l_src, l_src_k, u_rows, u_seg, u_tdesc, u_ref, u_slg, u_esrc,
         u_rent, u_sdof, u_q, u_q_k, prow, q, vperm, prow_k, q_k, ostart, fsrc32, kval, F64, T64, F32, T32, Ld64, Ld32, V, Z, w, r, y64, z64, y32,
         z32, dv, rr, xb, bi, xi, part, ctl, total;
+    size_t rt_desc, rt_seg, rt_src, rt_col, rt_item, rt_upd, rt_lq, rt_exp, rt_ext, rt_cmxn, rt_cmxs, rt_opos, rt_oslot,
+        X64, X32;
 };
 
-Offsets plan(const kkt_handle_t h) {
+// tiles: with the refactorization's tiles (the hand-out items' arrays are then left out), or
+// without.
+Offsets plan_for(const kkt_handle_t h, bool tiles) {
     const Analysis &a = h->an;
-    const int64_t n = a.n, f = a.nnz_f();
+    const int64_t n = a.n, f = a.nnz_f(), fi = tiles ? 0 : f, ni = tiles ? 0 : n;
     const int R = h->opts.restart;
     Planner p;
     Offsets o{};
-    o.fp = p.take<int64_t>(n + 1);
-    o.fi = p.take<int32_t>(f);
-    o.fdiag = p.take<int32_t>(n);
-    o.order = p.take<int32_t>(n);
-    o.clev = p.take<int32_t>(n);
-    o.f2t = p.take<int32_t>(f);
-    o.relptr = p.take<int64_t>(n + 1);
+    o.fp = p.take<int64_t>(ni + 1);
+    o.fi = p.take<int32_t>(fi);
+    o.fdiag = p.take<int32_t>(ni);
+    o.order = p.take<int32_t>(ni);
+    o.clev = p.take<int32_t>(ni);
+    o.f2t = p.take<int32_t>(fi);
+    o.relptr = p.take<int64_t>(ni + 1);
     // F positions' value sources: 32-bit for the flat refactorization (which reads them), 64-bit
     // for the other one (whose ingest initializes F)
-    o.fsrc = p.take<int64_t>(a.phys ? 0 : f);
-    o.fsrc32 = p.take<int32_t>(a.phys ? f : 0);
-    o.relpos = p.take<int32_t>(a.relpos.size());
-    o.relsrc = p.take<int32_t>(a.relsrc.size());
-    o.relslot = p.take<int32_t>(a.relslot.size());
-    o.pc = p.take<int64_t>(a.pc.size());
-    o.pu = p.take<int64_t>(a.pu.size());
-    o.pnu = p.take<int32_t>(a.pnu.size());
-    o.item = p.take<int32_t>(a.ref_item.size());
-    o.item_lane = p.take<uint8_t>(a.ref_item_lane.size());
+    o.fsrc = p.take<int64_t>(a.phys ? 0 : fi);
+    o.fsrc32 = p.take<int32_t>(a.phys ? fi : 0);
+    o.relpos = p.take<int32_t>(tiles ? 0 : a.relpos.size());
+    o.relsrc = p.take<int32_t>(tiles ? 0 : a.relsrc.size());
+    o.relslot = p.take<int32_t>(tiles ? 0 : a.relslot.size());
+    o.pc = p.take<int64_t>(tiles ? 0 : a.pc.size());
+    o.pu = p.take<int64_t>(tiles ? 0 : a.pu.size());
+    o.pnu = p.take<int32_t>(tiles ? 0 : a.pnu.size());
+    o.item = p.take<int32_t>(tiles ? 0 : a.ref_item.size());
+    o.item_lane = p.take<uint8_t>(tiles ? 0 : a.ref_item_lane.size());
+    if (tiles) {
+        const RefTiles &t = a.ref;
+        o.rt_desc = p.take<int32_t>(t.desc.size());
+        o.rt_seg = p.take<uint32_t>(t.seg.size());
+        o.rt_src = p.take<int32_t>(t.src.size());
+        o.rt_col = p.take<uint16_t>(t.col.size());
+        o.rt_item = p.take<uint32_t>(t.item.size());
+        o.rt_upd = p.take<uint32_t>(t.upd.size());
+        o.rt_lq = p.take<uint16_t>(t.lq.size());
+        o.rt_exp = p.take<uint16_t>(t.exp.size());
+        o.rt_ext = p.take<int32_t>(t.ext.size());
+        o.rt_cmxn = p.take<uint32_t>(t.cmx_node.size());
+        o.rt_cmxs = p.take<int32_t>(t.cmx_src.size());
+        o.rt_opos = p.take<int32_t>(t.out_pos.size());
+        o.rt_oslot = p.take<uint16_t>(t.out_slot.size());
+        o.X64 = p.take<double>(t.exp.size());
+        o.X32 = p.take<float>(t.exp.size());
+    }
     o.krp = p.take<int64_t>(n + 1);
     o.kci = p.take<int32_t>(a.nnz);
     o.l_rows = p.take<int32_t>(n);
@@ -2037,12 +2378,12 @@ Offsets plan(const kkt_handle_t h) {
     o.q_k = p.take<int32_t>(n);
     o.ostart = p.take<int64_t>(n);
     o.kval = p.take<double>(a.nnz);
-    o.F64 = p.take<double>(f);
+    o.F64 = p.take<double>(fi);
     o.T64 = p.take<double>(a.t_size);
-    o.F32 = p.take<float>(f);
+    o.F32 = p.take<float>(fi);
     o.T32 = p.take<float>(a.t_size);
-    o.Ld64 = p.take<double>(f);
-    o.Ld32 = p.take<float>(f);
+    o.Ld64 = p.take<double>(fi);
+    o.Ld32 = p.take<float>(fi);
     o.V = p.take<double>((size_t)(R + 1) * n);
     o.Z = p.take<double>((size_t)R * n);
     o.w = p.take<double>(n);
@@ -2059,6 +2400,14 @@ Offsets plan(const kkt_handle_t h) {
     o.part = p.take<double>((size_t)3 * kStreamGridMax * kPartStride);
     o.ctl = p.take<Control>(1);
     o.total = p.off;
+    return o;
+}
+
+// The workspace is never smaller than the layout without tiles: a re-pivoted factorization (which
+// may not qualify for tiles) then fits wherever it did.
+Offsets plan(const kkt_handle_t h) {
+    Offsets o = plan_for(h, h->an.ref.tiles() > 0);
+    if (h->an.ref.tiles() > 0) o.total = std::max(o.total, plan_for(h, false).total);
     return o;
 }
 
@@ -2211,15 +2560,24 @@ kkt_status_t refactor_batch_impl(const kkt_handle_t *hs, const double *const *va
         for (int b = 1; b < count; ++b) fail(hs[b], KKT_EDEVICE, m);
         return fail(h, KKT_EDEVICE, m);
     };
+    const bool tiles = a.ref.tiles() > 0;
     hipEvent_t e0 = prof_begin(h, KKT_K_INGEST, s);
     for (int b = 0; b < count; ++b) {
         DevLayout &d = hs[b]->d;
-        if (vals[b]) {
+        if (tiles) {
+            const int64_t nx = (int64_t)a.ref.exp.size();
+            const int gx = (int)std::max<int64_t>(1, std::min<int64_t>((nx + 255) / 256, 1024));
+            if (precision == KKT_PREC_MIXED) k_prep_tiles<float><<<gx, 256, 0, s>>>(d.ctl, vals[b] != nullptr, nx, d.X32);
+            else k_prep_tiles<double><<<gx, 256, 0, s>>>(d.ctl, vals[b] != nullptr, nx, d.X64);
+        } else if (vals[b]) {
             k_prep_values<<<1, 1, 0, s>>>(d.ctl);
-            k_ingest_rows<<<ingest_grid(a.n), 256, 0, s>>>(a.n, d.ostart, d.krp, vals[b], d.kval, d.ctl);
         }
-        k_prep_refactor<<<1, 1, 0, s>>>(d.ctl);
-        k_arm<<<2048, 256, 0, s>>>(f, a.phys ? nullptr : d.fsrc, d.kval, d.F64, d.F32, d.Ld64, d.Ld32, precision);
+        if (vals[b])
+            k_ingest_rows<<<ingest_grid(a.n), 256, 0, s>>>(a.n, d.ostart, d.krp, vals[b], d.kval, d.ctl);
+        if (!tiles) {
+            k_prep_refactor<<<1, 1, 0, s>>>(d.ctl);
+            k_arm<<<2048, 256, 0, s>>>(f, a.phys ? nullptr : d.fsrc, d.kval, d.F64, d.F32, d.Ld64, d.Ld32, precision);
+        }
     }
     prof_end(h, KKT_K_INGEST, e0, s);
     hipError_t e = hipGetLastError();
@@ -2227,7 +2585,26 @@ kkt_status_t refactor_batch_impl(const kkt_handle_t *hs, const double *const *va
     e0 = prof_begin(h, KKT_K_REFACTOR, s);
     const DevLayout &d = h->d;
     const int64_t nitems = (int64_t)a.ref_item.size() - 1;
-    if (precision == KKT_PREC_MIXED) {
+    if (tiles) {
+        const RefTileArgs r{a.ref.tiles(), d.rt_desc, d.rt_seg, d.rt_src, d.rt_col, d.rt_item, d.rt_upd, d.rt_lq,
+                            d.rt_exp, d.rt_ext, d.rt_cmxn, d.rt_cmxs, d.rt_opos, d.rt_oslot, h->opts.guard_policy};
+        auto launch = [&](auto zero, int resident) {
+            using T = decltype(zero);
+            constexpr bool is64 = sizeof(T) == 8;
+            RefTileBatch<T> bt{};
+            bt.nslots = count;
+            for (int b = 0; b < count; ++b) {
+                const DevLayout &db = hs[b]->d;
+                bt.slot[b] = {(T *)(is64 ? (void *)db.T64 : (void *)db.T32), (T *)(is64 ? (void *)db.X64 : (void *)db.X32),
+                              db.ctl, db.kval};
+            }
+            const int grid = (int)std::min<int64_t>(resident, a.ref.tiles() * count);
+            if (count > 1) k_refactor_tiles<T, true><<<grid, kCoopBlock, (size_t)a.ref.lds, s>>>(r, bt);
+            else k_refactor_tiles<T, false><<<grid, kCoopBlock, (size_t)a.ref.lds, s>>>(r, bt);
+        };
+        if (precision == KKT_PREC_MIXED) launch(0.0f, h->grid_refactor32);
+        else launch(0.0, h->grid_refactor64);
+    } else if (precision == KKT_PREC_MIXED) {
         RefactorArgs<float> r{a.n, d.fp, d.fi, d.fdiag, d.relptr, d.relpos, d.order, d.clev, d.f2t, d.relsrc,
                               d.relslot, d.pc, d.pu, d.pnu, d.fsrc32, d.kval, d.item, d.item_lane, nitems, d.F32,
                               d.T32, d.Ld32,
@@ -2629,6 +3006,8 @@ AnalysisOptions analysis_options(const kkt_opts_t &o, int64_t n) {
     ao.narrow_columns = o.narrow_columns > 0
                             ? o.narrow_columns
                             : (int)std::max<int64_t>(kResidentRefactorWaves, std::min<int64_t>(16384, n / 64));
+    // tiles unless the caller sets the hand-out of single columns
+    ao.ref_lds = o.narrow_columns > 0 ? 0 : kRefTileLds;
     return ao;
 }
 
@@ -2940,6 +3319,21 @@ kkt_status_t kkt_bind_workspace(kkt_handle_t h, void *dev_ptr, size_t bytes, voi
     d.pnu = (int32_t *)(b + o.pnu);
     d.item = (int32_t *)(b + o.item);
     d.item_lane = (uint8_t *)(b + o.item_lane);
+    d.rt_desc = (int32_t *)(b + o.rt_desc);
+    d.rt_seg = (uint32_t *)(b + o.rt_seg);
+    d.rt_src = (int32_t *)(b + o.rt_src);
+    d.rt_col = (uint16_t *)(b + o.rt_col);
+    d.rt_item = (uint32_t *)(b + o.rt_item);
+    d.rt_upd = (uint32_t *)(b + o.rt_upd);
+    d.rt_lq = (uint16_t *)(b + o.rt_lq);
+    d.rt_exp = (uint16_t *)(b + o.rt_exp);
+    d.rt_ext = (int32_t *)(b + o.rt_ext);
+    d.rt_cmxn = (uint32_t *)(b + o.rt_cmxn);
+    d.rt_cmxs = (int32_t *)(b + o.rt_cmxs);
+    d.rt_opos = (int32_t *)(b + o.rt_opos);
+    d.rt_oslot = (uint16_t *)(b + o.rt_oslot);
+    d.X64 = (double *)(b + o.X64);
+    d.X32 = (float *)(b + o.X32);
     d.krp = (int64_t *)(b + o.krp);
     d.kci = (int32_t *)(b + o.kci);
     d.l_rows = (int32_t *)(b + o.l_rows);
@@ -2991,28 +3385,45 @@ kkt_status_t kkt_bind_workspace(kkt_handle_t h, void *dev_ptr, size_t bytes, voi
     d.xi = (double *)(b + o.xi);
     d.part = (double *)(b + o.part);
     d.ctl = (Control *)(b + o.ctl);
-    KKT_HIP(h, up(b, o.fp, a.fp, s));
-    KKT_HIP(h, up(b, o.fi, a.fi, s));
-    KKT_HIP(h, up(b, o.fdiag, a.fdiag, s));
-    KKT_HIP(h, up(b, o.order, a.col_order, s));
-    KKT_HIP(h, up(b, o.clev, a.col_level, s));
-    KKT_HIP(h, up(b, o.f2t, a.f2t, s));
-    KKT_HIP(h, up(b, o.relptr, a.relptr, s));
-    if (a.phys) {
-        const std::vector<int32_t> f32(a.fsrc_k.begin(), a.fsrc_k.end());
-        KKT_HIP(h, up(b, o.fsrc32, f32, s));
-        KKT_HIP(h, hipStreamSynchronize(s));  // f32 is a local
+    if (a.ref.tiles() > 0) {
+        const RefTiles &t = a.ref;
+        KKT_HIP(h, up(b, o.rt_desc, t.desc, s));
+        KKT_HIP(h, up(b, o.rt_seg, t.seg, s));
+        KKT_HIP(h, up(b, o.rt_src, t.src, s));
+        KKT_HIP(h, up(b, o.rt_col, t.col, s));
+        KKT_HIP(h, up(b, o.rt_item, t.item, s));
+        KKT_HIP(h, up(b, o.rt_upd, t.upd, s));
+        KKT_HIP(h, up(b, o.rt_lq, t.lq, s));
+        KKT_HIP(h, up(b, o.rt_exp, t.exp, s));
+        KKT_HIP(h, up(b, o.rt_ext, t.ext, s));
+        KKT_HIP(h, up(b, o.rt_cmxn, t.cmx_node, s));
+        KKT_HIP(h, up(b, o.rt_cmxs, t.cmx_src, s));
+        KKT_HIP(h, up(b, o.rt_opos, t.out_pos, s));
+        KKT_HIP(h, up(b, o.rt_oslot, t.out_slot, s));
     } else {
-        KKT_HIP(h, up(b, o.fsrc, a.fsrc_k, s));
+        KKT_HIP(h, up(b, o.fp, a.fp, s));
+        KKT_HIP(h, up(b, o.fi, a.fi, s));
+        KKT_HIP(h, up(b, o.fdiag, a.fdiag, s));
+        KKT_HIP(h, up(b, o.order, a.col_order, s));
+        KKT_HIP(h, up(b, o.clev, a.col_level, s));
+        KKT_HIP(h, up(b, o.f2t, a.f2t, s));
+        KKT_HIP(h, up(b, o.relptr, a.relptr, s));
+        if (a.phys) {
+            const std::vector<int32_t> f32(a.fsrc_k.begin(), a.fsrc_k.end());
+            KKT_HIP(h, up(b, o.fsrc32, f32, s));
+            KKT_HIP(h, hipStreamSynchronize(s));  // f32 is a local
+        } else {
+            KKT_HIP(h, up(b, o.fsrc, a.fsrc_k, s));
+        }
+        KKT_HIP(h, up(b, o.relpos, a.relpos, s));
+        KKT_HIP(h, up(b, o.relsrc, a.relsrc, s));
+        KKT_HIP(h, up(b, o.relslot, a.relslot, s));
+        KKT_HIP(h, up(b, o.pc, a.pc, s));
+        KKT_HIP(h, up(b, o.pu, a.pu, s));
+        KKT_HIP(h, up(b, o.pnu, a.pnu, s));
+        KKT_HIP(h, up(b, o.item, a.ref_item, s));
+        KKT_HIP(h, up(b, o.item_lane, a.ref_item_lane, s));
     }
-    KKT_HIP(h, up(b, o.relpos, a.relpos, s));
-    KKT_HIP(h, up(b, o.relsrc, a.relsrc, s));
-    KKT_HIP(h, up(b, o.relslot, a.relslot, s));
-    KKT_HIP(h, up(b, o.pc, a.pc, s));
-    KKT_HIP(h, up(b, o.pu, a.pu, s));
-    KKT_HIP(h, up(b, o.pnu, a.pnu, s));
-    KKT_HIP(h, up(b, o.item, a.ref_item, s));
-    KKT_HIP(h, up(b, o.item_lane, a.ref_item_lane, s));
     KKT_HIP(h, up(b, o.krp, a.krp, s));
     KKT_HIP(h, up(b, o.kci, a.kci, s));
     {
@@ -3077,6 +3488,13 @@ kkt_status_t kkt_bind_workspace(kkt_handle_t h, void *dev_ptr, size_t bytes, voi
     h->grid_refactor32 = std::max(kWorkQueues, std::min(cap, coop_grid(flat ? (const void *)k_refactor<float, true>
                                                                             : (const void *)k_refactor<float, false>,
                                                                        h->device)));
+    if (a.ref.tiles() > 0) {
+        const size_t lds = (size_t)a.ref.lds;
+        h->grid_refactor64 = std::min(coop_grid((const void *)k_refactor_tiles<double, false>, h->device, lds),
+                                      coop_grid((const void *)k_refactor_tiles<double, true>, h->device, lds));
+        h->grid_refactor32 = std::min(coop_grid((const void *)k_refactor_tiles<float, false>, h->device, lds),
+                                      coop_grid((const void *)k_refactor_tiles<float, true>, h->device, lds));
+    }
     h->grid_trsv64 = std::min(std::min(coop_grid((const void *)k_trsv<double, true, true>, h->device, h->tile_lds),
                                        coop_grid((const void *)k_trsv<double, false, true>, h->device, h->tile_lds)),
                               std::min(coop_grid((const void *)k_trsv<double, true, false>, h->device, h->tile_lds),

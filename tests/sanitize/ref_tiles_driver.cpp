@@ -1,0 +1,161 @@
+// Host-only replay of the refactorization's tile schedule (RefTiles), built with
+// AddressSanitizer and UndefinedBehaviorSanitizer by tests/test_ref_tiles.py: reads a CSR system
+// from a binary file (int64 n, int64 nnz, double tau, int32 ordering, int32 ref_lds; then rowptr,
+// colidx, values of system 1, values of system 2), runs the analysis and refactors system 2 as
+// the tile kernel does: tiles in hand-out order, entries and externals in slots, segments of
+// items (each entry read before it is final, each export read before it is written, and each
+// solve-layout position written twice or never is an error), the pivot guard with column
+// maxima gathered from the tile's own entries and its extras.  Writes L and U in exchange
+// layout and prints tiles=<count> layers=<count> refactor=<ok or the first violated property>.
+#include <cmath>
+#include <cstdio>
+#include <cstdint>
+#include <limits>
+#include <string>
+#include <vector>
+
+#include "../../paper_2401_13926_amd/csrc/analysis.hpp"
+
+namespace {
+
+const double kNaN = std::numeric_limits<double>::quiet_NaN();
+
+std::string replay(const kkt::Analysis &a, int64_t budget, const std::vector<double> &vals, std::vector<double> &lx,
+                   std::vector<double> &ux, int64_t &guarded) {
+    const kkt::RefTiles &t = a.ref;
+    std::vector<double> kval(a.ksrc.size()), tv(a.t_size, 0.0), X(t.exp.size(), kNaN);
+    for (size_t k = 0; k < kval.size(); ++k) kval[k] = vals[a.ksrc[k]];
+    std::vector<int> written(a.t_size, 0);
+    guarded = 0;
+    int64_t entries = 0, nodes = 0;
+    for (int64_t ti = 0; ti < t.tiles(); ++ti) {
+        const int32_t *d = t.desc.data() + kkt::kRefDesc * ti;
+        const int32_t ns = d[1], ne = d[3], ni = d[5], nu = d[7], nl = d[9], nx = d[13], nn = d[14];
+        entries += ne;
+        nodes += nn;
+        if (kkt::ref_lds_bytes(8, ne, nx, nn, nu, ni, nl) > budget) return "lds_budget";
+        std::vector<double> xs(ne + nx), cm(nn, 0.0);
+        for (int32_t e = 0; e < ne; ++e) {
+            const int32_t s = t.src.at(d[2] + e);
+            xs[e] = s >= 0 ? kval.at(s) : 0.0;
+            const uint16_t c = t.col.at(d[2] + e);
+            if (c != 0xFFFF) cm.at(c) = std::fmax(cm[c], std::fabs(xs[e]));
+        }
+        for (int32_t k = 0; k < d[16]; ++k) {
+            double &c = cm.at(t.cmx_node.at(d[15] + k));
+            c = std::fmax(c, std::fabs(kval.at(t.cmx_src.at(d[15] + k))));
+        }
+        for (int32_t k = 0; k < nx; ++k) {
+            xs[ne + k] = X.at(t.ext.at(d[12] + k));
+            if (std::isnan(xs[ne + k])) return "external_not_final";
+        }
+        std::vector<uint8_t> final_(ne + nx, 0);
+        for (int32_t k = 0; k < nx; ++k) final_[ne + k] = 1;
+        int32_t i0 = 0, n0 = 0, q0 = 0, x0 = 0;
+        for (int32_t g = 0; g < ns; ++g) {
+            const uint32_t w0 = t.seg.at(3 * (d[0] + g)), w1 = t.seg.at(3 * (d[0] + g) + 1);
+            const int32_t i1 = w0 & 0xFFFF, sl0 = w0 >> 16, n1 = w1 & 0xFFFF, q1 = w1 >> 16;
+            const int32_t x1 = (int32_t)t.seg.at(3 * (d[0] + g) + 2), nd = n1 - n0;
+            if (nd < 1 || sl0 + nd + (q1 - q0) > ne) return "segment_shape";
+            std::vector<uint8_t> touched(ne, 0);
+            for (int32_t i = i0; i < i1; ++i) {
+                const uint32_t ia = t.item.at(d[4] + i), ie = t.item.at(d[4] + i + 1);
+                const uint32_t s = ia & 0xFFFF;
+                if ((int32_t)s >= ne || final_[s] || touched[s]++) return "item_target";
+                if ((ie >> 16) <= (ia >> 16) || (int32_t)(ie >> 16) > nu) return "item_updates";
+                for (uint32_t u = ia >> 16; u < ie >> 16; ++u) {
+                    const uint32_t p = t.upd.at(d[6] + u);
+                    if (!final_.at(p & 0xFFFF) || !final_.at(p >> 16)) return "factor_not_final";
+                    const double prod = xs[p & 0xFFFF] * xs[p >> 16];
+                    xs[s] = xs[s] - prod;
+                }
+            }
+            for (int32_t k = 0; k < nd; ++k) {
+                double &p = xs[sl0 + k];
+                const double c = cm.at(n0 + k) > 0.0 ? cm[n0 + k] : 1.0;
+                if (!(std::fabs(p) > 0x1p-53 * c) || !std::isfinite(p)) {
+                    p = (p < 0.0 ? -1.0 : 1.0) * 0x1p-53 * c;
+                    ++guarded;
+                }
+                final_[sl0 + k] = 1;
+            }
+            for (int32_t q = q0; q < q1; ++q) {
+                const int32_t node = t.lq.at(d[8] + q);
+                if (node >= nd) return "l_node";
+                const int32_t e = sl0 + nd + (q - q0);
+                xs[e] = xs[e] / xs[sl0 + node];
+                final_[e] = 1;
+            }
+            // the rest of the segment's slots are its nodes' U entries
+            const int32_t end = g + 1 < ns ? (int32_t)(t.seg.at(3 * (d[0] + g + 1)) >> 16) : ne;
+            for (int32_t e = sl0 + nd + (q1 - q0); e < end; ++e) final_[e] = 1;
+            for (int32_t k = x0; k < x1; ++k) {
+                const uint16_t e = t.exp.at(d[10] + k);
+                if (!final_.at(e)) return "export_not_final";
+                X.at(d[10] + k) = xs[e];
+            }
+            i0 = i1;
+            n0 = n1;
+            q0 = q1;
+            x0 = x1;
+        }
+        if (i0 != ni || n0 != nn || q0 != nl || x0 != d[11]) return "segment_totals";
+        for (int32_t e = 0; e < ne; ++e) {
+            const int32_t pos = t.out_pos.at(d[2] + e);
+            if (e && pos <= t.out_pos[d[2] + e - 1]) return "out_order";
+            if (written.at(pos)++) return "written_twice";
+            tv[pos] = xs.at(t.out_slot.at(d[2] + e));
+        }
+    }
+    if (entries != a.nnz_f() || nodes != a.n) return "entries_lost";
+    lx.resize(a.nnz_l());
+    ux.resize(a.nnz_u());
+    for (size_t p = 0; p < lx.size(); ++p) lx[p] = tv.at(a.f2t.at(a.l2f[p]));
+    for (size_t p = 0; p < ux.size(); ++p) ux[p] = tv.at(a.f2t.at(a.u2f[p]));
+    return "ok";
+}
+
+}  // namespace
+
+int main(int argc, char **argv) {
+    if (argc != 3) return 2;
+    std::FILE *f = std::fopen(argv[1], "rb");
+    if (!f) return 2;
+    int64_t n = 0, nnz = 0;
+    double tau = 0.0;
+    int32_t ordering = 0, lds = 0;
+    bool ok = std::fread(&n, 8, 1, f) == 1 && std::fread(&nnz, 8, 1, f) == 1 && std::fread(&tau, 8, 1, f) == 1 &&
+              std::fread(&ordering, 4, 1, f) == 1 && std::fread(&lds, 4, 1, f) == 1;
+    std::vector<int64_t> rp(ok ? n + 1 : 0);
+    std::vector<int32_t> ci(ok ? nnz : 0);
+    std::vector<double> v(ok ? nnz : 0), v2(ok ? nnz : 0);
+    ok = ok && std::fread(rp.data(), 8, rp.size(), f) == rp.size() && std::fread(ci.data(), 4, ci.size(), f) == ci.size() &&
+         std::fread(v.data(), 8, v.size(), f) == v.size() && std::fread(v2.data(), 8, v2.size(), f) == v2.size();
+    std::fclose(f);
+    if (!ok) return 2;
+    kkt::AnalysisOptions opt;
+    opt.ordering = ordering;
+    opt.pivot_tau = tau;
+    opt.ref_lds = lds;
+    kkt::Analysis a;
+    std::string msg;
+    const int rc = kkt::analyze(opt, n, rp.data(), ci.data(), v.data(), a, &msg);
+    if (rc != kkt::AN_OK) return 3;
+    std::printf("tiles=%lld layers=%lld ", (long long)a.ref.tiles(), (long long)a.ref.layers);
+    if (a.ref.tiles() > 0) {
+        std::vector<double> lx, ux;
+        int64_t guarded = 0;
+        const std::string r = replay(a, lds, v2, lx, ux, guarded);
+        std::printf("refactor=%s guarded=%lld", r.c_str(), (long long)guarded);
+        if (r == "ok") {
+            std::FILE *o = std::fopen(argv[2], "wb");
+            if (!o) return 2;
+            const bool w = std::fwrite(lx.data(), 8, lx.size(), o) == lx.size() &&
+                           std::fwrite(ux.data(), 8, ux.size(), o) == ux.size();
+            std::fclose(o);
+            if (!w) return 2;
+        }
+    }
+    std::printf("\n");
+    return 0;
+}
