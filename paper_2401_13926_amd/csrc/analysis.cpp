@@ -1144,21 +1144,249 @@ void build_vector_order(Analysis &a) {
     }
 }
 
-// The refactorization's tile schedule (RefTiles).  Leaves a.ref empty when the patterns of L and
-// U differ or a single node does not fit a tile; the hand-out items are used then.
-void build_ref_tiles(const AnalysisOptions &opt, Analysis &a) {
+// Tiles and layers of a symmetric factor's elimination tree: repeatedly, the maximal subtrees (of
+// what is left of the tree) whose cost fits `budget` are packed into tiles.  own(m): node m's
+// cost; entered(k, p): what an already placed node k adds to the cost of the subtree it enters
+// at its column's F position p (the first row of k's column that is still left); rooted(m):
+// what a subtree costs besides when m is its root.  Returns false when some node does not fit.
+template <typename Own, typename Entered, typename Rooted>
+bool subtree_tiles(const Analysis &a, int64_t budget, Own own, Entered entered, Rooted rooted,
+                   std::vector<int32_t> &tile_of, std::vector<std::vector<int32_t>> &members, int64_t &layers) {
+    const int64_t n = a.n;
+    auto l0 = [&](int64_t m) { return a.fp[m] + a.fdiag[m] + 1; };
+    tile_of.assign(n, -1);
+    members.clear();
+    layers = 0;
+    std::vector<int64_t> cost(n);
+    std::vector<int32_t> root(n, -1), tile_of_root(n, -1), roots;
+    std::vector<uint8_t> fit(n);
+    int64_t left = n;
+    while (left > 0) {
+        for (int64_t m = 0; m < n; ++m) {
+            cost[m] = tile_of[m] < 0 ? own(m) : 0;
+            fit[m] = 1;
+        }
+        for (int64_t k = 0; k < n; ++k) {
+            if (tile_of[k] < 0) continue;
+            for (int64_t p = l0(k); p < a.fp[k + 1]; ++p)
+                if (tile_of[a.fi[p]] < 0) {
+                    cost[a.fi[p]] += entered(k, p);
+                    break;
+                }
+        }
+        roots.clear();
+        for (int64_t m = 0; m < n; ++m) {
+            if (tile_of[m] >= 0) continue;
+            fit[m] = fit[m] && cost[m] + rooted(m) <= budget;
+            if (l0(m) == a.fp[m + 1]) continue;
+            const int32_t up = a.fi[l0(m)];
+            if (fit[m]) cost[up] += cost[m];
+            else fit[up] = 0;
+        }
+        for (int64_t m = n - 1; m >= 0; --m) {
+            if (tile_of[m] >= 0 || !fit[m]) continue;
+            const int64_t up = l0(m) < a.fp[m + 1] ? a.fi[l0(m)] : -1;
+            if (up >= 0 && fit[up]) {
+                root[m] = root[up];
+            } else {
+                root[m] = (int32_t)m;
+                roots.push_back((int32_t)m);
+            }
+        }
+        if (roots.empty()) return false;
+        // subtrees packed in the order of their roots in the vector order (entries of nearby rows
+        // of K's copy)
+        std::sort(roots.begin(), roots.end(), [&](int32_t x, int32_t y) { return a.q_k[x] < a.q_k[y]; });
+        int64_t fill = -1;
+        for (int32_t r : roots) {
+            const int64_t c = cost[r] + rooted(r);
+            if (fill < 0 || fill + c > budget) {
+                members.emplace_back();
+                fill = 0;
+            }
+            fill += c;
+            tile_of_root[r] = (int32_t)members.size() - 1;
+        }
+        for (int64_t m = 0; m < n; ++m) {
+            if (tile_of[m] >= 0 || !fit[m]) continue;
+            tile_of[m] = tile_of_root[root[m]];
+            members[tile_of[m]].push_back((int32_t)m);
+            --left;
+        }
+        ++layers;
+    }
+    return true;
+}
+
+// Whether the factor's patterns are each other's transposes: column m of L and row m of U have
+// the same indices.
+bool symmetric_factor(const Analysis &a) {
+    for (int64_t m = 0; m < a.n; ++m) {
+        const int64_t l0 = a.fp[m] + a.fdiag[m] + 1;
+        if (a.urp[m + 1] - a.urp[m] != a.fp[m + 1] - l0) return false;
+        if (!std::equal(a.uci.begin() + a.urp[m], a.uci.begin() + a.urp[m + 1], a.fi.begin() + l0)) return false;
+    }
+    return true;
+}
+
+// The solves' tile schedule (SolveTiles) and the solve layout that goes with it: T = [L places | U
+// places | U diagonal, by U position].  Sets a.f2t and a.t_size; returns false (nothing changed)
+// when a row does not fit a tile.
+bool build_solve_tiles(const AnalysisOptions &opt, Analysis &a) {
+    const int64_t n = a.n;
+    SolveTiles t;
+    auto l0 = [&](int64_t m) { return a.fp[m] + a.fdiag[m] + 1; };
+    auto deg = [&](int64_t m) { return a.fp[m + 1] - l0(m); };
+    std::vector<int32_t> tile_of;
+    std::vector<std::vector<int32_t>> members;
+    // a row's cost: its slots, and its L or U entries (a third more for places without an entry)
+    auto own = [&](int64_t m) { return 24 + 10 * (4 * std::max(deg(m), a.lrp[m + 1] - a.lrp[m]) / 3); };
+    auto entered = [&](int64_t, int64_t) { return (int64_t)8; };
+    auto rooted = [&](int64_t m) { return 8 * deg(m); };
+    if (!subtree_tiles(a, opt.sol_lds - 64, own, entered, rooted, tile_of, members, t.layers)) return false;
+    std::vector<int32_t> seg_of(n, 0), slot(n, 0), pos_l(n, -1), pos_u(n, -1);
+    std::vector<int32_t> lmap(a.lrp[n]), umap(a.urp[n]);  // CSR entry -> place (global)
+    std::vector<int32_t> ext_slot(n, -1);
+    // positions first (externals refer to them)
+    std::vector<std::vector<int32_t>> rows_l(members.size()), rows_u(members.size());
+    int64_t base = 0;
+    for (size_t ti = 0; ti < members.size(); ++ti) {
+        for (int dir = 0; dir < 2; ++dir) {
+            std::vector<int32_t> rows = members[ti];
+            if (dir) std::reverse(rows.begin(), rows.end());
+            const std::vector<int64_t> &rp = dir ? a.urp : a.lrp;
+            const std::vector<int32_t> &ci = dir ? a.uci : a.lci;
+            for (int32_t m : rows) {
+                int32_t g = 0;
+                for (int64_t p = rp[m]; p < rp[m + 1]; ++p)
+                    if (tile_of[ci[p]] == (int32_t)ti) g = std::max(g, seg_of[ci[p]] + 1);
+                seg_of[m] = g;
+            }
+            // by segment, longer rows first
+            std::stable_sort(rows.begin(), rows.end(), [&](int32_t x, int32_t y) {
+                if (seg_of[x] != seg_of[y]) return seg_of[x] < seg_of[y];
+                return rp[x + 1] - rp[x] > rp[y + 1] - rp[y];
+            });
+            for (size_t r = 0; r < rows.size(); ++r) (dir ? pos_u : pos_l)[rows[r]] = (int32_t)(base + r);
+            (dir ? rows_u : rows_l)[ti].swap(rows);
+        }
+        base += (int64_t)members[ti].size();
+    }
+    constexpr int32_t kMinor = 12;
+    auto sweep = [&](size_t ti, int dir, int32_t *d, std::vector<uint32_t> &chunk, std::vector<uint16_t> &ref,
+                     std::vector<int32_t> &ext, std::vector<int32_t> &map) -> bool {
+        const std::vector<int64_t> &rp = dir ? a.urp : a.lrp;
+        const std::vector<int32_t> &ci = dir ? a.uci : a.lci;
+        const std::vector<int32_t> &rows = dir ? rows_u[ti] : rows_l[ti];
+        const std::vector<int32_t> &pos = dir ? pos_u : pos_l;
+        const int32_t nr = (int32_t)rows.size();
+        d[0] = (int32_t)(chunk.size() / 2);
+        d[2] = (int32_t)ref.size();
+        d[4] = (int32_t)ext.size();
+        for (int32_t r = 0; r < nr; ++r) {
+            slot[rows[r]] = r;
+            int32_t g = 0;
+            for (int64_t p = rp[rows[r]]; p < rp[rows[r] + 1]; ++p)
+                if (tile_of[ci[p]] == (int32_t)ti) g = std::max(g, seg_of[ci[p]] + 1);
+                else if (ext_slot[ci[p]] < 0) {
+                    ext_slot[ci[p]] = 1;
+                    ext.push_back(ci[p]);
+                }
+            seg_of[rows[r]] = g;
+        }
+        // the external that is written last comes first: the closest tile of the sweep
+        std::sort(ext.begin() + d[4], ext.end(),
+                  [&](int32_t x, int32_t y) { return dir ? pos[x] < pos[y] : pos[x] > pos[y]; });
+        d[5] = (int32_t)(ext.size() - d[4]);
+        for (int32_t k = 0; k < d[5]; ++k) ext_slot[ext[d[4] + k]] = nr + k;
+        const int32_t zero = nr + d[5];
+        if (zero >= 8191) return false;
+        bool prev_single = false;
+        for (int32_t r = 0; r < nr;) {
+            int32_t re = r;
+            while (re < nr && seg_of[rows[re]] == seg_of[rows[r]]) ++re;
+            // chunks of the segment [r, re)
+            const size_t c0 = chunk.size();
+            for (int32_t q = r; q < re;) {
+                const int64_t len = rp[rows[q] + 1] - rp[rows[q]];  // the longest row left
+                int lg = 0;  // about eight entries per lane, fewer lanes rather than another pass
+                while (lg < 6 && ((int64_t)8 << lg) < len) ++lg;
+                while (lg > 0 && ((int64_t)(re - q) << lg) > 64 && ((int64_t)16 << lg) > len) --lg;
+                const int64_t g = (int64_t)1 << lg, half = (len + 2 * g - 1) / (2 * g), D = 2 * half;
+                // a pass holds 64 >> lg rows; a dozen rows or more with less than half as many
+                // places get a pass of their own
+                int32_t cnt = std::min<int32_t>(re - q, 64 >> lg);
+                for (int32_t c = 1; c < cnt; ++c)
+                    if (half >= 2 && re - q - c >= kMinor && rp[rows[q + c] + 1] - rp[rows[q + c]] <= g * half) cnt = c;
+                if (half > 255) return false;
+                const int64_t off = (int64_t)ref.size() - d[2];
+                chunk.push_back((uint32_t)q | ((uint32_t)cnt << 13) | ((uint32_t)lg << 20) | ((uint32_t)half << 23));
+                chunk.push_back((uint32_t)off);
+                ref.resize(ref.size() + (size_t)(cnt * g * D), (uint16_t)(8 * zero));
+                for (int32_t c = 0; c < cnt; ++c) {
+                    const int32_t m = rows[q + c];
+                    for (int64_t p = rp[m], e = 0; p < rp[m + 1]; ++p, ++e) {
+                        const int64_t at = d[2] + off + ((c << lg) + (e & (g - 1))) * D + (e >> lg);
+                        map[p] = (int32_t)at;
+                        ref[at] = (uint16_t)(8 * (tile_of[ci[p]] == (int32_t)ti ? slot[ci[p]] : ext_slot[ci[p]]));
+                    }
+                }
+                q += cnt;
+            }
+            const size_t nc = (chunk.size() - c0) / 2;
+            const bool single = nc == 1;
+            if (r > 0 && !(single && prev_single)) chunk[c0] |= 1u << 31;
+            for (size_t c = 0; c < nc; ++c) chunk[c0 + 2 * c + 1] |= (uint32_t)(c % 4) << 30;
+            prev_single = single;
+            r = re;
+        }
+        for (int32_t k = 0; k < d[5]; ++k) {
+            ext_slot[ext[d[4] + k]] = -1;
+            ext[d[4] + k] = pos[ext[d[4] + k]];
+        }
+        d[1] = (int32_t)(chunk.size() / 2) - d[0];
+        d[3] = (int32_t)ref.size() - d[2];
+        t.lds = std::max(t.lds, sol_lds_bytes(nr, d[5], d[3]));
+        return d[3] < (1 << 30);
+    };
+    base = 0;
+    for (size_t ti = 0; ti < members.size(); ++ti) {
+        int32_t d[kSolDesc] = {};
+        d[0] = (int32_t)base;
+        d[1] = (int32_t)members[ti].size();
+        if (d[1] >= 8191 || !sweep(ti, 0, d + 2, t.chunk_l, t.ref_l, t.ext_l, lmap) ||
+            !sweep(ti, 1, d + 8, t.chunk_u, t.ref_u, t.ext_u, umap))
+            return false;
+        t.desc.insert(t.desc.end(), d, d + kSolDesc);
+        t.node_l.insert(t.node_l.end(), rows_l[ti].begin(), rows_l[ti].end());
+        t.node_u.insert(t.node_u.end(), rows_u[ti].begin(), rows_u[ti].end());
+        base += d[1];
+    }
+    const int64_t ub = (int64_t)t.ref_l.size(), db = ub + (int64_t)t.ref_u.size();
+    if (db + n >= (int64_t)std::numeric_limits<int32_t>::max() || t.lds > 64 * 1024) return false;
+    t.pos_u.resize(n);
+    for (int64_t p = 0; p < n; ++p) t.pos_u[p] = pos_l[t.node_u[p]];
+    std::vector<int64_t> lnext(a.lrp.begin(), a.lrp.end() - 1), unext(a.urp.begin(), a.urp.end() - 1);
+    for (int64_t j = 0; j < n; ++j)  // columns ascending -> each row's entries in CSR order
+        for (int64_t f = a.fp[j]; f < a.fp[j + 1]; ++f) {
+            const int32_t r = a.fi[f];
+            if (r < j) a.f2t[f] = (int32_t)(ub + umap[unext[r]++]);
+            else if (r == j) a.f2t[f] = (int32_t)(db + pos_u[j]);
+            else a.f2t[f] = lmap[lnext[r]++];
+        }
+    a.t_size = db + n;
+    a.sol = std::move(t);
+    return true;
+}
+
+// The refactorization's tile schedule (RefTiles).  Returns false, leaving a.ref empty, when a single
+// node does not fit a tile.
+bool build_ref_tiles(const AnalysisOptions &opt, Analysis &a) {
     const int64_t n = a.n;
     RefTiles &t = a.ref;
     t = RefTiles();
-    if (opt.ref_lds <= 0 || n < 1) return;
-    // node m: column m of L (rows srow(m, .), ascending) and row m of U have the same indices
     auto l0 = [&](int64_t m) { return a.fp[m] + a.fdiag[m] + 1; };
     auto deg = [&](int64_t m) { return a.fp[m + 1] - l0(m); };
-    if (a.lrp[n] != a.urp[n]) return;
-    for (int64_t m = 0; m < n; ++m) {
-        if (a.urp[m + 1] - a.urp[m] != deg(m)) return;
-        if (!std::equal(a.uci.begin() + a.urp[m], a.uci.begin() + a.urp[m + 1], a.fi.begin() + l0(m))) return;
-    }
     // F positions of U's entries by rows, and for the entries of L's rows (sources of a node)
     // their offset within the source's column
     std::vector<int32_t> upos(a.urp[n]);
@@ -1170,74 +1398,21 @@ void build_ref_tiles(const AnalysisOptions &opt, Analysis &a) {
             for (int64_t p = l0(j); p < a.fp[j + 1]; ++p) loff[lnext[a.fi[p]]++] = (int32_t)(p - l0(j));
         }
     }
-    // layers of tiles
-    std::vector<int32_t> tile_of(n, -1), root(n, -1);
-    std::vector<int64_t> own(n), cost(n);
-    for (int64_t m = 0; m < n; ++m) {
-        int64_t upd = 0;
-        for (int64_t p = a.lrp[m]; p < a.lrp[m + 1]; ++p) upd += 1 + 2 * (deg(a.lci[p]) - loff[p] - 1);
-        // an item has at least one update
-        own[m] = ref_lds_bytes(8, 1 + 2 * deg(m), 0, 1, upd, upd, deg(m)) - 20;
-    }
-    std::vector<uint8_t> fit(n);
+    std::vector<int32_t> tile_of;
     std::vector<std::vector<int32_t>> members;  // nodes of each tile, ascending
-    int64_t left = n;
-    while (left > 0) {
+    {
+        std::vector<int64_t> own(n);
         for (int64_t m = 0; m < n; ++m) {
-            cost[m] = tile_of[m] < 0 ? own[m] : 0;
-            fit[m] = 1;
+            int64_t upd = 0;
+            for (int64_t p = a.lrp[m]; p < a.lrp[m + 1]; ++p) upd += 1 + 2 * (deg(a.lci[p]) - loff[p] - 1);
+            // an item has at least one update
+            own[m] = ref_lds_bytes(8, 1 + 2 * deg(m), 0, 1, upd, upd, deg(m)) - 28;
         }
-        for (int64_t k = 0; k < n; ++k) {
-            if (tile_of[k] < 0) continue;
-            for (int64_t p = l0(k); p < a.fp[k + 1]; ++p)
-                if (tile_of[a.fi[p]] < 0) {
-                    cost[a.fi[p]] += 8 * 2 * (a.fp[k + 1] - p);
-                    break;
-                }
-        }
-        std::vector<int32_t> roots;
-        for (int64_t m = 0; m < n; ++m) {
-            if (tile_of[m] >= 0) continue;
-            fit[m] = fit[m] && cost[m] + 20 <= opt.ref_lds;
-            if (deg(m) == 0) continue;
-            const int32_t up = a.fi[l0(m)];
-            if (fit[m]) cost[up] += cost[m];
-            else fit[up] = 0;
-        }
-        for (int64_t m = n - 1; m >= 0; --m) {
-            if (tile_of[m] >= 0 || !fit[m]) continue;
-            const int64_t up = deg(m) ? a.fi[l0(m)] : -1;
-            if (up >= 0 && fit[up]) {
-                root[m] = root[up];
-            } else {
-                root[m] = (int32_t)m;
-                roots.push_back((int32_t)m);
-            }
-        }
-        if (roots.empty()) {
-            t = RefTiles();
-            return;
-        }
-        // subtrees packed in the order of their roots in the vector order (entries of nearby rows
-        // of K's copy)
-        std::sort(roots.begin(), roots.end(), [&](int32_t x, int32_t y) { return a.q_k[x] < a.q_k[y]; });
-        std::vector<int32_t> tile_of_root(n, -1);
-        int64_t fill = 0;
-        for (int32_t r : roots) {
-            if (members.empty() || fill < 0 || fill + cost[r] + 20 > opt.ref_lds || fill == 0) {
-                members.emplace_back();
-                fill = 0;
-            }
-            fill += cost[r];
-            tile_of_root[r] = (int32_t)members.size() - 1;
-        }
-        for (int64_t m = 0; m < n; ++m) {
-            if (tile_of[m] >= 0 || !fit[m]) continue;
-            tile_of[m] = tile_of_root[root[m]];
-            members[tile_of[m]].push_back((int32_t)m);
-            --left;
-        }
-        ++t.layers;
+        // a placed node's column and row from its first index in the subtree on are externals
+        if (!subtree_tiles(a, opt.ref_lds - 28, [&](int64_t m) { return own[m]; },
+                           [&](int64_t k, int64_t p) { return 8 * 2 * (a.fp[k + 1] - p); },
+                           [](int64_t) { return (int64_t)0; }, tile_of, members, t.layers))
+            return false;
     }
     // exports: entries whose other index is in another (later) tile; the export of each entry
     std::vector<int32_t> export_of(a.nnz_f(), -1);
@@ -1289,7 +1464,7 @@ void build_ref_tiles(const AnalysisOptions &opt, Analysis &a) {
             for (int32_t k = first[g]; k < first[g + 1]; ++k)
                 for (int64_t p = l0(nodes[k]); p < a.fp[nodes[k] + 1]; ++p) {
                     add((int32_t)p, nodes[k]);
-                    t.lq.push_back((uint16_t)(k - first[g]));
+                    t.lq.push_back((uint16_t)(8 * (seg_slot[g] + k - first[g])));
                     if (tile_of[a.fi[p]] != tid) {
                         export_of[p] = (int32_t)t.exp.size();
                         t.exp.push_back((uint16_t)slot[p]);
@@ -1330,11 +1505,11 @@ void build_ref_tiles(const AnalysisOptions &opt, Analysis &a) {
                 const int64_t lk = l0(k), uk = a.urp[k];
                 const int32_t at = tile_of[k] == tid ? seg_of[k] + 1 : 0;
                 const uint32_t lmk = slot_of(lk + loff[p], k), ukm = slot_of(upos[uk + loff[p]], k);
-                chain[0].emplace_back(lmk | (ukm << 16), at);
+                chain[0].emplace_back(8 * lmk | (8 * ukm << 16), at);
                 for (int64_t b = loff[p] + 1; b < deg(k); ++b) {
                     const int32_t q = where[a.fi[lk + b]];
-                    chain[1 + q].emplace_back(slot_of(lk + b, k) | (ukm << 16), at);
-                    chain[1 + s + q].emplace_back(lmk | (slot_of(upos[uk + b], k) << 16), at);
+                    chain[1 + q].emplace_back(8 * slot_of(lk + b, k) | (8 * ukm << 16), at);
+                    chain[1 + s + q].emplace_back(8 * lmk | (8 * slot_of(upos[uk + b], k) << 16), at);
                 }
             }
             for (int64_t e = 0; e < 1 + 2 * s; ++e) {
@@ -1362,7 +1537,7 @@ void build_ref_tiles(const AnalysisOptions &opt, Analysis &a) {
         for (int32_t k : order) {
             const Item &it = items[k];
             ++seg_item[it.seg + 1];
-            t.item.push_back((uint32_t)it.slot | ((uint32_t)(t.upd.size() - d[6]) << 16));
+            t.item.push_back((uint32_t)(8 * it.slot) | ((uint32_t)(t.upd.size() - d[6]) << 16));
             t.upd.insert(t.upd.end(), upds.begin() + it.first, upds.begin() + it.first + it.count);
         }
         t.item.push_back((uint32_t)(t.upd.size() - d[6]) << 16);
@@ -1397,11 +1572,24 @@ void build_ref_tiles(const AnalysisOptions &opt, Analysis &a) {
         t.desc.insert(t.desc.end(), d, d + kRefDesc);
         t.lds = std::max(t.lds, ref_lds_bytes(8, ne, d[13], d[14], d[7], d[5], d[9]));
         for (size_t e = ne; e < fpos.size(); ++e) ext_slot[fpos[e]] = -1;
-        if (t.lds > opt.ref_lds || ne + d[13] > 0xFFFF || d[7] > 0xFFFF || d[5] > 0xFFFF) {
+        if (t.lds > opt.ref_lds || ne + d[13] >= 8192 || d[7] > 0xFFFF || d[5] > 0xFFFF) {
             t = RefTiles();
-            return;
+            return false;
         }
     }
+    return true;
+}
+
+// Tiles for the refactorization and the solves, or none (both are built, or neither).
+void build_tiles(const AnalysisOptions &opt, Analysis &a) {
+    if (opt.ref_lds <= 0 || a.n < 1 || !symmetric_factor(a)) return;
+    const std::vector<int32_t> f2t = a.f2t;
+    const int64_t t_size = a.t_size;
+    if (build_solve_tiles(opt, a) && build_ref_tiles(opt, a)) return;
+    a.f2t = f2t;
+    a.t_size = t_size;
+    a.sol = SolveTiles();
+    a.ref = RefTiles();
 }
 
 // The device layout of the flat refactorization (see Analysis::phys): F positions and update
@@ -1496,7 +1684,7 @@ int analyze(const AnalysisOptions &opt, int64_t n, const int64_t *rowptr, const 
         rc = build_layouts(opt, a, msg);
         if (rc != AN_OK) return rc;
         build_vector_order(a);
-        build_ref_tiles(opt, a);
+        build_tiles(opt, a);
         if (!a.relsrc.empty()) build_phys_layout(a);
     } catch (const std::bad_alloc &) {
         *msg = "out of host memory";

@@ -32,6 +32,7 @@ struct AnalysisOptions {
     int narrow_columns = 1024;   // refactorization levels with at most this many columns are
                                  // handed out one column at a time
     int64_t ref_lds = 0;         // LDS bytes of a refactorization tile (0: no tiles)
+    int64_t sol_lds = 20480;     // LDS bytes a solve tile is formed for (with refactorization tiles)
 };
 
 // Flags in TriSchedule::seg_lg: the segment's rows fit one wavefront; the segment is a
@@ -114,9 +115,10 @@ struct RefTiles {
     std::vector<uint32_t> seg;
     std::vector<int32_t> src;     // per entry slot: its value's entry in the copy of K, or -1 (fill)
     std::vector<uint16_t> col;    // per entry slot: tile-local node of its column, 0xFFFF if none
+    // (slots in the next three are byte offsets, 8 x the slot: a tile has fewer than 8,192)
     std::vector<uint32_t> item;   // per item (and one past a tile's last): slot | first update << 16
     std::vector<uint32_t> upd;    // per update: slot of its L factor | slot of its U factor << 16
-    std::vector<uint16_t> lq;     // per L entry: its node's index within the segment
+    std::vector<uint16_t> lq;     // per L entry: slot of its node's pivot
     std::vector<uint16_t> exp;    // per export: slot (entries whose other index is in a later tile)
     std::vector<int32_t> ext;     // per external: the export it is
     std::vector<uint32_t> cmx_node;  // column-maximum extras: entries of K in a node's column whose
@@ -127,11 +129,44 @@ struct RefTiles {
     int64_t layers = 0;
     int64_t tiles() const { return (int64_t)desc.size() / kRefDesc; }
 };
-// LDS bytes of a refactorization tile with values of `word` bytes: entry and external slots,
-// column maxima; updates, items; L entries' nodes.
+// LDS bytes of a refactorization tile with values of `word` bytes: entry and external slots (8
+// bytes each for either precision), column maxima; updates, items; L entries' pivots.
 inline int64_t ref_lds_bytes(int64_t word, int64_t entries, int64_t ext, int64_t nodes, int64_t upd, int64_t items,
                              int64_t nl) {
-    return word * (entries + ext + nodes) + 4 * (upd + items + 1) + 2 * nl + 16;
+    return 8 * (entries + ext) + word * (nodes + 1) + 4 * (upd + items + 1) + 2 * nl + 16;
+}
+
+// Schedule of both triangular solves by tiles, built together with RefTiles (the same factors
+// qualify).  A tile is again a set of whole subtrees of what earlier layers left over, but
+// formed for the solves' own footprint.  The L sweep takes the tiles in order, the U sweep in
+// reverse; one launch runs both, each tile twice.
+//
+// Rows of a tile are ordered by segment (level inside the tile, of the sweep's own direction);
+// the solution of tile t's row r (L order) is position base + r of the exchange vector of the L
+// sweep, and likewise for U.  A segment's rows are cut into chunks of one wavefront pass: 2^lg
+// lanes per row, every lane with the same even number of (value, reference) places, so a
+// lane's places are at a fixed distance from each other and the chunk needs no row offsets;
+// places without an entry hold the value 0 and refer to a zero slot.
+constexpr int kSolDesc = 16;  // int32 per tile descriptor
+struct SolveTiles {
+    // per tile: 0 first position, 1 rows; for L at 2 and for U at 8: first chunk, chunks, first
+    // place, places, first external, externals
+    std::vector<int32_t> desc;
+    // per chunk two words: first row | rows << 13 | lg << 20 | places per lane / 2 << 23 (8 bits) |
+    // barrier before the chunk << 31; first place (within the tile) | wavefront << 30
+    std::vector<uint32_t> chunk_l, chunk_u;
+    std::vector<uint16_t> ref_l, ref_u;  // per place: 8 x the slot it refers to (rows, externals, zero)
+    std::vector<int32_t> ext_l, ext_u;   // per external: exchange position; a tile's first is the
+                                         // one expected to be written last
+    std::vector<int32_t> node_l, node_u;  // pivot step of every position (L order, U order)
+    std::vector<int32_t> pos_u;           // per U position: the L position of the same step
+    int64_t lds = 0;                      // LDS bytes of the largest tile
+    int64_t layers = 0;
+    int64_t tiles() const { return (int64_t)desc.size() / kSolDesc; }
+};
+// LDS bytes of a solve tile: row, external and zero slots, U's reciprocal diagonals, places.
+inline int64_t sol_lds_bytes(int64_t rows, int64_t ext, int64_t places) {
+    return 8 * (rows + ext + 2) + 8 * (rows + 1) + 10 * places + 32;
 }
 
 // Everything derived from the pattern and the first system's values.
@@ -185,7 +220,8 @@ struct Analysis {
     std::vector<int32_t> ref_item;
     std::vector<uint8_t> ref_item_lane;
 
-    RefTiles ref;  // empty when the factor does not qualify (the items above are used then)
+    RefTiles ref;    // empty when the factor does not qualify (the items above are used then)
+    SolveTiles sol;  // empty exactly when ref is (lsched and usched are used then)
 
     // Row-wise triangles in step space (strict L, strict U), from which the solve schedules
     // are built.  Solve layout T = [L values | strict U values | U diagonal (n, step order)],

@@ -972,9 +972,11 @@ __global__ void __launch_bounds__(kCoopBlock) k_refactor_tiles(RefTileArgs a, Re
         const int s0 = td[0], ns = td[1], ne = td[3], ni = td[5], nu = td[7], nl = td[9], nx = td[13], nn = td[14],
                   nc = td[16];
         const int64_t eb = td[2], ib = td[4], ub = td[6], lb = td[8], pb = td[10], xb = td[12], cb = td[15];
-        T *cm = reinterpret_cast<T *>(smem);                      // nn column maxima
-        T *xs = cm + nn;                                          // ne entries, nx externals
-        uint32_t *upd = reinterpret_cast<uint32_t *>(xs + ne + nx);  // nu
+        // (entry and external slots of 8 bytes first: updates and items name them by byte offset)
+        double *slots = reinterpret_cast<double *>(smem);
+        auto xs_at = [&](uint32_t off) -> T & { return *reinterpret_cast<T *>(smem + off); };
+        T *cm = reinterpret_cast<T *>(slots + ne + nx);           // nn column maxima
+        uint32_t *upd = reinterpret_cast<uint32_t *>(cm + nn + (nn & 1));  // nu
         uint32_t *item = upd + nu;                                // ni + 1
         uint16_t *lq = reinterpret_cast<uint16_t *>(item + ni + 1);  // nl
         for (int k = tid; k < nn; k += kCoopBlock) cm[k] = T(0);
@@ -1062,7 +1064,7 @@ __global__ void __launch_bounds__(kCoopBlock) k_refactor_tiles(RefTileArgs a, Re
             for (int u = 0; u < kRefEnt; ++u) {
                 const int k = pe + tid + u * kCoopBlock;
                 const T x = (T)v[u];
-                if (k < ne) xs[k] = x;
+                if (k < ne) xs_at(8 * k) = x;
                 if (col[u] != 0xFFFF && fabs(x) > T(0)) lds_max(cm + col[u], fabs(x));
             }
 #pragma unroll
@@ -1076,7 +1078,7 @@ __global__ void __launch_bounds__(kCoopBlock) k_refactor_tiles(RefTileArgs a, Re
                 if (k < nx) {
                     T x = xv[u];
                     if (is_sentinel(x)) x = load_ready<T, 1>(X + xsrc[u], &ctl->hang);
-                    xs[ne + k] = x;
+                    xs_at(8 * (ne + k)) = x;
                 }
             }
         }
@@ -1085,13 +1087,42 @@ __global__ void __launch_bounds__(kCoopBlock) k_refactor_tiles(RefTileArgs a, Re
         // another NaN, so that no wait mistakes it for an unwritten one.
         auto do_exports = [&](int x0, int x1, int stride) {
             for (int k = x0 + tid; k < x1; k += stride) {
-                T x = xs[a.exp[pb + k]];
+                T x = xs_at(8 * a.exp[pb + k]);
                 if (is_sentinel(x)) x = T(NAN);
                 store_ready(X + pb + k, x);
             }
         };
+        // One item: its updates one after another (four at a time while there are that many).
+        auto run_item = [&](int i) {
+            const uint32_t ia = item[i], ie = item[i + 1];
+            const int u1 = (int)(ie >> 16);
+            int u = (int)(ia >> 16);
+            T &target = xs_at(ia & 0xFFFFu);
+            T x = target;
+            for (; u + 4 <= u1; u += 4) {
+                T l[4], f[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const uint32_t p = upd[u + k];
+                    l[k] = xs_at(p & 0xFFFFu);
+                    f[k] = xs_at(p >> 16);
+                }
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const T prod = l[k] * f[k];
+                    x = x - prod;
+                }
+            }
+            for (; u < u1; ++u) {
+                const uint32_t p = upd[u];
+                const T prod = xs_at(p & 0xFFFFu) * xs_at(p >> 16);
+                x = x - prod;
+            }
+            target = x;
+        };
         // The segments.  One whose items and L entries fit a wavefront is wavefront 0's alone,
         // without block barriers (a wavefront's LDS accesses complete in order).
+        const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
         bool prev_wave = false;
         int gb = 0, i0 = 0, n0 = 0, q0 = 0, x0 = 0, px0 = 0;
         for (int g = 0; g < ns; ++g) {
@@ -1112,52 +1143,41 @@ __global__ void __launch_bounds__(kCoopBlock) k_refactor_tiles(RefTileArgs a, Re
                 px0 = x0;
             }
             prev_wave = wave;
-            if (!wave || tid < 64) {
-                const int stride = wave ? 64 : kCoopBlock;
-                for (int i = i0 + tid; i < i1; i += stride) {
-                    const uint32_t ia = item[i], ie = item[i + 1];
-                    const int u1 = (int)(ie >> 16);
-                    T x = xs[ia & 0xFFFFu];
-                    for (int u = (int)(ia >> 16); u < u1; u += 4) {
-                        T l[4], f[4];
-#pragma unroll
-                        for (int k = 0; k < 4; ++k) {
-                            const uint32_t p = upd[u + k < u1 ? u + k : u];
-                            l[k] = xs[p & 0xFFFFu];
-                            f[k] = xs[p >> 16];
-                        }
-#pragma unroll
-                        for (int k = 0; k < 4; ++k) {
-                            const T prod = l[k] * f[k];
-                            if (u + k < u1) x = x - prod;
-                        }
-                    }
-                    xs[ia & 0xFFFFu] = x;
+            // L entry q: its pivot's slot and the column maximum that goes with it (every lane of a
+            // column guards its pivot by itself)
+            auto divide = [&](int q) {
+                const uint32_t piv = lq[q], e = 8u * (uint32_t)(sl0 + nd + (q - q0));
+                bool hit;
+                const T d = guarded_pivot(xs_at(piv), cm[n0 + (int)(piv >> 3) - sl0], hit);
+                xs_at(e) = xs_at(e) / d;
+            };
+            auto guard = [&](int k) {
+                bool hit;
+                const T d = guarded_pivot(xs_at(8u * (uint32_t)(sl0 + k)), cm[n0 + k], hit);
+                if (hit) {
+                    xs_at(8u * (uint32_t)(sl0 + k)) = d;
+                    atomicAdd(&ctl->nguard, 1ull);
+                    if (a.guard_fail_policy) atomicOr(&ctl->guard_fail, 1u);
                 }
-                if (wave) __builtin_amdgcn_wave_barrier();
-                else __syncthreads();
-                // pivots (every lane of a column guards its pivot by itself) and divisions
-                for (int q = q0 + tid; q < q1; q += stride) {
-                    const int node = lq[q], e = sl0 + nd + (q - q0);
-                    bool hit;
-                    const T d = guarded_pivot(xs[sl0 + node], cm[n0 + node], hit);
-                    xs[e] = xs[e] / d;
-                }
-                for (int k = tid; k < nd; k += stride) {
-                    bool hit;
-                    const T d = guarded_pivot(xs[sl0 + k], cm[n0 + k], hit);
-                    if (hit) {
-                        xs[sl0 + k] = d;
-                        atomicAdd(&ctl->nguard, 1ull);
-                        if (a.guard_fail_policy) atomicOr(&ctl->guard_fail, 1u);
-                    }
-                }
-                if (wave) {
+            };
+            if (wave) {
+                if (wid == 0) {
+                    if (i0 + lane < i1) run_item(i0 + lane);
                     __builtin_amdgcn_wave_barrier();
-                    do_exports(x0, x1, 64);
+                    if (q0 + lane < q1) divide(q0 + lane);
+                    if (lane < nd) guard(lane);
+                    if (x0 < x1) {
+                        __builtin_amdgcn_wave_barrier();
+                        do_exports(x0, x1, 64);
+                    }
                 }
+                px0 = x1;
+            } else {
+                for (int i = i0 + tid; i < i1; i += kCoopBlock) run_item(i);
+                __syncthreads();
+                for (int q = q0 + tid; q < q1; q += kCoopBlock) divide(q);
+                for (int k = tid; k < nd; k += kCoopBlock) guard(k);
             }
-            if (wave) px0 = x1;
             i0 = i1;
             n0 = n1;
             q0 = q1;
@@ -1176,7 +1196,7 @@ __global__ void __launch_bounds__(kCoopBlock) k_refactor_tiles(RefTileArgs a, Re
             }
 #pragma unroll
             for (int u = 0; u < 8; ++u)
-                if (e0 + tid + u * kCoopBlock < ne) Tv[pos[u]] = xs[sl[u]];
+                if (e0 + tid + u * kCoopBlock < ne) Tv[pos[u]] = xs_at(8 * sl[u]);
         }
         __syncthreads();
     }
@@ -1540,6 +1560,238 @@ __global__ void __launch_bounds__(kTileThreads) k_trsv(TrsvArgs<T> a) {
             }
         }
         __syncthreads();
+    }
+}
+
+// ---------------------------------------------------------------------------------------
+// both triangular solves in one launch, by tiles of subtrees (SolveTiles)
+// ---------------------------------------------------------------------------------------
+
+template <typename T> struct SolveTileArgs {
+    int64_t ntiles;
+    const int32_t *desc;
+    const uint32_t *chunk_l, *chunk_u;
+    const uint16_t *ref_l, *ref_u;
+    const int32_t *ext_l, *ext_u;
+    const T *val_l, *val_u, *diag;  // solve layout: L places, U places, U's diagonal by U position
+    const double *rhs;
+    const int32_t *rsrc;   // per L position: the right-hand-side entry it reads
+    const int32_t *pos_u;  // per U position: the L position of the same step
+    const int32_t *qpos;   // per U position: the solution entry it writes
+    T *y, *z;              // exchange vectors of the sweeps; sentinels on entry
+    double *xout;
+    const Control *stopflag;  // when non-null, skip if the FGMRES cycle has stopped
+    unsigned int *work;       // task counter (zeroed before the launch)
+    unsigned int *hang;
+};
+
+template <typename T> __device__ __forceinline__ T load_system(const T *p) {
+    using U = typename Bits<T>::U;
+    return __builtin_bit_cast(T, __hip_atomic_load(reinterpret_cast<const U *>(p), __ATOMIC_RELAXED,
+                                                   __HIP_MEMORY_SCOPE_SYSTEM));
+}
+template <typename T> struct Pair;
+template <> struct Pair<double> { using V = double2; };
+template <> struct Pair<float> { using V = float2; };
+
+// Staging loads per thread and pass of a solve tile: 4 pairs of places; rows and externals.
+constexpr int kSolPair = 4, kSolRow = 2;
+
+// One tile of one sweep.  Its places, then its right-hand sides and externals, go to LDS; the
+// chunks then run from LDS only; the rows' solutions leave together at the end, coalesced (a
+// store per row and segment costs the segment loop more than the later start of the tiles that
+// wait: its wavefront issues every instruction of the serial chain).
+template <typename T, bool kUpper>
+__device__ __forceinline__ void solve_tile(const SolveTileArgs<T> &a, int t, unsigned char *smem) {
+    using V2 = typename Pair<T>::V;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const auto td = uniform_ro(a.desc) + (int64_t)kSolDesc * t;
+    constexpr int o = kUpper ? 8 : 2;
+    const int base = td[0], nr = td[1], nc = td[o + 1], np = td[o + 3], nx = td[o + 5];
+    const uint32_t *chunk = (kUpper ? a.chunk_u : a.chunk_l) + 2 * (int64_t)td[o];
+    const V2 *gval = reinterpret_cast<const V2 *>((kUpper ? a.val_u : a.val_l) + td[o + 2]);
+    const uint32_t *gref = reinterpret_cast<const uint32_t *>((kUpper ? a.ref_u : a.ref_l) + td[o + 2]);
+    const int32_t *gext = (kUpper ? a.ext_u : a.ext_l) + td[o + 4];
+    const int32_t *gsrc = (kUpper ? a.pos_u : a.rsrc) + base;
+    T *out = (kUpper ? a.z : a.y) + base;
+    const int nslot = nr + nx + 1;  // rows, externals, the zero slot; 8 bytes each
+    V2 *vals = reinterpret_cast<V2 *>(smem + 8 * (nslot + (nslot & 1)));  // np / 2
+    T *dg = reinterpret_cast<T *>(vals + np / 2);                           // nr (upper)
+    uint32_t *refs = reinterpret_cast<uint32_t *>(dg + (kUpper ? nr + (nr & 1) : 0));  // np / 2
+    auto slot_at = [&](uint32_t off) -> T & { return *reinterpret_cast<T *>(smem + off); };
+    uint32_t m0 = 0, m1 = 0;  // lane l of every wavefront holds chunk l's words
+    auto chunk_words = [&](int c0) {
+        m0 = m1 = 0;
+        if (c0 + lane < nc) {
+            m0 = chunk[2 * (c0 + lane)];
+            m1 = chunk[2 * (c0 + lane) + 1];
+        }
+    };
+    chunk_words(0);
+    // first the sources of the rows' right-hand sides and the externals, then the places
+    int rs[kSolRow], xc[kSolRow], qp[kSolRow];
+    T rv[kSolRow], gv[kSolRow], xv[kSolRow];
+#pragma unroll
+    for (int u = 0; u < kSolRow; ++u) {
+        const int r = tid + u * kTileThreads;
+        rs[u] = r < nr ? gsrc[r] : 0;
+        xc[u] = r < nx ? gext[r] : 0;
+        qp[u] = kUpper && r < nr ? a.qpos[base + r] : 0;
+        gv[u] = kUpper && r < nr ? a.diag[base + r] : T(1);
+    }
+    const int np2 = np / 2;
+    for (int p0 = 0; p0 < np2; p0 += kSolPair * kTileThreads) {
+        V2 v[kSolPair];
+        uint32_t c[kSolPair];
+#pragma unroll
+        for (int u = 0; u < kSolPair; ++u) {
+            const int k = p0 + tid + u * kTileThreads;
+            if (k < np2) {
+                v[u] = gval[k];
+                c[u] = gref[k];
+            }
+        }
+        if (!kUpper && p0 == 0) {  // the right-hand side is always there: with the same round
+#pragma unroll
+            for (int u = 0; u < kSolRow; ++u) rv[u] = tid + u * kTileThreads < nr ? (T)a.rhs[rs[u]] : T(0);
+        }
+#pragma unroll
+        for (int u = 0; u < kSolPair; ++u) {
+            const int k = p0 + tid + u * kTileThreads;
+            if (k < np2) {
+                vals[k] = v[u];
+                refs[k] = c[u];
+            }
+        }
+    }
+    if (!kUpper && np2 == 0) {
+#pragma unroll
+        for (int u = 0; u < kSolRow; ++u) rv[u] = tid + u * kTileThreads < nr ? (T)a.rhs[rs[u]] : T(0);
+    }
+    if (kUpper) {
+#pragma unroll
+        for (int u = 0; u < kSolRow; ++u)
+            if (tid + u * kTileThreads < nr) dg[tid + u * kTileThreads] = T(1) / gv[u];
+        for (int r = tid + kSolRow * kTileThreads; r < nr; r += kTileThreads) dg[r] = T(1) / a.diag[base + r];
+    }
+    if (tid == 0) slot_at(8u * (uint32_t)(nr + nx)) = T(0);
+    // The values other blocks produce.  One lane waits for the one that is written last (the first
+    // external, of the closest tile; for a U tile without externals its own last row of the L
+    // sweep), so that the waiting blocks keep one load each in flight; the others are there by
+    // then, or are waited for one by one.
+    const bool gate = nx > 0 || kUpper;
+    if (gate) {
+        if (tid == 0) {
+            const T *p = nx > 0 ? (kUpper ? a.z : a.y) + gext[0] : a.y + base + nr - 1;
+            (void)load_ready<T, 1>(p, a.hang);
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int u = 0; u < kSolRow; ++u) {
+        const int r = tid + u * kTileThreads;
+        if (kUpper) rv[u] = r < nr ? load_system(a.y + rs[u]) : T(0);
+        xv[u] = r < nx ? load_system((kUpper ? a.z : a.y) + xc[u]) : T(0);
+    }
+#pragma unroll
+    for (int u = 0; u < kSolRow; ++u) {
+        const int r = tid + u * kTileThreads;
+        if (r < nr) {
+            if (kUpper && is_sentinel(rv[u])) rv[u] = load_ready<T, 1>(a.y + rs[u], a.hang);
+            slot_at(8 * r) = rv[u];
+        }
+        if (r < nx) {
+            if (is_sentinel(xv[u])) xv[u] = load_ready<T, 1>((kUpper ? a.z : a.y) + xc[u], a.hang);
+            slot_at(8 * (nr + r)) = xv[u];
+        }
+    }
+    for (int r = tid + kSolRow * kTileThreads; r < nr; r += kTileThreads)
+        slot_at(8 * r) = kUpper ? load_ready<T, 1>(a.y + gsrc[r], a.hang) : (T)a.rhs[gsrc[r]];
+    for (int r = tid + kSolRow * kTileThreads; r < nx; r += kTileThreads)
+        slot_at(8 * (nr + r)) = load_ready<T, 1>((kUpper ? a.z : a.y) + gext[r], a.hang);
+    __syncthreads();
+    // The chunks, each one wavefront's.  A chunk of a segment that one wavefront covers is
+    // wavefront 0's, without barriers between such segments (a wavefront's LDS accesses complete
+    // in order).
+    for (int c = 0; c < nc; ++c) {
+        if ((c & 63) == 0 && c > 0) chunk_words(c);
+        const uint32_t w0 = (uint32_t)__builtin_amdgcn_readlane((int)m0, c & 63);
+        const uint32_t w1 = (uint32_t)__builtin_amdgcn_readlane((int)m1, c & 63);
+        if (w0 >> 31) __syncthreads();
+        if ((int)(w1 >> 30) != wid) continue;
+        const int r0 = (int)(w0 & 0x1FFFu), cnt = (int)((w0 >> 13) & 0x7Fu), lg = (int)((w0 >> 20) & 7u);
+        const int half = (int)((w0 >> 23) & 0xFFu);
+        if (lane < cnt << lg) {
+            const int row = r0 + (lane >> lg);
+            const int p = (int)((w1 & 0x3FFFFFFFu) >> 1) + lane * half;
+            const uint32_t *rp = refs + p;
+            const V2 *vp = vals + p;
+            T &slot = slot_at(8 * row);
+            const T rh = slot;
+            const T d = kUpper ? dg[row] : T(1);
+            T acc = T(0);
+            int h = 0;
+            for (; h + 2 <= half; h += 2) {  // four places in flight
+                const uint32_t ra = rp[h], rb = rp[h + 1];
+                const V2 va = vp[h], vb = vp[h + 1];
+                const T x0 = slot_at(ra & 0xFFFFu), x1 = slot_at(ra >> 16);
+                const T x2 = slot_at(rb & 0xFFFFu), x3 = slot_at(rb >> 16);
+                acc = fma(va.x, x0, acc);
+                acc = fma(va.y, x1, acc);
+                acc = fma(vb.x, x2, acc);
+                acc = fma(vb.y, x3, acc);
+            }
+            if (h < half) {
+                const uint32_t ra = rp[h];
+                const V2 va = vp[h];
+                const T x0 = slot_at(ra & 0xFFFFu), x1 = slot_at(ra >> 16);
+                acc = fma(va.x, x0, acc);
+                acc = fma(va.y, x1, acc);
+            }
+            if (lg > 0) {
+                acc = group_sum_last(acc, lg);
+                const int g = 1 << lg;
+                if ((lane & (g - 1)) == g - 1) slot = kUpper ? (rh - acc) * d : rh - acc;
+            } else {
+                slot = kUpper ? (rh - acc) * d : rh - acc;
+            }
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kSolRow; ++u) {
+        const int r = tid + u * kTileThreads;
+        if (r < nr) {
+            const T res = slot_at(8 * r);
+            store_ready(out + r, res);
+            if (kUpper) a.xout[qp[u]] = (double)res;
+        }
+    }
+    for (int r = tid + kSolRow * kTileThreads; r < nr; r += kTileThreads) {
+        const T res = slot_at(8 * r);
+        store_ready(out + r, res);
+        if (kUpper) a.xout[a.qpos[base + r]] = (double)res;
+    }
+}
+
+// x = U^-1 L^-1 b: tasks 0..n-1 are the L sweep's tiles in order, tasks n..2n-1 the U sweep's from
+// the last to the first.  Tasks are handed out in order to running blocks and wait only for
+// earlier ones, so the earliest unfinished task is always held by a running block that can
+// finish it.
+template <typename T>
+__global__ void __launch_bounds__(kTileThreads) k_solve_tiles(SolveTileArgs<T> a) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ unsigned int task_sh;
+    if (a.stopflag && a.stopflag->stop) return;
+    for (;;) {
+        if (threadIdx.x == 0) task_sh = atomicAdd(a.work, 1u);
+        __syncthreads();
+        const int w = __builtin_amdgcn_readfirstlane((int)task_sh);
+        __syncthreads();
+        if ((int64_t)w >= 2 * a.ntiles) break;
+        if (w < (int)a.ntiles) solve_tile<T, false>(a, w, smem);
+        else solve_tile<T, true>(a, (int)(2 * a.ntiles - 1) - w, smem);
     }
 }
 
@@ -2147,6 +2399,10 @@ struct DevLayout {
     uint16_t *rt_col, *rt_lq, *rt_exp, *rt_oslot;
     double *X64;
     float *X32;
+    // solve tiles
+    int32_t *st_desc, *st_el, *st_eu, *st_src, *st_src_k, *st_posu, *st_q, *st_q_k;
+    uint32_t *st_cl, *st_cu;
+    uint16_t *st_rl, *st_ru;
     int64_t *krp;
     int32_t *lci, *uci, *kci;
     int32_t *prow, *q;
@@ -2191,6 +2447,7 @@ struct kkt_handle_s {
     bool have_factors = false;
     int factor_precision = 0;
     int grid_refactor64 = 0, grid_refactor32 = 0, grid_trsv64 = 0, grid_trsv32 = 0, grid_stream = 0;
+    int grid_solve64 = 0, grid_solve32 = 0;  // blocks of the one-launch solve (with tiles)
     kkt::ControlSummary *host_ctl = nullptr;  // pinned, mapped: written by k_resid_reduce
     kkt::ControlSummary *dev_ctl_sum = nullptr;  // the same memory as seen by kernels
     kkt::StepRecord *host_rec = nullptr;      // pinned, kRestartMax + 1 records (one per step)
@@ -2302,6 +2559,7 @@ struct Offsets {
         z32, dv, rr, xb, bi, xi, part, ctl, total;
     size_t rt_desc, rt_seg, rt_src, rt_col, rt_item, rt_upd, rt_lq, rt_exp, rt_ext, rt_cmxn, rt_cmxs, rt_opos, rt_oslot,
         X64, X32;
+    size_t st_desc, st_cl, st_cu, st_rl, st_ru, st_el, st_eu, st_src, st_src_k, st_posu, st_q, st_q_k;
 };
 
 // tiles: with the refactorization's tiles (the hand-out items' arrays are then left out), or
@@ -2348,29 +2606,38 @@ Offsets plan_for(const kkt_handle_t h, bool tiles) {
         o.rt_oslot = p.take<uint16_t>(t.out_slot.size());
         o.X64 = p.take<double>(t.exp.size());
         o.X32 = p.take<float>(t.exp.size());
+        const SolveTiles &q = a.sol;
+        o.st_desc = p.take<int32_t>(q.desc.size());
+        o.st_cl = p.take<uint32_t>(q.chunk_l.size());
+        o.st_cu = p.take<uint32_t>(q.chunk_u.size());
+        o.st_rl = p.take<uint16_t>(q.ref_l.size());
+        o.st_ru = p.take<uint16_t>(q.ref_u.size());
+        o.st_el = p.take<int32_t>(q.ext_l.size());
+        o.st_eu = p.take<int32_t>(q.ext_u.size());
+        for (size_t *v : {&o.st_src, &o.st_src_k, &o.st_posu, &o.st_q, &o.st_q_k}) *v = p.take<int32_t>(n);
     }
     o.krp = p.take<int64_t>(n + 1);
     o.kci = p.take<int32_t>(a.nnz);
-    o.l_rows = p.take<int32_t>(n);
-    o.l_seg = p.take<int32_t>(a.lsched.seg_row.size());
-    o.l_tdesc = p.take<int32_t>(kTileDesc * a.lsched.tiles());
-    o.l_src = p.take<int32_t>(n);
-    o.l_src_k = p.take<int32_t>(n);
-    o.l_ref = p.take<int32_t>(a.lsched.ent_ref.size());
-    o.l_esrc = p.take<int32_t>(a.lsched.ext_src.size());
-    o.l_rent = p.take<int64_t>(a.lsched.row_ent.size());
-    o.l_sdof = p.take<int32_t>(a.lsched.seg_dofs.size());
-    o.l_slg = p.take<int32_t>(a.lsched.seg_lg.size());
-    o.u_rows = p.take<int32_t>(n);
-    o.u_seg = p.take<int32_t>(a.usched.seg_row.size());
-    o.u_tdesc = p.take<int32_t>(kTileDesc * a.usched.tiles());
-    o.u_q = p.take<int32_t>(n);
-    o.u_q_k = p.take<int32_t>(n);
-    o.u_ref = p.take<int32_t>(a.usched.ent_ref.size());
-    o.u_esrc = p.take<int32_t>(a.usched.ext_src.size());
-    o.u_rent = p.take<int64_t>(a.usched.row_ent.size());
-    o.u_sdof = p.take<int32_t>(a.usched.seg_dofs.size());
-    o.u_slg = p.take<int32_t>(a.usched.seg_lg.size());
+    o.l_rows = p.take<int32_t>(ni);
+    o.l_seg = p.take<int32_t>(tiles ? 0 : a.lsched.seg_row.size());
+    o.l_tdesc = p.take<int32_t>(tiles ? 0 : kTileDesc * a.lsched.tiles());
+    o.l_src = p.take<int32_t>(ni);
+    o.l_src_k = p.take<int32_t>(ni);
+    o.l_ref = p.take<int32_t>(tiles ? 0 : a.lsched.ent_ref.size());
+    o.l_esrc = p.take<int32_t>(tiles ? 0 : a.lsched.ext_src.size());
+    o.l_rent = p.take<int64_t>(tiles ? 0 : a.lsched.row_ent.size());
+    o.l_sdof = p.take<int32_t>(tiles ? 0 : a.lsched.seg_dofs.size());
+    o.l_slg = p.take<int32_t>(tiles ? 0 : a.lsched.seg_lg.size());
+    o.u_rows = p.take<int32_t>(ni);
+    o.u_seg = p.take<int32_t>(tiles ? 0 : a.usched.seg_row.size());
+    o.u_tdesc = p.take<int32_t>(tiles ? 0 : kTileDesc * a.usched.tiles());
+    o.u_q = p.take<int32_t>(ni);
+    o.u_q_k = p.take<int32_t>(ni);
+    o.u_ref = p.take<int32_t>(tiles ? 0 : a.usched.ent_ref.size());
+    o.u_esrc = p.take<int32_t>(tiles ? 0 : a.usched.ext_src.size());
+    o.u_rent = p.take<int64_t>(tiles ? 0 : a.usched.row_ent.size());
+    o.u_sdof = p.take<int32_t>(tiles ? 0 : a.usched.seg_dofs.size());
+    o.u_slg = p.take<int32_t>(tiles ? 0 : a.usched.seg_lg.size());
     o.prow = p.take<int32_t>(n);
     o.q = p.take<int32_t>(n);
     o.vperm = p.take<int32_t>(n);
@@ -2379,9 +2646,11 @@ Offsets plan_for(const kkt_handle_t h, bool tiles) {
     o.ostart = p.take<int64_t>(n);
     o.kval = p.take<double>(a.nnz);
     o.F64 = p.take<double>(fi);
-    o.T64 = p.take<double>(a.t_size);
+    // (without tiles: the size of the solve layout of the schedules' own entries)
+    const int64_t ts = tiles ? a.t_size : a.lsched.values() + a.usched.values() + n;
+    o.T64 = p.take<double>(ts);
     o.F32 = p.take<float>(fi);
-    o.T32 = p.take<float>(a.t_size);
+    o.T32 = p.take<float>(ts);
     o.Ld64 = p.take<double>(fi);
     o.Ld32 = p.take<float>(fi);
     o.V = p.take<double>((size_t)(R + 1) * n);
@@ -2521,6 +2790,24 @@ hipError_t launch_trsv(kkt_handle_t h, bool lower, const double *rhs64, const T 
     return hipGetLastError();
 }
 
+// Both sweeps in one launch (analyses with tiles): x = Q U^-1 L^-1 P b through the exchange vectors y
+// and z (sentinels armed, *work zeroed before).
+template <typename T>
+hipError_t launch_solve_tiles(kkt_handle_t h, const double *rhs, T *y, T *z, double *xout, const Control *stopflag,
+                              hipStream_t s, bool vorder, unsigned int *work, unsigned int *hang) {
+    const SolveTiles &q = h->an.sol;
+    const DevLayout &d = h->d;
+    constexpr bool is64 = sizeof(T) == 8;
+    const T *val = (const T *)(is64 ? (void *)d.T64 : (void *)d.T32);
+    const T *val_u = val + q.ref_l.size();
+    const SolveTileArgs<T> t{q.tiles(), d.st_desc, d.st_cl, d.st_cu, d.st_rl, d.st_ru, d.st_el, d.st_eu, val, val_u,
+                             val_u + q.ref_u.size(), rhs, vorder ? d.st_src_k : d.st_src, d.st_posu,
+                             vorder ? d.st_q_k : d.st_q, y, z, xout, stopflag, work, hang};
+    const int grid = (int)std::min<int64_t>(is64 ? h->grid_solve64 : h->grid_solve32, 2 * q.tiles());
+    k_solve_tiles<T><<<grid, kTileThreads, (size_t)q.lds, s>>>(t);
+    return hipGetLastError();
+}
+
 // x = Q U^-1 L^-1 P b with the current factors of precision T (sentinels armed before); b and
 // x in the vector order of a solve (vorder) or in the original order.
 template <typename T>
@@ -2528,6 +2815,12 @@ hipError_t precond(kkt_handle_t h, const double *b, double *x, const Control *ct
     T *y = (T *)(sizeof(T) == 8 ? (void *)h->d.y64 : (void *)h->d.y32);
     T *z = (T *)(sizeof(T) == 8 ? (void *)h->d.z64 : (void *)h->d.z32);
     hipEvent_t e0 = prof_begin(h, KKT_K_TRSV_L, s);
+    if (h->an.sol.tiles() > 0) {
+        const hipError_t et = launch_solve_tiles<T>(h, b, y, z, x, ctl, s, vorder, &h->d.ctl->work_lower,
+                                                    &h->d.ctl->hang);
+        prof_end(h, KKT_K_TRSV_L, e0, s);
+        return et;
+    }
     hipError_t e = launch_trsv<T>(h, true, b, nullptr, y, nullptr, ctl, s, vorder);
     prof_end(h, KKT_K_TRSV_L, e0, s);
     if (e != hipSuccess) return e;
@@ -3006,8 +3299,8 @@ AnalysisOptions analysis_options(const kkt_opts_t &o, int64_t n) {
     ao.narrow_columns = o.narrow_columns > 0
                             ? o.narrow_columns
                             : (int)std::max<int64_t>(kResidentRefactorWaves, std::min<int64_t>(16384, n / 64));
-    // tiles unless the caller sets the hand-out of single columns
-    ao.ref_lds = o.narrow_columns > 0 ? 0 : kRefTileLds;
+    // tiles unless the caller sets the hand-out of single columns or the solve schedules' LDS budget
+    ao.ref_lds = o.narrow_columns > 0 || o.tile_lds_kib > 0 ? 0 : kRefTileLds;
     return ao;
 }
 
@@ -3141,6 +3434,8 @@ hipError_t direct_solve_scratch(kkt_handle_t h, const double *b, double *x, unsi
                                                                 &head->hang);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
+    if (h->an.sol.tiles() > 0)
+        return launch_solve_tiles<T>(h, b, y, z, x, nullptr, s, false, &head->work_lower, &head->hang);
     e = launch_trsv<T>(h, true, b, nullptr, y, nullptr, nullptr, s, false, &head->work_lower, &head->hang);
     if (e != hipSuccess) return e;
     return launch_trsv<T>(h, false, nullptr, y, z, x, nullptr, s, false, &head->work_upper, &head->hang);
@@ -3334,6 +3629,18 @@ kkt_status_t kkt_bind_workspace(kkt_handle_t h, void *dev_ptr, size_t bytes, voi
     d.rt_oslot = (uint16_t *)(b + o.rt_oslot);
     d.X64 = (double *)(b + o.X64);
     d.X32 = (float *)(b + o.X32);
+    d.st_desc = (int32_t *)(b + o.st_desc);
+    d.st_cl = (uint32_t *)(b + o.st_cl);
+    d.st_cu = (uint32_t *)(b + o.st_cu);
+    d.st_rl = (uint16_t *)(b + o.st_rl);
+    d.st_ru = (uint16_t *)(b + o.st_ru);
+    d.st_el = (int32_t *)(b + o.st_el);
+    d.st_eu = (int32_t *)(b + o.st_eu);
+    d.st_src = (int32_t *)(b + o.st_src);
+    d.st_src_k = (int32_t *)(b + o.st_src_k);
+    d.st_posu = (int32_t *)(b + o.st_posu);
+    d.st_q = (int32_t *)(b + o.st_q);
+    d.st_q_k = (int32_t *)(b + o.st_q_k);
     d.krp = (int64_t *)(b + o.krp);
     d.kci = (int32_t *)(b + o.kci);
     d.l_rows = (int32_t *)(b + o.l_rows);
@@ -3400,6 +3707,27 @@ kkt_status_t kkt_bind_workspace(kkt_handle_t h, void *dev_ptr, size_t bytes, voi
         KKT_HIP(h, up(b, o.rt_cmxs, t.cmx_src, s));
         KKT_HIP(h, up(b, o.rt_opos, t.out_pos, s));
         KKT_HIP(h, up(b, o.rt_oslot, t.out_slot, s));
+        const SolveTiles &q = a.sol;
+        std::vector<int32_t> src(a.n), srck(a.n), xq(a.n), xqk(a.n);
+        for (int64_t p = 0; p < a.n; ++p) {
+            src[p] = a.prow[q.node_l[p]];
+            srck[p] = a.prow_k[q.node_l[p]];
+            xq[p] = a.q[q.node_u[p]];
+            xqk[p] = a.q_k[q.node_u[p]];
+        }
+        KKT_HIP(h, up(b, o.st_desc, q.desc, s));
+        KKT_HIP(h, up(b, o.st_cl, q.chunk_l, s));
+        KKT_HIP(h, up(b, o.st_cu, q.chunk_u, s));
+        KKT_HIP(h, up(b, o.st_rl, q.ref_l, s));
+        KKT_HIP(h, up(b, o.st_ru, q.ref_u, s));
+        KKT_HIP(h, up(b, o.st_el, q.ext_l, s));
+        KKT_HIP(h, up(b, o.st_eu, q.ext_u, s));
+        KKT_HIP(h, up(b, o.st_src, src, s));
+        KKT_HIP(h, up(b, o.st_src_k, srck, s));
+        KKT_HIP(h, up(b, o.st_posu, q.pos_u, s));
+        KKT_HIP(h, up(b, o.st_q, xq, s));
+        KKT_HIP(h, up(b, o.st_q_k, xqk, s));
+        KKT_HIP(h, hipStreamSynchronize(s));  // the vectors are locals
     } else {
         KKT_HIP(h, up(b, o.fp, a.fp, s));
         KKT_HIP(h, up(b, o.fi, a.fi, s));
@@ -3435,38 +3763,40 @@ kkt_status_t kkt_bind_workspace(kkt_handle_t h, void *dev_ptr, size_t bytes, voi
     KKT_HIP(h, up(b, o.vperm, a.vperm, s));
     KKT_HIP(h, up(b, o.prow_k, a.prow_k, s));
     KKT_HIP(h, up(b, o.q_k, a.q_k, s));
-    KKT_HIP(h, up(b, o.l_rows, a.lsched.rows, s));
-    KKT_HIP(h, up(b, o.l_seg, a.lsched.seg_row, s));
-    // per-tile descriptors and the per-position right-hand-side sources / solution targets
-    {
-        const std::vector<int32_t> ld = tile_descriptors(a.lsched), ud = tile_descriptors(a.usched);
-        std::vector<int32_t> ls(a.n), lsk(a.n), uq(a.n), uqk(a.n);
-        for (int64_t p = 0; p < a.n; ++p) {
-            ls[p] = a.prow[a.lsched.rows[p]];
-            lsk[p] = a.prow_k[a.lsched.rows[p]];
-            uq[p] = a.q[a.usched.rows[p]];
-            uqk[p] = a.q_k[a.usched.rows[p]];
+    if (a.ref.tiles() == 0) {
+        KKT_HIP(h, up(b, o.l_rows, a.lsched.rows, s));
+        KKT_HIP(h, up(b, o.l_seg, a.lsched.seg_row, s));
+        // per-tile descriptors and the per-position right-hand-side sources / solution targets
+        {
+            const std::vector<int32_t> ld = tile_descriptors(a.lsched), ud = tile_descriptors(a.usched);
+            std::vector<int32_t> ls(a.n), lsk(a.n), uq(a.n), uqk(a.n);
+            for (int64_t p = 0; p < a.n; ++p) {
+                ls[p] = a.prow[a.lsched.rows[p]];
+                lsk[p] = a.prow_k[a.lsched.rows[p]];
+                uq[p] = a.q[a.usched.rows[p]];
+                uqk[p] = a.q_k[a.usched.rows[p]];
+            }
+            KKT_HIP(h, up(b, o.l_tdesc, ld, s));
+            KKT_HIP(h, up(b, o.u_tdesc, ud, s));
+            KKT_HIP(h, up(b, o.l_src, ls, s));
+            KKT_HIP(h, up(b, o.l_src_k, lsk, s));
+            KKT_HIP(h, up(b, o.u_q, uq, s));
+            KKT_HIP(h, up(b, o.u_q_k, uqk, s));
+            KKT_HIP(h, hipStreamSynchronize(s));  // the vectors are locals
         }
-        KKT_HIP(h, up(b, o.l_tdesc, ld, s));
-        KKT_HIP(h, up(b, o.u_tdesc, ud, s));
-        KKT_HIP(h, up(b, o.l_src, ls, s));
-        KKT_HIP(h, up(b, o.l_src_k, lsk, s));
-        KKT_HIP(h, up(b, o.u_q, uq, s));
-        KKT_HIP(h, up(b, o.u_q_k, uqk, s));
-        KKT_HIP(h, hipStreamSynchronize(s));  // the vectors are locals
+        KKT_HIP(h, up(b, o.l_ref, a.lsched.ent_ref, s));
+        KKT_HIP(h, up(b, o.l_esrc, a.lsched.ext_src, s));
+        KKT_HIP(h, up(b, o.l_rent, a.lsched.row_ent, s));
+        KKT_HIP(h, up(b, o.l_sdof, a.lsched.seg_dofs, s));
+        KKT_HIP(h, up(b, o.l_slg, a.lsched.seg_lg, s));
+        KKT_HIP(h, up(b, o.u_rows, a.usched.rows, s));
+        KKT_HIP(h, up(b, o.u_seg, a.usched.seg_row, s));
+        KKT_HIP(h, up(b, o.u_ref, a.usched.ent_ref, s));
+        KKT_HIP(h, up(b, o.u_esrc, a.usched.ext_src, s));
+        KKT_HIP(h, up(b, o.u_rent, a.usched.row_ent, s));
+        KKT_HIP(h, up(b, o.u_sdof, a.usched.seg_dofs, s));
+        KKT_HIP(h, up(b, o.u_slg, a.usched.seg_lg, s));
     }
-    KKT_HIP(h, up(b, o.l_ref, a.lsched.ent_ref, s));
-    KKT_HIP(h, up(b, o.l_esrc, a.lsched.ext_src, s));
-    KKT_HIP(h, up(b, o.l_rent, a.lsched.row_ent, s));
-    KKT_HIP(h, up(b, o.l_sdof, a.lsched.seg_dofs, s));
-    KKT_HIP(h, up(b, o.l_slg, a.lsched.seg_lg, s));
-    KKT_HIP(h, up(b, o.u_rows, a.usched.rows, s));
-    KKT_HIP(h, up(b, o.u_seg, a.usched.seg_row, s));
-    KKT_HIP(h, up(b, o.u_ref, a.usched.ent_ref, s));
-    KKT_HIP(h, up(b, o.u_esrc, a.usched.ext_src, s));
-    KKT_HIP(h, up(b, o.u_rent, a.usched.row_ent, s));
-    KKT_HIP(h, up(b, o.u_sdof, a.usched.seg_dofs, s));
-    KKT_HIP(h, up(b, o.u_slg, a.usched.seg_lg, s));
     KKT_HIP(h, up(b, o.prow, a.prow, s));
     KKT_HIP(h, up(b, o.q, a.q, s));
     KKT_HIP(h, hipMemsetAsync(d.ctl, 0, sizeof(Control), s));
@@ -3494,6 +3824,11 @@ kkt_status_t kkt_bind_workspace(kkt_handle_t h, void *dev_ptr, size_t bytes, voi
                                       coop_grid((const void *)k_refactor_tiles<double, true>, h->device, lds));
         h->grid_refactor32 = std::min(coop_grid((const void *)k_refactor_tiles<float, false>, h->device, lds),
                                       coop_grid((const void *)k_refactor_tiles<float, true>, h->device, lds));
+    }
+    if (a.sol.tiles() > 0) {
+        h->grid_solve64 = coop_grid((const void *)k_solve_tiles<double>, h->device, (size_t)a.sol.lds);
+        h->grid_solve32 = coop_grid((const void *)k_solve_tiles<float>, h->device, (size_t)a.sol.lds);
+        if (h->grid_solve64 <= 0 || h->grid_solve32 <= 0) return fail(h, KKT_EDEVICE, "occupancy query failed");
     }
     h->grid_trsv64 = std::min(std::min(coop_grid((const void *)k_trsv<double, true, true>, h->device, h->tile_lds),
                                        coop_grid((const void *)k_trsv<double, false, true>, h->device, h->tile_lds)),

@@ -1,5 +1,6 @@
-// Host-only replay of the refactorization's tile schedule (RefTiles), built with
-// AddressSanitizer and UndefinedBehaviorSanitizer by tests/test_ref_tiles.py: reads a CSR system
+// Host-only replay of the tile schedules of the refactorization (RefTiles) and of the solves
+// (SolveTiles), built with AddressSanitizer and UndefinedBehaviorSanitizer by
+// tests/test_ref_tiles.py: reads a CSR system
 // from a binary file (int64 n, int64 nnz, double tau, int32 ordering, int32 ref_lds; then rowptr,
 // colidx, values of system 1, values of system 2), runs the analysis and refactors system 2 as
 // the tile kernel does: tiles in hand-out order, entries and externals in slots, segments of
@@ -7,6 +8,9 @@
 // solve-layout position written twice or never is an error), the pivot guard with column
 // maxima gathered from the tile's own entries and its extras.  Writes L and U in exchange
 // layout and prints tiles=<count> layers=<count> refactor=<ok or the first violated property>.
+// Both sweeps are replayed with the factors of system 2 the same way (tasks in hand-out order,
+// chunks from slots; a value read before it is written, a place read out of range, a row solved
+// twice or never is an error) and compared with plain substitution: solve=ok:<relative difference>.
 #include <cmath>
 #include <cstdio>
 #include <cstdint>
@@ -60,13 +64,14 @@ std::string replay(const kkt::Analysis &a, int64_t budget, const std::vector<dou
             std::vector<uint8_t> touched(ne, 0);
             for (int32_t i = i0; i < i1; ++i) {
                 const uint32_t ia = t.item.at(d[4] + i), ie = t.item.at(d[4] + i + 1);
-                const uint32_t s = ia & 0xFFFF;
-                if ((int32_t)s >= ne || final_[s] || touched[s]++) return "item_target";
+                const uint32_t s = (ia & 0xFFFF) / 8;
+                if ((ia & 7) || (int32_t)s >= ne || final_[s] || touched[s]++) return "item_target";
                 if ((ie >> 16) <= (ia >> 16) || (int32_t)(ie >> 16) > nu) return "item_updates";
                 for (uint32_t u = ia >> 16; u < ie >> 16; ++u) {
                     const uint32_t p = t.upd.at(d[6] + u);
-                    if (!final_.at(p & 0xFFFF) || !final_.at(p >> 16)) return "factor_not_final";
-                    const double prod = xs[p & 0xFFFF] * xs[p >> 16];
+                    const uint32_t l = (p & 0xFFFF) / 8, f = (p >> 16) / 8;
+                    if ((p & 7) || (p >> 16 & 7) || !final_.at(l) || !final_.at(f)) return "factor_not_final";
+                    const double prod = xs[l] * xs[f];
                     xs[s] = xs[s] - prod;
                 }
             }
@@ -80,8 +85,8 @@ std::string replay(const kkt::Analysis &a, int64_t budget, const std::vector<dou
                 final_[sl0 + k] = 1;
             }
             for (int32_t q = q0; q < q1; ++q) {
-                const int32_t node = t.lq.at(d[8] + q);
-                if (node >= nd) return "l_node";
+                const int32_t node = t.lq.at(d[8] + q) / 8 - sl0;
+                if (node < 0 || node >= nd) return "l_node";
                 const int32_t e = sl0 + nd + (q - q0);
                 xs[e] = xs[e] / xs[sl0 + node];
                 final_[e] = 1;
@@ -113,6 +118,87 @@ std::string replay(const kkt::Analysis &a, int64_t budget, const std::vector<dou
     for (size_t p = 0; p < lx.size(); ++p) lx[p] = tv.at(a.f2t.at(a.l2f[p]));
     for (size_t p = 0; p < ux.size(); ++p) ux[p] = tv.at(a.f2t.at(a.u2f[p]));
     return "ok";
+}
+
+std::string replay_solve(const kkt::Analysis &a, const std::vector<double> &lx, const std::vector<double> &ux) {
+    const kkt::SolveTiles &t = a.sol;
+    const int64_t n = a.n;
+    std::vector<double> tv(a.t_size, 0.0), b(n), ref(n);
+    for (size_t p = 0; p < lx.size(); ++p) tv.at(a.f2t.at(a.l2f[p])) = lx[p];
+    for (size_t p = 0; p < ux.size(); ++p) tv.at(a.f2t.at(a.u2f[p])) = ux[p];
+    for (int64_t i = 0; i < n; ++i) b[i] = std::sin(1.0 + 0.7 * (double)i);
+    // plain substitution in step space from the exchange layout (li holds original rows)
+    for (int64_t k = 0; k < n; ++k) ref[k] = b[a.prow[k]];
+    for (int64_t k = 0; k < n; ++k)
+        for (int64_t p = a.lp[k]; p < a.lp[k + 1]; ++p) ref[a.pinv[a.li[p]]] -= lx[p] * ref[k];
+    for (int64_t k = n - 1; k >= 0; --k) {
+        ref[k] /= ux[a.up[k + 1] - 1];
+        for (int64_t p = a.up[k]; p < a.up[k + 1] - 1; ++p) ref[a.ui[p]] -= ux[p] * ref[k];
+    }
+    const int64_t ub = (int64_t)t.ref_l.size(), db = ub + (int64_t)t.ref_u.size();
+    if (db + n != a.t_size) return "solve_layout_size";
+    std::vector<double> y(n, kNaN), z(n, kNaN);
+    for (int64_t w = 0; w < 2 * t.tiles(); ++w) {
+        const bool up = w >= t.tiles();
+        const int32_t *d = t.desc.data() + kkt::kSolDesc * (up ? 2 * t.tiles() - 1 - w : w);
+        const int32_t *e = d + (up ? 8 : 2);
+        const int32_t base = d[0], nr = d[1], nc = e[1], np = e[3], nx = e[5];
+        const auto &chunk = up ? t.chunk_u : t.chunk_l;
+        const auto &ref16 = up ? t.ref_u : t.ref_l;
+        const auto &ext = up ? t.ext_u : t.ext_l;
+        std::vector<double> &out = up ? z : y;
+        if (kkt::sol_lds_bytes(nr, nx, np) > t.lds || (np & 1) || (e[2] & 1)) return "solve_lds";
+        std::vector<double> xs(nr + nx + 1, 0.0);
+        std::vector<uint8_t> fin(nr + nx + 1, 0);
+        for (int32_t r = 0; r < nr; ++r) xs[r] = up ? y.at(t.pos_u.at(base + r)) : b[a.prow[t.node_l.at(base + r)]];
+        for (int32_t k = 0; k <= nx; ++k) fin[nr + k] = 1;
+        for (int32_t k = 0; k < nx; ++k) xs[nr + k] = out.at(ext.at(e[4] + k));
+        for (double v : xs)
+            if (std::isnan(v)) return "solve_input_not_final";
+        std::vector<double> res(nr, kNaN);
+        std::vector<int32_t> fresh;  // rows of the segment under way: final only after it
+        bool one_wave = true;
+        for (int32_t c = 0; c < nc; ++c) {
+            const uint32_t w0 = chunk.at(2 * (e[0] + c)), w1 = chunk.at(2 * (e[0] + c) + 1);
+            const int32_t r0 = w0 & 0x1FFF, cnt = (w0 >> 13) & 0x7F, lg = (w0 >> 20) & 7, half = (w0 >> 23) & 0xFF;
+            const int32_t off = w1 & 0x3FFFFFFF, wave = w1 >> 30;
+            // rows become final at a barrier, or at the next chunk while only wavefront 0 works
+            if ((w0 >> 31) || (one_wave && wave == 0)) {
+                for (int32_t r : fresh) fin[r] = 1;
+                fresh.clear();
+                one_wave = true;
+            }
+            one_wave = one_wave && wave == 0;
+            if (cnt < 1 || (cnt << lg) > 64 || lg > 6 || off % 2 || off + (cnt << lg) * 2 * half > np) return "chunk_shape";
+            for (int32_t q = 0; q < cnt; ++q) {
+                double acc = 0.0;
+                for (int32_t k = 0; k < (1 << lg) * 2 * half; ++k) {
+                    const int64_t at = e[2] + off + (int64_t)(q << lg) * 2 * half + k;
+                    const uint16_t s = ref16.at(at);
+                    if (s % 8 || !fin.at(s / 8)) return "solve_ref_not_final";
+                    acc += tv.at((up ? ub : 0) + at) * xs[s / 8];
+                }
+                const int32_t row = r0 + q;
+                if (row >= nr || !std::isnan(res[row])) return "solve_row";
+                res[row] = xs[row] - acc;
+                if (up) res[row] /= tv.at(db + base + row);
+                fresh.push_back(row);
+            }
+            for (int32_t r : fresh) xs[r] = res[r];
+        }
+        for (int32_t r = 0; r < nr; ++r) {
+            if (std::isnan(res[r]) || !std::isnan(out.at(base + r))) return "solve_row_lost";
+            out[base + r] = res[r];
+        }
+    }
+    double diff = 0.0, scale = 0.0;
+    for (int64_t p = 0; p < n; ++p) {
+        diff = std::fmax(diff, std::fabs(z[p] - ref[t.node_u[p]]));
+        scale = std::fmax(scale, std::fabs(ref[t.node_u[p]]));
+    }
+    char buf[64];
+    std::snprintf(buf, sizeof buf, "ok:%.3e", diff / scale);
+    return buf;
 }
 
 }  // namespace
@@ -148,6 +234,7 @@ int main(int argc, char **argv) {
         const std::string r = replay(a, lds, v2, lx, ux, guarded);
         std::printf("refactor=%s guarded=%lld", r.c_str(), (long long)guarded);
         if (r == "ok") {
+            std::printf(" solve=%s", replay_solve(a, lx, ux).c_str());
             std::FILE *o = std::fopen(argv[2], "wb");
             if (!o) return 2;
             const bool w = std::fwrite(lx.data(), 8, lx.size(), o) == lx.size() &&

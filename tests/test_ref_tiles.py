@@ -1,7 +1,8 @@
-"""The refactorization's tile schedule: replayed on the CPU (a driver built with
+"""The tile schedules of the refactorization and of the solves: replayed on the CPU (a driver built with
 AddressSanitizer and UndefinedBehaviorSanitizer) it gives the oracle's static-pivot
 refactorization bit for bit, over tile budgets from one that holds a handful of nodes (many
-layers, mostly externals) to one that holds the whole system; patterns it does not serve keep the
+layers, mostly externals) to one that holds the whole system, and both sweeps give plain
+substitution's solution; patterns it does not serve keep the
 hand-out items.  On the GPU the tile kernel's factors equal the oracle's and the hand-out
 kernel's."""
 import os
@@ -68,6 +69,9 @@ def test_tiles_replay_matches_oracle(driver, tmp_path, case, lds):
     lx, ux, guarded = oracle.LU(p.rowptr, p.colidx, v1).refactor64(p.rowptr, p.colidx, v2)
     assert np.array_equal(fac[:lx.size], lx) and np.array_equal(fac[lx.size:], ux)
     assert int(out["guarded"]) == guarded
+    # sums in another order than plain substitution's: rounding of a few dozen terms a row, along
+    # chains of about a hundred rows
+    assert out["solve"].startswith("ok:") and float(out["solve"][3:]) <= 1e-9, out["solve"]
 
 
 def test_tiles_replay_guards_as_the_oracle(driver, tmp_path):
