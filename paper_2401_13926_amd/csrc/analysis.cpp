@@ -1301,53 +1301,129 @@ bool build_solve_tiles(const AnalysisOptions &opt, Analysis &a) {
         for (int32_t k = 0; k < d[5]; ++k) ext_slot[ext[d[4] + k]] = nr + k;
         const int32_t zero = nr + d[5];
         if (zero >= 8191) return false;
-        bool prev_single = false;
-        for (int32_t r = 0; r < nr;) {
-            int32_t re = r;
-            while (re < nr && seg_of[rows[re]] == seg_of[rows[r]]) ++re;
-            // chunks of the segment [r, re)
+        auto length = [&](int32_t r) { return rp[rows[r] + 1] - rp[rows[r]]; };
+        // the dense range [d0, d1): the tile's last (L) or first (U) levels, as many as pay.  A
+        // level costs about as much as nine columns of the sweep, the range's own passes about
+        // two levels (0.28 us a level, 0.03 us a column)
+        int32_t d0 = 0, d1 = 0;
+        {
+            int64_t places = 0;
+            for (int32_t r = 0; r < nr; ++r) places += 3 * length(r) / 2 + 1;
+            int64_t best = 20;
+            int32_t levels = 0;
+            for (int32_t r = 0; r < nr;) {  // r rows from the narrow end so far
+                const int32_t at = dir ? r : nr - 1 - r;
+                int32_t k = r;
+                while (k < nr && seg_of[rows[dir ? k : nr - 1 - k]] == seg_of[rows[at]]) ++k;
+                r = k;
+                if (r > 64 || sol_lds_bytes(nr, d[5], places, r) > opt.sol_dense_lds) break;
+                ++levels;
+                const int64_t gain = 9 * ((int64_t)levels - 2) - r;
+                if (gain > best) {
+                    best = gain;
+                    d0 = dir ? 0 : nr - r;
+                    d1 = dir ? r : nr;
+                }
+            }
+        }
+        auto in_dense = [&](int32_t c) { return tile_of[c] == (int32_t)ti && slot[c] >= d0 && slot[c] < d1; };
+        std::vector<std::pair<int64_t, uint16_t>> dense;  // CSR entry, place in the triangle
+        bool prev_single = false, first_work = true;
+        // rows [r, re) independent of each other: cut into chunks; raw: rows of the dense range,
+        // without the entries inside it
+        auto segment = [&](int32_t r, int32_t re, bool raw) -> bool {
+            auto places_of = [&](int32_t q) {
+                if (!raw) return length(q);
+                int64_t c = 0;
+                for (int64_t p = rp[rows[q]]; p < rp[rows[q] + 1]; ++p) c += !in_dense(ci[p]);
+                return c;
+            };
             const size_t c0 = chunk.size();
             for (int32_t q = r; q < re;) {
-                const int64_t len = rp[rows[q] + 1] - rp[rows[q]];  // the longest row left
+                const int64_t len = places_of(q);  // of the longest row of the pass
+                if (len == 0 && (raw || !dir)) {  // its slot holds the right-hand side already
+                    ++q;
+                    continue;
+                }
                 int lg = 0;  // about eight entries per lane, fewer lanes rather than another pass
                 while (lg < 6 && ((int64_t)8 << lg) < len) ++lg;
                 while (lg > 0 && ((int64_t)(re - q) << lg) > 64 && ((int64_t)16 << lg) > len) --lg;
                 const int64_t g = (int64_t)1 << lg, half = (len + 2 * g - 1) / (2 * g), D = 2 * half;
                 // a pass holds 64 >> lg rows; a dozen rows or more with less than half as many
-                // places get a pass of their own
+                // places get a pass of their own, and so do rows of a dense range (in sweep order,
+                // not by length) with more places or less than half as many
                 int32_t cnt = std::min<int32_t>(re - q, 64 >> lg);
                 for (int32_t c = 1; c < cnt; ++c)
-                    if (half >= 2 && re - q - c >= kMinor && rp[rows[q + c] + 1] - rp[rows[q + c]] <= g * half) cnt = c;
+                    if ((!raw && half >= 2 && re - q - c >= kMinor && length(q + c) <= g * half) ||
+                        (!raw && !dir && length(q + c) == 0) ||
+                        (raw && (places_of(q + c) > g * D || (half * g >= 4 && 2 * places_of(q + c) <= g * half))))
+                        cnt = c;
                 if (half > 255) return false;
                 const int64_t off = (int64_t)ref.size() - d[2];
+                if (off >= 1 << 29) return false;
                 chunk.push_back((uint32_t)q | ((uint32_t)cnt << 13) | ((uint32_t)lg << 20) | ((uint32_t)half << 23));
-                chunk.push_back((uint32_t)off);
+                chunk.push_back((uint32_t)off | (raw ? 1u << 29 : 0u));
                 ref.resize(ref.size() + (size_t)(cnt * g * D), (uint16_t)(8 * zero));
                 for (int32_t c = 0; c < cnt; ++c) {
                     const int32_t m = rows[q + c];
-                    for (int64_t p = rp[m], e = 0; p < rp[m + 1]; ++p, ++e) {
+                    for (int64_t p = rp[m], e = 0; p < rp[m + 1]; ++p) {
+                        if (raw && in_dense(ci[p])) continue;
                         const int64_t at = d[2] + off + ((c << lg) + (e & (g - 1))) * D + (e >> lg);
                         map[p] = (int32_t)at;
                         ref[at] = (uint16_t)(8 * (tile_of[ci[p]] == (int32_t)ti ? slot[ci[p]] : ext_slot[ci[p]]));
+                        ++e;
                     }
                 }
                 q += cnt;
             }
             const size_t nc = (chunk.size() - c0) / 2;
+            if (nc == 0) return true;
             const bool single = nc == 1;
-            if (r > 0 && !(single && prev_single)) chunk[c0] |= 1u << 31;
+            if (!first_work && !(single && prev_single)) chunk[c0] |= 1u << 31;
+            first_work = false;
             for (size_t c = 0; c < nc; ++c) chunk[c0 + 2 * c + 1] |= (uint32_t)(c % 4) << 30;
             prev_single = single;
+            return true;
+        };
+        auto dense_range = [&]() -> bool {
+            if (d1 == d0) return true;
+            if (!segment(d0, d1, true)) return false;
+            d[6] = d0;
+            d[7] = d1 - d0;
+            d[9] = (int32_t)(chunk.size() / 2) - d[0];
+            const int64_t m = d1 - d0;
+            for (int32_t r = d0; r < d1; ++r)
+                for (int64_t p = rp[rows[r]]; p < rp[rows[r] + 1]; ++p)
+                    if (in_dense(ci[p])) {
+                        const int64_t lr = r - d0, lc = slot[ci[p]] - d0;
+                        dense.emplace_back(p, (uint16_t)(lc * m - lc * (lc + 1) / 2 + (lr - lc - 1)));
+                    }
+            prev_single = true;  // the sweep is wavefront 0's
+            first_work = false;
+            return true;
+        };
+        if (dir && !dense_range()) return false;
+        for (int32_t r = dir ? d1 : 0; r < (dir ? nr : d1 > d0 ? d0 : nr);) {
+            int32_t re = r;
+            while (re < nr && seg_of[rows[re]] == seg_of[rows[r]]) ++re;
+            if (!segment(r, re, false)) return false;
             r = re;
         }
+        if (!dir && !dense_range()) return false;
+        d[3] = (int32_t)ref.size() - d[2];
+        for (const auto &e : dense) {
+            map[e.first] = (int32_t)ref.size();
+            ref.push_back(e.second);
+        }
+        if (dense.size() & 1) ref.push_back((uint16_t)(d[7] * (d[7] - 1) / 2));
+        d[8] = (int32_t)ref.size() - d[2] - d[3];
         for (int32_t k = 0; k < d[5]; ++k) {
             ext_slot[ext[d[4] + k]] = -1;
             ext[d[4] + k] = pos[ext[d[4] + k]];
         }
         d[1] = (int32_t)(chunk.size() / 2) - d[0];
-        d[3] = (int32_t)ref.size() - d[2];
-        t.lds = std::max(t.lds, sol_lds_bytes(nr, d[5], d[3]));
-        return d[3] < (1 << 30);
+        t.lds = std::max(t.lds, sol_lds_bytes(nr, d[5], d[3], d[7]));
+        return true;
     };
     base = 0;
     for (size_t ti = 0; ti < members.size(); ++ti) {
@@ -1355,7 +1431,7 @@ bool build_solve_tiles(const AnalysisOptions &opt, Analysis &a) {
         d[0] = (int32_t)base;
         d[1] = (int32_t)members[ti].size();
         if (d[1] >= 8191 || !sweep(ti, 0, d + 2, t.chunk_l, t.ref_l, t.ext_l, lmap) ||
-            !sweep(ti, 1, d + 8, t.chunk_u, t.ref_u, t.ext_u, umap))
+            !sweep(ti, 1, d + 2 + kSolSweep, t.chunk_u, t.ref_u, t.ext_u, umap))
             return false;
         t.desc.insert(t.desc.end(), d, d + kSolDesc);
         t.node_l.insert(t.node_l.end(), rows_l[ti].begin(), rows_l[ti].end());

@@ -33,6 +33,7 @@ struct AnalysisOptions {
                                  // handed out one column at a time
     int64_t ref_lds = 0;         // LDS bytes of a refactorization tile (0: no tiles)
     int64_t sol_lds = 20480;     // LDS bytes a solve tile is formed for (with refactorization tiles)
+    int64_t sol_dense_lds = 32768;  // LDS bytes of a solve tile with its dense range at most
 };
 
 // Flags in TriSchedule::seg_lg: the segment's rows fit one wavefront; the segment is a
@@ -147,15 +148,26 @@ inline int64_t ref_lds_bytes(int64_t word, int64_t entries, int64_t ext, int64_t
 // lanes per row, every lane with the same even number of (value, reference) places, so a
 // lane's places are at a fixed distance from each other and the chunk needs no row offsets;
 // places without an entry hold the value 0 and refer to a zero slot.
-constexpr int kSolDesc = 16;  // int32 per tile descriptor
+//
+// The narrow end of a tile (the last levels of the L sweep, the first of the U sweep) may form a
+// dense range: at most 64 rows, several levels, whose references to each other go to a packed
+// strictly lower triangle in LDS (column-major, in sweep order, zero where there is no entry) and
+// are resolved by one wavefront's column sweep; the rows' other entries are places of chunks
+// before it, which leave the right-hand side minus those terms.
+constexpr int kSolDesc = 24;  // int32 per tile descriptor
+constexpr int kSolSweep = 10;  // int32 of it per sweep
 struct SolveTiles {
-    // per tile: 0 first position, 1 rows; for L at 2 and for U at 8: first chunk, chunks, first
-    // place, places, first external, externals
+    // per tile: 0 first position, 1 rows; for L at 2 and for U at 12: first chunk, chunks, first
+    // place, places, first external, externals; dense range: first row, rows, entries (after the
+    // tile's places, an even number), chunks before it
     std::vector<int32_t> desc;
     // per chunk two words: first row | rows << 13 | lg << 20 | places per lane / 2 << 23 (8 bits) |
-    // barrier before the chunk << 31; first place (within the tile) | wavefront << 30
+    // barrier before the chunk << 31; first place (within the tile) | no division by the pivot yet
+    // (dense range) << 29 | wavefront << 30
     std::vector<uint32_t> chunk_l, chunk_u;
-    std::vector<uint16_t> ref_l, ref_u;  // per place: 8 x the slot it refers to (rows, externals, zero)
+    // per place: 8 x the slot it refers to (rows, externals, zero); per dense entry: its place in
+    // the triangle
+    std::vector<uint16_t> ref_l, ref_u;
     std::vector<int32_t> ext_l, ext_u;   // per external: exchange position; a tile's first is the
                                          // one expected to be written last
     std::vector<int32_t> node_l, node_u;  // pivot step of every position (L order, U order)
@@ -164,9 +176,10 @@ struct SolveTiles {
     int64_t layers = 0;
     int64_t tiles() const { return (int64_t)desc.size() / kSolDesc; }
 };
-// LDS bytes of a solve tile: row, external and zero slots, U's reciprocal diagonals, places.
-inline int64_t sol_lds_bytes(int64_t rows, int64_t ext, int64_t places) {
-    return 8 * (rows + ext + 2) + 8 * (rows + 1) + 10 * places + 32;
+// LDS bytes of a solve tile: row, external and zero slots, U's reciprocal diagonals, places, the
+// triangle of a dense range of m rows (and a place for the padding entry).
+inline int64_t sol_lds_bytes(int64_t rows, int64_t ext, int64_t places, int64_t m) {
+    return 8 * (rows + ext + 2) + 8 * (rows + 1) + 10 * places + (m > 0 ? 8 * (m * (m - 1) / 2 + 1) : 0) + 32;
 }
 
 // Everything derived from the pattern and the first system's values.

@@ -1590,9 +1590,9 @@ template <typename T> __device__ __forceinline__ T load_system(const T *p) {
     return __builtin_bit_cast(T, __hip_atomic_load(reinterpret_cast<const U *>(p), __ATOMIC_RELAXED,
                                                    __HIP_MEMORY_SCOPE_SYSTEM));
 }
-template <typename T> struct Pair;
-template <> struct Pair<double> { using V = double2; };
-template <> struct Pair<float> { using V = float2; };
+template <typename T> struct Pair;  // two values, loaded together
+template <> struct Pair<double> { typedef double V __attribute__((ext_vector_type(2))); };
+template <> struct Pair<float> { typedef float V __attribute__((ext_vector_type(2))); };
 
 // Staging loads per thread and pass of a solve tile: 4 pairs of places; rows and externals.
 constexpr int kSolPair = 4, kSolRow = 2;
@@ -1607,8 +1607,9 @@ __device__ __forceinline__ void solve_tile(const SolveTileArgs<T> &a, int t, uns
     const int tid = threadIdx.x, lane = tid & 63;
     const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
     const auto td = uniform_ro(a.desc) + (int64_t)kSolDesc * t;
-    constexpr int o = kUpper ? 8 : 2;
+    constexpr int o = kUpper ? 2 + kSolSweep : 2;
     const int base = td[0], nr = td[1], nc = td[o + 1], np = td[o + 3], nx = td[o + 5];
+    const int dr = td[o + 6], dm = td[o + 7], nd2 = td[o + 8] / 2, dafter = dm > 0 ? td[o + 9] : -1;
     const uint32_t *chunk = (kUpper ? a.chunk_u : a.chunk_l) + 2 * (int64_t)td[o];
     const V2 *gval = reinterpret_cast<const V2 *>((kUpper ? a.val_u : a.val_l) + td[o + 2]);
     const uint32_t *gref = reinterpret_cast<const uint32_t *>((kUpper ? a.ref_u : a.ref_l) + td[o + 2]);
@@ -1618,7 +1619,10 @@ __device__ __forceinline__ void solve_tile(const SolveTileArgs<T> &a, int t, uns
     const int nslot = nr + nx + 1;  // rows, externals, the zero slot; 8 bytes each
     V2 *vals = reinterpret_cast<V2 *>(smem + 8 * (nslot + (nslot & 1)));  // np / 2
     T *dg = reinterpret_cast<T *>(vals + np / 2);                           // nr (upper)
-    uint32_t *refs = reinterpret_cast<uint32_t *>(dg + (kUpper ? nr + (nr & 1) : 0));  // np / 2
+    T *tri = dg + (kUpper ? nr : 0);                                        // the dense range's triangle
+    const int ntri = dm > 0 ? dm * (dm - 1) / 2 + 1 : 0;
+    uint32_t *refs = reinterpret_cast<uint32_t *>(tri + ntri + ((kUpper ? nr : 0) + ntri & 1));  // np / 2
+    for (int k = tid; k < ntri; k += kTileThreads) tri[k] = T(0);
     auto slot_at = [&](uint32_t off) -> T & { return *reinterpret_cast<T *>(smem + off); };
     uint32_t m0 = 0, m1 = 0;  // lane l of every wavefront holds chunk l's words
     auto chunk_words = [&](int c0) {
@@ -1663,6 +1667,15 @@ __device__ __forceinline__ void solve_tile(const SolveTileArgs<T> &a, int t, uns
                 vals[k] = v[u];
                 refs[k] = c[u];
             }
+        }
+    }
+    if (dm > 0) {
+        __syncthreads();  // the triangle is zeroed
+        for (int k = tid; k < nd2; k += kTileThreads) {
+            const V2 v = gval[np2 + k];
+            const uint32_t c = gref[np2 + k];
+            tri[c & 0xFFFFu] = v.x;
+            tri[c >> 16] = v.y;
         }
     }
     if (!kUpper && np2 == 0) {
@@ -1714,7 +1727,40 @@ __device__ __forceinline__ void solve_tile(const SolveTileArgs<T> &a, int t, uns
     // The chunks, each one wavefront's.  A chunk of a segment that one wavefront covers is
     // wavefront 0's, without barriers between such segments (a wavefront's LDS accesses complete
     // in order).
+    auto sweep = [&]() {  // the dense range: lane l owns row dr + l
+        __syncthreads();
+        if (wid != 0) return;
+        const bool act = lane < dm;
+        T y = act ? slot_at(8 * (dr + lane)) : T(0);
+        const T inv = kUpper && act ? dg[dr + lane] : T(1);
+        // lane l's coefficient of column c, tri[c m - c (c + 1) / 2 + l - c - 1], four columns ahead of
+        // its use (lanes without one read another's and do not use it)
+        const T *row = tri + (lane < 1 ? 1 : lane < dm ? lane : dm - 1);
+        int next = -1, col = 0;  // offset of column `col`
+        auto coef = [&]() -> T {
+            const T v = col < dm - 1 ? row[next] : T(0);
+            next += dm - col - 2;
+            ++col;
+            return v;
+        };
+        T q[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) q[u] = coef();
+        for (int c = 0; c < dm; c += 4) {
+            T n[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) n[u] = coef();
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const T xc = lane_value(kUpper ? y * inv : y, c + u < 63 ? c + u : 63);
+                if (lane > c + u) y = fma(-q[u], xc, y);
+                q[u] = n[u];
+            }
+        }
+        if (act) slot_at(8 * (dr + lane)) = kUpper ? y * inv : y;
+    };
     for (int c = 0; c < nc; ++c) {
+        if (kUpper && c == dafter) sweep();
         if ((c & 63) == 0 && c > 0) chunk_words(c);
         const uint32_t w0 = (uint32_t)__builtin_amdgcn_readlane((int)m0, c & 63);
         const uint32_t w1 = (uint32_t)__builtin_amdgcn_readlane((int)m1, c & 63);
@@ -1724,12 +1770,12 @@ __device__ __forceinline__ void solve_tile(const SolveTileArgs<T> &a, int t, uns
         const int half = (int)((w0 >> 23) & 0xFFu);
         if (lane < cnt << lg) {
             const int row = r0 + (lane >> lg);
-            const int p = (int)((w1 & 0x3FFFFFFFu) >> 1) + lane * half;
+            const int p = (int)((w1 & 0x1FFFFFFFu) >> 1) + lane * half;
             const uint32_t *rp = refs + p;
             const V2 *vp = vals + p;
             T &slot = slot_at(8 * row);
             const T rh = slot;
-            const T d = kUpper ? dg[row] : T(1);
+            const T d = kUpper && !(w1 & (1u << 29)) ? dg[row] : T(1);
             T acc = T(0);
             int h = 0;
             for (; h + 2 <= half; h += 2) {  // four places in flight
@@ -1758,6 +1804,7 @@ __device__ __forceinline__ void solve_tile(const SolveTileArgs<T> &a, int t, uns
             }
         }
     }
+    if (dafter == nc) sweep();  // (always so in the L sweep)
     __syncthreads();
 #pragma unroll
     for (int u = 0; u < kSolRow; ++u) {
@@ -1780,7 +1827,7 @@ __device__ __forceinline__ void solve_tile(const SolveTileArgs<T> &a, int t, uns
 // earlier ones, so the earliest unfinished task is always held by a running block that can
 // finish it.
 template <typename T>
-__global__ void __launch_bounds__(kTileThreads) k_solve_tiles(SolveTileArgs<T> a) {
+__global__ void __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(5))) k_solve_tiles(SolveTileArgs<T> a) {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ unsigned int task_sh;
     if (a.stopflag && a.stopflag->stop) return;

@@ -141,32 +141,72 @@ std::string replay_solve(const kkt::Analysis &a, const std::vector<double> &lx, 
     for (int64_t w = 0; w < 2 * t.tiles(); ++w) {
         const bool up = w >= t.tiles();
         const int32_t *d = t.desc.data() + kkt::kSolDesc * (up ? 2 * t.tiles() - 1 - w : w);
-        const int32_t *e = d + (up ? 8 : 2);
+        const int32_t *e = d + (up ? 2 + kkt::kSolSweep : 2);
         const int32_t base = d[0], nr = d[1], nc = e[1], np = e[3], nx = e[5];
         const auto &chunk = up ? t.chunk_u : t.chunk_l;
         const auto &ref16 = up ? t.ref_u : t.ref_l;
         const auto &ext = up ? t.ext_u : t.ext_l;
         std::vector<double> &out = up ? z : y;
-        if (kkt::sol_lds_bytes(nr, nx, np) > t.lds || (np & 1) || (e[2] & 1)) return "solve_lds";
+        if (kkt::sol_lds_bytes(nr, nx, np, e[7]) > t.lds || (np & 1) || (e[2] & 1) || (e[8] & 1)) return "solve_lds";
+        if (e[7] && (e[7] > 64 || e[6] + e[7] > nr || (up ? e[9] > nc : e[9] != nc))) return "dense_shape";
         std::vector<double> xs(nr + nx + 1, 0.0);
-        std::vector<uint8_t> fin(nr + nx + 1, 0);
+        std::vector<uint8_t> fin(nr + nx + 1, 0);  // 0 not final, 1 for wavefront 0 only, 2 for all
         for (int32_t r = 0; r < nr; ++r) xs[r] = up ? y.at(t.pos_u.at(base + r)) : b[a.prow[t.node_l.at(base + r)]];
-        for (int32_t k = 0; k <= nx; ++k) fin[nr + k] = 1;
+        for (int32_t k = 0; k <= nx; ++k) fin[nr + k] = 2;
         for (int32_t k = 0; k < nx; ++k) xs[nr + k] = out.at(ext.at(e[4] + k));
         for (double v : xs)
             if (std::isnan(v)) return "solve_input_not_final";
         std::vector<double> res(nr, kNaN);
+        // rows of L without entries need no chunk: their slots hold the solution from the start
+        for (int32_t r = 0; r < nr && !up; ++r) {
+            const int32_t k = t.node_l[base + r];
+            if (a.lrp[k] == a.lrp[k + 1] && !(e[7] && r >= e[6] && r < e[6] + e[7])) {
+                res[r] = xs[r];
+                fin[r] = 2;
+            }
+        }
         std::vector<int32_t> fresh;  // rows of the segment under way: final only after it
+        std::vector<int32_t> seen0;  // rows with fin = 1
         bool one_wave = true;
+        auto barrier = [&]() {
+            for (int32_t r : fresh) fin[r] = 2;
+            for (int32_t r : seen0) fin[r] = 2;
+            fresh.clear();
+            seen0.clear();
+            one_wave = true;
+        };
+        std::vector<uint8_t> raw(nr, 0);
+        auto sweep = [&]() -> std::string {
+            const int32_t m = e[7], r0 = e[6];
+            std::vector<double> tri(m * (m - 1) / 2 + 1, 0.0);
+            for (int32_t k = 0; k < e[8]; ++k)
+                tri.at(ref16.at(e[2] + np + k)) = tv.at((up ? ub : 0) + e[2] + np + k);
+            barrier();
+            for (int32_t c = 0; c < m; ++c) {
+                if (!raw[r0 + c] && !std::isnan(res[r0 + c])) return "dense_row";
+                double x = xs[r0 + c];
+                if (up) x /= tv.at(db + base + r0 + c);
+                for (int32_t l = c + 1; l < m; ++l) xs[r0 + l] -= tri[c * m - c * (c + 1) / 2 + (l - c - 1)] * x;
+                xs[r0 + c] = res[r0 + c] = x;
+                fresh.push_back(r0 + c);
+            }
+            return "";
+        };
         for (int32_t c = 0; c < nc; ++c) {
+            if (up && e[7] && c == e[9]) {
+                const std::string s = sweep();
+                if (!s.empty()) return s;
+            }
             const uint32_t w0 = chunk.at(2 * (e[0] + c)), w1 = chunk.at(2 * (e[0] + c) + 1);
             const int32_t r0 = w0 & 0x1FFF, cnt = (w0 >> 13) & 0x7F, lg = (w0 >> 20) & 7, half = (w0 >> 23) & 0xFF;
-            const int32_t off = w1 & 0x3FFFFFFF, wave = w1 >> 30;
+            const int32_t off = w1 & 0x1FFFFFFF, wave = w1 >> 30;
+            const bool rw = (w1 >> 29) & 1;
             // rows become final at a barrier, or at the next chunk while only wavefront 0 works
-            if ((w0 >> 31) || (one_wave && wave == 0)) {
+            if (w0 >> 31) barrier();
+            if (one_wave && wave == 0) {
                 for (int32_t r : fresh) fin[r] = 1;
+                seen0.insert(seen0.end(), fresh.begin(), fresh.end());
                 fresh.clear();
-                one_wave = true;
             }
             one_wave = one_wave && wave == 0;
             if (cnt < 1 || (cnt << lg) > 64 || lg > 6 || off % 2 || off + (cnt << lg) * 2 * half > np) return "chunk_shape";
@@ -175,16 +215,22 @@ std::string replay_solve(const kkt::Analysis &a, const std::vector<double> &lx, 
                 for (int32_t k = 0; k < (1 << lg) * 2 * half; ++k) {
                     const int64_t at = e[2] + off + (int64_t)(q << lg) * 2 * half + k;
                     const uint16_t s = ref16.at(at);
-                    if (s % 8 || !fin.at(s / 8)) return "solve_ref_not_final";
+                    if (s % 8 || fin.at(s / 8) < (wave == 0 ? 1 : 2)) return "solve_ref_not_final";
                     acc += tv.at((up ? ub : 0) + at) * xs[s / 8];
                 }
                 const int32_t row = r0 + q;
                 if (row >= nr || !std::isnan(res[row])) return "solve_row";
                 res[row] = xs[row] - acc;
-                if (up) res[row] /= tv.at(db + base + row);
-                fresh.push_back(row);
+                if (up && !rw) res[row] /= tv.at(db + base + row);
+                raw[row] = rw;
+                if (!rw) fresh.push_back(row);
+                if (rw != (e[7] && row >= e[6] && row < e[6] + e[7])) return "dense_flag";
+                xs[row] = res[row];
             }
-            for (int32_t r : fresh) xs[r] = res[r];
+        }
+        if (e[7] && e[9] == nc) {
+            const std::string s = sweep();
+            if (!s.empty()) return s;
         }
         for (int32_t r = 0; r < nr; ++r) {
             if (std::isnan(res[r]) || !std::isnan(out.at(base + r))) return "solve_row_lost";
