@@ -48,7 +48,6 @@ struct Control {
     double rnorm2, xnorm2, bnorm2;  // sums of squares from the residual kernel
     double rinf, xinf;              // max |rho_i|, max |x_i| from the residual kernel
     double h1[kRestartMax + 1];     // first CGS pass coefficients
-    double h2[kRestartMax + 1];     // second CGS pass coefficients
     double g[kRestartMax + 1];      // g[j]: right-hand side entry j before rotation j is applied
     double gr[kRestartMax];         // gr[j]: entry j after rotation j (the least-squares rhs); kept
                                     // apart from g so that no block of the normalization kernel

@@ -183,11 +183,26 @@ __device__ __forceinline__ void block_rows(int64_t total, int64_t &r0, int64_t &
 // ingest: K values into the workspace and into the factor layout (fill entries = 0)
 // ---------------------------------------------------------------------------------------
 
-__global__ void k_prep_solve(Control *c) {
-    c->hang = 0;
-    c->nonfinite_b = 0;
-    c->counter = 0;
-    c->stop = 0;
+// Start of a solve, in one launch: the control block's solve state, the exchange vectors' sentinels,
+// the work counters and, when `in` is given, the right-hand side in the vector order
+// (out[k] = in[perm[k]]).  Three launches of 4.5 us each did this before, whatever n.
+template <typename T>
+__global__ void k_solve_begin(int64_t n, const int32_t *__restrict__ perm, const double *__restrict__ in,
+                              double *__restrict__ out, T *y, T *z, Control *c) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        c->hang = 0;
+        c->nonfinite_b = 0;
+        c->counter = 0;
+        c->stop = 0;
+        c->work_lower = 0;
+        c->work_upper = 0;
+    }
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < n; k += stride) {
+        if (in) out[k] = in[perm[k]];
+        y[k] = sentinel<T>();
+        z[k] = sentinel<T>();
+    }
 }
 
 // Before the values of a new system: the row-norm maximum and the finiteness flag.
@@ -1941,7 +1956,8 @@ __global__ void __launch_bounds__(kStreamBlock) k_spmv_dots(KrylovArgs a, int j)
     for (int t = threadIdx.x; t <= j + 1; t += blockDim.x) out[t] = block_col_get(red, t);
 }
 
-// h1 = reduce(buffer 0); w -= V h1; partials (buffer 1): V_t . w (second CGS pass)
+// h1 = reduce(buffer 0); w -= V h1; partials (buffer 1): V_t . w (second CGS pass) for t <= j, and w . w
+// at t = j + 1
 __global__ void __launch_bounds__(kStreamBlock) k_cgs_pass2(KrylovArgs a, int j) {
     __shared__ double red[(kRestartMax + 2) * (kStreamBlock / 64)];
     __shared__ double h[kRestartMax + 2];
@@ -1954,37 +1970,6 @@ __global__ void __launch_bounds__(kStreamBlock) k_cgs_pass2(KrylovArgs a, int j)
     }
     int64_t r0, r1;
     block_rows(a.n, r0, r1);
-    for (int64_t i = r0 + threadIdx.x; i < r1; i += blockDim.x) {
-        double s = a.w[i];
-        for (int t = 0; t <= j; ++t) {
-            const double prod = a.V[(int64_t)t * a.n + i] * h[t];
-            s = s - prod;
-        }
-        a.w[i] = s;
-    }
-    __syncthreads();
-    double *out = partbuf(a, 1) + (int64_t)blockIdx.x * kPartStride;
-    for (int t = 0; t <= j; ++t) {
-        const double *v = a.V + (int64_t)t * a.n;
-        double s = 0.0;
-        for (int64_t i = r0 + threadIdx.x; i < r1; i += blockDim.x) s += v[i] * a.w[i];
-        block_col_put(s, t, red);
-    }
-    __syncthreads();
-    for (int t = threadIdx.x; t <= j; t += blockDim.x) out[t] = block_col_get(red, t);
-}
-
-// h2 = reduce(buffer 1); w -= V h2; partial (buffer 2): w . w
-__global__ void __launch_bounds__(kStreamBlock) k_cgs_finish(KrylovArgs a, int j) {
-    __shared__ double red[(kRestartMax + 2) * (kStreamBlock / 64)];
-    __shared__ double h[kRestartMax + 1];
-    if (a.ctl->stop) return;
-    const int G = gridDim.x;
-    reduce_cols(partbuf(a, 1), G, j + 1, h, red);
-    if (blockIdx.x == 0 && threadIdx.x == 0)
-        for (int t = 0; t <= j; ++t) a.ctl->h2[t] = h[t];
-    int64_t r0, r1;
-    block_rows(a.n, r0, r1);
     double ss = 0.0;
     for (int64_t i = r0 + threadIdx.x; i < r1; i += blockDim.x) {
         double s = a.w[i];
@@ -1995,8 +1980,17 @@ __global__ void __launch_bounds__(kStreamBlock) k_cgs_finish(KrylovArgs a, int j
         a.w[i] = s;
         ss += s * s;
     }
-    ss = block_sum(ss, red);
-    if (threadIdx.x == 0) partbuf(a, 2)[(int64_t)blockIdx.x * kPartStride] = ss;
+    __syncthreads();
+    double *out = partbuf(a, 1) + (int64_t)blockIdx.x * kPartStride;
+    for (int t = 0; t <= j; ++t) {
+        const double *v = a.V + (int64_t)t * a.n;
+        double s = 0.0;
+        for (int64_t i = r0 + threadIdx.x; i < r1; i += blockDim.x) s += v[i] * a.w[i];
+        block_col_put(s, t, red);
+    }
+    block_col_put(ss, j + 1, red);
+    __syncthreads();
+    for (int t = threadIdx.x; t <= j + 1; t += blockDim.x) out[t] = block_col_get(red, t);
 }
 
 // Closes Arnoldi column j (thread 0 of every block, identical results): col[0..j] are the
@@ -2051,22 +2045,31 @@ __device__ void arnoldi_close(Control *c, int j, int restart, double hn, double 
     }
 }
 
-// hn = ||w|| (reduce buffer 2); Hessenberg column h1 + h2, rotation and stop test
-// (arnoldi_close); then v_{j+1} = w / hn unless the step broke down, and the solve
+// h2 = reduce(buffer 1), hn = ||w - V h2||; Hessenberg column h1 + h2, rotation and stop test
+// (arnoldi_close); then v_{j+1} = (w - V h2) / hn unless the step broke down, and the solve
 // sentinels are re-armed when the cycle goes on.
+// hn comes from ||w||^2 - ||h2||^2 (V's columns are orthonormal): after one Gram-Schmidt pass h2
+// is rounding, about 1e-16 of the vector before that pass, so nothing cancels unless w itself is
+// that small, and there the breakdown test (hn against 1e-14 of it) ends the cycle.  A kernel
+// of its own for w - V h2 and its norm took 5.2 us at 60k unknowns and 12 us at 2M.
 template <typename T>
 __global__ void __launch_bounds__(kStreamBlock) k_normalize(KrylovArgs a, int j, int restart, T *s1, T *s2,
                                                             StepRecord *rec, unsigned long long token) {
     __shared__ double sh[3];
-    __shared__ double red[kStreamBlock / 64];
-    __shared__ double hsq[1];
+    __shared__ double red[(kRestartMax + 2) * (kStreamBlock / 64)];
+    __shared__ double h[kRestartMax + 2];
     Control *c = a.ctl;
     if (c->stop) return;
-    reduce_cols(partbuf(a, 2), gridDim.x, 1, hsq, red);
+    reduce_cols(partbuf(a, 1), gridDim.x, j + 2, h, red);
     if (threadIdx.x == 0) {
         double col[kRestartMax + 1];
-        for (int t = 0; t <= j; ++t) col[t] = c->h1[t] + c->h2[t];
-        arnoldi_close(c, j, restart, sqrt(hsq[0]), c->wnorm_in, col, rec + j, token, sh);
+        double hh = 0.0;
+        for (int t = 0; t <= j; ++t) {
+            col[t] = c->h1[t] + h[t];
+            hh += h[t] * h[t];
+        }
+        const double d2 = h[j + 1] - hh;
+        arnoldi_close(c, j, restart, d2 > 0.0 ? sqrt(d2) : 0.0, c->wnorm_in, col, rec + j, token, sh);
     }
     __syncthreads();
     const double hn = sh[0];
@@ -2075,7 +2078,14 @@ __global__ void __launch_bounds__(kStreamBlock) k_normalize(KrylovArgs a, int j,
     double *v = a.V + (int64_t)(j + 1) * a.n;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < a.n; i += stride) {
-        if (write_v) v[i] = a.w[i] / hn;
+        if (write_v) {
+            double s = a.w[i];
+            for (int t = 0; t <= j; ++t) {
+                const double prod = a.V[(int64_t)t * a.n + i] * h[t];
+                s = s - prod;
+            }
+            v[i] = s / hn;
+        }
         if (rearm) {
             s1[i] = sentinel<T>();
             s2[i] = sentinel<T>();
@@ -2270,11 +2280,31 @@ __device__ __forceinline__ double resid_row(const KrylovArgs &a, const double *x
     return bi - row_dot(a.rp, a.ci, a.kval, x, i);
 }
 
-// rho = b - K x; partials (buffer 0): ||rho||^2, ||x||^2, ||b||^2, non-finite b flag,
-// max |rho_i|, max |x_i|
+// The control block starts with the fields of ControlSummary, in the same layout.
+static_assert(sizeof(ControlSummary) % 8 == 0 && sizeof(ControlSummary) <= sizeof(Control),
+              "ControlSummary is copied as 64-bit words from the start of Control");
+
+// Partial sums read by the block that arrives last, of the same launch: stored and loaded at
+// system scope (they pass the producers' L2), each block's stores complete before it counts
+// itself.
+__device__ __forceinline__ void store_part(double *p, double v) {
+    __hip_atomic_store(reinterpret_cast<unsigned long long *>(p), __builtin_bit_cast(unsigned long long, v),
+                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+__device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+// rho = b - K x with ||rho||^2, ||x||^2, ||b||^2, the non-finite b flag, max |rho_i|, max |x_i|.  Each
+// block leaves its partials (buffer 0); the block that arrives last adds them in block order
+// (the same bits whichever block that is), writes the control block and copies its summary into
+// pinned host memory, then the token the host waits for.  (A launch of its own for the
+// reduction took 4.5 us at 60k unknowns and 9.8 us at 2M, twice per solve.)
 template <bool kDD>
-__global__ void __launch_bounds__(kStreamBlock) k_resid(KrylovArgs a, const double *b, const double *x, double *r) {
-    __shared__ double red[kStreamBlock / 64];
+__global__ void __launch_bounds__(kStreamBlock) k_resid(KrylovArgs a, const double *b, const double *x, double *r,
+                                                        ControlSummary *pub, unsigned long long *pub_token,
+                                                        unsigned long long token) {
+    __shared__ double red[4 * (kStreamBlock / 64)];
+    __shared__ double h[4];
+    __shared__ bool last_sh;
     int64_t r0, r1;
     block_rows(a.n, r0, r1);
     double sr = 0.0, sx = 0.0, sb = 0.0, mr = 0.0, mx = 0.0;
@@ -2298,43 +2328,44 @@ __global__ void __launch_bounds__(kStreamBlock) k_resid(KrylovArgs a, const doub
     const double bad = block_sum((double)badb, red);
     if (threadIdx.x == 0) {
         double *p = partbuf(a, 0) + (int64_t)blockIdx.x * kPartStride;
-        p[0] = sr;
-        p[1] = sx;
-        p[2] = sb;
-        p[3] = bad;
-        p[4] = mr;
-        p[5] = mx;
+        store_part(p + 0, sr);
+        store_part(p + 1, sx);
+        store_part(p + 2, sb);
+        store_part(p + 3, bad);
+        store_part(p + 4, mr);
+        store_part(p + 5, mx);
+        stores_done();
+        last_sh = atomicAdd(&a.ctl->counter, 1u) == gridDim.x - 1;
     }
-}
-
-// One block: sums of the residual kernel's partials into the control block.
-// The control block starts with the fields of ControlSummary, in the same layout.
-static_assert(sizeof(ControlSummary) % 8 == 0 && sizeof(ControlSummary) <= sizeof(Control),
-              "ControlSummary is copied as 64-bit words from the start of Control");
-
-// Reduces the residual kernel's partials into the control block, then copies the control
-// summary into pinned host memory (system-scope stores: visible to the host once the stream
-// has been synchronized), so reading it back needs no separate copy.
-__global__ void __launch_bounds__(kStreamBlock) k_resid_reduce(KrylovArgs a, int G, ControlSummary *pub) {
-    __shared__ double h[4];
-    __shared__ double red[4 * (kStreamBlock / 64)];
-    reduce_cols(partbuf(a, 0), G, 4, h, red);
+    __syncthreads();
+    if (!last_sh) return;
     const double *buf = partbuf(a, 0);
-    const int bb = threadIdx.x;
-    double mr_t = 0.0, mx_t = 0.0;
-    for (int r = bb; r < G; r += kStreamBlock) {
-        mr_t = fmax(mr_t, buf[(int64_t)r * kPartStride + 4]);
-        mx_t = fmax(mx_t, buf[(int64_t)r * kPartStride + 5]);
+    const int G = gridDim.x, tid = threadIdx.x;
+    double v[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    for (int q = tid; q < G; q += kStreamBlock) {
+        double p[6];
+#pragma unroll
+        for (int t = 0; t < 6; ++t) p[t] = load_system(buf + (int64_t)q * kPartStride + t);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) v[t] += p[t];
+        v[4] = fmax(v[4], p[4]);
+        v[5] = fmax(v[5], p[5]);
     }
-    const double mr = block_max(mr_t, red);
-    const double mx = block_max(mx_t, red);
-    if (threadIdx.x == 0) {
+#pragma unroll
+    for (int t = 0; t < 4; ++t) block_col_put(v[t], t, red);
+    __syncthreads();
+    if (tid < 4) h[tid] = block_col_get(red, tid);
+    __syncthreads();
+    mr = block_max(v[4], red);
+    mx = block_max(v[5], red);
+    if (tid == 0) {
         a.ctl->rinf = mr;
         a.ctl->xinf = mx;
         a.ctl->rnorm2 = h[0];
         a.ctl->xnorm2 = h[1];
         a.ctl->bnorm2 = h[2];
         if (h[3] != 0.0) a.ctl->nonfinite_b = 1;
+        a.ctl->counter = 0;
         // every word loaded first, then stored: one round trip to the control block instead
         // of one per word (a load, its store, the next load ... took 10-16 us per launch)
         constexpr int kWords = sizeof(ControlSummary) / 8;
@@ -2345,6 +2376,21 @@ __global__ void __launch_bounds__(kStreamBlock) k_resid_reduce(KrylovArgs a, int
         for (int w = 0; w < kWords; ++w) wv[w] = src[w];
 #pragma unroll
         for (int w = 0; w < kWords; ++w) __hip_atomic_store(dst + w, wv[w], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        __hip_atomic_store(pub_token, token, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+}
+
+// kkt_residual: b and r in the caller's order (row k of the copy of K is original row perm[k]), x in
+// the vector order.
+template <bool kDD>
+__global__ void __launch_bounds__(kStreamBlock) k_resid_user(KrylovArgs a, const int32_t *__restrict__ perm,
+                                                             const double *__restrict__ b, const double *x,
+                                                             double *__restrict__ r) {
+    int64_t r0, r1;
+    block_rows(a.n, r0, r1);
+    for (int64_t i = r0 + threadIdx.x; i < r1; i += blockDim.x) {
+        const int32_t p = perm[i];
+        r[p] = resid_row<kDD>(a, x, b[p], i);
     }
 }
 
@@ -2495,11 +2541,11 @@ struct kkt_handle_s {
     int factor_precision = 0;
     int grid_refactor64 = 0, grid_refactor32 = 0, grid_trsv64 = 0, grid_trsv32 = 0, grid_stream = 0;
     int grid_solve64 = 0, grid_solve32 = 0;  // blocks of the one-launch solve (with tiles)
-    kkt::ControlSummary *host_ctl = nullptr;  // pinned, mapped: written by k_resid_reduce
+    kkt::ControlSummary *host_ctl = nullptr;  // pinned, mapped: written by k_resid
     kkt::ControlSummary *dev_ctl_sum = nullptr;  // the same memory as seen by kernels
-    kkt::StepRecord *host_rec = nullptr;      // pinned, kRestartMax + 1 records (one per step)
+    kkt::StepRecord *host_rec = nullptr;      // pinned: one record per step, then one whose token
+                                              // is the residual kernel's
     kkt::StepRecord *dev_rec = nullptr;       // the same memory as seen by kernels
-    hipEvent_t step_ev[2] = {nullptr, nullptr};
     int restart_alloc = 0;
     bool fp64_current = false;  // mixed mode: FP64 factors of the current system exist
     int64_t repivots = 0;       // re-pivoted factorizations so far
@@ -2983,14 +3029,32 @@ kkt_status_t refactor_impl(kkt_handle_t h, const double *dev_values, int precisi
     return refactor_batch_impl(&h, &dev_values, 1, precision, s);
 }
 
-void launch_resid(kkt_handle_t h, const KrylovArgs &ka, const double *b, const double *x, double *r, hipStream_t s) {
-    if (h->opts.residual == KKT_RESID_DD) k_resid<true><<<h->grid_stream, kStreamBlock, 0, s>>>(ka, b, x, r);
-    else k_resid<false><<<h->grid_stream, kStreamBlock, 0, s>>>(ka, b, x, r);
+// Watches a token in pinned host memory; false after about a tenth of a second without it (the
+// caller then waits for the stream).
+bool await_token(const unsigned long long *p, unsigned long long want) {
+    for (int spin = 0; spin < (1 << 21); ++spin) {
+        if (__atomic_load_n(p, __ATOMIC_ACQUIRE) == want) return true;
+        __builtin_ia32_pause();
+    }
+    return false;
 }
 
-// The summary is already in host memory (k_resid_reduce wrote it): wait for the stream.
-kkt_status_t read_ctl(kkt_handle_t h, hipStream_t s) {
-    KKT_HIP(h, hipStreamSynchronize(s));
+// rho = b - K x into the workspace's r and its norms into the host's summary (*h->host_ctl), waited
+// for: the host watches for the launch's token, written after the summary, for about a tenth of
+// a second, then waits for the stream (a kernel that never finishes shows there).
+kkt_status_t residual_norms(kkt_handle_t h, const KrylovArgs &ka, const double *b, const double *x, hipStream_t s) {
+    const unsigned long long token = ++h->step_token;
+    hipEvent_t e0 = prof_begin(h, KKT_K_RESID, s);
+    if (h->opts.residual == KKT_RESID_DD)
+        k_resid<true><<<h->grid_stream, kStreamBlock, 0, s>>>(ka, b, x, h->d.r, h->dev_ctl_sum, &h->dev_rec[kRestartMax + 1].token, token);
+    else
+        k_resid<false><<<h->grid_stream, kStreamBlock, 0, s>>>(ka, b, x, h->d.r, h->dev_ctl_sum, &h->dev_rec[kRestartMax + 1].token, token);
+    prof_end(h, KKT_K_RESID, e0, s);
+    KKT_HIP(h, hipGetLastError());
+    bool seen = false;
+    // (timed launches: their events are read after the stream has been synchronized)
+    if (!h->prof_mask) seen = await_token(&h->host_rec[kRestartMax + 1].token, token);
+    if (!seen) KKT_HIP(h, hipStreamSynchronize(s));
     prof_collect(h);
     if (h->host_ctl->hang) {
         h->device_failed = true;
@@ -3004,10 +3068,11 @@ kkt_status_t read_ctl(kkt_handle_t h, hipStream_t s) {
 // formed only at the end of the cycle.  The host reads each Arnoldi step's stop flag while
 // the next step runs; at most one step is enqueued past the end of a cycle, and its kernels
 // return at once.
+// gather: the right-hand side in the caller's order, put into b first (null: b holds it already).
 // require_nrbe = false runs FGMRES as an inner solver (acceptance on its estimate only).
 template <typename T>
-kkt_status_t solve_impl(kkt_handle_t h, const double *b, double *x, double tol, kkt_solve_info_t *info,
-                        hipStream_t s, int max_cycles, bool require_nrbe = true) {
+kkt_status_t solve_impl(kkt_handle_t h, const double *gather, double *b, double *x, double tol,
+                        kkt_solve_info_t *info, hipStream_t s, int max_cycles, bool require_nrbe = true) {
     const Analysis &a = h->an;
     DevLayout &d = h->d;
     const int R = h->opts.restart;
@@ -3016,16 +3081,10 @@ kkt_status_t solve_impl(kkt_handle_t h, const double *b, double *x, double tol, 
     T *y = (T *)(sizeof(T) == 8 ? (void *)d.y64 : (void *)d.y32);
     T *z = (T *)(sizeof(T) == 8 ? (void *)d.z64 : (void *)d.z32);
     hipEvent_t e0 = prof_begin(h, KKT_K_OTHER, s);
-    k_prep_solve<<<1, 1, 0, s>>>(d.ctl);
+    k_solve_begin<T><<<G, kStreamBlock, 0, s>>>(a.n, d.vperm, gather, b, y, z, d.ctl);
     prof_end(h, KKT_K_OTHER, e0, s);
-    rearm<T>(h, s);
     KKT_HIP(h, precond<T>(h, b, x, nullptr, s, true));
-    e0 = prof_begin(h, KKT_K_RESID, s);
-    launch_resid(h, ka, b, x, d.r, s);
-    k_resid_reduce<<<1, kStreamBlock, 0, s>>>(ka, G, h->dev_ctl_sum);
-    prof_end(h, KKT_K_RESID, e0, s);
-    KKT_HIP(h, hipGetLastError());
-    kkt_status_t st = read_ctl(h, s);
+    kkt_status_t st = residual_norms(h, ka, b, x, s);
     if (st != KKT_OK) return st;
     const ControlSummary &c = *h->host_ctl;
     if (c.nonfinite) return fail(h, KKT_EINVAL, "non-finite value in the matrix of the last refactorization");
@@ -3092,26 +3151,19 @@ kkt_status_t solve_impl(kkt_handle_t h, const double *b, double *x, double tol, 
                 k_dcgs2<T><<<G, kStreamBlock, 0, s>>>(ka, j, R, y, z, h->dev_rec, token);
             } else {
                 k_cgs_pass2<<<G, kStreamBlock, 0, s>>>(ka, j);
-                k_cgs_finish<<<G, kStreamBlock, 0, s>>>(ka, j);
                 k_normalize<T><<<G, kStreamBlock, 0, s>>>(ka, j, R, y, z, h->dev_rec, token);
             }
             prof_end(h, KKT_K_CGS, e0, s);
             KKT_HIP(h, hipGetLastError());
-            KKT_HIP(h, hipEventRecord(h->step_ev[j & 1], s));
             if (j == 0) continue;
-            KKT_HIP(h, hipEventSynchronize(h->step_ev[(j - 1) & 1]));
             // the record of step j - 1 carries the token it was launched with; until it shows,
             // the slot may still hold an older step's record, so wait for it (bounded, then
-            // fall back to a full synchronization)
+            // a full synchronization)
             StepRecord &rec = h->host_rec[j - 1];
             const unsigned long long want = h->step_token - 1;
-            bool seen = false;
-            for (int spin = 0; spin < (1 << 20) && !seen; ++spin)
-                seen = __atomic_load_n(&rec.token, __ATOMIC_ACQUIRE) == want;
-            if (!seen) {
+            if (!await_token(&rec.token, want)) {
                 KKT_HIP(h, hipStreamSynchronize(s));
-                seen = __atomic_load_n(&rec.token, __ATOMIC_ACQUIRE) == want;
-                if (!seen) {
+                if (__atomic_load_n(&rec.token, __ATOMIC_ACQUIRE) != want) {
                     h->device_failed = true;
                     return fail(h, KKT_EDEVICE, "an Arnoldi step record did not arrive");
                 }
@@ -3133,12 +3185,7 @@ kkt_status_t solve_impl(kkt_handle_t h, const double *b, double *x, double tol, 
         e0 = prof_begin(h, KKT_K_OTHER, s);
         k_xupdate<<<G, kStreamBlock, 0, s>>>(ka, x);
         prof_end(h, KKT_K_OTHER, e0, s);
-        e0 = prof_begin(h, KKT_K_RESID, s);
-        launch_resid(h, ka, b, x, d.r, s);
-        k_resid_reduce<<<1, kStreamBlock, 0, s>>>(ka, G, h->dev_ctl_sum);
-        prof_end(h, KKT_K_RESID, e0, s);
-        KKT_HIP(h, hipGetLastError());
-        st = read_ctl(h, s);
+        st = residual_norms(h, ka, b, x, s);
         if (st != KKT_OK) return st;
         iters += h->host_ctl->jdone;
         // a DCGS2 cycle that stops before its last step has applied M^-1 once more
@@ -3185,25 +3232,19 @@ kkt_status_t solve_impl(kkt_handle_t h, const double *b, double *x, double tol, 
 // and NRBE <= target, when MA57's ratio test fails (NSR_new > ratio * NSR_old), or after
 // richardson_max_it corrections.
 template <typename T>
-kkt_status_t richardson_impl(kkt_handle_t h, const double *b, double *x, double tol, kkt_solve_info_t *info,
-                             hipStream_t s, bool inner_fgmres) {
+kkt_status_t richardson_impl(kkt_handle_t h, const double *gather, double *b, double *x, double tol,
+                             kkt_solve_info_t *info, hipStream_t s, bool inner_fgmres) {
     const Analysis &a = h->an;
     DevLayout &d = h->d;
     const int G = h->grid_stream;
     KrylovArgs ka = kargs<T>(h);
+    T *y = (T *)(sizeof(T) == 8 ? (void *)d.y64 : (void *)d.y32);
+    T *z = (T *)(sizeof(T) == 8 ? (void *)d.z64 : (void *)d.z32);
     hipEvent_t e0 = prof_begin(h, KKT_K_OTHER, s);
-    k_prep_solve<<<1, 1, 0, s>>>(d.ctl);
+    k_solve_begin<T><<<G, kStreamBlock, 0, s>>>(a.n, d.vperm, gather, b, y, z, d.ctl);
     prof_end(h, KKT_K_OTHER, e0, s);
-    rearm<T>(h, s);
     KKT_HIP(h, precond<T>(h, b, x, nullptr, s, true));
-    auto residual = [&]() -> kkt_status_t {
-        hipEvent_t r0 = prof_begin(h, KKT_K_RESID, s);
-        launch_resid(h, ka, b, x, d.r, s);
-        k_resid_reduce<<<1, kStreamBlock, 0, s>>>(ka, G, h->dev_ctl_sum);
-        prof_end(h, KKT_K_RESID, r0, s);
-        KKT_HIP(h, hipGetLastError());
-        return read_ctl(h, s);
-    };
+    auto residual = [&]() -> kkt_status_t { return residual_norms(h, ka, b, x, s); };
     kkt_status_t st = residual();
     if (st != KKT_OK) return st;
     const ControlSummary &c = *h->host_ctl;
@@ -3240,7 +3281,7 @@ kkt_status_t richardson_impl(kkt_handle_t h, const double *b, double *x, double 
             k_copy<<<G, kStreamBlock, 0, s>>>(a.n, d.r, d.rr);
             prof_end(h, KKT_K_OTHER, c0, s);
             kkt_solve_info_t in{};
-            st = solve_impl<T>(h, d.rr, d.dv, h->opts.inner_tol, &in, s, 1, false);
+            st = solve_impl<T>(h, nullptr, d.rr, d.dv, h->opts.inner_tol, &in, s, 1, false);
             if (st != KKT_OK && st != KKT_ENOCONV) return st;
             inf.precond_applications += in.precond_applications;
             inf.iterations += in.iterations;
@@ -3636,12 +3677,12 @@ kkt_status_t kkt_bind_workspace(kkt_handle_t h, void *dev_ptr, size_t bytes, voi
         KKT_HIP(h, hipHostGetDevicePointer((void **)&h->dev_ctl_sum, h->host_ctl, 0));
     }
     if (!h->host_rec) {
-        KKT_HIP(h, hipHostMalloc((void **)&h->host_rec, sizeof(StepRecord) * (kRestartMax + 1),
+        KKT_HIP(h, hipHostMalloc((void **)&h->host_rec, sizeof(StepRecord) * (kRestartMax + 2),
                                  hipHostMallocMapped | hipHostMallocCoherent));
         KKT_HIP(h, hipHostGetDevicePointer((void **)&h->dev_rec, h->host_rec, 0));
+        // (a released handle's memory may come back with its tokens in it; this one's start at 1)
+        std::memset((void *)h->host_rec, 0, sizeof(StepRecord) * (kRestartMax + 2));
     }
-    for (int e = 0; e < 2; ++e)
-        if (!h->step_ev[e]) KKT_HIP(h, hipEventCreateWithFlags(&h->step_ev[e], hipEventDisableTiming));
     char *b = (char *)dev_ptr;
     DevLayout &d = h->d;
     const Analysis &a = h->an;
@@ -4016,17 +4057,11 @@ kkt_status_t kkt_solve(kkt_handle_t h, const double *dev_b, double *dev_x, doubl
 // the workspace, so both are taken from the layout after it (and b gathered again).
 static kkt_status_t solve_vorder(kkt_handle_t h, const double *dev_b, double tol, kkt_solve_info_t *info,
                                  hipStream_t s) {
-    auto gather_b = [&]() -> kkt_status_t {
-        k_vgather<<<h->grid_stream, kStreamBlock, 0, s>>>(h->an.n, h->d.vperm, dev_b, h->d.bi);
-        KKT_HIP(h, hipGetLastError());
-        return KKT_OK;
-    };
-    if (gather_b() != KKT_OK) return KKT_EDEVICE;
     const int cycles = h->opts.max_restarts + 1;
     if (h->factor_precision == KKT_PREC_MIXED && !h->fp64_current) {
         const int mixed_cycles = h->opts.mixed_fallback ? std::min(cycles, std::max(1, h->opts.mixed_max_cycles))
                                                         : cycles;
-        kkt_status_t st = solve_impl<float>(h, h->d.bi, h->d.xi, tol, info, s, mixed_cycles);
+        kkt_status_t st = solve_impl<float>(h, dev_b, h->d.bi, h->d.xi, tol, info, s, mixed_cycles);
         if (st != KKT_ENOCONV || !h->opts.mixed_fallback) return st;
         // FP64 fallback: refactor the values already in the workspace in FP64 (the FP32
         // factors stay valid); later solves of this system go straight to FP64
@@ -4037,16 +4072,15 @@ static kkt_status_t solve_vorder(kkt_handle_t h, const double *dev_b, double tol
     }
     kkt_status_t st;
     if (h->opts.ir_method == KKT_IR_RICHARDSON || h->opts.ir_method == KKT_IR_ERROR_FGMRES) {
-        st = richardson_impl<double>(h, h->d.bi, h->d.xi, tol, info, s, h->opts.ir_method == KKT_IR_ERROR_FGMRES);
+        st = richardson_impl<double>(h, dev_b, h->d.bi, h->d.xi, tol, info, s, h->opts.ir_method == KKT_IR_ERROR_FGMRES);
     } else {
         const bool rp = h->opts.repivot_cycles > 0;
-        st = solve_impl<double>(h, h->d.bi, h->d.xi, tol, info, s,
+        st = solve_impl<double>(h, dev_b, h->d.bi, h->d.xi, tol, info, s,
                                 rp ? std::min(cycles, h->opts.repivot_cycles) : cycles);
         if (st == KKT_ENOCONV && rp) {
             st = repivot_impl(h, s);
             if (st != KKT_OK) return st;
-            if (gather_b() != KKT_OK) return KKT_EDEVICE;
-            st = solve_impl<double>(h, h->d.bi, h->d.xi, tol, info, s, cycles);
+            st = solve_impl<double>(h, dev_b, h->d.bi, h->d.xi, tol, info, s, cycles);
             if (info) info->repivoted = 1;
         }
     }
@@ -4099,10 +4133,11 @@ kkt_status_t kkt_residual(kkt_handle_t h, const double *dev_b, const double *dev
     hipStream_t s = (hipStream_t)stream;
     const KrylovArgs ka = kargs<double>(h);
     const int G = h->grid_stream;
-    k_vgather<<<G, kStreamBlock, 0, s>>>(h->an.n, h->d.vperm, dev_b, h->d.bi);
     k_vgather<<<G, kStreamBlock, 0, s>>>(h->an.n, h->d.vperm, dev_x, h->d.xi);
-    launch_resid(h, ka, h->d.bi, h->d.xi, h->d.r, s);
-    k_vscatter<<<G, kStreamBlock, 0, s>>>(h->an.n, h->d.vperm, h->d.r, dev_r);
+    if (h->opts.residual == KKT_RESID_DD)
+        k_resid_user<true><<<G, kStreamBlock, 0, s>>>(ka, h->d.vperm, dev_b, h->d.xi, dev_r);
+    else
+        k_resid_user<false><<<G, kStreamBlock, 0, s>>>(ka, h->d.vperm, dev_b, h->d.xi, dev_r);
     KKT_HIP(h, hipGetLastError());
     return KKT_OK;
 }
@@ -4182,8 +4217,6 @@ kkt_status_t kkt_release(kkt_handle_t h) {
     for (auto e : h->ev_pool) (void)hipEventDestroy(e);
     if (h->host_ctl) (void)hipHostFree(h->host_ctl);
     if (h->host_rec) (void)hipHostFree(h->host_rec);
-    for (auto e : h->step_ev)
-        if (e) (void)hipEventDestroy(e);
     delete h;
     return KKT_OK;
 }
