@@ -1481,11 +1481,11 @@ bool build_ref_tiles(const AnalysisOptions &opt, Analysis &a) {
         for (int64_t m = 0; m < n; ++m) {
             int64_t upd = 0;
             for (int64_t p = a.lrp[m]; p < a.lrp[m + 1]; ++p) upd += 1 + 2 * (deg(a.lci[p]) - loff[p] - 1);
-            // an item has at least one update
-            own[m] = ref_lds_bytes(8, 1 + 2 * deg(m), 0, 1, upd, upd, deg(m)) - 28;
+            // at most an item for every update
+            own[m] = ref_lds_bytes(1 + 2 * deg(m), 0, 1, 0, upd, 1 + deg(m)) - 24;
         }
         // a placed node's column and row from its first index in the subtree on are externals
-        if (!subtree_tiles(a, opt.ref_lds - 28, [&](int64_t m) { return own[m]; },
+        if (!subtree_tiles(a, opt.ref_lds - 24, [&](int64_t m) { return own[m]; },
                            [&](int64_t k, int64_t p) { return 8 * 2 * (a.fp[k + 1] - p); },
                            [](int64_t) { return (int64_t)0; }, tile_of, members, t.layers))
             return false;
@@ -1515,10 +1515,10 @@ bool build_ref_tiles(const AnalysisOptions &opt, Analysis &a) {
         for (int32_t g = 0; g < nseg; ++g) first[g + 1] += first[g];
         for (size_t k = 0; k < nodes.size(); ++k) node_of[nodes[k]] = (int32_t)k;
         int32_t d[kRefDesc] = {};
-        d[0] = (int32_t)(t.seg.size() / 3);
+        d[0] = (int32_t)(t.seg.size() / 2);
         d[1] = nseg;
         d[2] = (int32_t)t.src.size();
-        d[4] = (int32_t)t.item.size();
+        d[4] = (int32_t)(t.item.size() / 2);
         d[6] = (int32_t)t.upd.size();
         d[8] = (int32_t)t.lq.size();
         d[10] = (int32_t)t.exp.size();
@@ -1527,35 +1527,37 @@ bool build_ref_tiles(const AnalysisOptions &opt, Analysis &a) {
         d[15] = (int32_t)t.cmx_src.size();
         // slots
         std::vector<int32_t> fpos;  // F position of each slot
-        std::vector<int32_t> seg_slot(nseg + 1, 0), seg_l(nseg + 1, 0), seg_exp(nseg + 1, 0);
+        std::vector<int32_t> seg_slot(nseg + 1, 0), seg_q(nseg + 1, 0);
         auto add = [&](int32_t f, int32_t col) {
             slot[f] = (int32_t)fpos.size();
             fpos.push_back(f);
             t.src.push_back((int32_t)a.fsrc_k[f]);
             t.col.push_back(tile_of[col] == tid ? (uint16_t)node_of[col] : (uint16_t)0xFFFF);
         };
+        auto add_export = [&](int32_t f) {
+            export_of[f] = (int32_t)t.exp.size();
+            t.exp.push_back((uint16_t)slot[f]);
+        };
         for (int32_t g = 0; g < nseg; ++g) {
             seg_slot[g] = (int32_t)fpos.size();
-            for (int32_t k = first[g]; k < first[g + 1]; ++k) add((int32_t)(a.fp[nodes[k]] + a.fdiag[nodes[k]]), nodes[k]);
+            int64_t nl = 0;
+            for (int32_t k = first[g]; k < first[g + 1]; ++k) nl += deg(nodes[k]);
             for (int32_t k = first[g]; k < first[g + 1]; ++k)
                 for (int64_t p = l0(nodes[k]); p < a.fp[nodes[k] + 1]; ++p) {
                     add((int32_t)p, nodes[k]);
-                    t.lq.push_back((uint16_t)(8 * (seg_slot[g] + k - first[g])));
-                    if (tile_of[a.fi[p]] != tid) {
-                        export_of[p] = (int32_t)t.exp.size();
-                        t.exp.push_back((uint16_t)slot[p]);
-                    }
+                    t.lq.push_back((uint16_t)(8 * (seg_slot[g] + nl + k - first[g])));
+                    if (tile_of[a.fi[p]] != tid) add_export((int32_t)p);
                 }
+            for (int32_t k = first[g]; k < first[g + 1]; ++k) {
+                t.lq.push_back((uint16_t)(8 * fpos.size()));
+                add((int32_t)(a.fp[nodes[k]] + a.fdiag[nodes[k]]), nodes[k]);
+            }
             for (int32_t k = first[g]; k < first[g + 1]; ++k)
                 for (int64_t p = a.urp[nodes[k]]; p < a.urp[nodes[k] + 1]; ++p) {
                     add(upos[p], a.uci[p]);
-                    if (tile_of[a.uci[p]] != tid) {
-                        export_of[upos[p]] = (int32_t)t.exp.size();
-                        t.exp.push_back((uint16_t)slot[upos[p]]);
-                    }
+                    if (tile_of[a.uci[p]] != tid) add_export(upos[p]);
                 }
-            seg_l[g + 1] = (int32_t)(t.lq.size() - d[8]);
-            seg_exp[g + 1] = (int32_t)(t.exp.size() - d[10]);
+            seg_q[g + 1] = (int32_t)(t.lq.size() - d[8]);
         }
         const int32_t ne = (int32_t)fpos.size();
         // updates: for each node, its sources k ascending, each giving one update of the
@@ -1614,14 +1616,15 @@ bool build_ref_tiles(const AnalysisOptions &opt, Analysis &a) {
             const Item &it = items[k];
             ++seg_item[it.seg + 1];
             t.item.push_back((uint32_t)(8 * it.slot) | ((uint32_t)(t.upd.size() - d[6]) << 16));
-            t.upd.insert(t.upd.end(), upds.begin() + it.first, upds.begin() + it.first + it.count);
+            t.item.push_back(upds[it.first]);
+            t.upd.insert(t.upd.end(), upds.begin() + it.first + 1, upds.begin() + it.first + it.count);
         }
         t.item.push_back((uint32_t)(t.upd.size() - d[6]) << 16);
+        t.item.push_back(0u);
         for (int32_t g = 0; g < nseg; ++g) {
             seg_item[g + 1] += seg_item[g];
             t.seg.push_back((uint32_t)seg_item[g + 1] | ((uint32_t)seg_slot[g] << 16));
-            t.seg.push_back((uint32_t)first[g + 1] | ((uint32_t)seg_l[g + 1] << 16));
-            t.seg.push_back((uint32_t)seg_exp[g + 1]);
+            t.seg.push_back((uint32_t)first[g + 1] | ((uint32_t)seg_q[g + 1] << 16));
         }
         // column maxima: a column's entries of K above the diagonal whose U entry is an earlier tile's
         for (size_t k = 0; k < nodes.size(); ++k)
@@ -1646,7 +1649,7 @@ bool build_ref_tiles(const AnalysisOptions &opt, Analysis &a) {
         d[13] = (int32_t)(t.ext.size() - d[12]);
         d[16] = (int32_t)(t.cmx_src.size() - d[15]);
         t.desc.insert(t.desc.end(), d, d + kRefDesc);
-        t.lds = std::max(t.lds, ref_lds_bytes(8, ne, d[13], d[14], d[7], d[5], d[9]));
+        t.lds = std::max(t.lds, ref_lds_bytes(ne, d[13], d[14], d[7], d[5], d[9]));
         for (size_t e = ne; e < fpos.size(); ++e) ext_slot[fpos[e]] = -1;
         if (t.lds > opt.ref_lds || ne + d[13] >= 8192 || d[7] > 0xFFFF || d[5] > 0xFFFF) {
             t = RefTiles();

@@ -103,38 +103,40 @@ inline int64_t dense_block_values(int64_t m) { return m * (m - 1) / 2; }
 //
 // Inside a tile, nodes are solved by level (segment) with a barrier in between.  Segment g
 // first runs its items (an item applies consecutive updates of one entry, in ascending k, whose
-// factors are all final by then), then divides the L entries of its nodes.  Entry slots are
-// ordered by segment: the nodes' diagonals, their L entries, their U entries.
+// factors are all final by then), then guards its nodes' pivots and divides their L entries.
+// Entry slots are ordered by segment: the nodes' L entries, their diagonals, their U entries.
 constexpr int kRefDesc = 20;  // int32 per tile descriptor
 struct RefTiles {
     // per tile: 0 first segment, 1 segments, 2 first entry, 3 entries, 4 first item, 5 items, 6 first
-    // update, 7 updates, 8 first L entry, 9 L entries, 10 first export, 11 exports, 12 first
-    // external, 13 externals, 14 nodes, 15 first column-maximum extra, 16 extras
+    // further update, 7 further updates, 8 first pivot reference, 9 pivot references, 10 first
+    // export, 11 exports, 12 first external, 13 externals, 14 nodes, 15 first column-maximum
+    // extra, 16 extras
     std::vector<int32_t> desc;
-    // per segment, three words of cumulative counts within the tile: items | first slot << 16,
-    // nodes | L entries << 16, exports (each at the segment's end, the slot at its start)
+    // per segment, two words of cumulative counts within the tile: items | first slot << 16, nodes |
+    // pivot references << 16 (each at the segment's end, the slot at its start)
     std::vector<uint32_t> seg;
     std::vector<int32_t> src;     // per entry slot: its value's entry in the copy of K, or -1 (fill)
     std::vector<uint16_t> col;    // per entry slot: tile-local node of its column, 0xFFFF if none
     // (slots in the next three are byte offsets, 8 x the slot: a tile has fewer than 8,192)
-    std::vector<uint32_t> item;   // per item (and one past a tile's last): slot | first update << 16
-    std::vector<uint32_t> upd;    // per update: slot of its L factor | slot of its U factor << 16
-    std::vector<uint16_t> lq;     // per L entry: slot of its node's pivot
+    // per item (and one past a tile's last) two words: slot | start of its further updates << 16;
+    // its first update
+    std::vector<uint32_t> item;
+    std::vector<uint32_t> upd;    // per update after an item's first: slots of its L | U factor << 16
+    std::vector<uint16_t> lq;     // pivot references, per L entry and diagonal in slot order: pivot slot
     std::vector<uint16_t> exp;    // per export: slot (entries whose other index is in a later tile)
     std::vector<int32_t> ext;     // per external: the export it is
     std::vector<uint32_t> cmx_node;  // column-maximum extras: entries of K in a node's column whose
     std::vector<int32_t> cmx_src;    // U entry belongs to an earlier tile (node; entry of K's copy)
     std::vector<int32_t> out_pos;   // per entry, by ascending position in the solve layout: that
     std::vector<uint16_t> out_slot;  // position and the entry's slot
-    int64_t lds = 0;              // LDS bytes of the largest tile (FP64)
+    int64_t lds = 0;              // LDS bytes of the largest tile
     int64_t layers = 0;
     int64_t tiles() const { return (int64_t)desc.size() / kRefDesc; }
 };
-// LDS bytes of a refactorization tile with values of `word` bytes: entry and external slots (8
-// bytes each for either precision), column maxima; updates, items; L entries' pivots.
-inline int64_t ref_lds_bytes(int64_t word, int64_t entries, int64_t ext, int64_t nodes, int64_t upd, int64_t items,
-                             int64_t nl) {
-    return 8 * (entries + ext) + word * (nodes + 1) + 4 * (upd + items + 1) + 2 * nl + 16;
+// LDS bytes of a refactorization tile: entry and external slots and pivot thresholds (8 bytes each
+// for either precision); items, further updates; pivot references.
+inline int64_t ref_lds_bytes(int64_t entries, int64_t ext, int64_t nodes, int64_t further, int64_t items, int64_t nq) {
+    return 8 * (entries + ext + nodes) + 8 * (items + 1) + 4 * further + 2 * nq + 16;
 }
 
 // Schedule of both triangular solves by tiles, built together with RefTiles (the same factors

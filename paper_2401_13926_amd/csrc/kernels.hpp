@@ -20,7 +20,7 @@ constexpr int kTileLdsMax = 150 * 1024; // per compute unit, the rest for the ke
 // 256 compute units.
 constexpr int kResidentRefactorWaves = 3 * 4 * 256;
 constexpr int kRefactorLds = 1024;     // factor entries staged in LDS per wavefront
-constexpr int kRefTileLds = 32768;     // LDS bytes of a refactorization tile
+constexpr int kRefTileLds = 32512;     // LDS bytes of a refactorization tile
 constexpr int kMaxBatch = 8;           // systems of one pattern refactored by one launch
 constexpr int kWorkQueues = 8;         // refactorization hand-out queues (one per XCD of MI355X: a
                                        // block's queue is its index mod 8, the XCD it runs on)

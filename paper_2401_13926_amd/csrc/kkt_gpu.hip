@@ -132,6 +132,12 @@ __device__ __forceinline__ T load_ready(const T *p, unsigned int *hang) {
     }
 }
 
+template <typename T> __device__ __forceinline__ T load_system(const T *p) {
+    using U = typename Bits<T>::U;
+    return __builtin_bit_cast(T, __hip_atomic_load(reinterpret_cast<const U *>(p), __ATOMIC_RELAXED,
+                                                   __HIP_MEMORY_SCOPE_SYSTEM));
+}
+
 // Wave-uniform: lane 0 takes `chunk` consecutive work items from *counter.
 __device__ __forceinline__ unsigned int grab(unsigned int *counter, unsigned int chunk) {
     unsigned int v = 0;
@@ -935,7 +941,9 @@ template <typename T> struct RefTileBatch {
 };
 
 // Staging loads per thread and pass of a refactorization tile.
-constexpr int kRefEnt = 8, kRefUpd = 8, kRefItem = 8, kRefL = 4, kRefExt = 4, kRefCmx = 2;
+constexpr int kRefEnt = 8, kRefUpd = 2, kRefItem = 8, kRefL = 5, kRefExt = 4, kRefCmx = 2;
+// Exports and items (of a wavefront segment) per thread that are held in registers.
+constexpr int kRefExp = 2;
 
 __device__ __forceinline__ void lds_max(double *p, double v) {
     atomicMax(reinterpret_cast<unsigned long long *>(p), (unsigned long long)__double_as_longlong(v));
@@ -944,18 +952,16 @@ __device__ __forceinline__ void lds_max(float *p, float v) {
     atomicMax(reinterpret_cast<unsigned int *>(p), (unsigned int)__float_as_int(v));
 }
 
-// The pivot d of a column whose largest entry of K is cm, under the tiny-pivot guard.  Applied
-// to a guarded pivot it gives the same value again.
-template <typename T> __device__ __forceinline__ T guarded_pivot(T d, T cm, bool &hit) {
-    const T ur = unit_roundoff<T>();
-    const T cmx = cm > T(0) ? cm : T(1);
-    hit = !(fabs(d) > ur * cmx) || !isfinite(d);
-    return hit ? (d < T(0) ? T(-1) : T(1)) * ur * cmx : d;
+// The pivot d of a column under the tiny-pivot guard; limit: unit roundoff x the largest entry of
+// K's column (1 for an empty one).  Applied to a guarded pivot it gives the same value again.
+template <typename T> __device__ __forceinline__ T guarded_pivot(T d, T limit, bool &hit) {
+    hit = !(fabs(d) > limit) || !isfinite(d);
+    return hit ? (d < T(0) ? -limit : limit) : d;
 }
 
 // kBatch: more than one slot (the slot table's pointers cost the single-system kernel spills).
 template <typename T, bool kBatch>
-__global__ void __launch_bounds__(kCoopBlock) k_refactor_tiles(RefTileArgs a, RefTileBatch<T> batch) {
+__global__ void __launch_bounds__(kCoopBlock) __attribute__((amdgpu_waves_per_eu(4))) k_refactor_tiles(RefTileArgs a, RefTileBatch<T> batch) {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ unsigned int tile_sh;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -986,49 +992,45 @@ __global__ void __launch_bounds__(kCoopBlock) k_refactor_tiles(RefTileArgs a, Re
         const auto td = uniform_ro(a.desc) + (int64_t)kRefDesc * t;
         const int s0 = td[0], ns = td[1], ne = td[3], ni = td[5], nu = td[7], nl = td[9], nx = td[13], nn = td[14],
                   nc = td[16];
-        const int64_t eb = td[2], ib = td[4], ub = td[6], lb = td[8], pb = td[10], xb = td[12], cb = td[15];
+        const int npx = td[11];
+        const int64_t eb = td[2], ub = td[6], lb = td[8], pb = td[10], xb = td[12], cb = td[15];
+        const uint2 *gitem = reinterpret_cast<const uint2 *>(a.item) + td[4];
         // (entry and external slots of 8 bytes first: updates and items name them by byte offset)
         double *slots = reinterpret_cast<double *>(smem);
         auto xs_at = [&](uint32_t off) -> T & { return *reinterpret_cast<T *>(smem + off); };
-        T *cm = reinterpret_cast<T *>(slots + ne + nx);           // nn column maxima
-        uint32_t *upd = reinterpret_cast<uint32_t *>(cm + nn + (nn & 1));  // nu
-        uint32_t *item = upd + nu;                                // ni + 1
-        uint16_t *lq = reinterpret_cast<uint16_t *>(item + ni + 1);  // nl
-        for (int k = tid; k < nn; k += kCoopBlock) cm[k] = T(0);
+        double *cm8 = slots + ne + nx;                            // nn column maxima, then limits
+        auto cm_at = [&](int k) -> T & { return *reinterpret_cast<T *>(cm8 + k); };
+        uint2 *item = reinterpret_cast<uint2 *>(cm8 + nn);        // ni + 1
+        uint32_t *upd = reinterpret_cast<uint32_t *>(item + ni + 1);  // nu
+        uint16_t *lq = reinterpret_cast<uint16_t *>(upd + nu);    // nl
+        for (int k = tid; k < nn; k += kCoopBlock) cm8[k] = 0.0;
         // lane l of every wavefront holds segment l's words
-        uint32_t m0 = 0, m1 = 0, m2 = 0;
+        uint32_t m0 = 0, m1 = 0;
         auto seg_words = [&](int g0) {
-            m0 = m1 = m2 = 0;
+            m0 = m1 = 0;
             if (g0 + lane < ns) {
-                const uint32_t *p = a.seg + 3 * (int64_t)(s0 + g0 + lane);
+                const uint32_t *p = a.seg + 2 * (int64_t)(s0 + g0 + lane);
                 m0 = p[0];
                 m1 = p[1];
-                m2 = p[2];
             }
         };
         seg_words(0);
         __syncthreads();
-        // Staging, in two rounds of loads per pass: the schedule's own data, then the values it
-        // points to (K's entries, the externals), then LDS.
-        for (int pe = 0, pu = 0, pi = 0, pl = 0, px = 0, pc = 0;
-             pe < ne || pu < nu || pi <= ni || pl < nl || px < nx || pc < nc;
+        // Staging, in two rounds of loads per pass: the schedule's own data, then K's entries it
+        // points to, then LDS.
+        for (int pe = 0, pu = 0, pi = 0, pl = 0, pc = 0; pe < ne || pu < nu || pi <= ni || pl < nl || pc < nc;
              pe += kRefEnt * kCoopBlock, pu += kRefUpd * kCoopBlock, pi += kRefItem * kCoopBlock,
-             pl += kRefL * kCoopBlock, px += kRefExt * kCoopBlock, pc += kRefCmx * kCoopBlock) {
-            int src[kRefEnt], xsrc[kRefExt], csrc[kRefCmx];
-            uint32_t uv[kRefUpd], iv[kRefItem], cn[kRefCmx];
+             pl += kRefL * kCoopBlock, pc += kRefCmx * kCoopBlock) {
+            int src[kRefEnt], csrc[kRefCmx];
+            uint32_t uv[kRefUpd], cn[kRefCmx];
+            uint2 iv[kRefItem];
             uint16_t col[kRefEnt], lv[kRefL];
             double v[kRefEnt], cv[kRefCmx];
-            T xv[kRefExt];
 #pragma unroll
             for (int u = 0; u < kRefEnt; ++u) {
                 const int k = pe + tid + u * kCoopBlock;
                 src[u] = k < ne ? a.src[eb + k] : -1;
                 col[u] = k < ne ? a.col[eb + k] : (uint16_t)0xFFFF;
-            }
-#pragma unroll
-            for (int u = 0; u < kRefExt; ++u) {
-                const int k = px + tid + u * kCoopBlock;
-                xsrc[u] = k < nx ? a.ext[xb + k] : 0;
             }
 #pragma unroll
             for (int u = 0; u < kRefCmx; ++u) {
@@ -1044,7 +1046,7 @@ __global__ void __launch_bounds__(kCoopBlock) k_refactor_tiles(RefTileArgs a, Re
 #pragma unroll
             for (int u = 0; u < kRefItem; ++u) {
                 const int k = pi + tid + u * kCoopBlock;
-                iv[u] = k <= ni ? a.item[ib + k] : 0u;
+                if (k <= ni) iv[u] = gitem[k];
             }
 #pragma unroll
             for (int u = 0; u < kRefL; ++u) {
@@ -1056,8 +1058,6 @@ __global__ void __launch_bounds__(kCoopBlock) k_refactor_tiles(RefTileArgs a, Re
             for (int u = 0; u < kRefEnt; ++u) v[u] = src[u] >= 0 ? kval[src[u]] : 0.0;
 #pragma unroll
             for (int u = 0; u < kRefCmx; ++u) cv[u] = csrc[u] >= 0 ? kval[csrc[u]] : 0.0;
-#pragma unroll
-            for (int u = 0; u < kRefExt; ++u) xv[u] = px + tid + u * kCoopBlock < nx ? X[xsrc[u]] : T(0);
             // LDS
 #pragma unroll
             for (int u = 0; u < kRefUpd; ++u) {
@@ -1080,40 +1080,49 @@ __global__ void __launch_bounds__(kCoopBlock) k_refactor_tiles(RefTileArgs a, Re
                 const int k = pe + tid + u * kCoopBlock;
                 const T x = (T)v[u];
                 if (k < ne) xs_at(8 * k) = x;
-                if (col[u] != 0xFFFF && fabs(x) > T(0)) lds_max(cm + col[u], fabs(x));
+                if (col[u] != 0xFFFF && fabs(x) > T(0)) lds_max(&cm_at(col[u]), fabs(x));
             }
 #pragma unroll
             for (int u = 0; u < kRefCmx; ++u) {
                 const T x = (T)cv[u];
-                if (csrc[u] >= 0 && fabs(x) > T(0)) lds_max(cm + cn[u], fabs(x));
+                if (csrc[u] >= 0 && fabs(x) > T(0)) lds_max(&cm_at((int)cn[u]), fabs(x));
             }
+        }
+        __syncthreads();
+        for (int k = tid; k < nn; k += kCoopBlock) {
+            const T m = cm_at(k);
+            cm_at(k) = unit_roundoff<T>() * (m > T(0) ? m : T(1));
+        }
+        // (read here, used at the end)
+        uint16_t ex[kRefExp];
+#pragma unroll
+        for (int u = 0; u < kRefExp; ++u) {
+            const int k = tid + u * kCoopBlock;
+            ex[u] = k < npx ? a.exp[pb + k] : (uint16_t)0;
+        }
+        // the externals last: a tile that waits for them has done everything else
+        for (int x0 = 0; x0 < nx; x0 += kRefExt * kCoopBlock) {
+            int xsrc[kRefExt];
+            T xv[kRefExt];
 #pragma unroll
             for (int u = 0; u < kRefExt; ++u) {
-                const int k = px + tid + u * kCoopBlock;
+                const int k = x0 + tid + u * kCoopBlock;
+                xsrc[u] = k < nx ? a.ext[xb + k] : 0;
+            }
+#pragma unroll
+            for (int u = 0; u < kRefExt; ++u) xv[u] = x0 + tid + u * kCoopBlock < nx ? load_system(X + xsrc[u]) : T(0);
+#pragma unroll
+            for (int u = 0; u < kRefExt; ++u) {
+                const int k = x0 + tid + u * kCoopBlock;
                 if (k < nx) {
-                    T x = xv[u];
-                    if (is_sentinel(x)) x = load_ready<T, 1>(X + xsrc[u], &ctl->hang);
-                    xs_at(8 * (ne + k)) = x;
+                    if (is_sentinel(xv[u])) xv[u] = load_ready<T, 1>(X + xsrc[u], &ctl->hang);
+                    xs_at(8 * (ne + k)) = xv[u];
                 }
             }
         }
         __syncthreads();
-        // An export that carries the sentinel's bits (only a value of K itself could) becomes
-        // another NaN, so that no wait mistakes it for an unwritten one.
-        auto do_exports = [&](int x0, int x1, int stride) {
-            for (int k = x0 + tid; k < x1; k += stride) {
-                T x = xs_at(8 * a.exp[pb + k]);
-                if (is_sentinel(x)) x = T(NAN);
-                store_ready(X + pb + k, x);
-            }
-        };
-        // One item: its updates one after another (four at a time while there are that many).
-        auto run_item = [&](int i) {
-            const uint32_t ia = item[i], ie = item[i + 1];
-            const int u1 = (int)(ie >> 16);
-            int u = (int)(ia >> 16);
-            T &target = xs_at(ia & 0xFFFFu);
-            T x = target;
+        // The updates of an item after its first.
+        auto further = [&](T x, int u, int u1) -> T {
             for (; u + 4 <= u1; u += 4) {
                 T l[4], f[4];
 #pragma unroll
@@ -1133,13 +1142,40 @@ __global__ void __launch_bounds__(kCoopBlock) k_refactor_tiles(RefTileArgs a, Re
                 const T prod = xs_at(p & 0xFFFFu) * xs_at(p >> 16);
                 x = x - prod;
             }
-            target = x;
+            return x;
         };
-        // The segments.  One whose items and L entries fit a wavefront is wavefront 0's alone,
-        // without block barriers (a wavefront's LDS accesses complete in order).
+        // Slot e holds an L entry (divide) or a pivot; piv: its column's pivot slot, limit: that
+        // pivot's.  Every lane of a column guards its pivot by itself.
+        auto finish = [&](uint32_t e, uint32_t piv, T limit, bool divide) {
+            bool hit;
+            const T d = guarded_pivot(xs_at(piv), limit, hit);
+            if (divide) {
+                xs_at(e) = xs_at(e) / d;
+            } else if (hit) {
+                xs_at(e) = d;
+                atomicAdd(&ctl->nguard, 1ull);
+                if (a.guard_fail_policy) atomicOr(&ctl->guard_fail, 1u);
+            }
+        };
+        // The segments.  One whose items, and L entries and pivots, fit a wavefront is wavefront 0's
+        // alone, without block barriers (a wavefront's LDS accesses complete in order).
+        // What bounds these is the serial chain of a level: read the factors, update, read the
+        // pivot, divide, with every instruction issued by one wavefront.  So the level's
+        // schedule words are read while the level before it is under way.
         const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
         bool prev_wave = false;
-        int gb = 0, i0 = 0, n0 = 0, q0 = 0, x0 = 0, px0 = 0;
+        int gb = 0, i0 = 0, n0 = 0, q0 = 0;
+        uint2 it_a = make_uint2(0, 0);  // this lane's item, the start of the next one's updates, its
+        uint32_t it_n = 0, lq_a = 0;    // pivot reference: of segment `ahead`
+        int ahead = -1;
+        auto read_ahead = [&](int g, int i, int q) {
+            // (lanes past the segment's own read the words of later ones or the end word)
+            const int il = i + lane < ni ? i + lane : ni;
+            it_a = item[il];
+            it_n = item[il < ni ? il + 1 : ni].x;
+            lq_a = lq[q + lane < nl ? q + lane : nl - 1];
+            ahead = g;
+        };
         for (int g = 0; g < ns; ++g) {
             if (g >= gb + 64) {
                 gb = g;
@@ -1147,59 +1183,73 @@ __global__ void __launch_bounds__(kCoopBlock) k_refactor_tiles(RefTileArgs a, Re
             }
             const uint32_t w0 = (uint32_t)__builtin_amdgcn_readlane((int)m0, g - gb);
             const uint32_t w1 = (uint32_t)__builtin_amdgcn_readlane((int)m1, g - gb);
-            const int x1 = __builtin_amdgcn_readlane((int)m2, g - gb);
             const int i1 = (int)(w0 & 0xFFFFu), sl0 = (int)(w0 >> 16);
             const int n1 = (int)(w1 & 0xFFFFu), q1 = (int)(w1 >> 16);
-            const int nd = n1 - n0;
-            const bool wave = i1 - i0 <= 64 && q1 - q0 <= 64 && nd <= 64;
+            const int nd = n1 - n0, nq = q1 - q0, nlq = nq - nd;
+            const bool wave = i1 - i0 <= 64 && nq <= 64;
             if (g > 0 && !(wave && prev_wave)) __syncthreads();
-            if (px0 < x0) {  // exports of the block segment before
-                do_exports(px0, x0, kCoopBlock);
-                px0 = x0;
-            }
             prev_wave = wave;
-            // L entry q: its pivot's slot and the column maximum that goes with it (every lane of a
-            // column guards its pivot by itself)
-            auto divide = [&](int q) {
-                const uint32_t piv = lq[q], e = 8u * (uint32_t)(sl0 + nd + (q - q0));
-                bool hit;
-                const T d = guarded_pivot(xs_at(piv), cm[n0 + (int)(piv >> 3) - sl0], hit);
-                xs_at(e) = xs_at(e) / d;
-            };
-            auto guard = [&](int k) {
-                bool hit;
-                const T d = guarded_pivot(xs_at(8u * (uint32_t)(sl0 + k)), cm[n0 + k], hit);
-                if (hit) {
-                    xs_at(8u * (uint32_t)(sl0 + k)) = d;
-                    atomicAdd(&ctl->nguard, 1ull);
-                    if (a.guard_fail_policy) atomicOr(&ctl->guard_fail, 1u);
-                }
+            // limit of the pivot in byte slot piv: cm_at(n0 + node), node = piv / 8 - (sl0 + nlq)
+            const int lim0 = 8 * (n0 - sl0 - nlq);
+            auto limit_of = [&](uint32_t piv) -> T {
+                return *reinterpret_cast<T *>(reinterpret_cast<unsigned char *>(cm8) + lim0 + (int)piv);
             };
             if (wave) {
                 if (wid == 0) {
-                    if (i0 + lane < i1) run_item(i0 + lane);
-                    __builtin_amdgcn_wave_barrier();
-                    if (q0 + lane < q1) divide(q0 + lane);
-                    if (lane < nd) guard(lane);
-                    if (x0 < x1) {
-                        __builtin_amdgcn_wave_barrier();
-                        do_exports(x0, x1, 64);
+                    if (ahead != g) read_ahead(g, i0, q0);
+                    const uint2 it = it_a;
+                    const uint32_t in = it_n, piv = lq_a;
+                    const bool act = lane < i1 - i0;
+                    T x = T(0), l = T(0), f = T(0);
+                    if (act) {
+                        x = xs_at(it.x & 0xFFFFu);
+                        l = xs_at(it.y & 0xFFFFu);
+                        f = xs_at(it.y >> 16);
                     }
+                    if (g + 1 < ns) read_ahead(g + 1, i1, q1);
+                    if (act) {
+                        const T prod = l * f;
+                        x = x - prod;
+                        if ((in >> 16) != (it.x >> 16)) x = further(x, (int)(it.x >> 16), (int)(in >> 16));
+                        xs_at(it.x & 0xFFFFu) = x;
+                    }
+                    __builtin_amdgcn_wave_barrier();
+                    if (lane < nq) finish(8u * (uint32_t)(sl0 + lane), piv, limit_of(piv), lane < nlq);
+                    __builtin_amdgcn_wave_barrier();
                 }
-                px0 = x1;
             } else {
-                for (int i = i0 + tid; i < i1; i += kCoopBlock) run_item(i);
+                for (int i = i0 + tid; i < i1; i += kCoopBlock) {
+                    const uint2 it = item[i];
+                    const uint32_t in = item[i + 1].x;
+                    T x = xs_at(it.x & 0xFFFFu);
+                    const T prod = xs_at(it.y & 0xFFFFu) * xs_at(it.y >> 16);
+                    x = further(x - prod, (int)(it.x >> 16), (int)(in >> 16));
+                    xs_at(it.x & 0xFFFFu) = x;
+                }
                 __syncthreads();
-                for (int q = q0 + tid; q < q1; q += kCoopBlock) divide(q);
-                for (int k = tid; k < nd; k += kCoopBlock) guard(k);
+                for (int q = tid; q < nq; q += kCoopBlock) {
+                    const uint32_t piv = lq[q0 + q];
+                    finish(8u * (uint32_t)(sl0 + q), piv, limit_of(piv), q < nlq);
+                }
             }
             i0 = i1;
             n0 = n1;
             q0 = q1;
-            x0 = x1;
         }
         __syncthreads();
-        if (px0 < x0) do_exports(px0, x0, kCoopBlock);
+        // Exports first: other tiles wait for them (all at the end: in the segments' chain each
+        // would cost its wavefront a store and its address).  One that carries the sentinel's
+        // bits (only a value of K itself could) becomes another NaN, so that no wait mistakes
+        // it for an unwritten one.
+        auto do_export = [&](int k, uint16_t slot) {
+            T x = xs_at(8u * slot);
+            if (is_sentinel(x)) x = T(NAN);
+            store_ready(X + pb + k, x);
+        };
+#pragma unroll
+        for (int u = 0; u < kRefExp; ++u)
+            if (tid + u * kCoopBlock < npx) do_export(tid + u * kCoopBlock, ex[u]);
+        for (int k = tid + kRefExp * kCoopBlock; k < npx; k += kCoopBlock) do_export(k, a.exp[pb + k]);
         // the finished entries into the solve layout, by ascending position
         for (int e0 = 0; e0 < ne; e0 += 8 * kCoopBlock) {
             int pos[8], sl[8];
@@ -1211,7 +1261,7 @@ __global__ void __launch_bounds__(kCoopBlock) k_refactor_tiles(RefTileArgs a, Re
             }
 #pragma unroll
             for (int u = 0; u < 8; ++u)
-                if (e0 + tid + u * kCoopBlock < ne) Tv[pos[u]] = xs_at(8 * sl[u]);
+                if (e0 + tid + u * kCoopBlock < ne) Tv[pos[u]] = xs_at(8u * (uint32_t)sl[u]);
         }
         __syncthreads();
     }
@@ -1600,11 +1650,6 @@ template <typename T> struct SolveTileArgs {
     unsigned int *hang;
 };
 
-template <typename T> __device__ __forceinline__ T load_system(const T *p) {
-    using U = typename Bits<T>::U;
-    return __builtin_bit_cast(T, __hip_atomic_load(reinterpret_cast<const U *>(p), __ATOMIC_RELAXED,
-                                                   __HIP_MEMORY_SCOPE_SYSTEM));
-}
 template <typename T> struct Pair;  // two values, loaded together
 template <> struct Pair<double> { typedef double V __attribute__((ext_vector_type(2))); };
 template <> struct Pair<float> { typedef float V __attribute__((ext_vector_type(2))); };

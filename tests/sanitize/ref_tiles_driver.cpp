@@ -37,7 +37,7 @@ std::string replay(const kkt::Analysis &a, int64_t budget, const std::vector<dou
         const int32_t ns = d[1], ne = d[3], ni = d[5], nu = d[7], nl = d[9], nx = d[13], nn = d[14];
         entries += ne;
         nodes += nn;
-        if (kkt::ref_lds_bytes(8, ne, nx, nn, nu, ni, nl) > budget) return "lds_budget";
+        if (kkt::ref_lds_bytes(ne, nx, nn, nu, ni, nl) > budget) return "lds_budget";
         std::vector<double> xs(ne + nx), cm(nn, 0.0);
         for (int32_t e = 0; e < ne; ++e) {
             const int32_t s = t.src.at(d[2] + e);
@@ -55,20 +55,20 @@ std::string replay(const kkt::Analysis &a, int64_t budget, const std::vector<dou
         }
         std::vector<uint8_t> final_(ne + nx, 0);
         for (int32_t k = 0; k < nx; ++k) final_[ne + k] = 1;
-        int32_t i0 = 0, n0 = 0, q0 = 0, x0 = 0;
+        int32_t i0 = 0, n0 = 0, q0 = 0;
         for (int32_t g = 0; g < ns; ++g) {
-            const uint32_t w0 = t.seg.at(3 * (d[0] + g)), w1 = t.seg.at(3 * (d[0] + g) + 1);
+            const uint32_t w0 = t.seg.at(2 * (d[0] + g)), w1 = t.seg.at(2 * (d[0] + g) + 1);
             const int32_t i1 = w0 & 0xFFFF, sl0 = w0 >> 16, n1 = w1 & 0xFFFF, q1 = w1 >> 16;
-            const int32_t x1 = (int32_t)t.seg.at(3 * (d[0] + g) + 2), nd = n1 - n0;
-            if (nd < 1 || sl0 + nd + (q1 - q0) > ne) return "segment_shape";
+            const int32_t nd = n1 - n0, nq = q1 - q0, nlq = nq - nd;
+            if (nd < 1 || nlq < 0 || sl0 + nq > ne) return "segment_shape";
             std::vector<uint8_t> touched(ne, 0);
             for (int32_t i = i0; i < i1; ++i) {
-                const uint32_t ia = t.item.at(d[4] + i), ie = t.item.at(d[4] + i + 1);
+                const uint32_t ia = t.item.at(2 * (d[4] + i)), ie = t.item.at(2 * (d[4] + i + 1));
                 const uint32_t s = (ia & 0xFFFF) / 8;
                 if ((ia & 7) || (int32_t)s >= ne || final_[s] || touched[s]++) return "item_target";
-                if ((ie >> 16) <= (ia >> 16) || (int32_t)(ie >> 16) > nu) return "item_updates";
-                for (uint32_t u = ia >> 16; u < ie >> 16; ++u) {
-                    const uint32_t p = t.upd.at(d[6] + u);
+                if ((ie >> 16) < (ia >> 16) || (int32_t)(ie >> 16) > nu) return "item_updates";
+                for (int64_t u = -1; u < (int64_t)(ie >> 16) - (int64_t)(ia >> 16); ++u) {
+                    const uint32_t p = u < 0 ? t.item.at(2 * (d[4] + i) + 1) : t.upd.at(d[6] + (ia >> 16) + u);
                     const uint32_t l = (p & 0xFFFF) / 8, f = (p >> 16) / 8;
                     if ((p & 7) || (p >> 16 & 7) || !final_.at(l) || !final_.at(f)) return "factor_not_final";
                     const double prod = xs[l] * xs[f];
@@ -76,35 +76,34 @@ std::string replay(const kkt::Analysis &a, int64_t budget, const std::vector<dou
                 }
             }
             for (int32_t k = 0; k < nd; ++k) {
-                double &p = xs[sl0 + k];
+                double &p = xs[sl0 + nlq + k];
                 const double c = cm.at(n0 + k) > 0.0 ? cm[n0 + k] : 1.0;
                 if (!(std::fabs(p) > 0x1p-53 * c) || !std::isfinite(p)) {
                     p = (p < 0.0 ? -1.0 : 1.0) * 0x1p-53 * c;
                     ++guarded;
                 }
-                final_[sl0 + k] = 1;
+                final_[sl0 + nlq + k] = 1;
             }
-            for (int32_t q = q0; q < q1; ++q) {
-                const int32_t node = t.lq.at(d[8] + q) / 8 - sl0;
-                if (node < 0 || node >= nd) return "l_node";
-                const int32_t e = sl0 + nd + (q - q0);
-                xs[e] = xs[e] / xs[sl0 + node];
+            for (int32_t q = 0; q < nq; ++q) {
+                const int32_t piv = t.lq.at(d[8] + q0 + q) / 8, e = sl0 + q;
+                if ((t.lq[d[8] + q0 + q] & 7) || piv < sl0 + nlq || piv >= sl0 + nq || (q >= nlq && piv != e)) return "pivot";
+                if (q >= nlq) continue;
+                xs[e] = xs[e] / xs[piv];
                 final_[e] = 1;
             }
             // the rest of the segment's slots are its nodes' U entries
-            const int32_t end = g + 1 < ns ? (int32_t)(t.seg.at(3 * (d[0] + g + 1)) >> 16) : ne;
-            for (int32_t e = sl0 + nd + (q1 - q0); e < end; ++e) final_[e] = 1;
-            for (int32_t k = x0; k < x1; ++k) {
-                const uint16_t e = t.exp.at(d[10] + k);
-                if (!final_.at(e)) return "export_not_final";
-                X.at(d[10] + k) = xs[e];
-            }
+            const int32_t end = g + 1 < ns ? (int32_t)(t.seg.at(2 * (d[0] + g + 1)) >> 16) : ne;
+            for (int32_t e = sl0 + nq; e < end; ++e) final_[e] = 1;
             i0 = i1;
             n0 = n1;
             q0 = q1;
-            x0 = x1;
         }
-        if (i0 != ni || n0 != nn || q0 != nl || x0 != d[11]) return "segment_totals";
+        if (i0 != ni || n0 != nn || q0 != nl) return "segment_totals";
+        for (int32_t k = 0; k < d[11]; ++k) {
+            const uint16_t e = t.exp.at(d[10] + k);
+            if (e >= ne) return "export_slot";
+            X.at(d[10] + k) = xs[e];
+        }
         for (int32_t e = 0; e < ne; ++e) {
             const int32_t pos = t.out_pos.at(d[2] + e);
             if (e && pos <= t.out_pos[d[2] + e - 1]) return "out_order";
