@@ -1381,7 +1381,7 @@ bool build_solve_tiles(const AnalysisOptions &opt, Analysis &a) {
             const bool single = nc == 1;
             if (!first_work && !(single && prev_single)) chunk[c0] |= 1u << 31;
             first_work = false;
-            for (size_t c = 0; c < nc; ++c) chunk[c0 + 2 * c + 1] |= (uint32_t)(c % 4) << 30;
+            for (size_t c = 0; c < nc; ++c) chunk[c0 + 2 * c + 1] |= (uint32_t)(c % kSolWaves) << 30;
             prev_single = single;
             return true;
         };

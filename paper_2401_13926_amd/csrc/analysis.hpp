@@ -158,6 +158,7 @@ inline int64_t ref_lds_bytes(int64_t entries, int64_t ext, int64_t nodes, int64_
 // before it, which leave the right-hand side minus those terms.
 constexpr int kSolDesc = 24;  // int32 per tile descriptor
 constexpr int kSolSweep = 10;  // int32 of it per sweep
+constexpr int kSolWaves = 4;   // wavefronts of a solve block (a segment's chunks go round robin)
 struct SolveTiles {
     // per tile: 0 first position, 1 rows; for L at 2 and for U at 12: first chunk, chunks, first
     // place, places, first external, externals; dense range: first row, rows, entries (after the

@@ -24,19 +24,26 @@
 #include <vector>
 
 #include "../../include/kkt.h"
+#include "kernels.hpp"
+
+namespace kkt {
+kkt_status_t solve_scratch(kkt_handle_t h, SolveScratch *o);
+kkt_status_t direct_solve_armed(kkt_handle_t h, const double *b, double *x, const int *stop, hipStream_t s);
+}  // namespace kkt
 
 namespace {
 
 constexpr int kBlock = 256;
 constexpr int kGridMax = 1024;
-constexpr int kCgGroup = 8;  // CG iterations enqueued between two reads of the stop flag
+constexpr int kCgGroup = 8;  // CG iterations enqueued between two reads of the stop flag (even: an
+                             // iteration's parity picks its place in CgControl::rr)
 
 // Scalars of one solve (device memory).  Partial sums: block b writes part[b * 4 + t].
 struct CgControl {
-    double rr;      // r.r of the current iterate
-    double rr_new;  // r.r after this iteration's update (moved to rr by k_hy_cg_finish)
+    double rr[2];   // r.r of the iterate of even and of odd iterations (one is written while the
+                    // other is read)
     double rr0;     // r.r at the start
-    double tol2;    // (cg_tol^2) rr0: stop when rr <= tol2
+    double tol2;    // (cg_tol^2) rr0: stop when r.r <= tol2
     int stop;       // CG finished (converged, iteration cap, or a zero residual)
     int iters;      // iterations done
     int max_iter;
@@ -61,11 +68,13 @@ __device__ double block_sum(double v, double *red) {
     return s;
 }
 
-// Sum of partial column t over the G blocks of the previous kernel (every thread, fixed order).
-__device__ double reduce_part(const double *part, int G, int t) {
+// Sum of partial column t over the G <= kGridMax blocks of the previous kernel, in every thread: the
+// threads' strided sums, then block_sum's fixed order (the same bits in every block).  A loop of
+// every thread over all G partials took 16 us a launch at 60k unknowns.
+__device__ double reduce_part(const double *part, int G, int t, double *red) {
     double s = 0.0;
-    for (int b = 0; b < G; ++b) s += part[b * 4 + t];
-    return s;
+    for (int b = threadIdx.x; b < G; b += kBlock) s += part[b * 4 + t];
+    return block_sum(s, red);
 }
 
 // H_gamma entries, and the values of J and J^T gathered from K's CSR values; K's values kept
@@ -100,13 +109,25 @@ __global__ void k_hy_ingest(int64_t nh, const int64_t *__restrict__ hd_src, cons
 }
 
 // out[i] = add[i] + alpha * sum_r JT(i, r) x[r] (add may be null: 0; the sum in ascending r,
-// then the product by alpha, then the addition).  Returns at once when *stop is set.
+// then the product by alpha, then the addition).  Returns at once when *stop is set.  Also arms the
+// H_gamma solve that follows (its exchange vectors have the same n entries).
 __global__ void k_hy_jt(int64_t n, const int64_t *__restrict__ rp, const int32_t *__restrict__ ci,
                         const double *__restrict__ val, const double *__restrict__ x, double alpha,
-                        const double *add, double *out, const int *stop) {
+                        const double *add, double *out, const int *stop, kkt::SolveScratch sc) {
     if (stop && *stop) return;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        *sc.work_lower = 0;
+        *sc.work_upper = 0;
+    }
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
+        if (sc.f32) {
+            static_cast<unsigned int *>(sc.y)[i] = kkt::kSent32;
+            static_cast<unsigned int *>(sc.z)[i] = kkt::kSent32;
+        } else {
+            static_cast<unsigned long long *>(sc.y)[i] = kkt::kSent64;
+            static_cast<unsigned long long *>(sc.z)[i] = kkt::kSent64;
+        }
         double s = 0.0;
         for (int64_t p = rp[i]; p < rp[i + 1]; ++p) {
             const double prod = val[p] * x[ci[p]];
@@ -148,11 +169,13 @@ __global__ void __launch_bounds__(kBlock) k_hy_j(int64_t m, const int64_t *__res
     if (threadIdx.x == 0) part[blockIdx.x * 4] = acc;
 }
 
-// CG start: rr0 = r.r from the partials; the stop threshold.
-__global__ void k_hy_cg_start(int G, const double *part, double tol, int max_iter, CgControl *c) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    const double rr = reduce_part(part, G, 0);
-    c->rr = rr;
+// CG start (one block): rr0 = r.r from the partials; the stop threshold.
+__global__ void __launch_bounds__(kBlock) k_hy_cg_start(int G, const double *part, double tol, int max_iter,
+                                                        CgControl *c) {
+    __shared__ double red[kBlock / 64];
+    const double rr = reduce_part(part, G, 0, red);
+    if (threadIdx.x != 0) return;
+    c->rr[0] = rr;
     c->rr0 = rr;
     c->tol2 = tol * tol * rr;
     c->iters = 0;
@@ -160,14 +183,15 @@ __global__ void k_hy_cg_start(int G, const double *part, double tol, int max_ite
     c->stop = (rr == 0.0 || max_iter <= 0) ? 1 : 0;
 }
 
-// alpha = rr / (p.q); lam += alpha p; r -= alpha q; partial r.r (into the other buffer).
+// alpha = rr / (p.q); lam += alpha p; r -= alpha q; partial r.r (into the other buffer).  k: parity
+// of the iteration.
 __global__ void __launch_bounds__(kBlock) k_hy_cg_update(int64_t m, int G, const double *part_in, double *part_out,
                                                          const double *p, const double *q, double *r, double *lam,
-                                                         const CgControl *c) {
+                                                         int k, const CgControl *c) {
     __shared__ double red[kBlock / 64];
     if (c->stop) return;
-    const double pq = reduce_part(part_in, G, 0);
-    const double alpha = c->rr / pq;
+    const double pq = reduce_part(part_in, G, 0, red);
+    const double alpha = c->rr[k] / pq;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     double acc = 0.0;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m; i += stride) {
@@ -180,24 +204,26 @@ __global__ void __launch_bounds__(kBlock) k_hy_cg_update(int64_t m, int G, const
     if (threadIdx.x == 0) part_out[blockIdx.x * 4] = acc;
 }
 
-// rr' = r.r; beta = rr' / rr; p = r + beta p.  Every block reads rr from the previous launch;
-// block 0 parks rr' in rr_new, which no block of this launch reads.
+// rr' = r.r; beta = rr' / rr; p = r + beta p; then (block 0) the end of the iteration: rr', the
+// count and the stop test.  rr' goes to the other parity's place, which no block of this launch
+// reads; a block that already sees the stop leaves its part of p, which no later kernel reads
+// then, as it is.
 __global__ void __launch_bounds__(kBlock) k_hy_cg_direction(int64_t m, int G, const double *part, const double *r,
-                                                            double *p, CgControl *c) {
-    if (c->stop) return;
-    const double rr_new = reduce_part(part, G, 0);
-    const double beta = rr_new / c->rr;
+                                                            double *p, int k, CgControl *c) {
+    __shared__ double red[kBlock / 64];
+    __shared__ int stop_sh;
+    if (threadIdx.x == 0) stop_sh = c->stop;  // one read for the block (reduce_part has barriers)
+    __syncthreads();
+    if (stop_sh) return;
+    const double rr_new = reduce_part(part, G, 0, red);
+    const double beta = rr_new / c->rr[k];
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m; i += stride) p[i] = r[i] + beta * p[i];
-    if (blockIdx.x == 0 && threadIdx.x == 0) c->rr_new = rr_new;
-}
-
-// Finishes an iteration (one thread): the new rr and the stop test.
-__global__ void k_hy_cg_finish(CgControl *c) {
-    if (c->stop) return;
-    c->rr = c->rr_new;
-    c->iters += 1;
-    if (c->rr <= c->tol2 || c->iters >= c->max_iter) c->stop = 1;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        c->rr[k ^ 1] = rr_new;
+        c->iters += 1;
+        if (rr_new <= c->tol2 || c->iters >= c->max_iter) c->stop = 1;
+    }
 }
 
 // ||K||_inf (row absolute sums, the maximum over blocks by an atomic on its bits).
@@ -266,13 +292,22 @@ __global__ void __launch_bounds__(kBlock) k_hy_resid(int64_t N, int64_t n, const
     }
 }
 
-__global__ void k_hy_resid_reduce(int G, const double *part, CgControl *c) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
+// One block: the residual's sums and maximum.
+__global__ void __launch_bounds__(kBlock) k_hy_resid_reduce(int G, const double *part, CgControl *c) {
+    __shared__ double red[kBlock / 64];
+    const double rn = reduce_part(part, G, 0, red), xn = reduce_part(part, G, 1, red),
+                 bn = reduce_part(part, G, 2, red);
     double mr = 0.0;
-    for (int b = 0; b < G; ++b) mr = fmax(mr, part[b * 4 + 3]);
-    c->rnorm2 = reduce_part(part, G, 0);
-    c->xnorm2 = reduce_part(part, G, 1);
-    c->bnorm2 = reduce_part(part, G, 2);
+    for (int b = threadIdx.x; b < G; b += kBlock) mr = fmax(mr, part[b * 4 + 3]);
+    for (int o = 32; o > 0; o >>= 1) mr = fmax(mr, __shfl_xor(mr, o, 64));
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = mr;
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    for (int w = 1; w < kBlock / 64; ++w) mr = fmax(mr, red[w]);
+    c->rnorm2 = rn;
+    c->xnorm2 = xn;
+    c->bnorm2 = bn;
     c->rinf = mr;
 }
 
@@ -647,28 +682,31 @@ kkt_status_t kkt_hykkt_solve(kkt_hykkt_t h, const double *dev_b, double *dev_x, 
     const int gn = grid_for(n), gm = grid_for(m), gN = grid_for(h->N);
     double *partA = d.part, *partB = d.part + 4 * kGridMax;
     const double *bx = dev_b, *bl = dev_b + n;
-    auto hinv = [&](const double *in, double *outv) -> kkt_status_t {
-        const kkt_status_t st = kkt_direct_solve(h->lu, in, outv, stream);
+    kkt::SolveScratch sc;
+    kkt_status_t st = kkt::solve_scratch(h->lu, &sc);
+    if (st != KKT_OK) return hy_fail(h, st, std::string("H_gamma solve: ") + kkt_last_error(h->lu));
+    // (the exchange vectors are armed by the kernel before, which also forms `in`)
+    auto hinv = [&](const double *in, double *outv, const int *stop) -> kkt_status_t {
+        const kkt_status_t st = kkt::direct_solve_armed(h->lu, in, outv, stop, s);
         return st == KKT_OK ? st : hy_fail(h, st, std::string("H_gamma solve: ") + kkt_last_error(h->lu));
     };
     // rhat = r_x + gamma J^T r_l;  y = H_gamma^-1 rhat;  c = J y - r_l  (r = p = c, lam = 0)
-    k_hy_jt<<<gn, kBlock, 0, s>>>(n, d.jtrp, d.jtci, d.jtval, bl, h->gamma, bx, d.rhat, nullptr);
-    kkt_status_t st = hinv(d.rhat, d.y);
+    k_hy_jt<<<gn, kBlock, 0, s>>>(n, d.jtrp, d.jtci, d.jtval, bl, h->gamma, bx, d.rhat, nullptr, sc);
+    st = hinv(d.rhat, d.y, nullptr);
     if (st != KKT_OK) return st;
     k_hy_j<<<gm, kBlock, 0, s>>>(m, d.jrp, d.jci, d.jval, d.y, bl, nullptr, d.r, d.p, d.lam, partA, nullptr);
-    k_hy_cg_start<<<1, 64, 0, s>>>(gm, partA, h->opts.cg_tol, h->opts.cg_max_iter, d.ctl);
+    k_hy_cg_start<<<1, kBlock, 0, s>>>(gm, partA, h->opts.cg_tol, h->opts.cg_max_iter, d.ctl);
     HY_HIP(h, hipGetLastError());
     const int *stop = &d.ctl->stop;
     for (;;) {
         for (int k = 0; k < kCgGroup; ++k) {
             // q = S p = J H_gamma^-1 J^T p
-            k_hy_jt<<<gn, kBlock, 0, s>>>(n, d.jtrp, d.jtci, d.jtval, d.p, 1.0, nullptr, d.u, stop);
-            st = hinv(d.u, d.t);
+            k_hy_jt<<<gn, kBlock, 0, s>>>(n, d.jtrp, d.jtci, d.jtval, d.p, 1.0, nullptr, d.u, stop, sc);
+            st = hinv(d.u, d.t, stop);
             if (st != KKT_OK) return st;
             k_hy_j<<<gm, kBlock, 0, s>>>(m, d.jrp, d.jci, d.jval, d.t, nullptr, d.q, d.r, d.p, d.lam, partA, stop);
-            k_hy_cg_update<<<gm, kBlock, 0, s>>>(m, gm, partA, partB, d.p, d.q, d.r, d.lam, d.ctl);
-            k_hy_cg_direction<<<gm, kBlock, 0, s>>>(m, gm, partB, d.r, d.p, d.ctl);
-            k_hy_cg_finish<<<1, 1, 0, s>>>(d.ctl);
+            k_hy_cg_update<<<gm, kBlock, 0, s>>>(m, gm, partA, partB, d.p, d.q, d.r, d.lam, k & 1, d.ctl);
+            k_hy_cg_direction<<<gm, kBlock, 0, s>>>(m, gm, partB, d.r, d.p, k & 1, d.ctl);
         }
         HY_HIP(h, hipGetLastError());
         HY_HIP(h, hipMemcpyAsync(h->host_ctl, d.ctl, sizeof(CgControl), hipMemcpyDeviceToHost, s));
@@ -676,12 +714,13 @@ kkt_status_t kkt_hykkt_solve(kkt_hykkt_t h, const double *dev_b, double *dev_x, 
         if (h->host_ctl->stop) break;
     }
     const CgControl cg = *h->host_ctl;
+    const double cg_rr = cg.rr[cg.iters & 1];
     // dx = H_gamma^-1 (rhat - J^T lam);  x = [dx; lam] and its residual in K
-    k_hy_jt<<<gn, kBlock, 0, s>>>(n, d.jtrp, d.jtci, d.jtval, d.lam, -1.0, d.rhat, d.w, nullptr);
-    st = hinv(d.w, d.dx);
+    k_hy_jt<<<gn, kBlock, 0, s>>>(n, d.jtrp, d.jtci, d.jtval, d.lam, -1.0, d.rhat, d.w, nullptr, sc);
+    st = hinv(d.w, d.dx, nullptr);
     if (st != KKT_OK) return st;
     k_hy_resid<<<gN, kBlock, 0, s>>>(h->N, n, d.krp, d.kci, d.kval, d.dx, d.lam, dev_b, dev_x, partA);
-    k_hy_resid_reduce<<<1, 64, 0, s>>>(gN, partA, d.ctl);
+    k_hy_resid_reduce<<<1, kBlock, 0, s>>>(gN, partA, d.ctl);
     HY_HIP(h, hipGetLastError());
     HY_HIP(h, hipMemcpyAsync(h->host_ctl, d.ctl, sizeof(CgControl), hipMemcpyDeviceToHost, s));
     unsigned int bad = 0;
@@ -692,12 +731,12 @@ kkt_status_t kkt_hykkt_solve(kkt_hykkt_t h, const double *dev_b, double *dev_x, 
     const double rn = std::sqrt(c.rnorm2), xn = std::sqrt(c.xnorm2), bn = std::sqrt(c.bnorm2);
     double knorm = 0.0;
     std::memcpy(&knorm, &c.knorm_bits, sizeof(double));
-    const bool converged = cg.rr <= cg.tol2;
+    const bool converged = cg_rr <= cg.tol2;
     if (info) {
         info->converged = converged ? 1 : 0;
         info->cg_iterations = cg.iters;
         info->gamma = h->gamma;
-        info->cg_rel_resid = cg.rr0 > 0.0 ? std::sqrt(cg.rr / cg.rr0) : 0.0;
+        info->cg_rel_resid = cg.rr0 > 0.0 ? std::sqrt(cg_rr / cg.rr0) : 0.0;
         info->true_resid = rn;
         info->knorm_inf = knorm;
         info->nrbe = rn / (knorm * xn + bn);

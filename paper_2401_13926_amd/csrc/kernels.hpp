@@ -75,6 +75,19 @@ struct StepRecord {
     unsigned long long token;  // written last (release): identifies the step the record is for
 };
 
+// Signalling-NaN bit patterns no arithmetic result takes: "not written yet" in the exchange vectors.
+constexpr unsigned long long kSent64 = 0x7FF4DEADBEEF0001ull;
+constexpr unsigned int kSent32 = 0x7FA0BEEFu;
+
+// What a caller inside the library arms before direct_solve_armed: n sentinels of the factors'
+// precision in each of y and z, the counters zeroed.
+struct SolveScratch {
+    int64_t n;
+    bool f32;
+    void *y, *z;
+    unsigned int *work_lower, *work_upper;
+};
+
 // Host-visible summary copied back once per cycle.
 struct ControlSummary {
     unsigned long long knorm_bits;

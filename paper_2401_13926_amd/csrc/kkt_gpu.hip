@@ -46,10 +46,6 @@ namespace kkt {
 // device helpers
 // ---------------------------------------------------------------------------------------
 
-// Sentinels: signalling-NaN bit patterns no arithmetic result can take.
-constexpr unsigned long long kSent64 = 0x7FF4DEADBEEF0001ull;
-constexpr unsigned int kSent32 = 0x7FA0BEEFu;
-
 template <typename T> struct Bits;
 template <> struct Bits<double> {
     using U = unsigned long long;
@@ -1290,7 +1286,7 @@ template <typename T> struct TrsvArgs {
     T *out;                   // step-order result; sentinel on entry
     double *xout;             // upper: solution, scattered by qpos
     const int32_t *qpos;      // upper: per position of rows, the solution entry it writes
-    const Control *stopflag;  // when non-null, skip if the FGMRES cycle has stopped
+    const int *stopflag;      // when non-null, skip if the cycle (or the caller's iteration) has stopped
     unsigned int *work;       // tile counter (zeroed before the launch)
     unsigned int *hang;
 };
@@ -1382,7 +1378,7 @@ __global__ void __launch_bounds__(kTileThreads) k_trsv(TrsvArgs<T> a) {
     extern __shared__ __align__(16) unsigned char smem[];  // the tile budget, sized at launch
     __shared__ T ys[kDenseRows];  // dense segment: rows' right-hand sides minus earlier terms
     __shared__ unsigned int tile_sh;
-    if (a.stopflag && a.stopflag->stop) return;
+    if (a.stopflag && *a.stopflag) return;
     const int tid = threadIdx.x;
     for (;;) {
         if (tid == 0) tile_sh = atomicAdd(a.work, 1u);
@@ -1645,7 +1641,7 @@ template <typename T> struct SolveTileArgs {
     const int32_t *qpos;   // per U position: the solution entry it writes
     T *y, *z;              // exchange vectors of the sweeps; sentinels on entry
     double *xout;
-    const Control *stopflag;  // when non-null, skip if the FGMRES cycle has stopped
+    const int *stopflag;      // when non-null, skip if the cycle (or the caller's iteration) has stopped
     unsigned int *work;       // task counter (zeroed before the launch)
     unsigned int *hang;
 };
@@ -1655,6 +1651,7 @@ template <> struct Pair<double> { typedef double V __attribute__((ext_vector_typ
 template <> struct Pair<float> { typedef float V __attribute__((ext_vector_type(2))); };
 
 // Staging loads per thread and pass of a solve tile: 4 pairs of places; rows and externals.
+constexpr int kSolThreads = 64 * kSolWaves;
 constexpr int kSolPair = 4, kSolRow = 2;
 
 // One tile of one sweep.  Its places, then its right-hand sides and externals, go to LDS; the
@@ -1682,7 +1679,7 @@ __device__ __forceinline__ void solve_tile(const SolveTileArgs<T> &a, int t, uns
     T *tri = dg + (kUpper ? nr : 0);                                        // the dense range's triangle
     const int ntri = dm > 0 ? dm * (dm - 1) / 2 + 1 : 0;
     uint32_t *refs = reinterpret_cast<uint32_t *>(tri + ntri + ((kUpper ? nr : 0) + ntri & 1));  // np / 2
-    for (int k = tid; k < ntri; k += kTileThreads) tri[k] = T(0);
+    for (int k = tid; k < ntri; k += kSolThreads) tri[k] = T(0);
     auto slot_at = [&](uint32_t off) -> T & { return *reinterpret_cast<T *>(smem + off); };
     uint32_t m0 = 0, m1 = 0;  // lane l of every wavefront holds chunk l's words
     auto chunk_words = [&](int c0) {
@@ -1698,19 +1695,19 @@ __device__ __forceinline__ void solve_tile(const SolveTileArgs<T> &a, int t, uns
     T rv[kSolRow], gv[kSolRow], xv[kSolRow];
 #pragma unroll
     for (int u = 0; u < kSolRow; ++u) {
-        const int r = tid + u * kTileThreads;
+        const int r = tid + u * kSolThreads;
         rs[u] = r < nr ? gsrc[r] : 0;
         xc[u] = r < nx ? gext[r] : 0;
         qp[u] = kUpper && r < nr ? a.qpos[base + r] : 0;
         gv[u] = kUpper && r < nr ? a.diag[base + r] : T(1);
     }
     const int np2 = np / 2;
-    for (int p0 = 0; p0 < np2; p0 += kSolPair * kTileThreads) {
+    for (int p0 = 0; p0 < np2; p0 += kSolPair * kSolThreads) {
         V2 v[kSolPair];
         uint32_t c[kSolPair];
 #pragma unroll
         for (int u = 0; u < kSolPair; ++u) {
-            const int k = p0 + tid + u * kTileThreads;
+            const int k = p0 + tid + u * kSolThreads;
             if (k < np2) {
                 v[u] = gval[k];
                 c[u] = gref[k];
@@ -1718,11 +1715,11 @@ __device__ __forceinline__ void solve_tile(const SolveTileArgs<T> &a, int t, uns
         }
         if (!kUpper && p0 == 0) {  // the right-hand side is always there: with the same round
 #pragma unroll
-            for (int u = 0; u < kSolRow; ++u) rv[u] = tid + u * kTileThreads < nr ? (T)a.rhs[rs[u]] : T(0);
+            for (int u = 0; u < kSolRow; ++u) rv[u] = tid + u * kSolThreads < nr ? (T)a.rhs[rs[u]] : T(0);
         }
 #pragma unroll
         for (int u = 0; u < kSolPair; ++u) {
-            const int k = p0 + tid + u * kTileThreads;
+            const int k = p0 + tid + u * kSolThreads;
             if (k < np2) {
                 vals[k] = v[u];
                 refs[k] = c[u];
@@ -1731,7 +1728,7 @@ __device__ __forceinline__ void solve_tile(const SolveTileArgs<T> &a, int t, uns
     }
     if (dm > 0) {
         __syncthreads();  // the triangle is zeroed
-        for (int k = tid; k < nd2; k += kTileThreads) {
+        for (int k = tid; k < nd2; k += kSolThreads) {
             const V2 v = gval[np2 + k];
             const uint32_t c = gref[np2 + k];
             tri[c & 0xFFFFu] = v.x;
@@ -1740,13 +1737,13 @@ __device__ __forceinline__ void solve_tile(const SolveTileArgs<T> &a, int t, uns
     }
     if (!kUpper && np2 == 0) {
 #pragma unroll
-        for (int u = 0; u < kSolRow; ++u) rv[u] = tid + u * kTileThreads < nr ? (T)a.rhs[rs[u]] : T(0);
+        for (int u = 0; u < kSolRow; ++u) rv[u] = tid + u * kSolThreads < nr ? (T)a.rhs[rs[u]] : T(0);
     }
     if (kUpper) {
 #pragma unroll
         for (int u = 0; u < kSolRow; ++u)
-            if (tid + u * kTileThreads < nr) dg[tid + u * kTileThreads] = T(1) / gv[u];
-        for (int r = tid + kSolRow * kTileThreads; r < nr; r += kTileThreads) dg[r] = T(1) / a.diag[base + r];
+            if (tid + u * kSolThreads < nr) dg[tid + u * kSolThreads] = T(1) / gv[u];
+        for (int r = tid + kSolRow * kSolThreads; r < nr; r += kSolThreads) dg[r] = T(1) / a.diag[base + r];
     }
     if (tid == 0) slot_at(8u * (uint32_t)(nr + nx)) = T(0);
     // The values other blocks produce.  One lane waits for the one that is written last (the first
@@ -1763,13 +1760,13 @@ __device__ __forceinline__ void solve_tile(const SolveTileArgs<T> &a, int t, uns
     }
 #pragma unroll
     for (int u = 0; u < kSolRow; ++u) {
-        const int r = tid + u * kTileThreads;
+        const int r = tid + u * kSolThreads;
         if (kUpper) rv[u] = r < nr ? load_system(a.y + rs[u]) : T(0);
         xv[u] = r < nx ? load_system((kUpper ? a.z : a.y) + xc[u]) : T(0);
     }
 #pragma unroll
     for (int u = 0; u < kSolRow; ++u) {
-        const int r = tid + u * kTileThreads;
+        const int r = tid + u * kSolThreads;
         if (r < nr) {
             if (kUpper && is_sentinel(rv[u])) rv[u] = load_ready<T, 1>(a.y + rs[u], a.hang);
             slot_at(8 * r) = rv[u];
@@ -1779,9 +1776,9 @@ __device__ __forceinline__ void solve_tile(const SolveTileArgs<T> &a, int t, uns
             slot_at(8 * (nr + r)) = xv[u];
         }
     }
-    for (int r = tid + kSolRow * kTileThreads; r < nr; r += kTileThreads)
+    for (int r = tid + kSolRow * kSolThreads; r < nr; r += kSolThreads)
         slot_at(8 * r) = kUpper ? load_ready<T, 1>(a.y + gsrc[r], a.hang) : (T)a.rhs[gsrc[r]];
-    for (int r = tid + kSolRow * kTileThreads; r < nx; r += kTileThreads)
+    for (int r = tid + kSolRow * kSolThreads; r < nx; r += kSolThreads)
         slot_at(8 * (nr + r)) = load_ready<T, 1>((kUpper ? a.z : a.y) + gext[r], a.hang);
     __syncthreads();
     // The chunks, each one wavefront's.  A chunk of a segment that one wavefront covers is
@@ -1868,14 +1865,14 @@ __device__ __forceinline__ void solve_tile(const SolveTileArgs<T> &a, int t, uns
     __syncthreads();
 #pragma unroll
     for (int u = 0; u < kSolRow; ++u) {
-        const int r = tid + u * kTileThreads;
+        const int r = tid + u * kSolThreads;
         if (r < nr) {
             const T res = slot_at(8 * r);
             store_ready(out + r, res);
             if (kUpper) a.xout[qp[u]] = (double)res;
         }
     }
-    for (int r = tid + kSolRow * kTileThreads; r < nr; r += kTileThreads) {
+    for (int r = tid + kSolRow * kSolThreads; r < nr; r += kSolThreads) {
         const T res = slot_at(8 * r);
         store_ready(out + r, res);
         if (kUpper) a.xout[a.qpos[base + r]] = (double)res;
@@ -1887,10 +1884,10 @@ __device__ __forceinline__ void solve_tile(const SolveTileArgs<T> &a, int t, uns
 // earlier ones, so the earliest unfinished task is always held by a running block that can
 // finish it.
 template <typename T>
-__global__ void __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(5))) k_solve_tiles(SolveTileArgs<T> a) {
+__global__ void __launch_bounds__(kSolThreads) __attribute__((amdgpu_waves_per_eu(5))) k_solve_tiles(SolveTileArgs<T> a) {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ unsigned int task_sh;
-    if (a.stopflag && a.stopflag->stop) return;
+    if (a.stopflag && *a.stopflag) return;
     for (;;) {
         if (threadIdx.x == 0) task_sh = atomicAdd(a.work, 1u);
         __syncthreads();
@@ -2848,13 +2845,13 @@ std::vector<int32_t> tile_descriptors(const TriSchedule &sc) {
     return d;
 }
 
-// Blocks of 256 threads that fit on the device at once (a persistent grid size).
-int coop_grid(const void *func, int device, size_t dyn_lds = 0) {
+// Blocks of `threads` threads that fit on the device at once (a persistent grid size).
+int coop_grid(const void *func, int device, size_t dyn_lds = 0, int threads = kCoopBlock) {
     int per_cu = 0, cus = 0;
     if (dyn_lds > 0 &&
         hipFuncSetAttribute(func, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn_lds) != hipSuccess)
         return 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, func, kCoopBlock, dyn_lds) != hipSuccess) return 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, func, threads, dyn_lds) != hipSuccess) return 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess) return 0;
     return per_cu * cus;
 }
@@ -2886,7 +2883,7 @@ template <typename T>
 // vorder: the right-hand side and the solution are in the vector order of a solve (else in
 // the caller's original order)
 hipError_t launch_trsv(kkt_handle_t h, bool lower, const double *rhs64, const T *rhs_step, T *out, double *xout,
-                       const Control *stopflag, hipStream_t s, bool vorder, unsigned int *work = nullptr,
+                       const int *stopflag, hipStream_t s, bool vorder, unsigned int *work = nullptr,
                        unsigned int *hang = nullptr) {
     const Analysis &a = h->an;
     TrsvArgs<T> t{};
@@ -2931,7 +2928,7 @@ hipError_t launch_trsv(kkt_handle_t h, bool lower, const double *rhs64, const T 
 // Both sweeps in one launch (analyses with tiles): x = Q U^-1 L^-1 P b through the exchange vectors y
 // and z (sentinels armed, *work zeroed before).
 template <typename T>
-hipError_t launch_solve_tiles(kkt_handle_t h, const double *rhs, T *y, T *z, double *xout, const Control *stopflag,
+hipError_t launch_solve_tiles(kkt_handle_t h, const double *rhs, T *y, T *z, double *xout, const int *stopflag,
                               hipStream_t s, bool vorder, unsigned int *work, unsigned int *hang) {
     const SolveTiles &q = h->an.sol;
     const DevLayout &d = h->d;
@@ -2942,28 +2939,28 @@ hipError_t launch_solve_tiles(kkt_handle_t h, const double *rhs, T *y, T *z, dou
                              val_u + q.ref_u.size(), rhs, vorder ? d.st_src_k : d.st_src, d.st_posu,
                              vorder ? d.st_q_k : d.st_q, y, z, xout, stopflag, work, hang};
     const int grid = (int)std::min<int64_t>(is64 ? h->grid_solve64 : h->grid_solve32, 2 * q.tiles());
-    k_solve_tiles<T><<<grid, kTileThreads, (size_t)q.lds, s>>>(t);
+    k_solve_tiles<T><<<grid, kSolThreads, (size_t)q.lds, s>>>(t);
     return hipGetLastError();
 }
 
 // x = Q U^-1 L^-1 P b with the current factors of precision T (sentinels armed before); b and
 // x in the vector order of a solve (vorder) or in the original order.
 template <typename T>
-hipError_t precond(kkt_handle_t h, const double *b, double *x, const Control *ctl, hipStream_t s, bool vorder) {
+hipError_t precond(kkt_handle_t h, const double *b, double *x, const int *stop, hipStream_t s, bool vorder) {
     T *y = (T *)(sizeof(T) == 8 ? (void *)h->d.y64 : (void *)h->d.y32);
     T *z = (T *)(sizeof(T) == 8 ? (void *)h->d.z64 : (void *)h->d.z32);
     hipEvent_t e0 = prof_begin(h, KKT_K_TRSV_L, s);
     if (h->an.sol.tiles() > 0) {
-        const hipError_t et = launch_solve_tiles<T>(h, b, y, z, x, ctl, s, vorder, &h->d.ctl->work_lower,
+        const hipError_t et = launch_solve_tiles<T>(h, b, y, z, x, stop, s, vorder, &h->d.ctl->work_lower,
                                                     &h->d.ctl->hang);
         prof_end(h, KKT_K_TRSV_L, e0, s);
         return et;
     }
-    hipError_t e = launch_trsv<T>(h, true, b, nullptr, y, nullptr, ctl, s, vorder);
+    hipError_t e = launch_trsv<T>(h, true, b, nullptr, y, nullptr, stop, s, vorder);
     prof_end(h, KKT_K_TRSV_L, e0, s);
     if (e != hipSuccess) return e;
     e0 = prof_begin(h, KKT_K_TRSV_U, s);
-    e = launch_trsv<T>(h, false, nullptr, y, z, x, ctl, s, vorder);
+    e = launch_trsv<T>(h, false, nullptr, y, z, x, stop, s, vorder);
     prof_end(h, KKT_K_TRSV_U, e0, s);
     return e;
 }
@@ -3185,7 +3182,7 @@ kkt_status_t solve_impl(kkt_handle_t h, const double *gather, double *b, double 
         const int steps = dcgs2 ? R + 1 : R;
         for (int j = 0; j < steps; ++j) {
             const size_t step_mark = h->ev_pending.size();
-            if (j < R) KKT_HIP(h, precond<T>(h, d.V + (int64_t)j * a.n, d.Z + (int64_t)j * a.n, d.ctl, s, true));
+            if (j < R) KKT_HIP(h, precond<T>(h, d.V + (int64_t)j * a.n, d.Z + (int64_t)j * a.n, &d.ctl->stop, s, true));
             e0 = prof_begin(h, KKT_K_SPMV, s);
             if (dcgs2) k_dcgs2_dots<<<G, kStreamBlock, 0, s>>>(ka, j, j < R ? 1 : 0);
             else k_spmv_dots<<<G, kStreamBlock, 0, s>>>(ka, j);
@@ -3580,6 +3577,27 @@ hipError_t direct_solve_scratch(kkt_handle_t h, const double *b, double *x, unsi
 static kkt_status_t solve_vorder(kkt_handle_t h, const double *dev_b, double tol, kkt_solve_info_t *info,
                                  hipStream_t s);
 
+namespace kkt {
+
+// kkt_direct_solve in two parts, for callers inside the library that arm the exchange vectors in a
+// kernel of their own; stop: when non-null and set on the device, the sweeps return at once.
+kkt_status_t solve_scratch(kkt_handle_t h, SolveScratch *o) {
+    if (h->device_failed) return fail(h, KKT_EDEVICE, "handle unusable after a device error");
+    if (!h->bound || !h->have_factors) return fail(h, KKT_ESTATE, "refactor before solve");
+    const bool f32 = h->factor_precision == KKT_PREC_MIXED;
+    *o = {h->an.n, f32, f32 ? (void *)h->d.y32 : (void *)h->d.y64, f32 ? (void *)h->d.z32 : (void *)h->d.z64,
+          &h->d.ctl->work_lower, &h->d.ctl->work_upper};
+    return KKT_OK;
+}
+
+kkt_status_t direct_solve_armed(kkt_handle_t h, const double *b, double *x, const int *stop, hipStream_t s) {
+    if (h->factor_precision == KKT_PREC_MIXED) KKT_HIP(h, precond<float>(h, b, x, stop, s, false));
+    else KKT_HIP(h, precond<double>(h, b, x, stop, s, false));
+    return KKT_OK;
+}
+
+}  // namespace kkt
+
 extern "C" {
 
 void kkt_opts_default(kkt_opts_t *o) {
@@ -3959,8 +3977,8 @@ kkt_status_t kkt_bind_workspace(kkt_handle_t h, void *dev_ptr, size_t bytes, voi
                                       coop_grid((const void *)k_refactor_tiles<float, true>, h->device, lds));
     }
     if (a.sol.tiles() > 0) {
-        h->grid_solve64 = coop_grid((const void *)k_solve_tiles<double>, h->device, (size_t)a.sol.lds);
-        h->grid_solve32 = coop_grid((const void *)k_solve_tiles<float>, h->device, (size_t)a.sol.lds);
+        h->grid_solve64 = coop_grid((const void *)k_solve_tiles<double>, h->device, (size_t)a.sol.lds, kSolThreads);
+        h->grid_solve32 = coop_grid((const void *)k_solve_tiles<float>, h->device, (size_t)a.sol.lds, kSolThreads);
         if (h->grid_solve64 <= 0 || h->grid_solve32 <= 0) return fail(h, KKT_EDEVICE, "occupancy query failed");
     }
     h->grid_trsv64 = std::min(std::min(coop_grid((const void *)k_trsv<double, true, true>, h->device, h->tile_lds),
