@@ -115,10 +115,7 @@ __global__ void k_hy_jt(int64_t n, const int64_t *__restrict__ rp, const int32_t
                         const double *__restrict__ val, const double *__restrict__ x, double alpha,
                         const double *add, double *out, const int *stop, kkt::SolveScratch sc) {
     if (stop && *stop) return;
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        *sc.work_lower = 0;
-        *sc.work_upper = 0;
-    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) kkt::reset_work(sc.work);
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
         if (sc.f32) {

@@ -21,12 +21,28 @@ constexpr int kTileLdsMax = 150 * 1024; // per compute unit, the rest for the ke
 constexpr int kResidentRefactorWaves = 3 * 4 * 256;
 constexpr int kRefactorLds = 1024;     // factor entries staged in LDS per wavefront
 constexpr int kRefTileLds = 32512;     // LDS bytes of a refactorization tile
+constexpr int64_t kSolSmallRows = 250000;  // fewer rows: solve tiles of 12 KiB, else 16 KiB
 constexpr int kMaxBatch = 8;           // systems of one pattern refactored by one launch
 constexpr int kWorkQueues = 8;         // refactorization hand-out queues (one per XCD of MI355X: a
                                        // block's queue is its index mod 8, the XCD it runs on)
 // Spin limit of one dependency wait (iterations of a short sleep, a few seconds in all);
 // exceeding it marks Control::hang and lets every wave run to completion.
 constexpr unsigned int kSpinLimit = 1u << 22;
+
+// Hand-out counters of the triangular solves (device memory, zeroed before a launch): the window
+// kernels' next tile of each sweep, and the tile kernel's queues, each on a 256-byte line of its
+// own (one counter hands out about 85 tasks per microsecond: 18,600 tasks at 2M unknowns
+// took most of a 340 us launch).
+struct SolveWork {
+    unsigned int lower, upper;
+    unsigned int pad[62];
+    unsigned int queue[kWorkQueues * 64];
+};
+__device__ __forceinline__ void reset_work(SolveWork *w) {
+    w->lower = 0;
+    w->upper = 0;
+    for (int q = 0; q < kWorkQueues; ++q) w->queue[q * 64] = 0;
+}
 
 // Scalars shared between kernels of one refactor/solve (device memory).
 struct Control {
@@ -60,8 +76,7 @@ struct Control {
     // Refactorization hand-out: kWorkQueues counters, one per 256-byte line; queue q hands out
     // items q, q + kWorkQueues, ... to the blocks b with b % kWorkQueues == q.
     unsigned int work_refactor[kWorkQueues * 64];
-    unsigned int work_lower;        // next task index to hand out (L solve)
-    unsigned int work_upper;        // next task index to hand out (U solve)
+    SolveWork work;                 // hand-out of the triangular solves
 };
 
 // What the host needs after each Arnoldi step, written by the normalization kernel into
@@ -80,12 +95,12 @@ constexpr unsigned long long kSent64 = 0x7FF4DEADBEEF0001ull;
 constexpr unsigned int kSent32 = 0x7FA0BEEFu;
 
 // What a caller inside the library arms before direct_solve_armed: n sentinels of the factors'
-// precision in each of y and z, the counters zeroed.
+// precision in each of y and z, *work reset.
 struct SolveScratch {
     int64_t n;
     bool f32;
     void *y, *z;
-    unsigned int *work_lower, *work_upper;
+    SolveWork *work;
 };
 
 // Host-visible summary copied back once per cycle.

@@ -134,6 +134,22 @@ template <typename T> __device__ __forceinline__ T load_system(const T *p) {
                                                    __HIP_MEMORY_SCOPE_SYSTEM));
 }
 
+// The next of `total` tasks for a block (called by its thread 0; total when none is left).  Tasks go
+// round robin to kWorkQueues counters, task t to counter t % kWorkQueues; block b starts on
+// counter b % kWorkQueues (the XCD it runs on) and moves on when it is exhausted.  Each counter
+// hands out its tasks in order, so the earliest unfinished task is held by a running block or will
+// be taken by one as long as every counter has a resident block: blocks are dispatched in index
+// order, so any kWorkQueues resident blocks cover all of them (a smaller grid has a block per
+// task).
+__device__ __forceinline__ unsigned int next_task(unsigned int *queues, unsigned int total, unsigned int &queue) {
+    for (int tries = 0; tries < kWorkQueues; ++tries) {
+        const unsigned int t = queue + kWorkQueues * atomicAdd(queues + queue * 64, 1u);
+        if (t < total) return t;
+        queue = (queue + 1) % kWorkQueues;
+    }
+    return total;
+}
+
 // Wave-uniform: lane 0 takes `chunk` consecutive work items from *counter.
 __device__ __forceinline__ unsigned int grab(unsigned int *counter, unsigned int chunk) {
     unsigned int v = 0;
@@ -196,8 +212,7 @@ __global__ void k_solve_begin(int64_t n, const int32_t *__restrict__ perm, const
         c->nonfinite_b = 0;
         c->counter = 0;
         c->stop = 0;
-        c->work_lower = 0;
-        c->work_upper = 0;
+        reset_work(&c->work);
     }
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < n; k += stride) {
@@ -231,7 +246,7 @@ template <typename T> __global__ void k_prep_tiles(Control *c, int values, int64
             c->knorm_bits = 0;
             c->nonfinite = 0;
         }
-        c->work_refactor[0] = 0;
+        for (int q = 0; q < kWorkQueues; ++q) c->work_refactor[q * 64] = 0;
         c->hang = 0;
         c->guard_fail = 0;
         c->nguard = 0;
@@ -963,8 +978,9 @@ __global__ void __launch_bounds__(kCoopBlock) __attribute__((amdgpu_waves_per_eu
     const int tid = threadIdx.x, lane = tid & 63;
     const int nslots = kBatch ? batch.nslots : 1;
     Control *const ctl0 = batch.slot[0].ctl;
+    unsigned int queue = blockIdx.x % kWorkQueues;  // thread 0's
     for (;;) {
-        if (tid == 0) tile_sh = atomicAdd(&ctl0->work_refactor[0], 1u);
+        if (tid == 0) tile_sh = next_task(ctl0->work_refactor, (unsigned int)a.ntiles * nslots, queue);
         __syncthreads();
         const unsigned int w = (unsigned int)__builtin_amdgcn_readfirstlane((int)tile_sh);
         __syncthreads();
@@ -1642,7 +1658,7 @@ template <typename T> struct SolveTileArgs {
     T *y, *z;              // exchange vectors of the sweeps; sentinels on entry
     double *xout;
     const int *stopflag;      // when non-null, skip if the cycle (or the caller's iteration) has stopped
-    unsigned int *work;       // task counter (zeroed before the launch)
+    unsigned int *work;       // hand-out queues (zeroed before the launch)
     unsigned int *hang;
 };
 
@@ -1650,9 +1666,10 @@ template <typename T> struct Pair;  // two values, loaded together
 template <> struct Pair<double> { typedef double V __attribute__((ext_vector_type(2))); };
 template <> struct Pair<float> { typedef float V __attribute__((ext_vector_type(2))); };
 
-// Staging loads per thread and pass of a solve tile: 4 pairs of places; rows and externals.
+// Staging loads per thread and pass of a solve tile: pairs of places; rows and externals.  (Four
+// pairs need 96 registers; two fit 72, so that six blocks share a compute unit.)
 constexpr int kSolThreads = 64 * kSolWaves;
-constexpr int kSolPair = 4, kSolRow = 2;
+constexpr int kSolPair = 2, kSolRow = 2;
 
 // One tile of one sweep.  Its places, then its right-hand sides and externals, go to LDS; the
 // chunks then run from LDS only; the rows' solutions leave together at the end, coalesced (a
@@ -1884,12 +1901,13 @@ __device__ __forceinline__ void solve_tile(const SolveTileArgs<T> &a, int t, uns
 // earlier ones, so the earliest unfinished task is always held by a running block that can
 // finish it.
 template <typename T>
-__global__ void __launch_bounds__(kSolThreads) __attribute__((amdgpu_waves_per_eu(5))) k_solve_tiles(SolveTileArgs<T> a) {
+__global__ void __launch_bounds__(kSolThreads) __attribute__((amdgpu_waves_per_eu(6))) k_solve_tiles(SolveTileArgs<T> a) {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ unsigned int task_sh;
     if (a.stopflag && *a.stopflag) return;
+    unsigned int queue = blockIdx.x % kWorkQueues;  // thread 0's
     for (;;) {
-        if (threadIdx.x == 0) task_sh = atomicAdd(a.work, 1u);
+        if (threadIdx.x == 0) task_sh = next_task(a.work, 2 * (unsigned int)a.ntiles, queue);
         __syncthreads();
         const int w = __builtin_amdgcn_readfirstlane((int)task_sh);
         __syncthreads();
@@ -1902,11 +1920,9 @@ __global__ void __launch_bounds__(kSolThreads) __attribute__((amdgpu_waves_per_e
 // Arms the two solve vectors with the sentinel and zeroes the tile counters of the two
 // sweeps (and the wait-failure flag, when given).
 template <typename T>
-__global__ void k_fill_sentinel(int64_t n, T *a, T *b, unsigned int *work_lower, unsigned int *work_upper,
-                                unsigned int *hang) {
+__global__ void k_fill_sentinel(int64_t n, T *a, T *b, SolveWork *work, unsigned int *hang) {
     if (blockIdx.x == 0 && threadIdx.x == 0) {
-        *work_lower = 0;
-        *work_upper = 0;
+        reset_work(work);
         if (hang) *hang = 0;
     }
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
@@ -2076,8 +2092,7 @@ __device__ void arnoldi_close(Control *c, int j, int restart, double hn, double 
         c->breakdown = brk;
         c->stop = stop;
         if (!stop) {
-            c->work_lower = 0;
-            c->work_upper = 0;
+            reset_work(&c->work);
         }
         __hip_atomic_store(&r->est, est, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         __hip_atomic_store(&r->jdone, j + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
@@ -2213,8 +2228,7 @@ __global__ void __launch_bounds__(kStreamBlock) k_dcgs2(KrylovArgs a, int j, int
                 for (int t = 0; t <= j; ++t) c->Hbar[(j - 1) * (kRestartMax + 1) + t] = fin[t];
             arnoldi_close(c, j - 1, restart, beta, sqrt(cn), col, rec + j, token, sh);
         } else if (blockIdx.x == 0) {
-            c->work_lower = 0;
-            c->work_upper = 0;
+            reset_work(&c->work);
             StepRecord *r = rec;
             __hip_atomic_store(&r->est, c->est, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
             __hip_atomic_store(&r->jdone, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
@@ -2451,8 +2465,7 @@ __global__ void __launch_bounds__(kStreamBlock) k_cycle_start(KrylovArgs a, cons
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         Control *c = a.ctl;
-        c->work_lower = 0;
-        c->work_upper = 0;
+        reset_work(&c->work);
         c->beta = beta;
         c->inner_tol = inner_tol;
         c->stop = 0;
@@ -2883,7 +2896,7 @@ template <typename T>
 // vorder: the right-hand side and the solution are in the vector order of a solve (else in
 // the caller's original order)
 hipError_t launch_trsv(kkt_handle_t h, bool lower, const double *rhs64, const T *rhs_step, T *out, double *xout,
-                       const int *stopflag, hipStream_t s, bool vorder, unsigned int *work = nullptr,
+                       const int *stopflag, hipStream_t s, bool vorder, SolveWork *work = nullptr,
                        unsigned int *hang = nullptr) {
     const Analysis &a = h->an;
     TrsvArgs<T> t{};
@@ -2913,7 +2926,8 @@ hipError_t launch_trsv(kkt_handle_t h, bool lower, const double *rhs64, const T 
     }
     t.out = out;
     t.stopflag = stopflag;
-    t.work = work ? work : lower ? &d.ctl->work_lower : &d.ctl->work_upper;
+    if (!work) work = &d.ctl->work;
+    t.work = lower ? &work->lower : &work->upper;
     t.hang = hang ? hang : &d.ctl->hang;
     const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(is64 ? h->grid_trsv64 : h->grid_trsv32, t.ntiles));
     // the variant without the dense-segment path when the schedule has none
@@ -2929,7 +2943,7 @@ hipError_t launch_trsv(kkt_handle_t h, bool lower, const double *rhs64, const T 
 // and z (sentinels armed, *work zeroed before).
 template <typename T>
 hipError_t launch_solve_tiles(kkt_handle_t h, const double *rhs, T *y, T *z, double *xout, const int *stopflag,
-                              hipStream_t s, bool vorder, unsigned int *work, unsigned int *hang) {
+                              hipStream_t s, bool vorder, SolveWork *work, unsigned int *hang) {
     const SolveTiles &q = h->an.sol;
     const DevLayout &d = h->d;
     constexpr bool is64 = sizeof(T) == 8;
@@ -2937,7 +2951,7 @@ hipError_t launch_solve_tiles(kkt_handle_t h, const double *rhs, T *y, T *z, dou
     const T *val_u = val + q.ref_l.size();
     const SolveTileArgs<T> t{q.tiles(), d.st_desc, d.st_cl, d.st_cu, d.st_rl, d.st_ru, d.st_el, d.st_eu, val, val_u,
                              val_u + q.ref_u.size(), rhs, vorder ? d.st_src_k : d.st_src, d.st_posu,
-                             vorder ? d.st_q_k : d.st_q, y, z, xout, stopflag, work, hang};
+                             vorder ? d.st_q_k : d.st_q, y, z, xout, stopflag, work->queue, hang};
     const int grid = (int)std::min<int64_t>(is64 ? h->grid_solve64 : h->grid_solve32, 2 * q.tiles());
     k_solve_tiles<T><<<grid, kSolThreads, (size_t)q.lds, s>>>(t);
     return hipGetLastError();
@@ -2951,7 +2965,7 @@ hipError_t precond(kkt_handle_t h, const double *b, double *x, const int *stop, 
     T *z = (T *)(sizeof(T) == 8 ? (void *)h->d.z64 : (void *)h->d.z32);
     hipEvent_t e0 = prof_begin(h, KKT_K_TRSV_L, s);
     if (h->an.sol.tiles() > 0) {
-        const hipError_t et = launch_solve_tiles<T>(h, b, y, z, x, stop, s, vorder, &h->d.ctl->work_lower,
+        const hipError_t et = launch_solve_tiles<T>(h, b, y, z, x, stop, s, vorder, &h->d.ctl->work,
                                                     &h->d.ctl->hang);
         prof_end(h, KKT_K_TRSV_L, e0, s);
         return et;
@@ -2969,8 +2983,7 @@ template <typename T> void rearm(kkt_handle_t h, hipStream_t s) {
     T *y = (T *)(sizeof(T) == 8 ? (void *)h->d.y64 : (void *)h->d.y32);
     T *z = (T *)(sizeof(T) == 8 ? (void *)h->d.z64 : (void *)h->d.z32);
     hipEvent_t e0 = prof_begin(h, KKT_K_OTHER, s);
-    k_fill_sentinel<T><<<h->grid_stream, kStreamBlock, 0, s>>>(h->an.n, y, z, &h->d.ctl->work_lower,
-                                                                &h->d.ctl->work_upper, nullptr);
+    k_fill_sentinel<T><<<h->grid_stream, kStreamBlock, 0, s>>>(h->an.n, y, z, &h->d.ctl->work, nullptr);
     prof_end(h, KKT_K_OTHER, e0, s);
 }
 
@@ -3379,7 +3392,7 @@ kkt_status_t richardson_impl(kkt_handle_t h, const double *gather, double *b, do
 
 // ---------------------------------------------------------------------------------------
 // Scratch of the allocation-free direct solve (kkt_direct_solve_noalloc): the two tile
-// counters and the wait-failure flag in the first 256 bytes, then the intermediate vectors
+// counters and the wait-failure flag in the first 4 KiB, then the intermediate vectors
 // y = L^-1 P b and z = U^-1 y, kNoAllocMaxRows values of 8 bytes each (FP32 factors use the
 // first half of each).  One copy per GPU, for the life of the process; calls on one GPU
 // share it.
@@ -3387,11 +3400,13 @@ kkt_status_t richardson_impl(kkt_handle_t h, const double *gather, double *b, do
 
 namespace kkt {
 constexpr int64_t kNoAllocMaxRows = int64_t(1) << 21;  // 2,097,152 rows
-constexpr size_t kNoAllocHead = 256;
-constexpr size_t kNoAllocBytes = kNoAllocHead + 2 * sizeof(double) * (size_t)kNoAllocMaxRows;  // 32 MiB + 256 B
+constexpr size_t kNoAllocHead = 4096;
+constexpr size_t kNoAllocBytes = kNoAllocHead + 2 * sizeof(double) * (size_t)kNoAllocMaxRows;  // 32 MiB + 4 KiB
 struct NoAllocHead {
-    unsigned int work_lower, work_upper, hang;
+    SolveWork work;
+    unsigned int hang;
 };
+static_assert(sizeof(NoAllocHead) <= kNoAllocHead, "the counters precede the vectors");
 }  // namespace kkt
 
 static __device__ __align__(256) unsigned char scratch[kkt::kNoAllocBytes];
@@ -3431,6 +3446,12 @@ AnalysisOptions analysis_options(const kkt_opts_t &o, int64_t n) {
                             : (int)std::max<int64_t>(kResidentRefactorWaves, std::min<int64_t>(16384, n / 64));
     // tiles unless the caller sets the hand-out of single columns or the solve schedules' LDS budget
     ao.ref_lds = o.narrow_columns > 0 || o.tile_lds_kib > 0 ? 0 : kRefTileLds;
+    // Solve tiles: while every tile is resident at once, small ones start sooner and their leaves run
+    // side by side; beyond that the number of tasks counts.  A pair of sweeps with 12 KiB tiles
+    // (20,000 bytes with the dense range) / 16 KiB (26,000): 7k 46 / 56 us, 60k 61 / 65 us, 500k
+    // 121 / 114 us, 2M 299 / 272 us (20 KiB and 32 KiB: 60, 73, 133 and 321 us).
+    ao.sol_lds = n < kSolSmallRows ? 12288 : 16384;
+    ao.sol_dense_lds = n < kSolSmallRows ? 20000 : 26000;
     return ao;
 }
 
@@ -3560,15 +3581,14 @@ hipError_t direct_solve_scratch(kkt_handle_t h, const double *b, double *x, unsi
     NoAllocHead *head = (NoAllocHead *)base;
     T *y = (T *)(base + kNoAllocHead);
     T *z = (T *)(base + kNoAllocHead + sizeof(double) * (size_t)kNoAllocMaxRows);
-    k_fill_sentinel<T><<<h->grid_stream, kStreamBlock, 0, s>>>(h->an.n, y, z, &head->work_lower, &head->work_upper,
-                                                                &head->hang);
+    k_fill_sentinel<T><<<h->grid_stream, kStreamBlock, 0, s>>>(h->an.n, y, z, &head->work, &head->hang);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (h->an.sol.tiles() > 0)
-        return launch_solve_tiles<T>(h, b, y, z, x, nullptr, s, false, &head->work_lower, &head->hang);
-    e = launch_trsv<T>(h, true, b, nullptr, y, nullptr, nullptr, s, false, &head->work_lower, &head->hang);
+        return launch_solve_tiles<T>(h, b, y, z, x, nullptr, s, false, &head->work, &head->hang);
+    e = launch_trsv<T>(h, true, b, nullptr, y, nullptr, nullptr, s, false, &head->work, &head->hang);
     if (e != hipSuccess) return e;
-    return launch_trsv<T>(h, false, nullptr, y, z, x, nullptr, s, false, &head->work_upper, &head->hang);
+    return launch_trsv<T>(h, false, nullptr, y, z, x, nullptr, s, false, &head->work, &head->hang);
 }
 
 }  // namespace
@@ -3586,7 +3606,7 @@ kkt_status_t solve_scratch(kkt_handle_t h, SolveScratch *o) {
     if (!h->bound || !h->have_factors) return fail(h, KKT_ESTATE, "refactor before solve");
     const bool f32 = h->factor_precision == KKT_PREC_MIXED;
     *o = {h->an.n, f32, f32 ? (void *)h->d.y32 : (void *)h->d.y64, f32 ? (void *)h->d.z32 : (void *)h->d.z64,
-          &h->d.ctl->work_lower, &h->d.ctl->work_upper};
+          &h->d.ctl->work};
     return KKT_OK;
 }
 
