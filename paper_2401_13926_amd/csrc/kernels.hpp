@@ -50,7 +50,7 @@ struct Control {
     unsigned int nonfinite;         // a non-finite matrix value was ingested
     unsigned int guard_fail;        // a guarded pivot under the FAIL policy
     unsigned long long nguard;      // guarded (perturbed) pivots
-    unsigned int counter;           // arrival counter of the "last block reduces" pattern
+    unsigned int counter;           // arrivals of complete groups (last_arrival)
     int stop;                       // current FGMRES cycle has ended
     int jdone;                      // Arnoldi steps completed in the current cycle
     int breakdown;                  // happy breakdown in the current cycle
@@ -77,6 +77,7 @@ struct Control {
     // items q, q + kWorkQueues, ... to the blocks b with b % kWorkQueues == q.
     unsigned int work_refactor[kWorkQueues * 64];
     SolveWork work;                 // hand-out of the triangular solves
+    unsigned int arrive[kWorkQueues * 64];  // arrivals of the blocks of each group, a line each
 };
 
 // What the host needs after each Arnoldi step, written by the normalization kernel into

@@ -257,29 +257,53 @@ template <typename T> __global__ void k_prep_tiles(Control *c, int values, int64
 }
 
 // New values: K's values (original CSR order, vals) into the Krylov side's copy in the vector
-// order, one thread per row of the copy (row k is an original row whose entries start at
-// ostart[k] and keep their order); also ||K||_inf (each row's absolute values summed in
-// order, one atomic maximum per block) and the finiteness of every value.
-__global__ void k_ingest_rows(int64_t n, const int64_t *__restrict__ ostart, const int64_t *__restrict__ krp,
-                              const double *__restrict__ vals, double *__restrict__ kval, Control *c) {
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+// order (row k is an original row whose entries start at ostart[k] and keep their order); also
+// ||K||_inf (each row's absolute values summed in order, one atomic maximum per block) and the
+// finiteness of every value.  Blocks of 256 rows: the source of every entry goes to LDS, then
+// consecutive lanes copy consecutive entries, so a row's line is touched by one load instead of
+// one per entry; rows are summed from LDS.  Blocks of rows with more than kIngestLds entries go
+// one row per thread.
+constexpr int kIngestLds = 2048;
+__global__ void __launch_bounds__(256) k_ingest_rows(int64_t n, const int64_t *__restrict__ ostart,
+                                                     const int64_t *__restrict__ krp, const double *__restrict__ vals,
+                                                     double *__restrict__ kval, Control *c) {
+    __shared__ int32_t src[kIngestLds];
+    __shared__ double val[kIngestLds];
+    const int64_t stride = (int64_t)gridDim.x * 256;
     double m = 0.0;
     bool bad = false;
-    for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < n; k += stride) {
-        const int64_t s = ostart[k], e0 = krp[k];
-        const int len = (int)(krp[k + 1] - e0);
+    for (int64_t i0 = (int64_t)blockIdx.x * 256; i0 < n; i0 += stride) {
+        const int64_t ie = i0 + 256 < n ? i0 + 256 : n, k = i0 + threadIdx.x;
+        const int64_t e0 = krp[i0], cnt = krp[ie] - e0;
+        const int64_t s = k < ie ? ostart[k] : 0, p0 = k < ie ? krp[k] : 0;
+        const int len = k < ie ? (int)(krp[k + 1] - p0) : 0;
         double sum = 0.0;
-        for (int t0 = 0; t0 < len; t0 += 8) {
-            double v[8];
+        if (cnt <= kIngestLds) {
+            for (int t = 0; t < len; ++t) src[p0 - e0 + t] = (int32_t)(s + t);
+            __syncthreads();
+            constexpr int kPer = kIngestLds / 256;
+            double v[kPer];
 #pragma unroll
-            for (int t = 0; t < 8; ++t) v[t] = t0 + t < len ? vals[s + t0 + t] : 0.0;
+            for (int t = 0; t < kPer; ++t) v[t] = threadIdx.x + t * 256 < cnt ? vals[src[threadIdx.x + t * 256]] : 0.0;
 #pragma unroll
-            for (int t = 0; t < 8; ++t)
-                if (t0 + t < len) {
-                    kval[e0 + t0 + t] = v[t];
-                    sum += fabs(v[t]);
+            for (int t = 0; t < kPer; ++t) {
+                const int64_t q = threadIdx.x + t * 256;
+                if (q < cnt) {
+                    kval[e0 + q] = v[t];
+                    val[q] = fabs(v[t]);
                     bad |= !isfinite(v[t]);
                 }
+            }
+            __syncthreads();
+            for (int t = 0; t < len; ++t) sum += val[p0 - e0 + t];
+            __syncthreads();
+        } else {
+            for (int t = 0; t < len; ++t) {
+                const double v = vals[s + t];
+                kval[p0 + t] = v;
+                sum += fabs(v);
+                bad |= !isfinite(v);
+            }
         }
         m = fmax(m, sum);
     }
@@ -344,33 +368,6 @@ __global__ void k_vscatter(int64_t n, const int32_t *__restrict__ perm, const do
 // the gathers), so a short row costs one round of dependent loads instead of one per entry;
 // the terms are still combined one by one in ascending position.
 constexpr int kRowBatch = 8;
-
-// sum over p in [rp[i], rp[i+1]) of kval[p] * x[ci[p]], each product and sum rounded, in
-// ascending p
-__device__ __forceinline__ double row_dot(const int64_t *__restrict__ rp, const int32_t *__restrict__ ci,
-                                          const double *__restrict__ kval, const double *x, int64_t i) {
-    const int64_t e = rp[i + 1];
-    double s = 0.0;
-    for (int64_t p = rp[i]; p < e; p += kRowBatch) {
-        int c[kRowBatch];
-        double v[kRowBatch], xv[kRowBatch];
-#pragma unroll
-        for (int t = 0; t < kRowBatch; ++t) {
-            c[t] = p + t < e ? ci[p + t] : 0;
-            v[t] = p + t < e ? kval[p + t] : 0.0;
-        }
-#pragma unroll
-        for (int t = 0; t < kRowBatch; ++t) xv[t] = p + t < e ? x[c[t]] : 0.0;
-#pragma unroll
-        for (int t = 0; t < kRowBatch; ++t) {
-            if (p + t < e) {
-                const double prod = v[t] * xv[t];
-                s = s + prod;
-            }
-        }
-    }
-    return s;
-}
 
 // ||K||_inf of the values already in the workspace's copy of K (after a re-pivot, which
 // uploads them from the host).
@@ -1935,13 +1932,15 @@ __global__ void k_fill_sentinel(int64_t n, T *a, T *b, SolveWork *work, unsigned
 // ---------------------------------------------------------------------------------------
 // Krylov kernels (FP64).  Streaming grid: G <= kStreamGridMax blocks of kStreamBlock threads,
 // block b owns a contiguous chunk of rows and writes its partial sums to
-// part[b * kPartStride + t] with plain stores; the NEXT kernel reduces the partials in every
+// part[t * kStreamGridMax + b] with plain stores; the NEXT kernel reduces the partials in every
 // block, in block order (deterministic, identical in every block), so no reduction needs a
 // memory fence: the kernel boundary makes the partials visible.  Three partial buffers
 // rotate so a kernel never overwrites the partials it is reading.
 // ---------------------------------------------------------------------------------------
 
-constexpr int kPartStride = 2 * kRestartMax + 4;  // room for the 2 (j + 1) dots of a DCGS2 step
+constexpr int kPartCols = 2 * kRestartMax + 4;  // room for the 2 (j + 1) dots of a DCGS2 step
+// (A column's partials are contiguous.  With a block's side by side, every block read a cache line
+// per partial: 134 MB of L2 traffic per reduction with 1,024 blocks, 10 us of a 23 us kernel.)
 
 struct KrylovArgs {
     int64_t n;
@@ -1951,20 +1950,78 @@ struct KrylovArgs {
     double *V;        // (R+1) columns of n
     double *Z;        // R columns of n
     double *w;
-    double *part;     // 3 buffers of kStreamGridMax * kPartStride
+    double *part;     // 3 buffers of kPartCols * kStreamGridMax
     Control *ctl;
 };
 
 __device__ __forceinline__ double *partbuf(const KrylovArgs &a, int which) {
-    return a.part + (int64_t)which * kStreamGridMax * kPartStride;
+    return a.part + (int64_t)which * kStreamGridMax * kPartCols;
 }
 
-// Sum of partial column t over the G blocks of the previous kernel (fixed order; one thread).
-__device__ __forceinline__ double reduce_part(const double *buf, int G, int t) {
+// Products of a block's next kStreamBlock rows [i0, i0 + 256) with x, in LDS.  One thread per row read
+// its entries at a stride of the row length (42 bytes here), 24 loads a row whose lines eight of
+// them shared; with the rows' contiguous entries read by the whole block, one coalesced load of
+// a value and of an index and one gather per entry remain.  Every row still adds its rounded
+// products in ascending position.  Blocks of rows with more than kRowLds entries go without.
+constexpr int kRowLds = 2048;
+struct RowSpan {
+    int64_t e0, p0, p1;  // first entry of the block's rows; this thread's row's entries
+    const double *prod;  // the products from e0 on (kDD: then their rounding errors), or null
+};
+template <bool kDD>
+__device__ __forceinline__ RowSpan block_products(const KrylovArgs &a, const double *x, int64_t i0, int64_t r1,
+                                                  double *lds) {
+    const int64_t ie = i0 + kStreamBlock < r1 ? i0 + kStreamBlock : r1;
+    const int64_t i = i0 + threadIdx.x;
+    RowSpan sp;
+    sp.e0 = a.rp[i0];
+    sp.p0 = i < ie ? a.rp[i] : 0;
+    sp.p1 = i < ie ? a.rp[i + 1] : 0;
+    const int64_t cnt = a.rp[ie] - sp.e0;
+    sp.prod = cnt <= kRowLds ? lds : nullptr;
+    if (!sp.prod) return sp;
+    __syncthreads();  // the sums of the rows before are done
+    constexpr int kPer = kRowLds / kStreamBlock;
+    int c[kPer];
+    double v[kPer], xv[kPer];
+#pragma unroll
+    for (int t = 0; t < kPer; ++t) {
+        const int64_t k = threadIdx.x + t * kStreamBlock;
+        c[t] = k < cnt ? a.ci[sp.e0 + k] : 0;
+        v[t] = k < cnt ? a.kval[sp.e0 + k] : 0.0;
+    }
+#pragma unroll
+    for (int t = 0; t < kPer; ++t) xv[t] = threadIdx.x + t * kStreamBlock < cnt ? x[c[t]] : 0.0;
+#pragma unroll
+    for (int t = 0; t < kPer; ++t) {
+        const int64_t k = threadIdx.x + t * kStreamBlock;
+        if (k < cnt) {
+            const double ph = v[t] * xv[t];
+            lds[k] = ph;
+            if (kDD) lds[kRowLds + k] = fma(v[t], xv[t], -ph);
+        }
+    }
+    __syncthreads();
+    return sp;
+}
+
+// Sum of this thread's row's products in ascending position.
+__device__ __forceinline__ double span_sum(const KrylovArgs &a, const double *x, const RowSpan &sp) {
     double s = 0.0;
-    for (int b = 0; b < G; ++b) s += buf[(int64_t)b * kPartStride + t];
+    if (sp.prod) {
+        for (int64_t p = sp.p0; p < sp.p1; ++p) s = s + sp.prod[p - sp.e0];
+    } else {
+        for (int64_t p = sp.p0; p < sp.p1; ++p) {
+            const double prod = a.kval[p] * x[a.ci[p]];
+            s = s + prod;
+        }
+    }
     return s;
 }
+
+// Columns of V whose dot products are accumulated while a row is in registers (the first ones;
+// later ones take a pass of their own).
+constexpr int kFusedDots = 4;
 
 // Per-column partial sums of one block without a barrier per column: each wavefront reduces
 // its value with shuffles and lane 0 parks it in red[t][wave]; block_cols_finish() (one
@@ -1986,7 +2043,7 @@ __device__ void reduce_cols(const double *buf, int G, int m, double *out, double
     const int b = threadIdx.x;
     for (int t = 0; t < m; ++t) {
         double v = 0.0;
-        for (int r = b; r < G; r += kStreamBlock) v += buf[(int64_t)r * kPartStride + t];
+        for (int r = b; r < G; r += kStreamBlock) v += buf[(int64_t)t * kStreamGridMax + r];
         block_col_put(v, t, red);
     }
     __syncthreads();
@@ -1997,21 +2054,39 @@ __device__ void reduce_cols(const double *buf, int G, int m, double *out, double
 // w = K z_j; partials (buffer 0): V_t . w for t <= j, and w . w at t = j + 1
 __global__ void __launch_bounds__(kStreamBlock) k_spmv_dots(KrylovArgs a, int j) {
     __shared__ double red[(kRestartMax + 2) * (kStreamBlock / 64)];
+    __shared__ double lds[kRowLds];
     if (a.ctl->stop) return;  // enqueued ahead of the host's stop test
     int64_t r0, r1;
     block_rows(a.n, r0, r1);
     const double *z = a.Z + (int64_t)j * a.n;
-    for (int64_t i = r0 + threadIdx.x; i < r1; i += blockDim.x) a.w[i] = row_dot(a.rp, a.ci, a.kval, z, i);
-    __syncthreads();
-    double *out = partbuf(a, 0) + (int64_t)blockIdx.x * kPartStride;
-    for (int t = 0; t <= j + 1; ++t) {
-        const double *v = t <= j ? a.V + (int64_t)t * a.n : a.w;
+    double dot[kFusedDots] = {}, ss = 0.0;
+    for (int64_t i0 = r0; i0 < r1; i0 += kStreamBlock) {
+        const RowSpan sp = block_products<false>(a, z, i0, r1, lds);
+        const int64_t i = i0 + threadIdx.x;
+        if (i < r1) {
+            double v[kFusedDots];
+#pragma unroll
+            for (int t = 0; t < kFusedDots; ++t) v[t] = t <= j ? a.V[(int64_t)t * a.n + i] : 0.0;
+            const double w = span_sum(a, z, sp);
+            a.w[i] = w;
+#pragma unroll
+            for (int t = 0; t < kFusedDots; ++t) dot[t] += v[t] * w;
+            ss += w * w;
+        }
+    }
+    double *out = partbuf(a, 0) + blockIdx.x;
+#pragma unroll
+    for (int t = 0; t < kFusedDots; ++t)
+        if (t <= j) block_col_put(dot[t], t, red);
+    for (int t = kFusedDots; t <= j; ++t) {
+        const double *v = a.V + (int64_t)t * a.n;
         double s = 0.0;
         for (int64_t i = r0 + threadIdx.x; i < r1; i += blockDim.x) s += v[i] * a.w[i];
         block_col_put(s, t, red);
     }
+    block_col_put(ss, j + 1, red);
     __syncthreads();
-    for (int t = threadIdx.x; t <= j + 1; t += blockDim.x) out[t] = block_col_get(red, t);
+    for (int t = threadIdx.x; t <= j + 1; t += blockDim.x) out[(int64_t)t * kStreamGridMax] = block_col_get(red, t);
 }
 
 // h1 = reduce(buffer 0); w -= V h1; partials (buffer 1): V_t . w (second CGS pass) for t <= j, and w . w
@@ -2028,19 +2103,33 @@ __global__ void __launch_bounds__(kStreamBlock) k_cgs_pass2(KrylovArgs a, int j)
     }
     int64_t r0, r1;
     block_rows(a.n, r0, r1);
-    double ss = 0.0;
+    double dot[kFusedDots] = {}, ss = 0.0;
     for (int64_t i = r0 + threadIdx.x; i < r1; i += blockDim.x) {
+        double v[kFusedDots];
+#pragma unroll
+        for (int t = 0; t < kFusedDots; ++t) v[t] = t <= j ? a.V[(int64_t)t * a.n + i] : 0.0;
         double s = a.w[i];
-        for (int t = 0; t <= j; ++t) {
+#pragma unroll
+        for (int t = 0; t < kFusedDots; ++t)
+            if (t <= j) {
+                const double prod = v[t] * h[t];
+                s = s - prod;
+            }
+        for (int t = kFusedDots; t <= j; ++t) {
             const double prod = a.V[(int64_t)t * a.n + i] * h[t];
             s = s - prod;
         }
         a.w[i] = s;
+#pragma unroll
+        for (int t = 0; t < kFusedDots; ++t) dot[t] += v[t] * s;
         ss += s * s;
     }
-    __syncthreads();
-    double *out = partbuf(a, 1) + (int64_t)blockIdx.x * kPartStride;
-    for (int t = 0; t <= j; ++t) {
+    double *out = partbuf(a, 1) + blockIdx.x;
+    __syncthreads();  // red was the reduction's
+#pragma unroll
+    for (int t = 0; t < kFusedDots; ++t)
+        if (t <= j) block_col_put(dot[t], t, red);
+    for (int t = kFusedDots; t <= j; ++t) {
         const double *v = a.V + (int64_t)t * a.n;
         double s = 0.0;
         for (int64_t i = r0 + threadIdx.x; i < r1; i += blockDim.x) s += v[i] * a.w[i];
@@ -2048,7 +2137,7 @@ __global__ void __launch_bounds__(kStreamBlock) k_cgs_pass2(KrylovArgs a, int j)
     }
     block_col_put(ss, j + 1, red);
     __syncthreads();
-    for (int t = threadIdx.x; t <= j + 1; t += blockDim.x) out[t] = block_col_get(red, t);
+    for (int t = threadIdx.x; t <= j + 1; t += blockDim.x) out[(int64_t)t * kStreamGridMax] = block_col_get(red, t);
 }
 
 // Closes Arnoldi column j (thread 0 of every block, identical results): col[0..j] are the
@@ -2168,12 +2257,16 @@ __global__ void __launch_bounds__(kStreamBlock) k_normalize(KrylovArgs a, int j,
 // w = K z_j (when matvec); partials (buffer 0): V_t . w at t and V_t . u_j at j + 1 + t, t <= j
 __global__ void __launch_bounds__(kStreamBlock) k_dcgs2_dots(KrylovArgs a, int j, int matvec) {
     __shared__ double red[(2 * kRestartMax + 4) * (kStreamBlock / 64)];
+    __shared__ double lds[kRowLds];
     if (a.ctl->stop) return;
     int64_t r0, r1;
     block_rows(a.n, r0, r1);
     if (matvec) {
         const double *z = a.Z + (int64_t)j * a.n;
-        for (int64_t i = r0 + threadIdx.x; i < r1; i += blockDim.x) a.w[i] = row_dot(a.rp, a.ci, a.kval, z, i);
+        for (int64_t i0 = r0; i0 < r1; i0 += kStreamBlock) {
+            const RowSpan sp = block_products<false>(a, z, i0, r1, lds);
+            if (i0 + threadIdx.x < r1) a.w[i0 + threadIdx.x] = span_sum(a, z, sp);
+        }
     }
     __syncthreads();
     const double *u = a.V + (int64_t)j * a.n;
@@ -2189,8 +2282,8 @@ __global__ void __launch_bounds__(kStreamBlock) k_dcgs2_dots(KrylovArgs a, int j
         block_col_put(su, j + 1 + t, red);
     }
     __syncthreads();
-    double *out = partbuf(a, 0) + (int64_t)blockIdx.x * kPartStride;
-    for (int t = threadIdx.x; t < 2 * (j + 1); t += blockDim.x) out[t] = block_col_get(red, t);
+    double *out = partbuf(a, 0) + blockIdx.x;
+    for (int t = threadIdx.x; t < 2 * (j + 1); t += blockDim.x) out[(int64_t)t * kStreamGridMax] = block_col_get(red, t);
 }
 
 // The rest of DCGS2 step j (see above): every block reduces the partials and forms the same
@@ -2288,12 +2381,10 @@ __global__ void __launch_bounds__(kStreamBlock) k_dcgs2(KrylovArgs a, int j, int
 }
 
 // Row i of rho = b - K x in double-double: the pair (hi, lo) starts at (b_i, 0) and each
-// product v*x enters as its exact pair (v*x rounded, and the rounding error from one fused
+// product v*x enters as its exact pair (ph: v*x rounded, pl: the rounding error from one fused
 // multiply-add), added with the accurate double-word sum of Joldes, Muller and Popescu
 // (ACM TOMS 2017, relative error <= 3u^2); the row is rounded once, to hi.
-__device__ __forceinline__ void dd_accumulate(double &hi, double &lo, double v, double x) {
-    const double ph = v * x;
-    const double pl = fma(v, x, -ph);
+__device__ __forceinline__ void dd_accumulate(double &hi, double &lo, double ph, double pl) {
     const double yh = -ph, yl = -pl;
     // exact sums of the high and of the low parts (Knuth)
     const double sh = hi + yh;
@@ -2312,28 +2403,26 @@ __device__ __forceinline__ void dd_accumulate(double &hi, double &lo, double v, 
     hi = zh;
 }
 
+// Row i of rho: b_i minus the row's products (from LDS where block_products put them).
 template <bool kDD>
-__device__ __forceinline__ double resid_row(const KrylovArgs &a, const double *x, double bi, int64_t i) {
+__device__ __forceinline__ double resid_row(const KrylovArgs &a, const double *x, double bi, const RowSpan &sp) {
     if (kDD) {
         double hi = bi, lo = 0.0;
-        const int64_t e = a.rp[i + 1];
-        for (int64_t p = a.rp[i]; p < e; p += kRowBatch) {
-            int c[kRowBatch];
-            double v[kRowBatch], xv[kRowBatch];
-#pragma unroll
-            for (int t = 0; t < kRowBatch; ++t) {
-                c[t] = p + t < e ? a.ci[p + t] : 0;
-                v[t] = p + t < e ? a.kval[p + t] : 0.0;
+        for (int64_t p = sp.p0; p < sp.p1; ++p) {
+            double ph, pl;
+            if (sp.prod) {
+                ph = sp.prod[p - sp.e0];
+                pl = sp.prod[kRowLds + p - sp.e0];
+            } else {
+                const double v = a.kval[p], xv = x[a.ci[p]];
+                ph = v * xv;
+                pl = fma(v, xv, -ph);
             }
-#pragma unroll
-            for (int t = 0; t < kRowBatch; ++t) xv[t] = p + t < e ? x[c[t]] : 0.0;
-#pragma unroll
-            for (int t = 0; t < kRowBatch; ++t)
-                if (p + t < e) dd_accumulate(hi, lo, v[t], xv[t]);
+            dd_accumulate(hi, lo, ph, pl);
         }
         return hi;
     }
-    return bi - row_dot(a.rp, a.ci, a.kval, x, i);
+    return bi - span_sum(a, x, sp);
 }
 
 // The control block starts with the fields of ControlSummary, in the same layout.
@@ -2349,6 +2438,20 @@ __device__ __forceinline__ void store_part(double *p, double v) {
 }
 __device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
+// Whether the calling block is the launch's last to arrive (one thread per block).  Blocks count
+// themselves in kWorkQueues groups, the last of a group counts the group: one counter for all
+// took 12 us with 1,024 blocks.  Leaves the counters at zero.
+__device__ __forceinline__ bool last_arrival(Control *c) {
+    const unsigned int G = gridDim.x, g = blockIdx.x % kWorkQueues;
+    const unsigned int members = (G - g + kWorkQueues - 1) / kWorkQueues;
+    if (atomicAdd(&c->arrive[g * 64], 1u) != members - 1) return false;
+    atomicExch(&c->arrive[g * 64], 0u);
+    const unsigned int groups = G < (unsigned int)kWorkQueues ? G : (unsigned int)kWorkQueues;
+    if (atomicAdd(&c->counter, 1u) != groups - 1) return false;
+    atomicExch(&c->counter, 0u);
+    return true;
+}
+
 // rho = b - K x with ||rho||^2, ||x||^2, ||b||^2, the non-finite b flag, max |rho_i|, max |x_i|.  Each
 // block leaves its partials (buffer 0); the block that arrives last adds them in block order
 // (the same bits whichever block that is), writes the control block and copies its summary into
@@ -2360,21 +2463,26 @@ __global__ void __launch_bounds__(kStreamBlock) k_resid(KrylovArgs a, const doub
                                                         unsigned long long token) {
     __shared__ double red[4 * (kStreamBlock / 64)];
     __shared__ double h[4];
+    __shared__ double lds[(kDD ? 2 : 1) * kRowLds];
     __shared__ bool last_sh;
     int64_t r0, r1;
     block_rows(a.n, r0, r1);
     double sr = 0.0, sx = 0.0, sb = 0.0, mr = 0.0, mx = 0.0;
     int badb = 0;
-    for (int64_t i = r0 + threadIdx.x; i < r1; i += blockDim.x) {
-        const double bi = b[i];
-        const double ri = resid_row<kDD>(a, x, bi, i);
-        r[i] = ri;
-        sr += ri * ri;
-        sx += x[i] * x[i];
-        sb += bi * bi;
-        mr = fmax(mr, fabs(ri));
-        mx = fmax(mx, fabs(x[i]));
-        badb |= !isfinite(bi);
+    for (int64_t i0 = r0; i0 < r1; i0 += kStreamBlock) {
+        const RowSpan sp = block_products<kDD>(a, x, i0, r1, lds);
+        const int64_t i = i0 + threadIdx.x;
+        if (i < r1) {
+            const double bi = b[i], xi = x[i];
+            const double ri = resid_row<kDD>(a, x, bi, sp);
+            r[i] = ri;
+            sr += ri * ri;
+            sx += xi * xi;
+            sb += bi * bi;
+            mr = fmax(mr, fabs(ri));
+            mx = fmax(mx, fabs(xi));
+            badb |= !isfinite(bi);
+        }
     }
     sr = block_sum(sr, red);
     mr = block_max(mr, red);
@@ -2383,15 +2491,15 @@ __global__ void __launch_bounds__(kStreamBlock) k_resid(KrylovArgs a, const doub
     sb = block_sum(sb, red);
     const double bad = block_sum((double)badb, red);
     if (threadIdx.x == 0) {
-        double *p = partbuf(a, 0) + (int64_t)blockIdx.x * kPartStride;
-        store_part(p + 0, sr);
-        store_part(p + 1, sx);
-        store_part(p + 2, sb);
-        store_part(p + 3, bad);
-        store_part(p + 4, mr);
-        store_part(p + 5, mx);
+        double *p = partbuf(a, 0) + blockIdx.x;
+        store_part(p + 0 * kStreamGridMax, sr);
+        store_part(p + 1 * kStreamGridMax, sx);
+        store_part(p + 2 * kStreamGridMax, sb);
+        store_part(p + 3 * kStreamGridMax, bad);
+        store_part(p + 4 * kStreamGridMax, mr);
+        store_part(p + 5 * kStreamGridMax, mx);
         stores_done();
-        last_sh = atomicAdd(&a.ctl->counter, 1u) == gridDim.x - 1;
+        last_sh = last_arrival(a.ctl);
     }
     __syncthreads();
     if (!last_sh) return;
@@ -2401,7 +2509,7 @@ __global__ void __launch_bounds__(kStreamBlock) k_resid(KrylovArgs a, const doub
     for (int q = tid; q < G; q += kStreamBlock) {
         double p[6];
 #pragma unroll
-        for (int t = 0; t < 6; ++t) p[t] = load_system(buf + (int64_t)q * kPartStride + t);
+        for (int t = 0; t < 6; ++t) p[t] = load_system(buf + (int64_t)t * kStreamGridMax + q);
 #pragma unroll
         for (int t = 0; t < 4; ++t) v[t] += p[t];
         v[4] = fmax(v[4], p[4]);
@@ -2421,7 +2529,6 @@ __global__ void __launch_bounds__(kStreamBlock) k_resid(KrylovArgs a, const doub
         a.ctl->xnorm2 = h[1];
         a.ctl->bnorm2 = h[2];
         if (h[3] != 0.0) a.ctl->nonfinite_b = 1;
-        a.ctl->counter = 0;
         // every word loaded first, then stored: one round trip to the control block instead
         // of one per word (a load, its store, the next load ... took 10-16 us per launch)
         constexpr int kWords = sizeof(ControlSummary) / 8;
@@ -2442,11 +2549,15 @@ template <bool kDD>
 __global__ void __launch_bounds__(kStreamBlock) k_resid_user(KrylovArgs a, const int32_t *__restrict__ perm,
                                                              const double *__restrict__ b, const double *x,
                                                              double *__restrict__ r) {
+    __shared__ double lds[(kDD ? 2 : 1) * kRowLds];
     int64_t r0, r1;
     block_rows(a.n, r0, r1);
-    for (int64_t i = r0 + threadIdx.x; i < r1; i += blockDim.x) {
-        const int32_t p = perm[i];
-        r[p] = resid_row<kDD>(a, x, b[p], i);
+    for (int64_t i0 = r0; i0 < r1; i0 += kStreamBlock) {
+        const int64_t i = i0 + threadIdx.x;
+        const int32_t p = i < r1 ? perm[i] : 0;
+        const double bp = i < r1 ? b[p] : 0.0;
+        const RowSpan sp = block_products<kDD>(a, x, i0, r1, lds);
+        if (i < r1) r[p] = resid_row<kDD>(a, x, bp, sp);
     }
 }
 
@@ -2814,7 +2925,7 @@ Offsets plan_for(const kkt_handle_t h, bool tiles) {
     o.xb = p.take<double>(n);
     o.bi = p.take<double>(n);
     o.xi = p.take<double>(n);
-    o.part = p.take<double>((size_t)3 * kStreamGridMax * kPartStride);
+    o.part = p.take<double>((size_t)3 * kStreamGridMax * kPartCols);
     o.ctl = p.take<Control>(1);
     o.total = p.off;
     return o;
@@ -3974,7 +4085,7 @@ kkt_status_t kkt_bind_workspace(kkt_handle_t h, void *dev_ptr, size_t bytes, voi
     // dense blocks of the solve layout hold explicit zeros that the refactorization never writes
     KKT_HIP(h, hipMemsetAsync(d.T64, 0, a.t_size * sizeof(double), s));
     KKT_HIP(h, hipMemsetAsync(d.T32, 0, a.t_size * sizeof(float), s));
-    KKT_HIP(h, hipMemsetAsync(d.part, 0, (size_t)3 * kStreamGridMax * kPartStride * sizeof(double), s));
+    KKT_HIP(h, hipMemsetAsync(d.part, 0, (size_t)3 * kStreamGridMax * kPartCols * sizeof(double), s));
     KKT_HIP(h, hipStreamSynchronize(s));
     // at least one block per hand-out queue
     const bool flat = !h->an.relsrc.empty();
