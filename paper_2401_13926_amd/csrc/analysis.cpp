@@ -1345,22 +1345,31 @@ bool build_solve_tiles(const AnalysisOptions &opt, Analysis &a) {
                     ++q;
                     continue;
                 }
-                int lg = 0;  // about eight entries per lane, fewer lanes rather than another pass
-                while (lg < 6 && ((int64_t)8 << lg) < len) ++lg;
-                while (lg > 0 && ((int64_t)(re - q) << lg) > 64 && ((int64_t)16 << lg) > len) --lg;
-                const int64_t g = (int64_t)1 << lg, half = (len + 2 * g - 1) / (2 * g), D = 2 * half;
+                // Rows that fit one pass with at most four places per lane take four (a short
+                // chunk, when its segment is one pass); other segments about eight per lane, fewer
+                // lanes rather than another pass.
+                int lg = 0;
+                while (lg < 6 && ((int64_t)4 << lg) < len) ++lg;
+                const bool fits = !raw && q == r && ((int64_t)(re - q) << lg) <= 64 && ((int64_t)4 << lg) >= len &&
+                                  (re - q <= 32 || len > 2);
+                if (!fits) {
+                    lg = 0;
+                    while (lg < 6 && ((int64_t)8 << lg) < len) ++lg;
+                    while (lg > 0 && ((int64_t)(re - q) << lg) > 64 && ((int64_t)16 << lg) > len) --lg;
+                }
+                const int64_t g = (int64_t)1 << lg, half = fits ? 2 : (len + 2 * g - 1) / (2 * g), D = 2 * half;
                 // a pass holds 64 >> lg rows; a dozen rows or more with less than half as many
                 // places get a pass of their own, and so do rows of a dense range (in sweep order,
                 // not by length) with more places or less than half as many
                 int32_t cnt = std::min<int32_t>(re - q, 64 >> lg);
-                for (int32_t c = 1; c < cnt; ++c)
+                for (int32_t c = 1; c < cnt && !fits; ++c)
                     if ((!raw && half >= 2 && re - q - c >= kMinor && length(q + c) <= g * half) ||
                         (!raw && !dir && length(q + c) == 0) ||
                         (raw && (places_of(q + c) > g * D || (half * g >= 4 && 2 * places_of(q + c) <= g * half))))
                         cnt = c;
                 if (half > 255) return false;
                 const int64_t off = (int64_t)ref.size() - d[2];
-                if (off >= 1 << 29) return false;
+                if (off >= 1 << 28) return false;
                 chunk.push_back((uint32_t)q | ((uint32_t)cnt << 13) | ((uint32_t)lg << 20) | ((uint32_t)half << 23));
                 chunk.push_back((uint32_t)off | (raw ? 1u << 29 : 0u));
                 ref.resize(ref.size() + (size_t)(cnt * g * D), (uint16_t)(8 * zero));
@@ -1380,6 +1389,7 @@ bool build_solve_tiles(const AnalysisOptions &opt, Analysis &a) {
             if (nc == 0) return true;
             const bool single = nc == 1;
             if (!first_work && !(single && prev_single)) chunk[c0] |= 1u << 31;
+            else if (single && !raw && ((chunk[c0] >> 23) & 0xFF) == 2) chunk[c0 + 1] |= 1u << 28;
             first_work = false;
             for (size_t c = 0; c < nc; ++c) chunk[c0 + 2 * c + 1] |= (uint32_t)(c % kSolWaves) << 30;
             prev_single = single;

@@ -165,8 +165,9 @@ struct SolveTiles {
     // tile's places, an even number), chunks before it
     std::vector<int32_t> desc;
     // per chunk two words: first row | rows << 13 | lg << 20 | places per lane / 2 << 23 (8 bits) |
-    // barrier before the chunk << 31; first place (within the tile) | no division by the pivot yet
-    // (dense range) << 29 | wavefront << 30
+    // barrier before the chunk << 31; first place (within the tile) | short << 28 | no division by the
+    // pivot yet (dense range) << 29 | wavefront << 30.  short: the only chunk of its segment, after
+    // another such one (no barrier, wavefront 0), with four places per lane
     std::vector<uint32_t> chunk_l, chunk_u;
     // per place: 8 x the slot it refers to (rows, externals, zero); per dense entry: its place in
     // the triangle

@@ -1690,6 +1690,7 @@ __device__ __forceinline__ void solve_tile(const SolveTileArgs<T> &a, int t, uns
     const int nslot = nr + nx + 1;  // rows, externals, the zero slot; 8 bytes each
     V2 *vals = reinterpret_cast<V2 *>(smem + 8 * (nslot + (nslot & 1)));  // np / 2
     T *dg = reinterpret_cast<T *>(vals + np / 2);                           // nr (upper)
+    const unsigned char *dgb = reinterpret_cast<const unsigned char *>(dg);
     T *tri = dg + (kUpper ? nr : 0);                                        // the dense range's triangle
     const int ntri = dm > 0 ? dm * (dm - 1) / 2 + 1 : 0;
     uint32_t *refs = reinterpret_cast<uint32_t *>(tri + ntri + ((kUpper ? nr : 0) + ntri & 1));  // np / 2
@@ -1833,15 +1834,53 @@ __device__ __forceinline__ void solve_tile(const SolveTileArgs<T> &a, int t, uns
     for (int c = 0; c < nc; ++c) {
         if (kUpper && c == dafter) sweep();
         if ((c & 63) == 0 && c > 0) chunk_words(c);
-        const uint32_t w0 = (uint32_t)__builtin_amdgcn_readlane((int)m0, c & 63);
-        const uint32_t w1 = (uint32_t)__builtin_amdgcn_readlane((int)m1, c & 63);
+        uint32_t w0 = (uint32_t)__builtin_amdgcn_readlane((int)m0, c & 63);
+        uint32_t w1 = (uint32_t)__builtin_amdgcn_readlane((int)m1, c & 63);
+        if (w1 & (1u << 28)) {
+            // Short chunks, one after another: four places per lane, no barrier, no other wavefront,
+            // so one straight line of code per level (the general code below takes twice the
+            // instructions, and their issue is what a level costs).
+            if (wid != 0) continue;
+            for (;;) {
+                const int lg = (int)((w0 >> 20) & 7u), lanes = (int)((w0 >> 13) & 0x7Fu) << lg;
+                if (lane < lanes) {
+                    const uint32_t at = 8u * ((w0 & 0x1FFFu) + (uint32_t)(lane >> lg));
+                    const int p = (int)((w1 & 0x0FFFFFFFu) >> 1) + 2 * lane;
+                    const uint32_t ra = refs[p], rb = refs[p + 1];
+                    const V2 va = vals[p], vb = vals[p + 1];
+                    const T rh = slot_at(at);
+                    const T d = kUpper ? *reinterpret_cast<const T *>(dgb + (sizeof(T) == 8 ? at : at >> 1)) : T(1);
+                    const T x0 = slot_at(ra & 0xFFFFu), x1 = slot_at(ra >> 16);
+                    const T x2 = slot_at(rb & 0xFFFFu), x3 = slot_at(rb >> 16);
+                    T acc = va.x * x0;
+                    acc = fma(va.y, x1, acc);
+                    acc = fma(vb.x, x2, acc);
+                    acc = fma(vb.y, x3, acc);
+                    if (lg > 0) {
+                        acc = group_sum_last(acc, lg);
+                        const int g = 1 << lg;
+                        if ((lane & (g - 1)) == g - 1) slot_at(at) = kUpper ? (rh - acc) * d : rh - acc;
+                    } else {
+                        slot_at(at) = kUpper ? (rh - acc) * d : rh - acc;
+                    }
+                }
+                const int next = c + 1;
+                if (next >= nc || (next & 63) == 0 || (kUpper && next == dafter)) break;
+                const uint32_t n1 = (uint32_t)__builtin_amdgcn_readlane((int)m1, next & 63);
+                if (!(n1 & (1u << 28))) break;
+                c = next;
+                w1 = n1;
+                w0 = (uint32_t)__builtin_amdgcn_readlane((int)m0, c & 63);
+            }
+            continue;
+        }
         if (w0 >> 31) __syncthreads();
         if ((int)(w1 >> 30) != wid) continue;
         const int r0 = (int)(w0 & 0x1FFFu), cnt = (int)((w0 >> 13) & 0x7Fu), lg = (int)((w0 >> 20) & 7u);
         const int half = (int)((w0 >> 23) & 0xFFu);
         if (lane < cnt << lg) {
             const int row = r0 + (lane >> lg);
-            const int p = (int)((w1 & 0x1FFFFFFFu) >> 1) + lane * half;
+            const int p = (int)((w1 & 0x0FFFFFFFu) >> 1) + lane * half;
             const uint32_t *rp = refs + p;
             const V2 *vp = vals + p;
             T &slot = slot_at(8 * row);

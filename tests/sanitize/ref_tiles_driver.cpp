@@ -198,7 +198,8 @@ std::string replay_solve(const kkt::Analysis &a, const std::vector<double> &lx, 
             }
             const uint32_t w0 = chunk.at(2 * (e[0] + c)), w1 = chunk.at(2 * (e[0] + c) + 1);
             const int32_t r0 = w0 & 0x1FFF, cnt = (w0 >> 13) & 0x7F, lg = (w0 >> 20) & 7, half = (w0 >> 23) & 0xFF;
-            const int32_t off = w1 & 0x1FFFFFFF, wave = w1 >> 30;
+            const int32_t off = w1 & 0x0FFFFFFF, wave = w1 >> 30;
+            if ((w1 >> 28 & 1) && (half != 2 || wave != 0 || (w0 >> 31) || (w1 >> 29 & 1))) return "short_chunk";
             const bool rw = (w1 >> 29) & 1;
             // rows become final at a barrier, or at the next chunk while only wavefront 0 works
             if (w0 >> 31) barrier();
