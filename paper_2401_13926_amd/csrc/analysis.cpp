@@ -1586,7 +1586,8 @@ bool build_ref_tiles(const AnalysisOptions &opt, Analysis &a) {
         };
         for (int32_t m : nodes) {
             const int64_t s = deg(m), lm = l0(m);
-            chain.assign(1 + 2 * s, {});
+            if ((int64_t)chain.size() < 1 + 2 * s) chain.resize(1 + 2 * s);
+            for (int64_t e = 0; e < 1 + 2 * s; ++e) chain[e].clear();  // (their memory is kept)
             for (int64_t q = 0; q < s; ++q) where[a.fi[lm + q]] = (int32_t)q;
             for (int64_t p = a.lrp[m]; p < a.lrp[m + 1]; ++p) {
                 const int32_t k = a.lci[p];

@@ -2732,6 +2732,8 @@ struct DevLayout {
 
 struct kkt_handle_s {
     size_t tile_lds = kkt::kTileLds;  // dynamic LDS bytes of a solve block (the tile budget)
+    size_t untiled_bytes = 0;   // with tiles: workspace bytes of the layout without them
+    int64_t updates = 0;        // scalar updates per refactorization
     kkt_opts_t opts{};
     kkt::Analysis an;
     std::string err;
@@ -2974,8 +2976,48 @@ Offsets plan_for(const kkt_handle_t h, bool tiles) {
 // may not qualify for tiles) then fits wherever it did.
 Offsets plan(const kkt_handle_t h) {
     Offsets o = plan_for(h, h->an.ref.tiles() > 0);
-    if (h->an.ref.tiles() > 0) o.total = std::max(o.total, plan_for(h, false).total);
+    if (h->an.ref.tiles() > 0) o.total = std::max(o.total, h->untiled_bytes);
     return o;
+}
+
+// After an analysis: the sizes that are asked for later, then, with tiles, the arrays that only the
+// layout without them needs go (a clone copies the analysis).
+void settle_analysis(kkt_handle_t h) {
+    Analysis &a = h->an;
+    h->updates = a.updates();
+    h->untiled_bytes = 0;
+    if (a.ref.tiles() == 0) return;
+    h->untiled_bytes = plan_for(h, false).total;
+    auto drop = [](auto &v) { std::decay_t<decltype(v)>().swap(v); };
+    drop(a.fi);
+    drop(a.fx);
+    drop(a.fdiag);
+    drop(a.fsrc);
+    drop(a.fsrc_k);
+    drop(a.relptr);
+    drop(a.relpos);
+    drop(a.relsrc);
+    drop(a.relslot);
+    drop(a.pc);
+    drop(a.pu);
+    drop(a.pnu);
+    drop(a.col_order);
+    drop(a.col_level);
+    drop(a.ref_item);
+    drop(a.ref_item_lane);
+    drop(a.lrp);
+    drop(a.urp);
+    drop(a.lci);
+    drop(a.uci);
+    for (TriSchedule *t : {&a.lsched, &a.usched}) {
+        drop(t->rows);
+        drop(t->row_ent);
+        drop(t->ent_ref);
+        drop(t->ext_src);
+        drop(t->csr2ent);
+        drop(t->seg_lg);
+        drop(t->seg_dofs);
+    }
 }
 
 template <typename T> hipError_t up(char *base, size_t off, const std::vector<T> &v, hipStream_t s) {
@@ -3627,11 +3669,16 @@ kkt_status_t repivot_impl(kkt_handle_t h, hipStream_t s) {
     Analysis keep = std::move(h->an);
     h->an = std::move(na);
     const uint64_t keep_id = h->analysis_id;
+    const size_t keep_untiled = h->untiled_bytes;
+    const int64_t keep_updates = h->updates;
     h->analysis_id = next_analysis_id();
+    settle_analysis(h);
     const size_t need = plan(h).total;
     if (need > h->ws_bytes) {
         h->an = std::move(keep);
         h->analysis_id = keep_id;
+        h->untiled_bytes = keep_untiled;
+        h->updates = keep_updates;
         return fail(h, KKT_ENOMEM, "re-pivoting needs a workspace of " + std::to_string(need) + " bytes, " +
                                        std::to_string(h->ws_bytes) + " are bound");
     }
@@ -3838,6 +3885,7 @@ kkt_status_t kkt_analyze(const kkt_opts_t *opts, int64_t n, const int64_t *rowpt
         const kkt_status_t s = rc == AN_EINVAL ? KKT_EINVAL : rc == AN_ESINGULAR ? KKT_ESINGULAR : KKT_ENOMEM;
         return fail(nullptr, s, msg);
     }
+    settle_analysis(h);
     *out = h;
     return KKT_OK;
 }
@@ -3853,7 +3901,7 @@ kkt_status_t kkt_get_analysis_info(kkt_handle_t h, kkt_analysis_info_t *info) {
     info->levels_refactor = a.levels_refactor;
     info->levels_l = a.lsched.levels;
     info->levels_u = a.usched.levels;
-    info->updates = a.updates();
+    info->updates = h->updates;
     info->analysis_seconds = a.seconds;
     info->max_column = 0;
     for (int64_t j = 0; j < a.n; ++j) info->max_column = std::max(info->max_column, a.fp[j + 1] - a.fp[j]);
@@ -4431,6 +4479,8 @@ kkt_status_t kkt_clone(kkt_handle_t src, kkt_handle_t *out) {
         h->opts = src->opts;
         h->an = src->an;
         h->tile_lds = src->tile_lds;
+        h->untiled_bytes = src->untiled_bytes;
+        h->updates = src->updates;
         h->analysis_id = src->analysis_id;
     } catch (const std::bad_alloc &) {
         delete h;
