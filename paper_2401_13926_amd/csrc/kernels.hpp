@@ -22,6 +22,7 @@ constexpr int kResidentRefactorWaves = 3 * 4 * 256;
 constexpr int kRefactorLds = 1024;     // factor entries staged in LDS per wavefront
 constexpr int kRefTileLds = 32512;     // LDS bytes of a refactorization tile
 constexpr int64_t kSolSmallRows = 250000;  // fewer rows: solve tiles of 12 KiB, else 16 KiB
+constexpr int64_t kDirectResidRows = 400000;  // kkt_residual gathers x in its own launch beyond
 constexpr int kMaxBatch = 8;           // systems of one pattern refactored by one launch
 constexpr int kWorkQueues = 8;         // refactorization hand-out queues (one per XCD of MI355X: a
                                        // block's queue is its index mod 8, the XCD it runs on)

@@ -2007,9 +2007,10 @@ struct RowSpan {
     int64_t e0, p0, p1;  // first entry of the block's rows; this thread's row's entries
     const double *prod;  // the products from e0 on (kDD: then their rounding errors), or null
 };
-template <bool kDD>
+// kPerm: x is in the caller's order, entry perm[c] belongs to column c.
+template <bool kDD, bool kPerm = false>
 __device__ __forceinline__ RowSpan block_products(const KrylovArgs &a, const double *x, int64_t i0, int64_t r1,
-                                                  double *lds) {
+                                                  double *lds, const int32_t *perm = nullptr) {
     const int64_t ie = i0 + kStreamBlock < r1 ? i0 + kStreamBlock : r1;
     const int64_t i = i0 + threadIdx.x;
     RowSpan sp;
@@ -2029,6 +2030,10 @@ __device__ __forceinline__ RowSpan block_products(const KrylovArgs &a, const dou
         c[t] = k < cnt ? a.ci[sp.e0 + k] : 0;
         v[t] = k < cnt ? a.kval[sp.e0 + k] : 0.0;
     }
+    if (kPerm) {
+#pragma unroll
+        for (int t = 0; t < kPer; ++t) c[t] = perm[c[t]];  // (0 where there is no entry: in range)
+    }
 #pragma unroll
     for (int t = 0; t < kPer; ++t) xv[t] = threadIdx.x + t * kStreamBlock < cnt ? x[c[t]] : 0.0;
 #pragma unroll
@@ -2045,13 +2050,15 @@ __device__ __forceinline__ RowSpan block_products(const KrylovArgs &a, const dou
 }
 
 // Sum of this thread's row's products in ascending position.
-__device__ __forceinline__ double span_sum(const KrylovArgs &a, const double *x, const RowSpan &sp) {
+__device__ __forceinline__ double span_sum(const KrylovArgs &a, const double *x, const RowSpan &sp,
+                                           const int32_t *perm = nullptr) {
     double s = 0.0;
     if (sp.prod) {
         for (int64_t p = sp.p0; p < sp.p1; ++p) s = s + sp.prod[p - sp.e0];
     } else {
         for (int64_t p = sp.p0; p < sp.p1; ++p) {
-            const double prod = a.kval[p] * x[a.ci[p]];
+            const int32_t c = perm ? perm[a.ci[p]] : a.ci[p];
+            const double prod = a.kval[p] * x[c];
             s = s + prod;
         }
     }
@@ -2444,7 +2451,8 @@ __device__ __forceinline__ void dd_accumulate(double &hi, double &lo, double ph,
 
 // Row i of rho: b_i minus the row's products (from LDS where block_products put them).
 template <bool kDD>
-__device__ __forceinline__ double resid_row(const KrylovArgs &a, const double *x, double bi, const RowSpan &sp) {
+__device__ __forceinline__ double resid_row(const KrylovArgs &a, const double *x, double bi, const RowSpan &sp,
+                                            const int32_t *perm = nullptr) {
     if (kDD) {
         double hi = bi, lo = 0.0;
         for (int64_t p = sp.p0; p < sp.p1; ++p) {
@@ -2453,7 +2461,7 @@ __device__ __forceinline__ double resid_row(const KrylovArgs &a, const double *x
                 ph = sp.prod[p - sp.e0];
                 pl = sp.prod[kRowLds + p - sp.e0];
             } else {
-                const double v = a.kval[p], xv = x[a.ci[p]];
+                const double v = a.kval[p], xv = x[perm ? perm[a.ci[p]] : a.ci[p]];
                 ph = v * xv;
                 pl = fma(v, xv, -ph);
             }
@@ -2461,7 +2469,7 @@ __device__ __forceinline__ double resid_row(const KrylovArgs &a, const double *x
         }
         return hi;
     }
-    return bi - span_sum(a, x, sp);
+    return bi - span_sum(a, x, sp, perm);
 }
 
 // The control block starts with the fields of ControlSummary, in the same layout.
@@ -2582,9 +2590,9 @@ __global__ void __launch_bounds__(kStreamBlock) k_resid(KrylovArgs a, const doub
     }
 }
 
-// kkt_residual: b and r in the caller's order (row k of the copy of K is original row perm[k]), x in
-// the vector order.
-template <bool kDD>
+// kkt_residual: b and r in the caller's order (row k of the copy of K is original row perm[k]); x too
+// (kDirect), or in the vector order.
+template <bool kDD, bool kDirect>
 __global__ void __launch_bounds__(kStreamBlock) k_resid_user(KrylovArgs a, const int32_t *__restrict__ perm,
                                                              const double *__restrict__ b, const double *x,
                                                              double *__restrict__ r) {
@@ -2595,8 +2603,8 @@ __global__ void __launch_bounds__(kStreamBlock) k_resid_user(KrylovArgs a, const
         const int64_t i = i0 + threadIdx.x;
         const int32_t p = i < r1 ? perm[i] : 0;
         const double bp = i < r1 ? b[p] : 0.0;
-        const RowSpan sp = block_products<kDD>(a, x, i0, r1, lds);
-        if (i < r1) r[p] = resid_row<kDD>(a, x, bp, sp);
+        const RowSpan sp = block_products<kDD, kDirect>(a, x, i0, r1, lds, perm);
+        if (i < r1) r[p] = resid_row<kDD>(a, x, bp, sp, kDirect ? perm : nullptr);
     }
 }
 
@@ -4414,11 +4422,19 @@ kkt_status_t kkt_residual(kkt_handle_t h, const double *dev_b, const double *dev
     hipStream_t s = (hipStream_t)stream;
     const KrylovArgs ka = kargs<double>(h);
     const int G = h->grid_stream;
-    k_vgather<<<G, kStreamBlock, 0, s>>>(h->an.n, h->d.vperm, dev_x, h->d.xi);
-    if (h->opts.residual == KKT_RESID_DD)
-        k_resid_user<true><<<G, kStreamBlock, 0, s>>>(ka, h->d.vperm, dev_b, h->d.xi, dev_r);
-    else
-        k_resid_user<false><<<G, kStreamBlock, 0, s>>>(ka, h->d.vperm, dev_b, h->d.xi, dev_r);
+    const bool dd = h->opts.residual == KKT_RESID_DD;
+    // x's gather through the permutation hits L2 while x fits it (3.2 MB at the limit) and saves a
+    // launch; beyond, a pass that puts x in the vector order first costs less than the scattered
+    // reads.  Direct / gathered, double-double: 60k 7.9 / 10.7 us, 218k 14.4 / 16.4, 500k 30.0 /
+    // 30.5 (binary64 29.0 / 27.2), 1M 68.3 / 59.3.
+    if (h->an.n <= kDirectResidRows) {
+        if (dd) k_resid_user<true, true><<<G, kStreamBlock, 0, s>>>(ka, h->d.vperm, dev_b, dev_x, dev_r);
+        else k_resid_user<false, true><<<G, kStreamBlock, 0, s>>>(ka, h->d.vperm, dev_b, dev_x, dev_r);
+    } else {
+        k_vgather<<<G, kStreamBlock, 0, s>>>(h->an.n, h->d.vperm, dev_x, h->d.xi);
+        if (dd) k_resid_user<true, false><<<G, kStreamBlock, 0, s>>>(ka, h->d.vperm, dev_b, h->d.xi, dev_r);
+        else k_resid_user<false, false><<<G, kStreamBlock, 0, s>>>(ka, h->d.vperm, dev_b, h->d.xi, dev_r);
+    }
     KKT_HIP(h, hipGetLastError());
     return KKT_OK;
 }
