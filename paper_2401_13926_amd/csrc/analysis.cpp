@@ -12,11 +12,14 @@
 
 #include <algorithm>
 #include <chrono>
+#include <exception>
 #include <iterator>
 #include <set>
 #include <cmath>
 #include <limits>
 #include <new>
+#include <system_error>
+#include <thread>
 
 namespace kkt {
 namespace {
@@ -891,6 +894,39 @@ bool tri_schedule(const AnalysisOptions &opt, int64_t n, const std::vector<int64
     return true;
 }
 
+// Work on a second thread beside the caller's (on the caller's, at once, where no thread can be had);
+// wait() returns when it is done and passes on what it threw.
+class Beside {
+  public:
+    template <typename F> explicit Beside(F f) {
+        const auto run = [this, f] {
+            try {
+                f();
+            } catch (...) {
+                error = std::current_exception();
+            }
+        };
+        try {
+            thread = std::thread(run);
+        } catch (const std::system_error &) {
+            run();
+        }
+    }
+    ~Beside() {
+        if (thread.joinable()) thread.join();
+    }
+    Beside(const Beside &) = delete;
+    Beside &operator=(const Beside &) = delete;
+    void wait() {
+        if (thread.joinable()) thread.join();
+        if (error) std::rethrow_exception(error);
+    }
+
+  private:
+    std::thread thread;
+    std::exception_ptr error;
+};
+
 int build_layouts(const AnalysisOptions &opt, Analysis &a, std::string *msg) {
     const int64_t n = a.n;
     const int64_t lnz = a.nnz_l(), unz = a.nnz_u();
@@ -1096,9 +1132,15 @@ int build_layouts(const AnalysisOptions &opt, Analysis &a, std::string *msg) {
     }
     // --- triangular-solve schedules; T then holds each triangle's entries packed in solve
     // order (L, then strict U), followed by the diagonal of U in step order
-    if (!tri_schedule(opt, n, a.lrp, a.lci, true, opt.dense_reserve_l, a.lsched, msg) ||
-        !tri_schedule(opt, n, a.urp, a.uci, false, opt.dense_reserve_u, a.usched, msg))
-        return AN_EINVAL;
+    {
+        std::string umsg;
+        bool uok = false;
+        Beside upper([&] { uok = tri_schedule(opt, n, a.urp, a.uci, false, opt.dense_reserve_u, a.usched, &umsg); });
+        const bool lok = tri_schedule(opt, n, a.lrp, a.lci, true, opt.dense_reserve_l, a.lsched, msg);
+        upper.wait();
+        if (lok && !uok) *msg = umsg;
+        if (!lok || !uok) return AN_EINVAL;
+    }
     {
         const int64_t ubase = a.lrp[n], dbase = a.lrp[n] + a.urp[n];
         const int64_t tu = a.lsched.values(), td = tu + a.usched.values();
@@ -1644,14 +1686,7 @@ bool build_ref_tiles(const AnalysisOptions &opt, Analysis &a) {
                     t.cmx_node.push_back((uint32_t)k);
                     t.cmx_src.push_back((int32_t)a.fsrc_k[p]);
                 }
-        // the way out: entries by their position in the solve layout
-        std::vector<std::pair<int32_t, uint16_t>> out(ne);
-        for (int32_t e = 0; e < ne; ++e) out[e] = {a.f2t[fpos[e]], (uint16_t)e};
-        std::sort(out.begin(), out.end());
-        for (const auto &e : out) {
-            t.out_pos.push_back(e.first);
-            t.out_slot.push_back(e.second);
-        }
+        t.out_pos.insert(t.out_pos.end(), fpos.begin(), fpos.begin() + ne);  // (until place_out)
         d[3] = ne;
         d[5] = (int32_t)items.size();
         d[7] = (int32_t)(t.upd.size() - d[6]);
@@ -1670,12 +1705,38 @@ bool build_ref_tiles(const AnalysisOptions &opt, Analysis &a) {
     return true;
 }
 
-// Tiles for the refactorization and the solves, or none (both are built, or neither).
+// The refactorization tiles' way out: entries (out_pos holds their F positions, in slot order) by
+// their position in the solve layout.
+void place_out(Analysis &a) {
+    RefTiles &t = a.ref;
+    t.out_slot.resize(t.out_pos.size());
+    std::vector<std::pair<int32_t, uint16_t>> out;
+    for (int64_t k = 0; k < t.tiles(); ++k) {
+        const int32_t e0 = t.desc[kRefDesc * k + 2], ne = t.desc[kRefDesc * k + 3];
+        out.resize(ne);
+        for (int32_t e = 0; e < ne; ++e) out[e] = {a.f2t[t.out_pos[e0 + e]], (uint16_t)e};
+        std::sort(out.begin(), out.end());
+        for (int32_t e = 0; e < ne; ++e) {
+            t.out_pos[e0 + e] = out[e].first;
+            t.out_slot[e0 + e] = out[e].second;
+        }
+    }
+}
+
+// Tiles for the refactorization and the solves, or none (both are built, or neither).  The two
+// are built side by side: neither reads what the other writes.
 void build_tiles(const AnalysisOptions &opt, Analysis &a) {
     if (opt.ref_lds <= 0 || a.n < 1 || !symmetric_factor(a)) return;
     const std::vector<int32_t> f2t = a.f2t;
     const int64_t t_size = a.t_size;
-    if (build_solve_tiles(opt, a) && build_ref_tiles(opt, a)) return;
+    bool ref_ok = false;
+    Beside ref([&] { ref_ok = build_ref_tiles(opt, a); });
+    const bool sol_ok = build_solve_tiles(opt, a);
+    ref.wait();
+    if (sol_ok && ref_ok) {
+        place_out(a);
+        return;
+    }
     a.f2t = f2t;
     a.t_size = t_size;
     a.sol = SolveTiles();
@@ -1758,6 +1819,7 @@ int analyze(const AnalysisOptions &opt, int64_t n, const int64_t *rowptr, const 
         a.nnz = rowptr[n];
         a.rowptr.assign(rowptr, rowptr + n + 1);
         a.colidx.assign(colidx, colidx + a.nnz);
+        Beside vector_numbers([&] { rcm_order(n, rowptr, colidx, a.vperm); });
         int rc = AN_OK;
         if (opt.fixed_order) a.q.assign(opt.fixed_order, opt.fixed_order + n);
         else if (opt.ordering == ORDER_ND) rc = nested_dissection(n, rowptr, colidx, opt.nd_leaf, a.q);
@@ -1768,7 +1830,7 @@ int analyze(const AnalysisOptions &opt, int64_t n, const int64_t *rowptr, const 
         }
         rc = pivoted_lu(n, rowptr, colidx, values, opt.pivot_tau, a, msg);
         if (rc != AN_OK) return rc;
-        rcm_order(n, rowptr, colidx, a.vperm);
+        vector_numbers.wait();
         a.vpinv.assign(n, 0);
         for (int64_t k = 0; k < n; ++k) a.vpinv[a.vperm[k]] = (int32_t)k;
         rc = build_layouts(opt, a, msg);
