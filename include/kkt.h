@@ -113,19 +113,24 @@ typedef struct {
                                reduction; 2 kernels per step after the triangular solves
                                instead of 4, the same Krylov basis, and one preconditioner
                                application more per cycle that converges before its restart */
-    int32_t tile_lds_kib;   /* LDS budget of one staged triangular-solve tile in KiB, 16..150
-                               (0: 32).  Larger tiles hold more levels of the elimination tree,
-                               so fewer cross-block hands-offs lie on a solve's critical path;
-                               smaller ones let more blocks share a compute unit (measured
-                               faster at 32 than at 64 on 60k and 2M unknowns); above 80 KiB
+    int32_t tile_lds_kib;   /* 0 (default): where L's and U's patterns are each other's
+                               transpose and narrow_columns is 0, both sweeps run in one
+                               launch on tiles of whole elimination subtrees (12 KiB of LDS
+                               below 250,000 rows, 16 KiB from there), else on staged tiles
+                               of 32 KiB, one launch per sweep.  16..150: always staged tiles, with this LDS budget in
+                               KiB.  Larger tiles hold more levels of the elimination tree, so
+                               fewer cross-block hand-offs lie on a solve's critical path;
+                               smaller ones let more blocks share a compute unit; above 80 KiB
                                one solve block occupies a compute unit alone */
-    int32_t narrow_columns; /* refactorization levels with at most this many columns are handed
-                               out one column per wavefront, wider ones as lane items (64
-                               short columns, one per lane) and chunks of 8 longer columns (0:
-                               automatic, the larger of 3,072 (the refactorization's resident
-                               wavefronts) and n/64 capped at 16,384; measured best at 60k,
-                               500k and 2M unknowns); negative values are rejected
-                               (KKT_EINVAL).  The factors do not depend on it. */
+    int32_t narrow_columns; /* 0 (default): where L's and U's patterns are each other's
+                               transpose and tile_lds_kib is 0, the refactorization runs on
+                               tiles of whole elimination subtrees; else it hands out levels.
+                               Positive: always levels, those with at most this many columns
+                               one column per wavefront, wider ones as lane items (64 short
+                               columns, one per lane) and chunks of 8 longer columns (0 there:
+                               the larger of 3,072, the resident wavefronts, and n/64 capped
+                               at 16,384); negative values are rejected (KKT_EINVAL).  The
+                               factors do not depend on it. */
     int32_t deterministic;  /* 1 (default): bitwise-repeatable results.  Every kernel reduces in
                                a fixed order and none uses floating-point atomics, so a solve
                                gives the same bits alone, batched, in a serving mix or on a
@@ -141,8 +146,9 @@ enum { KKT_GS_CGS2 = 0, KKT_GS_DCGS2 = 1 };
 enum {
     KKT_K_INGEST = 0,   /* values into factor storage, ||K||_inf, finiteness checks */
     KKT_K_REFACTOR = 1, /* numeric refactorization */
-    KKT_K_TRSV_L = 2,   /* forward substitution with L (one launch per preconditioner use) */
-    KKT_K_TRSV_U = 3,   /* backward substitution with U */
+    KKT_K_TRSV_L = 2,   /* forward substitution with L; both substitutions where one launch runs
+                           them (tile_lds_kib) */
+    KKT_K_TRSV_U = 3,   /* backward substitution with U, where it has a launch of its own */
     KKT_K_SPMV = 4,     /* w = K z_j with the first Gram-Schmidt projections */
     KKT_K_CGS = 5,      /* second Gram-Schmidt pass, norm, rotation, normalization */
     KKT_K_RESID = 6,    /* true residual rho = b - K x with norms */
@@ -271,9 +277,10 @@ kkt_status_t kkt_graph_launches(kkt_handle_t h, int64_t *launches);
 /* Solve K x = b for the last refactored K: direct solve, refine decision, FGMRES-IR
  * (Section 2).  dev_b, dev_x: DEVICE arrays of n float64 (distinct).  tol <= 0 uses
  * opts.delta_tol.  Waits for each Arnoldi step's stop flag while the next step runs, and
- * synchronizes `stream` at each restart and before returning; *info
- * (may be NULL) is filled on return.  Errors: KKT_ESTATE (no refactor yet), KKT_EINVAL
- * (non-finite K values or b), KKT_ESINGULAR (guard_policy = FAIL and a guarded pivot),
+ * for each true residual's norms (both arrive in pinned host memory); the last write of dev_x
+ * is in stream order, not waited for.  *info (may be NULL) is filled on return.  Errors:
+ * KKT_ESTATE (no refactor yet), KKT_EINVAL (non-finite K values or b), KKT_ESINGULAR
+ * (guard_policy = FAIL and a guarded pivot),
  * KKT_ENOCONV (tolerance not met; x holds the iterate with the lowest true residual seen,
  * x0 included, and info describes it).  An iterate whose true residual exceeds that of x0 is
  * never accepted, in either stop_mode. */

@@ -7,18 +7,20 @@
 // Section 2.2: NRBE (eq. (nbre)); Section 2.3: the refine decision.
 //
 // Kernels (all wave64):
-//   k_ingest_rows / k_arm    new values -> the solve's copy of K, ||K||_inf, finiteness;
-//                            sentinels (and, without the flat list, the factor storage)
-//   k_refactor<T>            eager left-looking numeric LU, one wavefront per column, columns
-//                            handed out in dependency-level order; a column starts its update
-//                            chain at once and waits per entry of each source column (every
-//                            finished L entry is its own ready flag, so no memory fences)
-//   k_trsv<T, LOWER>         row-oriented triangular solve by tiles (a block walks the
-//                            segments of its tile, g lanes per row); a solution entry is its
-//                            own ready flag (a NaN sentinel until written)
-//   k_spmv_dots, k_cgs_*, k_normalize, k_resid, k_xupdate   Krylov kernels; block partial
-//                            sums are reduced by the next kernel in fixed order (deterministic,
-//                            no fences)
+//   k_ingest_rows            new values -> the solve's copy of K, ||K||_inf, finiteness
+//   k_refactor_tiles<T>      numeric LU on tiles of whole elimination subtrees kept in LDS, columns in
+//                            ascending updates; what a tile passes to tiles above it is its own
+//                            ready flag (a NaN sentinel until written, so no memory fences)
+//   k_solve_tiles<T>         both triangular sweeps in one launch on subtree tiles, the lower sweep
+//                            from the leaves up, the upper one back down; solution entries are
+//                            their own ready flags
+//   k_arm, k_refactor<T>, k_trsv<T, LOWER>   the same for factors whose patterns are not each
+//                            other's transpose, and for chosen tile or hand-out sizes: columns
+//                            handed out in dependency-level order, one launch per sweep by
+//                            staged row tiles
+//   k_spmv_dots, k_cgs_pass2, k_normalize, k_dcgs2*, k_resid, k_xupdate   Krylov kernels; block
+//                            partial sums are reduced by the next kernel or the last block in
+//                            fixed order (deterministic)
 //
 // Floating point: compiled with -ffp-contract=off, so the refactorization performs exactly
 // the roundings of a left-looking column LU with ascending updates (reproducible factors).
@@ -920,6 +922,14 @@ template <typename P> __device__ __forceinline__ const __attribute__((address_sp
 // ---------------------------------------------------------------------------------------
 // refactorization by tiles (RefTiles): subtrees of the elimination tree kept in LDS
 // ---------------------------------------------------------------------------------------
+//
+// Bound: the serial chain of levels, about 0.2-0.3 us each inside a tile (one wavefront's
+// instruction issue and a barrier) plus about 3 us per layer of tiles, not the bytes.  One column per
+// wavefront with every value in HBM (k_refactor) paid a hand-off through memory per level and a
+// cache line per 8-byte gather, 2.9 GB moved at 2M unknowns for 0.3 GB needed; a tile reads and
+// writes each value once.  Per launch, k_refactor / this kernel: 60k 150 / 83 us, 500k 443 / 157 us,
+// 2M 1,047 / 320 us (0.29 / 0.94 TB/s).  32 KiB tiles: with the ingest at 2M, 421 us; 20,000 bytes
+// 489, 26,000 450, 40,700 413.
 
 struct RefTileArgs {
     int64_t ntiles;
@@ -1932,6 +1942,11 @@ __device__ __forceinline__ void solve_tile(const SolveTileArgs<T> &a, int t, uns
     }
 }
 
+// Bound: the chain of levels, 0.18-0.28 us each (instruction issue of one wavefront: loading the next
+// chunk's places ahead made it slower), and about 3 us per hand-off between tiles; one launch
+// saves the gap between the sweeps.  Two k_trsv launches / this kernel: 1k 57 / 25 us, 60k 130 / 58 us,
+// 500k 227 / 112 us, 2M 370 / 272 us (226 MB needed: 0.61 / 0.83 TB/s).  256 threads per block: with 128
+// 60k 66 and 2M 293 us.
 // x = U^-1 L^-1 b: tasks 0..n-1 are the L sweep's tiles in order, tasks n..2n-1 the U sweep's from
 // the last to the first.  Tasks are handed out in order to running blocks and wait only for
 // earlier ones, so the earliest unfinished task is always held by a running block that can
