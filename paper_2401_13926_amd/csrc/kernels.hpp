@@ -24,8 +24,7 @@ constexpr int kRefTileLds = 32512;     // LDS bytes of a refactorization tile
 constexpr int64_t kSolSmallRows = 250000;  // fewer rows: solve tiles of 12 KiB, else 16 KiB
 constexpr int64_t kDirectResidRows = 400000;  // kkt_residual gathers x in its own launch beyond
 constexpr int kMaxBatch = 8;           // systems of one pattern refactored by one launch
-constexpr int kWorkQueues = 8;         // refactorization hand-out queues (one per XCD of MI355X: a
-                                       // block's queue is its index mod 8, the XCD it runs on)
+constexpr int kWorkQueues = 8;         // hand-out queues of the refactorization and the solve tiles
 // Spin limit of one dependency wait (iterations of a short sleep, a few seconds in all);
 // exceeding it marks Control::hang and lets every wave run to completion.
 constexpr unsigned int kSpinLimit = 1u << 22;

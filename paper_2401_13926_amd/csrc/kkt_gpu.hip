@@ -137,12 +137,10 @@ template <typename T> __device__ __forceinline__ T load_system(const T *p) {
 }
 
 // The next of `total` tasks for a block (called by its thread 0; total when none is left).  Tasks go
-// round robin to kWorkQueues counters, task t to counter t % kWorkQueues; block b starts on
-// counter b % kWorkQueues (the XCD it runs on) and moves on when it is exhausted.  Each counter
-// hands out its tasks in order, so the earliest unfinished task is held by a running block or will
-// be taken by one as long as every counter has a resident block: blocks are dispatched in index
-// order, so any kWorkQueues resident blocks cover all of them (a smaller grid has a block per
-// task).
+// round robin to kWorkQueues counters, task t to counter t % kWorkQueues; a block starts on
+// first_queue() and moves on when that is exhausted.  Each counter hands out its tasks in order,
+// so the earliest unfinished task is held by a running block or will be taken by one as long as
+// every counter has a resident block.
 __device__ __forceinline__ unsigned int next_task(unsigned int *queues, unsigned int total, unsigned int &queue) {
     for (int tries = 0; tries < kWorkQueues; ++tries) {
         const unsigned int t = queue + kWorkQueues * atomicAdd(queues + queue * 64, 1u);
@@ -150,6 +148,15 @@ __device__ __forceinline__ unsigned int next_task(unsigned int *queues, unsigned
         queue = (queue + 1) % kWorkQueues;
     }
     return total;
+}
+
+// The counter a block starts on.  XCDs fill with blocks independently of each other (block b on XCD
+// b % 8), and two launches on different streams can each take whole XCDs before the other: eight
+// blocks in a row of one XCD therefore start on eight different counters, so a launch with no more
+// than those resident still reaches every task.  Launches of fewer than 64 blocks do not fill an
+// XCD; there each of the first blocks starts on a counter of its own.
+__device__ __forceinline__ unsigned int first_queue() {
+    return (gridDim.x < kWorkQueues * kWorkQueues ? blockIdx.x : blockIdx.x / kWorkQueues) % kWorkQueues;
 }
 
 // Wave-uniform: lane 0 takes `chunk` consecutive work items from *counter.
@@ -784,12 +791,11 @@ k_refactor(RefactorArgs<T> args, RefactorBatch<T> batch) {
     // serializes its atomics: about 85 grabs per microsecond measured at 2M unknowns, which
     // bounded the hand-out).  Each queue is in level order, so the minimal unfinished item is
     // either held by a running wave or will be taken by one as long as every queue has a
-    // resident block: block b serves queue b % kWorkQueues (blocks are dispatched in index
-    // order, so any 8 resident blocks cover every queue), and a block whose queue is exhausted
-    // moves on to the next queue.
+    // resident block: a block starts on first_queue(), and one whose queue is exhausted moves on
+    // to the next.
     // With a batch of slots, hand-out position g is item g / nslots of slot g % nslots: the
     // slots' items interleave in level order, taken from the first slot's counters.
-    unsigned int queue = blockIdx.x % kWorkQueues;
+    unsigned int queue = first_queue();
     int exhausted = 0;
     const int nslots = batch.nslots;
     for (;;) {
@@ -985,7 +991,7 @@ __global__ void __launch_bounds__(kCoopBlock) __attribute__((amdgpu_waves_per_eu
     const int tid = threadIdx.x, lane = tid & 63;
     const int nslots = kBatch ? batch.nslots : 1;
     Control *const ctl0 = batch.slot[0].ctl;
-    unsigned int queue = blockIdx.x % kWorkQueues;  // thread 0's
+    unsigned int queue = first_queue();  // thread 0's
     for (;;) {
         if (tid == 0) tile_sh = next_task(ctl0->work_refactor, (unsigned int)a.ntiles * nslots, queue);
         __syncthreads();
@@ -1956,7 +1962,7 @@ __global__ void __launch_bounds__(kSolThreads) __attribute__((amdgpu_waves_per_e
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ unsigned int task_sh;
     if (a.stopflag && *a.stopflag) return;
-    unsigned int queue = blockIdx.x % kWorkQueues;  // thread 0's
+    unsigned int queue = first_queue();  // thread 0's
     for (;;) {
         if (threadIdx.x == 0) task_sh = next_task(a.work, 2 * (unsigned int)a.ntiles, queue);
         __syncthreads();
