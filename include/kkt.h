@@ -288,8 +288,8 @@ kkt_status_t kkt_solve(kkt_handle_t h, const double *dev_b, double *dev_x, doubl
                        kkt_solve_info_t *info, void *stream);
 
 /* Apply the current preconditioner once: x = Q U^-1 L^-1 P b with the last refactored
- * factors (the direct solve of Section 1.3, no refinement).  DEVICE arrays of n float64.
- * Enqueued on `stream`, not synchronized. */
+ * factors (the direct solve of Section 1.3, no refinement).  DEVICE arrays of n float64; they
+ * may overlap (x in b's place).  Enqueued on `stream`, not synchronized. */
 kkt_status_t kkt_direct_solve(kkt_handle_t h, const double *dev_b, double *dev_x, void *stream);
 
 /* kkt_direct_solve for callers that cannot allocate device memory (code under HIP graph

@@ -1,0 +1,95 @@
+"""The one-launch solve on patterns and arguments beside the usual ones: a solution that is written over
+its right-hand side (both sweeps share the launch only where no entry of b can be overwritten
+before it is read)."""
+import os
+import pathlib
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+
+import kkt_synth as ks
+import paper_2401_13926_amd as P
+
+ROOT = pathlib.Path(__file__).resolve().parents[1]
+CSRC = ROOT / "paper_2401_13926_amd" / "csrc"
+REF_LDS = 32_512  # LDS bytes of a refactorization tile
+# LDS bytes of a solve tile and of one with its dense range: below 250,000 rows, and from there
+SOL_LDS = {"small": (12_288, 20_000), "large": (16_384, 26_000)}
+
+
+def compiled(tmp_path_factory, name):
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("no g++")
+    out = tmp_path_factory.mktemp("tiles") / name
+    cmd = [gxx, "-std=c++17", "-O1", "-g", "-fsanitize=address,undefined", "-fno-sanitize-recover=undefined",
+           "-ffp-contract=off", "-I", str(CSRC), "-o", str(out), str(ROOT / "tests" / "sanitize" / (name + ".cpp")),
+           str(CSRC / "analysis.cpp")]
+    subprocess.run(cmd, check=True)
+    return out
+
+
+@pytest.fixture(scope="module")
+def order_driver(tmp_path_factory):
+    return compiled(tmp_path_factory, "solve_order_driver")
+
+
+def cycles(n, k=7, c=2.0):
+    """n / k blocks that are cyclic permutations: every pivot off the diagonal, every row a tree of its
+    own (k = 2: symmetric)."""
+    i = np.arange(n)
+    v = np.full(n, c) * (1.0 + 0.25 * (i // k % 3))
+    return np.arange(n + 1, dtype=np.int64), (i // k * k + (i % k + 1) % k).astype(np.int64), v
+
+
+def system(case, n=7_000):
+    if case == "cycles":
+        return cycles(n // 7 * 7)
+    if case == "pairs":
+        return cycles(n, 2)
+    p = ks.small_kkt(1801, 1203, 9)
+    return p.rowptr, p.colidx, p.system(1)[0]
+
+
+@pytest.mark.parametrize("sol", sorted(SOL_LDS))
+@pytest.mark.parametrize("case", ["cycles", "kkt"])
+def test_one_launch_only_where_b_is_read_first(order_driver, tmp_path, case, sol):
+    rp, ci, v = system(case)
+    f = tmp_path / "in.bin"
+    with open(f, "wb") as fh:
+        fh.write(np.array([len(rp) - 1, len(ci)], np.int64).tobytes() + np.array([1e-10], np.float64).tobytes())
+        fh.write(np.array([0, REF_LDS], np.int32).tobytes() + np.array(SOL_LDS[sol], np.int64).tobytes())
+        fh.write(rp.astype(np.int64).tobytes() + ci.astype(np.int32).tobytes() + v.tobytes())
+    r = subprocess.run([str(order_driver), str(f)], capture_output=True, text=True, env=dict(os.environ), timeout=600)
+    assert r.returncode == 0, r.stderr[-4000:]
+    out = {k: int(x) for k, x in (kv.split("=") for kv in r.stdout.split())}
+    assert out["tiles"] > 1
+    assert (out["offdiag"] > 0) == (case == "cycles") and (out["early"] > 0) == (case == "cycles"), out
+    assert out["same"] == (out["early"] == 0) and out["shifted"] == 0 and out["apart"] == 1, out
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("precision", [P.PREC_FP64, P.PREC_MIXED])
+@pytest.mark.parametrize("case", ["cycles", "pairs", "kkt"])
+def test_direct_solve_over_its_right_hand_side(case, precision):
+    """x in b's place, and one entry after it, against x in an array of its own: the same bits."""
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    print("in place", case, precision, flush=True)
+    rp, ci, v = system(case, 200_000)
+    n = len(rp) - 1
+    s = P.Solver(rp, ci, v, precision=precision).bind("cuda")
+    s.refactor(torch.as_tensor(v, device="cuda"))
+    b = torch.as_tensor(np.random.default_rng(3).standard_normal(n), device="cuda")
+    want = s.direct_solve(b)
+    assert torch.isfinite(want).all()
+    for solve in (s.direct_solve, s.direct_solve_noalloc):
+        for shift in (0, 1):
+            for _ in range(3):
+                buf = torch.empty(n + 1, dtype=torch.float64, device="cuda")
+                buf[:n] = b
+                solve(buf[:n], buf[shift:shift + n])
+                assert torch.equal(buf[shift:shift + n], want)
