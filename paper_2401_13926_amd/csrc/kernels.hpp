@@ -92,6 +92,7 @@ struct StepRecord {
 };
 
 // Signalling-NaN bit patterns no arithmetic result takes: "not written yet" in the exchange vectors.
+// (A value of the caller's may: it is changed before it is stored there.)
 constexpr unsigned long long kSent64 = 0x7FF4DEADBEEF0001ull;
 constexpr unsigned int kSent32 = 0x7FA0BEEFu;
 

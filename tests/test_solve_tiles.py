@@ -1,6 +1,7 @@
 """The one-launch solve on patterns and arguments beside the usual ones: a solution that is written over
 its right-hand side (both sweeps share the launch only where no entry of b can be overwritten
-before it is read)."""
+before it is read), and a right-hand side that holds the bits of the exchange vectors' "not
+written" mark."""
 import os
 import pathlib
 import shutil
@@ -93,3 +94,50 @@ def test_direct_solve_over_its_right_hand_side(case, precision):
                 buf[:n] = b
                 solve(buf[:n], buf[shift:shift + n])
                 assert torch.equal(buf[shift:shift + n], want)
+
+
+SENTINEL = np.array([0x7FF4DEADBEEF0001], np.uint64).view(np.float64)[0]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("precision", [P.PREC_FP64, P.PREC_MIXED])
+@pytest.mark.parametrize("where", ["one", "all"])
+def test_right_hand_side_with_the_unwritten_mark(where, precision):
+    """A NaN like any other: the direct solve passes it on, the solve refuses b, the handle goes on."""
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    print("sentinel in b", where, precision, flush=True)
+    # 30 systems side by side: a NaN in one leaves the others finite
+    p = ks.small_kkt(60, 40, 7)
+    k = 30
+    rp = np.concatenate([[0]] + [p.rowptr[1:] + c * p.rowptr[-1] for c in range(k)]).astype(np.int64)
+    ci = np.concatenate([p.colidx + c * p.N for c in range(k)])
+    v = np.tile(p.system(1)[0], k)
+    s = P.Solver(rp, ci, v, precision=precision).bind("cuda")
+    s.refactor(torch.as_tensor(v, device="cuda"))
+    b0 = np.random.default_rng(3).standard_normal(k * p.N)
+
+    def on_gpu(b):
+        return torch.as_tensor(b.view(np.int64), device="cuda").view(torch.float64)
+
+    want = s.direct_solve(on_gpu(b0)).cpu().numpy()
+    assert np.isfinite(want).all()
+    rows = range(p.N * 4, p.N * 5) if where == "one" else [None]  # every row of a system in turn: leaves, roots
+    for row in rows:
+        mark, nan = b0.copy(), b0.copy()
+        mark[slice(None) if row is None else row] = SENTINEL
+        nan[slice(None) if row is None else row] = np.nan
+        assert (mark.view(np.int64) != b0.view(np.int64)).any()
+        ref = s.direct_solve(on_gpu(nan)).cpu().numpy()
+        assert np.isnan(ref).any()
+        x = on_gpu(np.zeros_like(b0))
+        for got in (s.direct_solve(on_gpu(mark)), s.direct_solve_noalloc(on_gpu(mark), x)):
+            got = got.cpu().numpy()
+            assert np.array_equal(np.isnan(got), np.isnan(ref))
+            assert np.array_equal(got[~np.isnan(ref)], want[~np.isnan(ref)])
+    with pytest.raises(P.KKTError) as e:
+        s.solve(on_gpu(mark))
+    assert e.value.args and "non-finite" in str(e.value)
+    x, info = s.solve(on_gpu(b0))
+    assert info["converged"] == 1 and bool(torch.isfinite(x).all())
