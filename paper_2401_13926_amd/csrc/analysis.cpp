@@ -1286,9 +1286,11 @@ bool build_solve_tiles(const AnalysisOptions &opt, Analysis &a) {
     auto entered = [&](int64_t, int64_t) { return (int64_t)8; };
     auto rooted = [&](int64_t m) { return 8 * deg(m); };
     if (!subtree_tiles(a, opt.sol_lds - 64, own, entered, rooted, tile_of, members, t.layers)) return false;
-    std::vector<int32_t> seg_of(n, 0), slot(n, 0), pos_l(n, -1), pos_u(n, -1);
+    std::vector<int32_t> seg_l(n, 0), seg_u(n, 0), slot(n, 0), pos_l(n, -1), pos_u(n, -1);
     std::vector<int32_t> lmap(a.lrp[n]), umap(a.urp[n]);  // CSR entry -> place (global)
     std::vector<int32_t> ext_slot(n, -1);
+    std::vector<int32_t> tree(n), depth(n, 0);  // root of every step's elimination tree; by root
+    for (int64_t m = n - 1; m >= 0; --m) tree[m] = deg(m) ? tree[a.fi[l0(m)]] : (int32_t)m;
     // positions first (externals refer to them)
     std::vector<std::vector<int32_t>> rows_l(members.size()), rows_u(members.size());
     int64_t base = 0;
@@ -1298,12 +1300,21 @@ bool build_solve_tiles(const AnalysisOptions &opt, Analysis &a) {
             if (dir) std::reverse(rows.begin(), rows.end());
             const std::vector<int64_t> &rp = dir ? a.urp : a.lrp;
             const std::vector<int32_t> &ci = dir ? a.uci : a.lci;
+            std::vector<int32_t> &seg_of = dir ? seg_u : seg_l;
+            int32_t deepest = 0;
+            for (int32_t m : rows) depth[tree[m]] = 0;
             for (int32_t m : rows) {
                 int32_t g = 0;
                 for (int64_t p = rp[m]; p < rp[m + 1]; ++p)
                     if (tile_of[ci[p]] == (int32_t)ti) g = std::max(g, seg_of[ci[p]] + 1);
                 seg_of[m] = g;
+                depth[tree[m]] = std::max(depth[tree[m]], g);
+                deepest = std::max(deepest, g);
             }
+            // trees of the U sweep end together, as those of the L sweep start together: the
+            // deepest has the narrow end for itself
+            if (dir)
+                for (int32_t m : rows) seg_of[m] += deepest - depth[tree[m]];
             // by segment, longer rows first
             std::stable_sort(rows.begin(), rows.end(), [&](int32_t x, int32_t y) {
                 if (seg_of[x] != seg_of[y]) return seg_of[x] < seg_of[y];
@@ -1320,21 +1331,18 @@ bool build_solve_tiles(const AnalysisOptions &opt, Analysis &a) {
         const std::vector<int64_t> &rp = dir ? a.urp : a.lrp;
         const std::vector<int32_t> &ci = dir ? a.uci : a.lci;
         const std::vector<int32_t> &rows = dir ? rows_u[ti] : rows_l[ti];
-        const std::vector<int32_t> &pos = dir ? pos_u : pos_l;
+        const std::vector<int32_t> &pos = dir ? pos_u : pos_l, &seg_of = dir ? seg_u : seg_l;
         const int32_t nr = (int32_t)rows.size();
         d[0] = (int32_t)(chunk.size() / 2);
         d[2] = (int32_t)ref.size();
         d[4] = (int32_t)ext.size();
         for (int32_t r = 0; r < nr; ++r) {
             slot[rows[r]] = r;
-            int32_t g = 0;
             for (int64_t p = rp[rows[r]]; p < rp[rows[r] + 1]; ++p)
-                if (tile_of[ci[p]] == (int32_t)ti) g = std::max(g, seg_of[ci[p]] + 1);
-                else if (ext_slot[ci[p]] < 0) {
+                if (tile_of[ci[p]] != (int32_t)ti && ext_slot[ci[p]] < 0) {
                     ext_slot[ci[p]] = 1;
                     ext.push_back(ci[p]);
                 }
-            seg_of[rows[r]] = g;
         }
         // the external that is written last comes first: the closest tile of the sweep
         std::sort(ext.begin() + d[4], ext.end(),
@@ -1346,7 +1354,9 @@ bool build_solve_tiles(const AnalysisOptions &opt, Analysis &a) {
         auto length = [&](int32_t r) { return rp[rows[r] + 1] - rp[rows[r]]; };
         // the dense range [d0, d1): the tile's last (L) or first (U) levels, as many as pay.  A
         // level costs about as much as nine columns of the sweep, the range's own passes about
-        // two levels (0.28 us a level, 0.03 us a column)
+        // two levels (0.28 us a level, 0.03 us a column).  All of one elimination tree: the column
+        // sweep multiplies by the triangle's zeros too, and an infinity in one tree must not turn
+        // another's rows into NaN (within a tree it reaches every row through the root anyhow)
         int32_t d0 = 0, d1 = 0;
         {
             int64_t places = 0;
@@ -1356,9 +1366,13 @@ bool build_solve_tiles(const AnalysisOptions &opt, Analysis &a) {
             for (int32_t r = 0; r < nr;) {  // r rows from the narrow end so far
                 const int32_t at = dir ? r : nr - 1 - r;
                 int32_t k = r;
-                while (k < nr && seg_of[rows[dir ? k : nr - 1 - k]] == seg_of[rows[at]]) ++k;
+                bool mixed = false;
+                while (k < nr && seg_of[rows[dir ? k : nr - 1 - k]] == seg_of[rows[at]]) {
+                    mixed = mixed || tree[rows[dir ? k : nr - 1 - k]] != tree[rows[dir ? 0 : nr - 1]];
+                    ++k;
+                }
                 r = k;
-                if (r > 64 || sol_lds_bytes(nr, d[5], places, r) > opt.sol_dense_lds) break;
+                if (mixed || r > 64 || sol_lds_bytes(nr, d[5], places, r) > opt.sol_dense_lds) break;
                 ++levels;
                 const int64_t gain = 9 * ((int64_t)levels - 2) - r;
                 if (gain > best) {

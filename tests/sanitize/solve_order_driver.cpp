@@ -6,10 +6,12 @@
 // early=<entries of x that a U tile may write before the L tile that reads the same entry of b has
 // started: that L task is not among those the U task waits for, directly or not>
 // same=, shifted=, apart=<what one_launch_solve answers for x = b, for x one entry after b and for
-// x behind b>.
+// x behind b>
+// dense=<dense ranges> mixed=<those with rows of several elimination trees>.
 #include <cstdio>
 #include <cstdint>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "../../paper_2401_13926_amd/csrc/analysis.hpp"
@@ -53,6 +55,28 @@ int64_t early_writes(const kkt::Analysis &a) {
     return early;
 }
 
+// Dense ranges (first) and those that mix trees (second).
+std::pair<int64_t, int64_t> dense_ranges(const kkt::Analysis &a) {
+    std::vector<int32_t> tree(a.n);
+    for (int64_t m = a.n - 1; m >= 0; --m) {
+        const int64_t p = a.fp[m] + a.fdiag[m] + 1;
+        tree[m] = p < a.fp[m + 1] ? tree.at(a.fi[p]) : (int32_t)m;
+    }
+    std::pair<int64_t, int64_t> c{0, 0};
+    for (int64_t k = 0; k < 2 * a.sol.tiles(); ++k) {
+        const int32_t *d = a.sol.desc.data() + kkt::kSolDesc * (k / 2);
+        const int32_t *e = d + 2 + (k & 1) * kkt::kSolSweep;
+        const std::vector<int32_t> &node = k & 1 ? a.sol.node_u : a.sol.node_l;
+        c.first += e[7] > 0;
+        for (int32_t r = 1; r < e[7]; ++r)
+            if (tree[node.at(d[0] + e[6] + r)] != tree[node.at(d[0] + e[6])]) {
+                ++c.second;
+                break;
+            }
+    }
+    return c;
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
@@ -81,10 +105,11 @@ int main(int argc, char **argv) {
     std::string msg;
     if (kkt::analyze(opt, n, rp.data(), ci.data(), v.data(), a, &msg) != kkt::AN_OK) return 3;
     std::vector<double> b(2 * n + 1);
-    std::printf("tiles=%lld offdiag=%lld early=%lld same=%d shifted=%d apart=%d\n", (long long)a.sol.tiles(),
+    std::printf("tiles=%lld offdiag=%lld early=%lld same=%d shifted=%d apart=%d dense=%lld mixed=%lld\n", (long long)a.sol.tiles(),
                 (long long)a.offdiag_pivots, (long long)early_writes(a),
                 (int)kkt::one_launch_solve(a, b.data(), b.data()),
                 (int)kkt::one_launch_solve(a, b.data(), b.data() + 1),
-                (int)kkt::one_launch_solve(a, b.data(), b.data() + n));
+                (int)kkt::one_launch_solve(a, b.data(), b.data() + n), (long long)dense_ranges(a).first,
+                (long long)dense_ranges(a).second);
     return 0;
 }

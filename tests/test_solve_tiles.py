@@ -45,7 +45,36 @@ def cycles(n, k=7, c=2.0):
     return np.arange(n + 1, dtype=np.int64), (i // k * k + (i % k + 1) % k).astype(np.int64), v
 
 
+def stacked(p, k):
+    """k copies of the system of p side by side."""
+    rp = np.concatenate([[0]] + [p.rowptr[1:] + c * p.rowptr[-1] for c in range(k)]).astype(np.int64)
+    return rp, np.concatenate([p.colidx + c * p.N for c in range(k)]), np.tile(p.system(1)[0], k)
+
+
+def paths(n, k):
+    """n / k paths of k vertices."""
+    i = np.arange(n - 1)
+    i = i[(i + 1) % k != 0]
+    rows, cols = np.concatenate([np.arange(n), i, i + 1]), np.concatenate([np.arange(n), i + 1, i])
+    vals = np.concatenate([np.full(n, 4.0), np.full(2 * len(i), -1.0)])
+    order = np.lexsort((cols, rows))
+    return np.concatenate([[0], np.cumsum(np.bincount(rows, minlength=n))]).astype(np.int64), cols[order], vals[order]
+
+
+# systems side by side: (system, size of one)
+FORESTS = {
+    "kkt-100": lambda: (stacked(ks.small_kkt(60, 40, 7), 100), 100),
+    "kkt-1000": lambda: (stacked(ks.small_kkt(600, 400, 7), 6), 1000),
+    "path-500": lambda: (paths(10_000, 500), 500),
+    "path-50": lambda: (paths(10_000, 50), 50),
+}
+
+
 def system(case, n=7_000):
+    if case in FORESTS:
+        return FORESTS[case]()[0]
+    if case == "path":
+        return paths(n, n)
     if case == "cycles":
         return cycles(n // 7 * 7)
     if case == "pairs":
@@ -54,9 +83,7 @@ def system(case, n=7_000):
     return p.rowptr, p.colidx, p.system(1)[0]
 
 
-@pytest.mark.parametrize("sol", sorted(SOL_LDS))
-@pytest.mark.parametrize("case", ["cycles", "kkt"])
-def test_one_launch_only_where_b_is_read_first(order_driver, tmp_path, case, sol):
+def look(order_driver, tmp_path, case, sol):
     rp, ci, v = system(case)
     f = tmp_path / "in.bin"
     with open(f, "wb") as fh:
@@ -65,10 +92,24 @@ def test_one_launch_only_where_b_is_read_first(order_driver, tmp_path, case, sol
         fh.write(rp.astype(np.int64).tobytes() + ci.astype(np.int32).tobytes() + v.tobytes())
     r = subprocess.run([str(order_driver), str(f)], capture_output=True, text=True, env=dict(os.environ), timeout=600)
     assert r.returncode == 0, r.stderr[-4000:]
-    out = {k: int(x) for k, x in (kv.split("=") for kv in r.stdout.split())}
+    return {k: int(x) for k, x in (kv.split("=") for kv in r.stdout.split())}
+
+
+@pytest.mark.parametrize("sol", sorted(SOL_LDS))
+@pytest.mark.parametrize("case", ["cycles", "kkt"])
+def test_one_launch_only_where_b_is_read_first(order_driver, tmp_path, case, sol):
+    out = look(order_driver, tmp_path, case, sol)
     assert out["tiles"] > 1
     assert (out["offdiag"] > 0) == (case == "cycles") and (out["early"] > 0) == (case == "cycles"), out
     assert out["same"] == (out["early"] == 0) and out["shifted"] == 0 and out["apart"] == 1, out
+
+
+@pytest.mark.parametrize("sol", sorted(SOL_LDS))
+@pytest.mark.parametrize("case", ["kkt", "path"] + sorted(FORESTS))
+def test_dense_ranges_keep_to_one_tree(order_driver, tmp_path, case, sol):
+    out = look(order_driver, tmp_path, case, sol)
+    assert out["tiles"] > 0 and out["mixed"] == 0, out
+    assert case in FORESTS or out["dense"] > 0, out
 
 
 @pytest.mark.gpu
@@ -108,12 +149,9 @@ def test_right_hand_side_with_the_unwritten_mark(where, precision):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     print("sentinel in b", where, precision, flush=True)
-    # 30 systems side by side: a NaN in one leaves the others finite
-    p = ks.small_kkt(60, 40, 7)
-    k = 30
-    rp = np.concatenate([[0]] + [p.rowptr[1:] + c * p.rowptr[-1] for c in range(k)]).astype(np.int64)
-    ci = np.concatenate([p.colidx + c * p.N for c in range(k)])
-    v = np.tile(p.system(1)[0], k)
+    # a NaN in one of 30 systems side by side leaves the others finite
+    p, k = ks.small_kkt(60, 40, 7), 30
+    rp, ci, v = stacked(p, k)
     s = P.Solver(rp, ci, v, precision=precision).bind("cuda")
     s.refactor(torch.as_tensor(v, device="cuda"))
     b0 = np.random.default_rng(3).standard_normal(k * p.N)
@@ -141,3 +179,26 @@ def test_right_hand_side_with_the_unwritten_mark(where, precision):
     assert e.value.args and "non-finite" in str(e.value)
     x, info = s.solve(on_gpu(b0))
     assert info["converged"] == 1 and bool(torch.isfinite(x).all())
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("precision", [P.PREC_FP64, P.PREC_MIXED])
+@pytest.mark.parametrize("case", sorted(FORESTS))
+def test_infinity_stays_in_its_system(case, precision):
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    print("infinity in b", case, precision, flush=True)
+    (rp, ci, v), size = FORESTS[case]()
+    n = len(rp) - 1
+    s = P.Solver(rp, ci, v, precision=precision).bind("cuda")
+    s.refactor(torch.as_tensor(v, device="cuda"))
+    rng = np.random.default_rng(5)
+    b0 = rng.standard_normal(n)
+    want = s.direct_solve(torch.as_tensor(b0, device="cuda")).cpu().numpy()
+    for i in rng.integers(0, n, 12):
+        b = b0.copy()
+        b[i] = np.inf
+        got = s.direct_solve(torch.as_tensor(b, device="cuda")).cpu().numpy()
+        other = np.arange(n) // size != i // size
+        assert np.array_equal(got[other], want[other])
