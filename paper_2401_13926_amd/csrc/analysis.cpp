@@ -1522,7 +1522,8 @@ bool build_solve_tiles(const AnalysisOptions &opt, Analysis &a) {
 }
 
 // The refactorization's tile schedule (RefTiles).  Returns false, leaving a.ref empty, when a single
-// node does not fit a tile.
+// node does not fit a tile or a list outgrows the descriptors' 32-bit positions (the updates may,
+// although the factor's entries do not).
 bool build_ref_tiles(const AnalysisOptions &opt, Analysis &a) {
     const int64_t n = a.n;
     RefTiles &t = a.ref;
@@ -1711,7 +1712,9 @@ bool build_ref_tiles(const AnalysisOptions &opt, Analysis &a) {
         t.desc.insert(t.desc.end(), d, d + kRefDesc);
         t.lds = std::max(t.lds, ref_lds_bytes(ne, d[13], d[14], d[7], d[5], d[9]));
         for (size_t e = ne; e < fpos.size(); ++e) ext_slot[fpos[e]] = -1;
-        if (t.lds > opt.ref_lds || ne + d[13] >= 8192 || d[7] > 0xFFFF || d[5] > 0xFFFF) {
+        const size_t longest = std::max(std::max(t.upd.size(), t.item.size() / 2), std::max(t.ext.size(), t.src.size()));
+        if (t.lds > opt.ref_lds || ne + d[13] >= 8192 || d[7] > 0xFFFF || d[5] > 0xFFFF ||
+            longest > (size_t)opt.list_max) {
             t = RefTiles();
             return false;
         }

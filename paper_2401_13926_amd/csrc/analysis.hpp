@@ -34,6 +34,7 @@ struct AnalysisOptions {
     int64_t ref_lds = 0;         // LDS bytes of a refactorization tile (0: no tiles)
     int64_t sol_lds = 20480;     // LDS bytes a solve tile is formed for (with refactorization tiles)
     int64_t sol_dense_lds = 32768;  // LDS bytes of a solve tile with its dense range at most
+    int64_t list_max = INT32_MAX;   // entries of a list of the refactorization tiles at most
 };
 
 // Flags in TriSchedule::seg_lg: the segment's rows fit one wavefront; the segment is a

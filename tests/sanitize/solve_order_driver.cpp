@@ -1,13 +1,15 @@
 // Host-only look at the order in which the solve tiles' one launch may read b and write x, built with
 // AddressSanitizer and UndefinedBehaviorSanitizer by tests/test_solve_tiles.py: reads a CSR system
 // from a binary file (int64 n, int64 nnz, double tau, int32 ordering, int32 ref_lds, int64 sol_lds,
-// int64 sol_dense_lds; then rowptr, colidx, values), runs the analysis and prints
-// tiles=<solve tiles> offdiag=<pivots off the diagonal>
+// int64 sol_dense_lds; then rowptr, colidx, values), runs the analysis (one argument more:
+// its list_max) and prints
+// tiles=<solve tiles> longest=<entries of the refactorization tiles' longest list> offdiag=<pivots off the diagonal>
 // early=<entries of x that a U tile may write before the L tile that reads the same entry of b has
 // started: that L task is not among those the U task waits for, directly or not>
 // same=, shifted=, apart=<what one_launch_solve answers for x = b, for x one entry after b and for
 // x behind b>
 // dense=<dense ranges> mixed=<those with rows of several elimination trees>.
+#include <algorithm>
 #include <cstdio>
 #include <cstdint>
 #include <string>
@@ -80,7 +82,7 @@ std::pair<int64_t, int64_t> dense_ranges(const kkt::Analysis &a) {
 }  // namespace
 
 int main(int argc, char **argv) {
-    if (argc != 2) return 2;
+    if (argc != 2 && argc != 3) return 2;
     std::FILE *f = std::fopen(argv[1], "rb");
     if (!f) return 2;
     int64_t n = 0, nnz = 0, lds[2] = {};
@@ -101,11 +103,14 @@ int main(int argc, char **argv) {
     opt.ref_lds = opt2[1];
     opt.sol_lds = lds[0];
     opt.sol_dense_lds = lds[1];
+    if (argc == 3) opt.list_max = std::stoll(argv[2]);
     kkt::Analysis a;
     std::string msg;
     if (kkt::analyze(opt, n, rp.data(), ci.data(), v.data(), a, &msg) != kkt::AN_OK) return 3;
     std::vector<double> b(2 * n + 1);
-    std::printf("tiles=%lld offdiag=%lld early=%lld same=%d shifted=%d apart=%d dense=%lld mixed=%lld\n", (long long)a.sol.tiles(),
+    const size_t longest =
+        std::max(std::max(a.ref.upd.size(), a.ref.item.size() / 2), std::max(a.ref.ext.size(), a.ref.src.size()));
+    std::printf("tiles=%lld longest=%lld offdiag=%lld early=%lld same=%d shifted=%d apart=%d dense=%lld mixed=%lld\n", (long long)a.sol.tiles(), (long long)longest,
                 (long long)a.offdiag_pivots, (long long)early_writes(a),
                 (int)kkt::one_launch_solve(a, b.data(), b.data()),
                 (int)kkt::one_launch_solve(a, b.data(), b.data() + 1),

@@ -83,14 +83,14 @@ def system(case, n=7_000):
     return p.rowptr, p.colidx, p.system(1)[0]
 
 
-def look(order_driver, tmp_path, case, sol):
+def look(order_driver, tmp_path, case, sol, *more):
     rp, ci, v = system(case)
     f = tmp_path / "in.bin"
     with open(f, "wb") as fh:
         fh.write(np.array([len(rp) - 1, len(ci)], np.int64).tobytes() + np.array([1e-10], np.float64).tobytes())
         fh.write(np.array([0, REF_LDS], np.int32).tobytes() + np.array(SOL_LDS[sol], np.int64).tobytes())
         fh.write(rp.astype(np.int64).tobytes() + ci.astype(np.int32).tobytes() + v.tobytes())
-    r = subprocess.run([str(order_driver), str(f)], capture_output=True, text=True, env=dict(os.environ), timeout=600)
+    r = subprocess.run([str(order_driver), str(f), *map(str, more)], capture_output=True, text=True, env=dict(os.environ), timeout=600)
     assert r.returncode == 0, r.stderr[-4000:]
     return {k: int(x) for k, x in (kv.split("=") for kv in r.stdout.split())}
 
@@ -110,6 +110,13 @@ def test_dense_ranges_keep_to_one_tree(order_driver, tmp_path, case, sol):
     out = look(order_driver, tmp_path, case, sol)
     assert out["tiles"] > 0 and out["mixed"] == 0, out
     assert case in FORESTS or out["dense"] > 0, out
+
+
+def test_no_tiles_beyond_the_positions(order_driver, tmp_path):
+    """Lists longer than a position can name (2^31 in earnest): no tiles, as for a node that does not fit."""
+    longest = look(order_driver, tmp_path, "kkt", "small")["longest"]
+    assert look(order_driver, tmp_path, "kkt", "small", longest)["tiles"] > 0
+    assert look(order_driver, tmp_path, "kkt", "small", longest - 1)["tiles"] == 0
 
 
 @pytest.mark.gpu
