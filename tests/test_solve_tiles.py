@@ -119,6 +119,19 @@ def test_no_tiles_beyond_the_positions(order_driver, tmp_path):
     assert look(order_driver, tmp_path, "kkt", "small", longest - 1)["tiles"] == 0
 
 
+def test_analysis_of_a_long_chain():
+    """An elimination tree that is one path (thousands of layers of tiles): the tiles cost a part of what
+    the analysis costs without them, not a pass over the tree per layer."""
+    rp, ci, v = paths(600_000, 600_000)
+
+    def seconds(**opts):
+        return min(P.Solver(rp, ci, v, **opts).info()["analysis_seconds"] for _ in range(2))
+
+    with_tiles, without = seconds(), seconds(tile_lds_kib=32)
+    # 1.1 times as long; 4.4 times with passes over all nodes for each layer
+    assert with_tiles < 2.5 * without, (with_tiles, without)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("precision", [P.PREC_FP64, P.PREC_MIXED])
 @pytest.mark.parametrize("case", ["cycles", "pairs", "kkt"])
