@@ -270,9 +270,10 @@ template <typename T> __global__ void k_prep_tiles(Control *c, int values, int64
 // ||K||_inf (each row's absolute values summed in order, one atomic maximum per block) and the
 // finiteness of every value.  Blocks of 256 rows: the source of every entry goes to LDS, then
 // consecutive lanes copy consecutive entries, so a row's line is touched by one load instead of
-// one per entry; rows are summed from LDS.  Blocks of rows with more than kIngestLds entries go
-// one row per thread.
+// one per entry; rows are summed from LDS.  Rows with more than kIngestLds entries together take
+// several passes.
 constexpr int kIngestLds = 2048;
+__device__ __forceinline__ int clamped(int64_t p, int limit) { return p < 0 ? 0 : p < limit ? (int)p : limit; }
 __global__ void __launch_bounds__(256) k_ingest_rows(int64_t n, const int64_t *__restrict__ ostart,
                                                      const int64_t *__restrict__ krp, const double *__restrict__ vals,
                                                      double *__restrict__ kval, Control *c) {
@@ -283,12 +284,14 @@ __global__ void __launch_bounds__(256) k_ingest_rows(int64_t n, const int64_t *_
     bool bad = false;
     for (int64_t i0 = (int64_t)blockIdx.x * 256; i0 < n; i0 += stride) {
         const int64_t ie = i0 + 256 < n ? i0 + 256 : n, k = i0 + threadIdx.x;
-        const int64_t e0 = krp[i0], cnt = krp[ie] - e0;
-        const int64_t s = k < ie ? ostart[k] : 0, p0 = k < ie ? krp[k] : 0;
-        const int len = k < ie ? (int)(krp[k + 1] - p0) : 0;
+        const int64_t s = k < ie ? ostart[k] : 0, p0 = k < ie ? krp[k] : 0, p1 = k < ie ? krp[k + 1] : 0;
+        const int64_t e1 = krp[ie];
         double sum = 0.0;
-        if (cnt <= kIngestLds) {
-            for (int t = 0; t < len; ++t) src[p0 - e0 + t] = (int32_t)(s + t);
+        for (int64_t e0 = krp[i0]; e0 < e1; e0 += kIngestLds) {
+            const int64_t cnt = e1 - e0;
+            const int q0 = clamped(p0 - e0, kIngestLds), q1 = clamped(p1 - e0, kIngestLds);
+            const int32_t from = (int32_t)(s - (p0 - e0));
+            for (int q = q0; q < q1; ++q) src[q] = from + q;
             __syncthreads();
             constexpr int kPer = kIngestLds / 256;
             double v[kPer];
@@ -304,15 +307,8 @@ __global__ void __launch_bounds__(256) k_ingest_rows(int64_t n, const int64_t *_
                 }
             }
             __syncthreads();
-            for (int t = 0; t < len; ++t) sum += val[p0 - e0 + t];
+            for (int q = q0; q < q1; ++q) sum += val[q];
             __syncthreads();
-        } else {
-            for (int t = 0; t < len; ++t) {
-                const double v = vals[s + t];
-                kval[p0 + t] = v;
-                sum += fabs(v);
-                bad |= !isfinite(v);
-            }
         }
         m = fmax(m, sum);
     }
@@ -373,13 +369,10 @@ __global__ void k_vscatter(int64_t n, const int32_t *__restrict__ perm, const do
     for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < n; k += stride) out[perm[k]] = in[k];
 }
 
-// CSR row loops issue a row's loads kRowBatch at a time (index and value loads together, then
-// the gathers), so a short row costs one round of dependent loads instead of one per entry;
-// the terms are still combined one by one in ascending position.
-constexpr int kRowBatch = 8;
+constexpr int kRowBatch = 8;  // loads of a row in flight in k_rownorm
 
 // ||K||_inf of the values already in the workspace's copy of K (after a re-pivot, which
-// uploads them from the host).
+// uploads them from the host), each row's absolute values summed in ascending position.
 __global__ void k_rownorm(int64_t n, const int64_t *__restrict__ rp, const double *__restrict__ kval,
                           Control *c) {
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
@@ -2033,72 +2026,66 @@ __device__ __forceinline__ double *partbuf(const KrylovArgs &a, int which) {
     return a.part + (int64_t)which * kStreamGridMax * kPartCols;
 }
 
-// Products of a block's next kStreamBlock rows [i0, i0 + 256) with x, in LDS.  One thread per row read
-// its entries at a stride of the row length (42 bytes here), 24 loads a row whose lines eight of
-// them shared; with the rows' contiguous entries read by the whole block, one coalesced load of
-// a value and of an index and one gather per entry remain.  Every row still adds its rounded
-// products in ascending position.  Blocks of rows with more than kRowLds entries go without.
+// The pair hi, lo minus the pair ph, pl (below).
+__device__ __forceinline__ void dd_accumulate(double &hi, double &lo, double ph, double pl);
+
+// Row sums of K x for a block's next kStreamBlock rows [i0, i0 + 256): every row adds its rounded
+// products to hi in ascending position (kDD: subtracts the exact ones from the pair hi, lo).  The
+// block first puts the products of up to kRowLds consecutive entries into LDS (kDD: their
+// rounding errors behind them), then each thread adds those of its row; rows of more entries
+// together take several passes.  One thread per row read its entries at a stride of the row
+// length (42 bytes on KKT patterns), 24 loads a row whose lines eight of them shared; read by the
+// whole block, one coalesced load of a value and of an index and one gather per entry remain.
+// A residual of 480,000 rows of 16 entries takes 30 us (2,048 entries in one pass only, and beyond them
+// every row from memory, entry by entry: 200 us; in batches of 8 loads: 53 us).
+// kPerm: x is in the caller's order, entry perm[c] belongs to column c.  between() runs once, when the
+// first products are in LDS (loads that the sums need, or that can complete beside them).
 constexpr int kRowLds = 2048;
-struct RowSpan {
-    int64_t e0, p0, p1;  // first entry of the block's rows; this thread's row's entries
-    const double *prod;  // the products from e0 on (kDD: then their rounding errors), or null
-};
-// kPerm: x is in the caller's order, entry perm[c] belongs to column c.
-template <bool kDD, bool kPerm = false>
-__device__ __forceinline__ RowSpan block_products(const KrylovArgs &a, const double *x, int64_t i0, int64_t r1,
-                                                  double *lds, const int32_t *perm = nullptr) {
+template <bool kDD, bool kPerm = false, typename Between>
+__device__ __forceinline__ void row_sums(const KrylovArgs &a, const double *x, int64_t i0, int64_t r1, double *lds,
+                                         double &hi, double &lo, Between between, const int32_t *perm = nullptr) {
     const int64_t ie = i0 + kStreamBlock < r1 ? i0 + kStreamBlock : r1;
     const int64_t i = i0 + threadIdx.x;
-    RowSpan sp;
-    sp.e0 = a.rp[i0];
-    sp.p0 = i < ie ? a.rp[i] : 0;
-    sp.p1 = i < ie ? a.rp[i + 1] : 0;
-    const int64_t cnt = a.rp[ie] - sp.e0;
-    sp.prod = cnt <= kRowLds ? lds : nullptr;
-    if (!sp.prod) return sp;
-    __syncthreads();  // the sums of the rows before are done
-    constexpr int kPer = kRowLds / kStreamBlock;
-    int c[kPer];
-    double v[kPer], xv[kPer];
+    int64_t e0 = a.rp[i0];
+    const int64_t p0 = i < ie ? a.rp[i] : 0, p1 = i < ie ? a.rp[i + 1] : 0, e1 = a.rp[ie];
+    bool first = true;
+    do {
+        const int64_t cnt = e1 - e0;
+        __syncthreads();  // the sums before are done
+        constexpr int kPer = kRowLds / kStreamBlock;
+        int c[kPer];
+        double v[kPer], xv[kPer];
 #pragma unroll
-    for (int t = 0; t < kPer; ++t) {
-        const int64_t k = threadIdx.x + t * kStreamBlock;
-        c[t] = k < cnt ? a.ci[sp.e0 + k] : 0;
-        v[t] = k < cnt ? a.kval[sp.e0 + k] : 0.0;
-    }
-    if (kPerm) {
-#pragma unroll
-        for (int t = 0; t < kPer; ++t) c[t] = perm[c[t]];  // (0 where there is no entry: in range)
-    }
-#pragma unroll
-    for (int t = 0; t < kPer; ++t) xv[t] = threadIdx.x + t * kStreamBlock < cnt ? x[c[t]] : 0.0;
-#pragma unroll
-    for (int t = 0; t < kPer; ++t) {
-        const int64_t k = threadIdx.x + t * kStreamBlock;
-        if (k < cnt) {
-            const double ph = v[t] * xv[t];
-            lds[k] = ph;
-            if (kDD) lds[kRowLds + k] = fma(v[t], xv[t], -ph);
+        for (int t = 0; t < kPer; ++t) {
+            const int64_t k = threadIdx.x + t * kStreamBlock;
+            c[t] = k < cnt ? a.ci[e0 + k] : 0;
+            v[t] = k < cnt ? a.kval[e0 + k] : 0.0;
         }
-    }
-    __syncthreads();
-    return sp;
-}
-
-// Sum of this thread's row's products in ascending position.
-__device__ __forceinline__ double span_sum(const KrylovArgs &a, const double *x, const RowSpan &sp,
-                                           const int32_t *perm = nullptr) {
-    double s = 0.0;
-    if (sp.prod) {
-        for (int64_t p = sp.p0; p < sp.p1; ++p) s = s + sp.prod[p - sp.e0];
-    } else {
-        for (int64_t p = sp.p0; p < sp.p1; ++p) {
-            const int32_t c = perm ? perm[a.ci[p]] : a.ci[p];
-            const double prod = a.kval[p] * x[c];
-            s = s + prod;
+        if (kPerm) {
+#pragma unroll
+            for (int t = 0; t < kPer; ++t) c[t] = perm[c[t]];  // (0 where there is no entry: in range)
         }
-    }
-    return s;
+#pragma unroll
+        for (int t = 0; t < kPer; ++t) xv[t] = threadIdx.x + t * kStreamBlock < cnt ? x[c[t]] : 0.0;
+#pragma unroll
+        for (int t = 0; t < kPer; ++t) {
+            const int64_t k = threadIdx.x + t * kStreamBlock;
+            if (k < cnt) {
+                const double ph = v[t] * xv[t];
+                lds[k] = ph;
+                if (kDD) lds[kRowLds + k] = fma(v[t], xv[t], -ph);
+            }
+        }
+        __syncthreads();
+        if (first) between();
+        first = false;
+        const int64_t q0 = p0 > e0 ? p0 : e0, q1 = p1 < e0 + kRowLds ? p1 : e0 + kRowLds;
+        for (int64_t p = q0; p < q1; ++p) {
+            if (kDD) dd_accumulate(hi, lo, lds[p - e0], lds[kRowLds + p - e0]);
+            else hi = hi + lds[p - e0];
+        }
+        e0 += kRowLds;
+    } while (e0 < e1);
 }
 
 // Columns of V whose dot products are accumulated while a row is in registers (the first ones;
@@ -2143,13 +2130,13 @@ __global__ void __launch_bounds__(kStreamBlock) k_spmv_dots(KrylovArgs a, int j)
     const double *z = a.Z + (int64_t)j * a.n;
     double dot[kFusedDots] = {}, ss = 0.0;
     for (int64_t i0 = r0; i0 < r1; i0 += kStreamBlock) {
-        const RowSpan sp = block_products<false>(a, z, i0, r1, lds);
         const int64_t i = i0 + threadIdx.x;
-        if (i < r1) {
-            double v[kFusedDots];
+        double v[kFusedDots], w = 0.0, lo = 0.0;
+        row_sums<false>(a, z, i0, r1, lds, w, lo, [&] {
 #pragma unroll
-            for (int t = 0; t < kFusedDots; ++t) v[t] = t <= j ? a.V[(int64_t)t * a.n + i] : 0.0;
-            const double w = span_sum(a, z, sp);
+            for (int t = 0; t < kFusedDots; ++t) v[t] = t <= j && i < r1 ? a.V[(int64_t)t * a.n + i] : 0.0;
+        });
+        if (i < r1) {
             a.w[i] = w;
 #pragma unroll
             for (int t = 0; t < kFusedDots; ++t) dot[t] += v[t] * w;
@@ -2346,8 +2333,9 @@ __global__ void __launch_bounds__(kStreamBlock) k_dcgs2_dots(KrylovArgs a, int j
     if (matvec) {
         const double *z = a.Z + (int64_t)j * a.n;
         for (int64_t i0 = r0; i0 < r1; i0 += kStreamBlock) {
-            const RowSpan sp = block_products<false>(a, z, i0, r1, lds);
-            if (i0 + threadIdx.x < r1) a.w[i0 + threadIdx.x] = span_sum(a, z, sp);
+            double w = 0.0, lo = 0.0;
+            row_sums<false>(a, z, i0, r1, lds, w, lo, [] {});
+            if (i0 + threadIdx.x < r1) a.w[i0 + threadIdx.x] = w;
         }
     }
     __syncthreads();
@@ -2485,29 +2473,6 @@ __device__ __forceinline__ void dd_accumulate(double &hi, double &lo, double ph,
     hi = zh;
 }
 
-// Row i of rho: b_i minus the row's products (from LDS where block_products put them).
-template <bool kDD>
-__device__ __forceinline__ double resid_row(const KrylovArgs &a, const double *x, double bi, const RowSpan &sp,
-                                            const int32_t *perm = nullptr) {
-    if (kDD) {
-        double hi = bi, lo = 0.0;
-        for (int64_t p = sp.p0; p < sp.p1; ++p) {
-            double ph, pl;
-            if (sp.prod) {
-                ph = sp.prod[p - sp.e0];
-                pl = sp.prod[kRowLds + p - sp.e0];
-            } else {
-                const double v = a.kval[p], xv = x[perm ? perm[a.ci[p]] : a.ci[p]];
-                ph = v * xv;
-                pl = fma(v, xv, -ph);
-            }
-            dd_accumulate(hi, lo, ph, pl);
-        }
-        return hi;
-    }
-    return bi - span_sum(a, x, sp, perm);
-}
-
 // The control block starts with the fields of ControlSummary, in the same layout.
 static_assert(sizeof(ControlSummary) % 8 == 0 && sizeof(ControlSummary) <= sizeof(Control),
               "ControlSummary is copied as 64-bit words from the start of Control");
@@ -2553,11 +2518,16 @@ __global__ void __launch_bounds__(kStreamBlock) k_resid(KrylovArgs a, const doub
     double sr = 0.0, sx = 0.0, sb = 0.0, mr = 0.0, mx = 0.0;
     int badb = 0;
     for (int64_t i0 = r0; i0 < r1; i0 += kStreamBlock) {
-        const RowSpan sp = block_products<kDD>(a, x, i0, r1, lds);
         const int64_t i = i0 + threadIdx.x;
+        double bi, xi, hi = 0.0, lo = 0.0;
+        row_sums<kDD>(a, x, i0, r1, lds, hi, lo, [&] {
+            const int64_t q = i < r1 ? i : i0;
+            bi = b[q];
+            xi = x[q];
+            if (kDD) hi = bi;
+        });
         if (i < r1) {
-            const double bi = b[i], xi = x[i];
-            const double ri = resid_row<kDD>(a, x, bi, sp);
+            const double ri = kDD ? hi : bi - hi;
             r[i] = ri;
             sr += ri * ri;
             sx += xi * xi;
@@ -2639,8 +2609,9 @@ __global__ void __launch_bounds__(kStreamBlock) k_resid_user(KrylovArgs a, const
         const int64_t i = i0 + threadIdx.x;
         const int32_t p = i < r1 ? perm[i] : 0;
         const double bp = i < r1 ? b[p] : 0.0;
-        const RowSpan sp = block_products<kDD, kDirect>(a, x, i0, r1, lds, perm);
-        if (i < r1) r[p] = resid_row<kDD>(a, x, bp, sp, kDirect ? perm : nullptr);
+        double hi = kDD ? bp : 0.0, lo = 0.0;
+        row_sums<kDD, kDirect>(a, x, i0, r1, lds, hi, lo, [] {}, perm);
+        if (i < r1) r[p] = kDD ? hi : bp - hi;
     }
 }
 
