@@ -295,7 +295,7 @@ kkt_status_t kkt_direct_solve(kkt_handle_t h, const double *dev_b, double *dev_x
 /* kkt_direct_solve for callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): the same kernels and the same
  * result bit for bit, but the intermediate vectors of the two sweeps and their tile counters
- * live in a static device array of the library (32 MiB + 4 KiB per GPU, held until the process
+ * live in a static device array of the library (48 MiB + 4 KiB per GPU, held until the process
  * ends) instead of the handle's workspace.  It calls no allocating routine.  The handle must be
  * bound and refactored (its factors are read from its workspace), n <= 2,097,152 (else
  * KKT_EINVAL, checked before any device call) and the handle's device current (else

@@ -1666,7 +1666,6 @@ template <typename T> struct SolveTileArgs {
     const int *stopflag;      // when non-null, skip if the cycle (or the caller's iteration) has stopped
     unsigned int *work;       // hand-out queues (zeroed before the launch)
     unsigned int *hang;
-    unsigned int first;       // first task of a launch of one sweep
 };
 
 template <typename T> struct Pair;  // two values, loaded together
@@ -1958,29 +1957,23 @@ __device__ __forceinline__ void solve_tile(const SolveTileArgs<T> &a, int t, uns
 // x = U^-1 L^-1 b: tasks 0..n-1 are the L sweep's tiles in order, tasks n..2n-1 the U sweep's from
 // the last to the first.  Tasks are handed out in order to running blocks and wait only for
 // earlier ones, so the earliest unfinished task is always held by a running block that can
-// finish it.  kOneSweep: only the n tasks from a.first on, where the solution goes over the right-hand
-// side (one_launch_solve).  (A variant of its own: with the range as arguments of every launch
-// a solve of 1,000 unknowns took 27.1 instead of 26.6 us.)
-template <typename T, bool kOneSweep>
+// finish it.
+template <typename T>
 __global__ void __launch_bounds__(kSolThreads) __attribute__((amdgpu_waves_per_eu(6))) k_solve_tiles(SolveTileArgs<T> a) {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ unsigned int task_sh;
     if (a.stopflag && *a.stopflag) return;
     unsigned int queue = first_queue();  // thread 0's
     for (;;) {
-        if (threadIdx.x == 0)
-            task_sh = kOneSweep ? a.first + next_task(a.work, (unsigned int)a.ntiles, queue)
-                                : next_task(a.work, 2 * (unsigned int)a.ntiles, queue);
+        if (threadIdx.x == 0) task_sh = next_task(a.work, 2 * (unsigned int)a.ntiles, queue);
         __syncthreads();
         const int w = __builtin_amdgcn_readfirstlane((int)task_sh);
         __syncthreads();
-        if ((int64_t)w >= (kOneSweep ? a.first + a.ntiles : 2 * a.ntiles)) break;
+        if ((int64_t)w >= 2 * a.ntiles) break;
         if (w < (int)a.ntiles) solve_tile<T, false>(a, w, smem);
         else solve_tile<T, true>(a, (int)(2 * a.ntiles - 1) - w, smem);
     }
 }
-
-__global__ void k_reset_work(SolveWork *work) { reset_work(work); }
 
 // Arms the two solve vectors with the sentinel and zeroes the tile counters of the two
 // sweeps (and the wait-failure flag, when given).
@@ -3146,9 +3139,8 @@ hipError_t launch_trsv(kkt_handle_t h, bool lower, const double *rhs64, const T 
     return hipGetLastError();
 }
 
-// Both sweeps (analyses with tiles): x = Q U^-1 L^-1 P b through the exchange vectors y and z (sentinels
-// armed, *work zeroed before).  In one launch where the solution cannot overwrite entries of b
-// that are still to be read, else one launch per sweep.
+// Both sweeps in one launch (analyses with tiles): x = Q U^-1 L^-1 P b through the exchange vectors y
+// and z (sentinels armed, *work zeroed before).  b and x: as may_overwrite demands.
 template <typename T>
 hipError_t launch_solve_tiles(kkt_handle_t h, const double *rhs, T *y, T *z, double *xout, const int *stopflag,
                               hipStream_t s, bool vorder, SolveWork *work, unsigned int *hang) {
@@ -3157,19 +3149,11 @@ hipError_t launch_solve_tiles(kkt_handle_t h, const double *rhs, T *y, T *z, dou
     constexpr bool is64 = sizeof(T) == 8;
     const T *val = (const T *)(is64 ? (void *)d.T64 : (void *)d.T32);
     const T *val_u = val + q.ref_l.size();
-    SolveTileArgs<T> t{q.tiles(), d.st_desc, d.st_cl, d.st_cu, d.st_rl, d.st_ru, d.st_el, d.st_eu, val, val_u,
+    const SolveTileArgs<T> t{q.tiles(), d.st_desc, d.st_cl, d.st_cu, d.st_rl, d.st_ru, d.st_el, d.st_eu, val, val_u,
                              val_u + q.ref_u.size(), rhs, vorder ? d.st_src_k : d.st_src, d.st_posu,
-                             vorder ? d.st_q_k : d.st_q, y, z, xout, stopflag, work->queue, hang, 0u};
-    const int resident = is64 ? h->grid_solve64 : h->grid_solve32;
-    if (!one_launch_solve(h->an, rhs, xout)) {
-        const int grid = (int)std::min<int64_t>(resident, q.tiles());
-        k_solve_tiles<T, true><<<grid, kSolThreads, (size_t)q.lds, s>>>(t);
-        k_reset_work<<<1, 1, 0, s>>>(work);
-        t.first = (unsigned int)q.tiles();
-        k_solve_tiles<T, true><<<grid, kSolThreads, (size_t)q.lds, s>>>(t);
-        return hipGetLastError();
-    }
-    k_solve_tiles<T, false><<<(int)std::min<int64_t>(resident, 2 * q.tiles()), kSolThreads, (size_t)q.lds, s>>>(t);
+                             vorder ? d.st_q_k : d.st_q, y, z, xout, stopflag, work->queue, hang};
+    const int grid = (int)std::min<int64_t>(is64 ? h->grid_solve64 : h->grid_solve32, 2 * q.tiles());
+    k_solve_tiles<T><<<grid, kSolThreads, (size_t)q.lds, s>>>(t);
     return hipGetLastError();
 }
 
@@ -3609,15 +3593,15 @@ kkt_status_t richardson_impl(kkt_handle_t h, const double *gather, double *b, do
 // ---------------------------------------------------------------------------------------
 // Scratch of the allocation-free direct solve (kkt_direct_solve_noalloc): the two tile
 // counters and the wait-failure flag in the first 4 KiB, then the intermediate vectors
-// y = L^-1 P b and z = U^-1 y, kNoAllocMaxRows values of 8 bytes each (FP32 factors use the
-// first half of each).  One copy per GPU, for the life of the process; calls on one GPU
+// y = L^-1 P b and z = U^-1 y and a place for a copy of b, kNoAllocMaxRows values of 8 bytes each
+// (FP32 factors use the first half of y and z).  One copy per GPU, for the life of the process; calls on one GPU
 // share it.
 // ---------------------------------------------------------------------------------------
 
 namespace kkt {
 constexpr int64_t kNoAllocMaxRows = int64_t(1) << 21;  // 2,097,152 rows
 constexpr size_t kNoAllocHead = 4096;
-constexpr size_t kNoAllocBytes = kNoAllocHead + 2 * sizeof(double) * (size_t)kNoAllocMaxRows;  // 32 MiB + 4 KiB
+constexpr size_t kNoAllocBytes = kNoAllocHead + 3 * sizeof(double) * (size_t)kNoAllocMaxRows;  // 48 MiB + 4 KiB
 struct NoAllocHead {
     SolveWork work;
     unsigned int hang;
@@ -3802,6 +3786,11 @@ hipError_t direct_solve_scratch(kkt_handle_t h, const double *b, double *x, unsi
     NoAllocHead *head = (NoAllocHead *)base;
     T *y = (T *)(base + kNoAllocHead);
     T *z = (T *)(base + kNoAllocHead + sizeof(double) * (size_t)kNoAllocMaxRows);
+    if (h->an.sol.tiles() > 0 && may_overwrite(h->an, b, x)) {
+        double *copy = (double *)(base + kNoAllocHead + 2 * sizeof(double) * (size_t)kNoAllocMaxRows);
+        k_copy<<<h->grid_stream, kStreamBlock, 0, s>>>(h->an.n, b, copy);
+        b = copy;
+    }
     k_fill_sentinel<T><<<h->grid_stream, kStreamBlock, 0, s>>>(h->an.n, y, z, &head->work, &head->hang);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -4219,11 +4208,8 @@ kkt_status_t kkt_bind_workspace(kkt_handle_t h, void *dev_ptr, size_t bytes, voi
                                       coop_grid((const void *)k_refactor_tiles<float, true>, h->device, lds));
     }
     if (a.sol.tiles() > 0) {
-        const size_t lds = (size_t)a.sol.lds;
-        h->grid_solve64 = std::min(coop_grid((const void *)k_solve_tiles<double, false>, h->device, lds, kSolThreads),
-                                   coop_grid((const void *)k_solve_tiles<double, true>, h->device, lds, kSolThreads));
-        h->grid_solve32 = std::min(coop_grid((const void *)k_solve_tiles<float, false>, h->device, lds, kSolThreads),
-                                   coop_grid((const void *)k_solve_tiles<float, true>, h->device, lds, kSolThreads));
+        h->grid_solve64 = coop_grid((const void *)k_solve_tiles<double>, h->device, (size_t)a.sol.lds, kSolThreads);
+        h->grid_solve32 = coop_grid((const void *)k_solve_tiles<float>, h->device, (size_t)a.sol.lds, kSolThreads);
         if (h->grid_solve64 <= 0 || h->grid_solve32 <= 0) return fail(h, KKT_EDEVICE, "occupancy query failed");
     }
     h->grid_trsv64 = std::min(std::min(coop_grid((const void *)k_trsv<double, true, true>, h->device, h->tile_lds),
@@ -4403,6 +4389,10 @@ kkt_status_t kkt_direct_solve(kkt_handle_t h, const double *dev_b, double *dev_x
     if (h->device_failed) return fail(h, KKT_EDEVICE, "handle unusable after a device error");
     if (!h->bound || !h->have_factors) return fail(h, KKT_ESTATE, "refactor before solve");
     hipStream_t s = (hipStream_t)stream;
+    if (h->an.sol.tiles() > 0 && may_overwrite(h->an, dev_b, dev_x)) {
+        k_copy<<<h->grid_stream, kStreamBlock, 0, s>>>(h->an.n, dev_b, h->d.bi);
+        dev_b = h->d.bi;
+    }
     if (h->factor_precision == KKT_PREC_MIXED) {
         rearm<float>(h, s);
         KKT_HIP(h, precond<float>(h, dev_b, dev_x, nullptr, s, false));

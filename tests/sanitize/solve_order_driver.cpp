@@ -6,7 +6,7 @@
 // tiles=<solve tiles> longest=<entries of the refactorization tiles' longest list> offdiag=<pivots off the diagonal>
 // early=<entries of x that a U tile may write before the L tile that reads the same entry of b has
 // started: that L task is not among those the U task waits for, directly or not>
-// same=, shifted=, apart=<what one_launch_solve answers for x = b, for x one entry after b and for
+// same=, shifted=, apart=<what may_overwrite answers for x = b, for x one entry after b and for
 // x behind b>
 // dense=<dense ranges> mixed=<those with rows of several elimination trees>.
 #include <algorithm>
@@ -112,9 +112,9 @@ int main(int argc, char **argv) {
         std::max(std::max(a.ref.upd.size(), a.ref.item.size() / 2), std::max(a.ref.ext.size(), a.ref.src.size()));
     std::printf("tiles=%lld longest=%lld offdiag=%lld early=%lld same=%d shifted=%d apart=%d dense=%lld mixed=%lld\n", (long long)a.sol.tiles(), (long long)longest,
                 (long long)a.offdiag_pivots, (long long)early_writes(a),
-                (int)kkt::one_launch_solve(a, b.data(), b.data()),
-                (int)kkt::one_launch_solve(a, b.data(), b.data() + 1),
-                (int)kkt::one_launch_solve(a, b.data(), b.data() + n), (long long)dense_ranges(a).first,
+                (int)kkt::may_overwrite(a, b.data(), b.data()),
+                (int)kkt::may_overwrite(a, b.data(), b.data() + 1),
+                (int)kkt::may_overwrite(a, b.data(), b.data() + n), (long long)dense_ranges(a).first,
                 (long long)dense_ranges(a).second);
     return 0;
 }
