@@ -270,10 +270,10 @@ template <typename T> __global__ void k_prep_tiles(Control *c, int values, int64
 // ||K||_inf (each row's absolute values summed in order, one atomic maximum per block) and the
 // finiteness of every value.  Blocks of 256 rows: the source of every entry goes to LDS, then
 // consecutive lanes copy consecutive entries, so a row's line is touched by one load instead of
-// one per entry; rows are summed from LDS.  Rows with more than kIngestLds entries together take
-// several passes.
+// one per entry; rows are summed from LDS.  Blocks of rows with more than kIngestLds entries go
+// one row per thread, 8 loads in flight (passes through LDS for them cost the others: 78 -> 89 us at
+// 2M unknowns).
 constexpr int kIngestLds = 2048;
-__device__ __forceinline__ int clamped(int64_t p, int limit) { return p < 0 ? 0 : p < limit ? (int)p : limit; }
 __global__ void __launch_bounds__(256) k_ingest_rows(int64_t n, const int64_t *__restrict__ ostart,
                                                      const int64_t *__restrict__ krp, const double *__restrict__ vals,
                                                      double *__restrict__ kval, Control *c) {
@@ -284,14 +284,12 @@ __global__ void __launch_bounds__(256) k_ingest_rows(int64_t n, const int64_t *_
     bool bad = false;
     for (int64_t i0 = (int64_t)blockIdx.x * 256; i0 < n; i0 += stride) {
         const int64_t ie = i0 + 256 < n ? i0 + 256 : n, k = i0 + threadIdx.x;
-        const int64_t s = k < ie ? ostart[k] : 0, p0 = k < ie ? krp[k] : 0, p1 = k < ie ? krp[k + 1] : 0;
-        const int64_t e1 = krp[ie];
+        const int64_t e0 = krp[i0], cnt = krp[ie] - e0;
+        const int64_t s = k < ie ? ostart[k] : 0, p0 = k < ie ? krp[k] : 0;
+        const int len = k < ie ? (int)(krp[k + 1] - p0) : 0;
         double sum = 0.0;
-        for (int64_t e0 = krp[i0]; e0 < e1; e0 += kIngestLds) {
-            const int64_t cnt = e1 - e0;
-            const int q0 = clamped(p0 - e0, kIngestLds), q1 = clamped(p1 - e0, kIngestLds);
-            const int32_t from = (int32_t)(s - (p0 - e0));
-            for (int q = q0; q < q1; ++q) src[q] = from + q;
+        if (cnt <= kIngestLds) {
+            for (int t = 0; t < len; ++t) src[p0 - e0 + t] = (int32_t)(s + t);
             __syncthreads();
             constexpr int kPer = kIngestLds / 256;
             double v[kPer];
@@ -307,8 +305,21 @@ __global__ void __launch_bounds__(256) k_ingest_rows(int64_t n, const int64_t *_
                 }
             }
             __syncthreads();
-            for (int q = q0; q < q1; ++q) sum += val[q];
+            for (int t = 0; t < len; ++t) sum += val[p0 - e0 + t];
             __syncthreads();
+        } else {
+            for (int t0 = 0; t0 < len; t0 += 8) {
+                double v[8];
+#pragma unroll
+                for (int t = 0; t < 8; ++t) v[t] = t0 + t < len ? vals[s + t0 + t] : 0.0;
+#pragma unroll
+                for (int t = 0; t < 8; ++t)
+                    if (t0 + t < len) {
+                        kval[p0 + t0 + t] = v[t];
+                        sum += fabs(v[t]);
+                        bad |= !isfinite(v[t]);
+                    }
+            }
         }
         m = fmax(m, sum);
     }
@@ -2039,10 +2050,8 @@ __device__ __forceinline__ void row_sums(const KrylovArgs &a, const double *x, i
                                          double &hi, double &lo, Between between, const int32_t *perm = nullptr) {
     const int64_t ie = i0 + kStreamBlock < r1 ? i0 + kStreamBlock : r1;
     const int64_t i = i0 + threadIdx.x;
-    int64_t e0 = a.rp[i0];
     const int64_t p0 = i < ie ? a.rp[i] : 0, p1 = i < ie ? a.rp[i + 1] : 0, e1 = a.rp[ie];
-    bool first = true;
-    do {
+    auto stage = [&](int64_t e0) {
         const int64_t cnt = e1 - e0;
         __syncthreads();  // the sums before are done
         constexpr int kPer = kRowLds / kStreamBlock;
@@ -2070,15 +2079,26 @@ __device__ __forceinline__ void row_sums(const KrylovArgs &a, const double *x, i
             }
         }
         __syncthreads();
-        if (first) between();
-        first = false;
-        const int64_t q0 = p0 > e0 ? p0 : e0, q1 = p1 < e0 + kRowLds ? p1 : e0 + kRowLds;
+    };
+    auto sum = [&](int64_t e0, int64_t q0, int64_t q1) {
         for (int64_t p = q0; p < q1; ++p) {
             if (kDD) dd_accumulate(hi, lo, lds[p - e0], lds[kRowLds + p - e0]);
             else hi = hi + lds[p - e0];
         }
+    };
+    int64_t e0 = a.rp[i0];
+    stage(e0);
+    between();
+    if (e1 <= e0 + kRowLds) {
+        sum(e0, p0, p1);
+        return;
+    }
+    for (;;) {
+        sum(e0, p0 > e0 ? p0 : e0, p1 < e0 + kRowLds ? p1 : e0 + kRowLds);
         e0 += kRowLds;
-    } while (e0 < e1);
+        if (e0 >= e1) return;
+        stage(e0);
+    }
 }
 
 // Columns of V whose dot products are accumulated while a row is in registers (the first ones;
