@@ -44,6 +44,15 @@ __device__ __forceinline__ void reset_work(SolveWork *w) {
     for (int q = 0; q < kWorkQueues; ++q) w->queue[q * 64] = 0;
 }
 
+// ||w - V h||, h = V^T w, from ww = ||w||^2 and hh = ||h||^2 (V's columns are orthonormal), where w has
+// been through one Gram-Schmidt pass: h is then rounding, about 1e-16 of the vector before that
+// pass, so nothing cancels unless w is that small too, and there the breakdown test (the norm
+// against 1e-14 of it) ends the cycle.  A NaN stays one.
+__device__ __forceinline__ double second_pass_norm(double ww, double hh) {
+    const double d2 = ww - hh;
+    return d2 < 0.0 ? 0.0 : sqrt(d2);
+}
+
 // Scalars shared between kernels of one refactor/solve (device memory).
 struct Control {
     unsigned long long knorm_bits;  // max_i sum_j |K_ij| as the bits of a non-negative double

@@ -2276,10 +2276,8 @@ __device__ void arnoldi_close(Control *c, int j, int restart, double hn, double 
 // h2 = reduce(buffer 1), hn = ||w - V h2||; Hessenberg column h1 + h2, rotation and stop test
 // (arnoldi_close); then v_{j+1} = (w - V h2) / hn unless the step broke down, and the solve
 // sentinels are re-armed when the cycle goes on.
-// hn comes from ||w||^2 - ||h2||^2 (V's columns are orthonormal): after one Gram-Schmidt pass h2
-// is rounding, about 1e-16 of the vector before that pass, so nothing cancels unless w itself is
-// that small, and there the breakdown test (hn against 1e-14 of it) ends the cycle.  A kernel
-// of its own for w - V h2 and its norm took 5.2 us at 60k unknowns and 12 us at 2M.
+// hn is second_pass_norm's.  A kernel of its own for w - V h2 and its norm took 5.2 us at 60k unknowns
+// and 12 us at 2M.
 template <typename T>
 __global__ void __launch_bounds__(kStreamBlock) k_normalize(KrylovArgs a, int j, int restart, T *s1, T *s2,
                                                             StepRecord *rec, unsigned long long token) {
@@ -2296,8 +2294,7 @@ __global__ void __launch_bounds__(kStreamBlock) k_normalize(KrylovArgs a, int j,
             col[t] = c->h1[t] + h[t];
             hh += h[t] * h[t];
         }
-        const double d2 = h[j + 1] - hh;
-        arnoldi_close(c, j, restart, d2 > 0.0 ? sqrt(d2) : 0.0, c->wnorm_in, col, rec + j, token, sh);
+        arnoldi_close(c, j, restart, second_pass_norm(h[j + 1], hh), c->wnorm_in, col, rec + j, token, sh);
     }
     __syncthreads();
     const double hn = sh[0];
