@@ -1,7 +1,9 @@
 """The one-launch solve on patterns and arguments beside the usual ones: a solution that is written over
 its right-hand side (b is copied first where an entry of it could be overwritten before it is
 read), systems side by side, a right-hand side with infinities or with the bits of the exchange
-vectors' "not written" mark, a long chain, lists beyond the positions."""
+vectors' "not written" mark, a long chain, lists beyond the positions.  And the schedules of the
+budgets that the library uses, replayed on the CPU, and on the GPU against the solve without
+tiles."""
 import os
 import pathlib
 import shutil
@@ -11,6 +13,7 @@ import numpy as np
 import pytest
 
 import kkt_synth as ks
+import oracle
 import paper_2401_13926_amd as P
 
 ROOT = pathlib.Path(__file__).resolve().parents[1]
@@ -37,6 +40,11 @@ def order_driver(tmp_path_factory):
     return compiled(tmp_path_factory, "solve_order_driver")
 
 
+@pytest.fixture(scope="module")
+def replay_driver(tmp_path_factory):
+    return compiled(tmp_path_factory, "solve_tiles_driver")
+
+
 def cycles(n, k=7, c=2.0):
     """n / k blocks that are cyclic permutations: every pivot off the diagonal, every row a tree of its
     own (k = 2: symmetric)."""
@@ -61,6 +69,16 @@ def paths(n, k):
     return np.concatenate([[0], np.cumsum(np.bincount(rows, minlength=n))]).astype(np.int64), cols[order], vals[order]
 
 
+def twisted(n, k):
+    """Paths of k vertices with the rows of each moved on by k / 2: off-diagonal pivots (K has a zero diagonal), and fill."""
+    rp, ci, v = paths(n, k)
+    i = np.arange(n)
+    src = i // k * k + (i % k + k // 2) % k
+    rows = [np.arange(rp[r], rp[r + 1]) for r in src]
+    take = np.concatenate(rows)
+    return np.concatenate([[0], np.cumsum([len(r) for r in rows])]).astype(np.int64), ci[take], v[take]
+
+
 # systems side by side: (system, size of one)
 FORESTS = {
     "kkt-100": lambda: (stacked(ks.small_kkt(60, 40, 7), 100), 100),
@@ -75,6 +93,8 @@ def system(case, n=7_000):
         return FORESTS[case]()[0]
     if case == "path":
         return paths(n, n)
+    if case == "twisted":
+        return twisted(n // 9 * 9, 9)
     if case == "cycles":
         return cycles(n // 7 * 7)
     if case == "pairs":
@@ -96,12 +116,13 @@ def look(order_driver, tmp_path, case, sol, *more):
 
 
 @pytest.mark.parametrize("sol", sorted(SOL_LDS))
-@pytest.mark.parametrize("case", ["cycles", "kkt"])
+@pytest.mark.parametrize("case", ["cycles", "twisted", "kkt"])
 def test_overwriting_is_seen(order_driver, tmp_path, case, sol):
     out = look(order_driver, tmp_path, case, sol)
     assert out["tiles"] > 1
-    assert (out["offdiag"] > 0) == (case == "cycles") and (out["early"] > 0) == (case == "cycles"), out
-    assert out["same"] == (out["early"] > 0) and out["shifted"] == 1 and out["apart"] == 0, out
+    assert (out["offdiag"] > 0) == (case != "kkt"), out
+    assert (out["early"] > 0) == (case == "cycles") or case == "twisted", out  # (its trees may fill whole tiles)
+    assert out["same"] == (out["offdiag"] > 0) and out["shifted"] == 1 and out["apart"] == 0, out
 
 
 @pytest.mark.parametrize("sol", sorted(SOL_LDS))
@@ -110,6 +131,33 @@ def test_dense_ranges_keep_to_one_tree(order_driver, tmp_path, case, sol):
     out = look(order_driver, tmp_path, case, sol)
     assert out["tiles"] > 0 and out["mixed"] == 0, out
     assert case in FORESTS or out["dense"] > 0, out
+
+
+REPLAYED = ["kkt", "path", "twisted"] + sorted(FORESTS)
+# the library's budgets, and one of a few rows a tile: many layers of the solve, mostly externals
+BUDGETS = dict(SOL_LDS, tiny=(1_200, 2_400))
+
+
+@pytest.mark.parametrize("sol", sorted(BUDGETS))
+@pytest.mark.parametrize("case", REPLAYED)
+def test_replay_of_the_solve_tiles(replay_driver, tmp_path, case, sol):
+    rp, ci, v1 = system(case, 3_500)
+    v2 = v1 * (1.0 + 0.01 * np.random.default_rng(2).standard_normal(len(v1)))
+    f = tmp_path / "in.bin"
+    with open(f, "wb") as fh:
+        fh.write(np.array([len(rp) - 1, len(ci)], np.int64).tobytes() + np.array([1e-10], np.float64).tobytes())
+        fh.write(np.array([0, REF_LDS], np.int32).tobytes() + rp.astype(np.int64).tobytes())
+        fh.write(ci.astype(np.int32).tobytes() + v1.tobytes() + v2.tobytes())
+    r = subprocess.run([str(replay_driver), str(f), str(tmp_path / "factors.bin")], capture_output=True, text=True,
+                       env=dict(os.environ, SOL_LDS=str(BUDGETS[sol][0]), SOL_DENSE_LDS=str(BUDGETS[sol][1])), timeout=600)
+    assert r.returncode == 0, r.stderr[-4000:]
+    out = dict(kv.split("=", 1) for kv in r.stdout.split())
+    assert int(out["tiles"]) > 0 and out["refactor"] == "ok", out
+    fac = np.fromfile(tmp_path / "factors.bin", np.float64)
+    lx, ux, _ = oracle.LU(rp, ci, v1).refactor64(rp, ci, v2)
+    assert np.array_equal(fac[:lx.size], lx) and np.array_equal(fac[lx.size:], ux)
+    # sums in another order than plain substitution's, along chains of up to a few hundred rows
+    assert out["solve"].startswith("ok:") and float(out["solve"][3:]) <= 1e-9, out["solve"]
 
 
 def test_no_tiles_beyond_the_positions(order_driver, tmp_path):
@@ -134,7 +182,7 @@ def test_analysis_of_a_long_chain():
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("precision", [P.PREC_FP64, P.PREC_MIXED])
-@pytest.mark.parametrize("case", ["cycles", "pairs", "kkt"])
+@pytest.mark.parametrize("case", ["cycles", "pairs", "twisted", "kkt"])
 def test_direct_solve_over_its_right_hand_side(case, precision):
     """x in b's place, and one entry after it, against x in an array of its own: the same bits."""
     torch = pytest.importorskip("torch")
@@ -155,6 +203,30 @@ def test_direct_solve_over_its_right_hand_side(case, precision):
                 buf[:n] = b
                 solve(buf[:n], buf[shift:shift + n])
                 assert torch.equal(buf[shift:shift + n], want)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("precision", [P.PREC_FP64, P.PREC_MIXED])
+@pytest.mark.parametrize("case", REPLAYED + ["cycles", "pairs"])
+def test_solve_with_tiles_against_without(case, precision):
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    print("tiles against none", case, precision, flush=True)
+    rp, ci, v = system(case, 14_000)
+    b = torch.as_tensor(np.random.default_rng(3).standard_normal(len(rp) - 1), device="cuda")
+    x = []
+    for lds in (0, 32):  # 0: tiles
+        s = P.Solver(rp, ci, v, precision=precision, tile_lds_kib=lds).bind("cuda")
+        s.refactor(torch.as_tensor(v, device="cuda"))
+        x.append(s.direct_solve(b))
+    # the replay's bound, at the factors' unit roundoff for FP32 (2^29 times as large; the KKT systems
+    # lose all digits there)
+    if precision == P.PREC_FP64:
+        assert float((x[0] - x[1]).abs().max()) <= 1e-9 * float(x[1].abs().max())
+    elif "kkt" not in case:
+        assert float((x[0] - x[1]).abs().max()) <= 1e-4 * float(x[1].abs().max())
+    assert bool(torch.isfinite(x[0]).all())
 
 
 SENTINEL = np.array([0x7FF4DEADBEEF0001], np.uint64).view(np.float64)[0]
