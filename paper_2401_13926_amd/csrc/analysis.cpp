@@ -927,7 +927,8 @@ class Beside {
     std::exception_ptr error;
 };
 
-int build_layouts(const AnalysisOptions &opt, Analysis &a, std::string *msg) {
+// The factor's columns (F) and where their entries come from in K.
+int build_factor_columns(Analysis &a, std::string *msg) {
     const int64_t n = a.n;
     const int64_t lnz = a.nnz_l(), unz = a.nnz_u();
     const int64_t f = lnz + unz;
@@ -997,6 +998,52 @@ int build_layouts(const AnalysisOptions &opt, Analysis &a, std::string *msg) {
             }
         }
     }
+    return AN_OK;
+}
+
+// The triangles by rows.
+void build_triangles(Analysis &a) {
+    const int64_t n = a.n, f = a.nnz_f();
+    // --- solve layout: L strict CSR, U strict CSR, diagonal; map F -> T
+    {
+        a.lrp.assign(n + 1, 0);
+        a.urp.assign(n + 1, 0);
+        for (int64_t j = 0; j < n; ++j) {
+            for (int64_t t = a.fp[j]; t < a.fp[j] + a.fdiag[j]; ++t) ++a.urp[a.fi[t] + 1];
+            for (int64_t t = a.fp[j] + a.fdiag[j] + 1; t < a.fp[j + 1]; ++t) ++a.lrp[a.fi[t] + 1];
+        }
+        for (int64_t i = 0; i < n; ++i) {
+            a.lrp[i + 1] += a.lrp[i];
+            a.urp[i + 1] += a.urp[i];
+        }
+        a.lci.resize(a.lrp[n]);
+        a.uci.resize(a.urp[n]);
+        a.f2t.resize(f);
+        std::vector<int64_t> lnext(a.lrp.begin(), a.lrp.end() - 1), unext(a.urp.begin(), a.urp.end() - 1);
+        const int64_t ubase = a.lrp[n], dbase = a.lrp[n] + a.urp[n];
+        for (int64_t j = 0; j < n; ++j) {  // columns ascending -> column indices ascending per row
+            for (int64_t t = a.fp[j]; t < a.fp[j + 1]; ++t) {
+                const int32_t r = a.fi[t];
+                if (r < j) {
+                    const int64_t d = unext[r]++;
+                    a.uci[d] = (int32_t)j;
+                    a.f2t[t] = (int32_t)(ubase + d);
+                } else if (r == j) {
+                    a.f2t[t] = (int32_t)(dbase + j);
+                } else {
+                    const int64_t d = lnext[r]++;
+                    a.lci[d] = (int32_t)j;
+                    a.f2t[t] = (int32_t)d;
+                }
+            }
+        }
+    }
+}
+
+// The schedules that need no tiles: the refactorization's update lists and hand-out items, the sweeps'
+// windows.
+int build_schedules(const AnalysisOptions &opt, Analysis &a, std::string *msg) {
+    const int64_t n = a.n, f = a.nnz_f();
     // --- update positions and refactorization levels
     {
         int64_t total = 0;
@@ -1093,40 +1140,6 @@ int build_layouts(const AnalysisOptions &opt, Analysis &a, std::string *msg) {
             if (!ok) {
                 *msg = "internal: refactorization hand-out item " + std::to_string(t);
                 return AN_EINVAL;
-            }
-        }
-    }
-    // --- solve layout: L strict CSR, U strict CSR, diagonal; map F -> T
-    {
-        a.lrp.assign(n + 1, 0);
-        a.urp.assign(n + 1, 0);
-        for (int64_t j = 0; j < n; ++j) {
-            for (int64_t t = a.fp[j]; t < a.fp[j] + a.fdiag[j]; ++t) ++a.urp[a.fi[t] + 1];
-            for (int64_t t = a.fp[j] + a.fdiag[j] + 1; t < a.fp[j + 1]; ++t) ++a.lrp[a.fi[t] + 1];
-        }
-        for (int64_t i = 0; i < n; ++i) {
-            a.lrp[i + 1] += a.lrp[i];
-            a.urp[i + 1] += a.urp[i];
-        }
-        a.lci.resize(a.lrp[n]);
-        a.uci.resize(a.urp[n]);
-        a.f2t.resize(f);
-        std::vector<int64_t> lnext(a.lrp.begin(), a.lrp.end() - 1), unext(a.urp.begin(), a.urp.end() - 1);
-        const int64_t ubase = a.lrp[n], dbase = a.lrp[n] + a.urp[n];
-        for (int64_t j = 0; j < n; ++j) {  // columns ascending -> column indices ascending per row
-            for (int64_t t = a.fp[j]; t < a.fp[j + 1]; ++t) {
-                const int32_t r = a.fi[t];
-                if (r < j) {
-                    const int64_t d = unext[r]++;
-                    a.uci[d] = (int32_t)j;
-                    a.f2t[t] = (int32_t)(ubase + d);
-                } else if (r == j) {
-                    a.f2t[t] = (int32_t)(dbase + j);
-                } else {
-                    const int64_t d = lnext[r]++;
-                    a.lci[d] = (int32_t)j;
-                    a.f2t[t] = (int32_t)d;
-                }
             }
         }
     }
@@ -1279,9 +1292,9 @@ bool symmetric_factor(const Analysis &a) {
 }
 
 // The solves' tile schedule (SolveTiles) and the solve layout that goes with it: T = [L places | U
-// places | U diagonal, by U position].  Sets a.f2t and a.t_size; returns false (nothing changed)
-// when a row does not fit a tile.
-bool build_solve_tiles(const AnalysisOptions &opt, Analysis &a) {
+// places | U diagonal, by U position], by F position in f2t.  Returns false (a.sol as it was) when a row
+// does not fit a tile.
+bool build_solve_tiles(const AnalysisOptions &opt, Analysis &a, std::vector<int32_t> &f2t) {
     const int64_t n = a.n;
     SolveTiles t;
     auto l0 = [&](int64_t m) { return a.fp[m] + a.fdiag[m] + 1; };
@@ -1516,14 +1529,14 @@ bool build_solve_tiles(const AnalysisOptions &opt, Analysis &a) {
     t.pos_u.resize(n);
     for (int64_t p = 0; p < n; ++p) t.pos_u[p] = pos_l[t.node_u[p]];
     std::vector<int64_t> lnext(a.lrp.begin(), a.lrp.end() - 1), unext(a.urp.begin(), a.urp.end() - 1);
+    f2t.resize(a.nnz_f());
     for (int64_t j = 0; j < n; ++j)  // columns ascending -> each row's entries in CSR order
         for (int64_t f = a.fp[j]; f < a.fp[j + 1]; ++f) {
             const int32_t r = a.fi[f];
-            if (r < j) a.f2t[f] = (int32_t)(ub + umap[unext[r]++]);
-            else if (r == j) a.f2t[f] = (int32_t)(db + pos_u[j]);
-            else a.f2t[f] = lmap[lnext[r]++];
+            if (r < j) f2t[f] = (int32_t)(ub + umap[unext[r]++]);
+            else if (r == j) f2t[f] = (int32_t)(db + pos_u[j]);
+            else f2t[f] = lmap[lnext[r]++];
         }
-    a.t_size = db + n;
     a.sol = std::move(t);
     return true;
 }
@@ -1734,47 +1747,44 @@ bool build_ref_tiles(const AnalysisOptions &opt, Analysis &a) {
 void place_out(Analysis &a) {
     RefTiles &t = a.ref;
     t.out_slot.resize(t.out_pos.size());
-    std::vector<std::pair<int32_t, uint16_t>> out;
+    std::vector<uint64_t> out;  // position << 16 | slot
     for (int64_t k = 0; k < t.tiles(); ++k) {
         const int32_t e0 = t.desc[kRefDesc * k + 2], ne = t.desc[kRefDesc * k + 3];
         out.resize(ne);
-        for (int32_t e = 0; e < ne; ++e) out[e] = {a.f2t[t.out_pos[e0 + e]], (uint16_t)e};
+        for (int32_t e = 0; e < ne; ++e) out[e] = (uint64_t)a.f2t[t.out_pos[e0 + e]] << 16 | (uint64_t)e;
         std::sort(out.begin(), out.end());
         for (int32_t e = 0; e < ne; ++e) {
-            t.out_pos[e0 + e] = out[e].first;
-            t.out_slot[e0 + e] = out[e].second;
+            t.out_pos[e0 + e] = (int32_t)(out[e] >> 16);
+            t.out_slot[e0 + e] = (uint16_t)out[e];
         }
     }
 }
 
-// Tiles for the refactorization and the solves, or none (both are built, or neither).  The two
-// are built side by side: neither reads what the other writes.
-void build_tiles(const AnalysisOptions &opt, Analysis &a) {
-    if (opt.ref_lds <= 0 || a.n < 1 || !symmetric_factor(a)) return;
-    const std::vector<int32_t> f2t = a.f2t;
-    const int64_t t_size = a.t_size;
+// Tiles for the refactorization and the solves, or none (both are built, or neither), with the solve
+// layout that goes with them in f2t.  The two are built side by side: neither reads what the
+// other writes, nor what build_schedules does.
+bool build_tiles(const AnalysisOptions &opt, Analysis &a, std::vector<int32_t> &f2t) {
+    if (opt.ref_lds <= 0 || a.n < 1 || !symmetric_factor(a)) return false;
     bool ref_ok = false;
     Beside ref([&] { ref_ok = build_ref_tiles(opt, a); });
-    const bool sol_ok = build_solve_tiles(opt, a);
+    const bool sol_ok = build_solve_tiles(opt, a, f2t);
     ref.wait();
-    if (sol_ok && ref_ok) {
-        place_out(a);
-        return;
-    }
-    a.f2t = f2t;
-    a.t_size = t_size;
+    if (sol_ok && ref_ok) return true;
     a.sol = SolveTiles();
     a.ref = RefTiles();
+    return false;
 }
 
 // The device layout of the flat refactorization (see Analysis::phys): F positions and update
-// lists renumbered in col_order.
-void build_phys_layout(Analysis &a) {
+// lists renumbered in col_order; sizes_only: its arrays' sizes.
+void build_phys_layout(Analysis &a, bool sizes_only) {
     const int64_t n = a.n, f = a.nnz_f();
-    std::vector<int64_t> phys(f);
     a.pc.assign(n + 1, 0);
     a.pu.assign(n + 1, 0);
     a.pnu.assign(n, 0);
+    a.phys = true;
+    if (sizes_only) return;
+    std::vector<int64_t> phys(f);
     int64_t w = 0, u = 0;
     for (int64_t p = 0; p < n; ++p) {
         const int32_t j = a.col_order[p];
@@ -1808,7 +1818,6 @@ void build_phys_layout(Analysis &a) {
     a.fsrc_k.swap(fsrc);
     for (auto &t : a.l2f) t = phys[t];
     for (auto &t : a.u2f) t = phys[t];
-    a.phys = true;
 }
 
 }  // namespace
@@ -1857,11 +1866,25 @@ int analyze(const AnalysisOptions &opt, int64_t n, const int64_t *rowptr, const 
         vector_numbers.wait();
         a.vpinv.assign(n, 0);
         for (int64_t k = 0; k < n; ++k) a.vpinv[a.vperm[k]] = (int32_t)k;
-        rc = build_layouts(opt, a, msg);
+        rc = build_factor_columns(a, msg);
         if (rc != AN_OK) return rc;
+        build_triangles(a);
         build_vector_order(a);
-        build_tiles(opt, a);
-        if (!a.relsrc.empty()) build_phys_layout(a);
+        {
+            bool tiled = false;
+            std::vector<int32_t> f2t;  // of the tiles' solve layout
+            Beside tiles([&] { tiled = build_tiles(opt, a, f2t); });
+            rc = build_schedules(opt, a, msg);
+            tiles.wait();
+            if (rc != AN_OK) return rc;
+            if (tiled) {
+                a.f2t.swap(f2t);
+                a.t_size = (int64_t)(a.sol.ref_l.size() + a.sol.ref_u.size()) + n;
+                place_out(a);
+            }
+            // (with tiles only the sizes of the hand-out's layout are asked for)
+            if (!a.relsrc.empty()) build_phys_layout(a, tiled);
+        }
     } catch (const std::bad_alloc &) {
         *msg = "out of host memory";
         return AN_ENOMEM;
