@@ -55,10 +55,12 @@ def algorithmic_bytes(cls: str, ai: dict) -> float:
 
 ROOT = os.path.dirname(os.path.abspath(__file__))
 PROFILES = os.path.join(ROOT, "profiles")
-# kernel-name prefixes of each class in the counter summary (both sweeps are one launch, timed as
-# trsv_l, on patterns that get tiles, as this benchmark's do)
-KERNEL_NAMES = {"trsv_l": "kkt::k_solve_tiles<double", "trsv_u": "kkt::k_trsv<double,false",
-                "refactor": "kkt::k_refactor_tiles<double", "spmv": "kkt::k_spmv_dots"}
+# kernel-name prefixes of each class in the counter summary: on patterns that get tiles (as this
+# benchmark's do; both sweeps are then one launch, timed as trsv_l), and on others
+KERNEL_NAMES = {"trsv_l": ("kkt::k_solve_tiles<double", "kkt::k_trsv<double,true"),
+                "trsv_u": ("kkt::k_trsv<double,false",),
+                "refactor": ("kkt::k_refactor_tiles<double", "kkt::k_refactor<double"),
+                "spmv": ("kkt::k_spmv_dots",)}
 
 
 def launch_bytes(cls: str, ai: dict, breakdown: dict) -> float:

@@ -116,21 +116,24 @@ typedef struct {
     int32_t tile_lds_kib;   /* 0 (default): where L's and U's patterns are each other's
                                transpose and narrow_columns is 0, both sweeps run in one
                                launch on tiles of whole elimination subtrees (12 KiB of LDS
-                               below 250,000 rows, 16 KiB from there), else on staged tiles
-                               of 32 KiB, one launch per sweep.  16..150: always staged tiles, with this LDS budget in
-                               KiB.  Larger tiles hold more levels of the elimination tree, so
+                               below 250,000 rows, 16 KiB from there) if every row and every
+                               pivot step's entries and updates fit a tile, else on staged
+                               tiles of 32 KiB, one launch per sweep.  16..150: always staged
+                               tiles, with this LDS budget in KiB (and no subtree tiles in the
+                               refactorization).  Larger tiles hold more levels of the elimination tree, so
                                fewer cross-block hand-offs lie on a solve's critical path;
                                smaller ones let more blocks share a compute unit; above 80 KiB
                                one solve block occupies a compute unit alone */
     int32_t narrow_columns; /* 0 (default): where L's and U's patterns are each other's
                                transpose and tile_lds_kib is 0, the refactorization runs on
-                               tiles of whole elimination subtrees; else it hands out levels.
-                               Positive: always levels, those with at most this many columns
-                               one column per wavefront, wider ones as lane items (64 short
-                               columns, one per lane) and chunks of 8 longer columns (0 there:
-                               the larger of 3,072, the resident wavefronts, and n/64 capped
-                               at 16,384); negative values are rejected (KKT_EINVAL).  The
-                               factors do not depend on it. */
+                               tiles of whole elimination subtrees (if they fit, as above);
+                               else it hands out levels with a limit of the larger of 3,072
+                               (the resident wavefronts) and n/64 capped at 16,384.  Positive:
+                               always levels, with this limit (and staged tiles in the
+                               solves).  Levels of at most that many columns go one column per
+                               wavefront, wider ones as lane items (64 short columns, one per
+                               lane) and chunks of 8 longer columns.  Negative values are
+                               rejected (KKT_EINVAL).  The factors do not depend on it. */
     int32_t deterministic;  /* 1 (default): bitwise-repeatable results.  Every kernel reduces in
                                a fixed order and none uses floating-point atomics, so a solve
                                gives the same bits alone, batched, in a serving mix or on a

@@ -83,7 +83,7 @@ struct Control {
     double Hbar[(kRestartMax + 1) * kRestartMax];  // DCGS2: final columns before rotation
     double hp[2][kRestartMax + 1];  // DCGS2: one-pass column j in hp[j & 1] (read by step j + 1)
     // Refactorization hand-out: kWorkQueues counters, one per 256-byte line; queue q hands out
-    // items q, q + kWorkQueues, ... to the blocks b with b % kWorkQueues == q.
+    // items q, q + kWorkQueues, ... (next_task; first_queue says where a block starts).
     unsigned int work_refactor[kWorkQueues * 64];
     SolveWork work;                 // hand-out of the triangular solves
     unsigned int arrive[kWorkQueues * 64];  // arrivals of the blocks of each group, a line each

@@ -153,8 +153,10 @@ __device__ __forceinline__ unsigned int next_task(unsigned int *queues, unsigned
 // The counter a block starts on.  XCDs fill with blocks independently of each other (block b on XCD
 // b % 8), and two launches on different streams can each take whole XCDs before the other: eight
 // blocks in a row of one XCD therefore start on eight different counters, so a launch with no more
-// than those resident still reaches every task.  Launches of fewer than 64 blocks do not fill an
-// XCD; there each of the first blocks starts on a counter of its own.
+// than those resident still reaches every task.  What has to hold: eight consecutive blocks of the
+// launch are resident on some XCD.  (An XCD has places for well over a hundred, and a process runs
+// at most four launches at once by default.)  Launches of fewer than 64 blocks do not fill an
+// XCD; there each of the first eight blocks starts on a counter of its own.
 __device__ __forceinline__ unsigned int first_queue() {
     return (gridDim.x < kWorkQueues * kWorkQueues ? blockIdx.x : blockIdx.x / kWorkQueues) % kWorkQueues;
 }
